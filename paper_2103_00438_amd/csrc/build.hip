@@ -530,7 +530,11 @@ void build_structure(Structure& s, const wfq_geometry* g, const wfq_params* p, c
         s.sphere = dev_alloc<double>(s, sph.size());
         h2d_sync(s, s.sphere, sph.data(), sph.size() * 8, st);
         s.width_max = 0.0;
-        for (int64_t k = 0; k < n; ++k) s.width_max = std::max(s.width_max, width_h[k]);
+        s.eta_max = 0.0;
+        for (int64_t k = 0; k < n; ++k) {
+            s.width_max = std::max(s.width_max, width_h[k]);
+            s.eta_max = std::max(s.eta_max, eta_h[k]);
+        }
     }
 
     // ---- a1: neighbour search and CSR of L = P - Kbar

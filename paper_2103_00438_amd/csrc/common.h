@@ -26,7 +26,14 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes, kept in registers
+
+// a column of X in an FP16-split product: the exponent of its scale and its class
+struct ColInfo {
+    int exp;   // entries were multiplied by 2^exp
+    int cls;   // 0 finite; 1 +inf only, 2 -inf only, 3 anything else that is not finite
+};
 
 struct Error {
     int code;
@@ -61,6 +68,7 @@ struct Structure {
     double* width = nullptr;     // device [npad], d_i
     double* sphere = nullptr;    // device [npad / 64][4]: centre and radius of each 64-atom block (bohr)
     double width_max = 0.0;      // largest d_i
+    double eta_max = 0.0;        // largest eta_i, a bound on every element of T
     int64_t nnz = 0;
     int32_t* rowptr = nullptr;   // device [n + 1]
     int32_t* col = nullptr;      // device [nnz]
@@ -169,13 +177,17 @@ void build_rhs(const Structure& s, const double* dirs_dev, int n_dir, double E0,
 // Y[c][i] = sum_k T[i][k] X[c][k] for c < ncol, i < npad; X, Y row-major with leading dimension ld.
 // X must hold round_up(ncol, kColPad) rows (rows >= ncol zero). Y likewise.
 void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st);
-void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st);
+void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, bool split = false);
 void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st);
-const char* tx_variant(int precision, int ncol);
 // true when a product of ncol columns in `prec` recomputes the elements with the narrow kernel
 bool tx_is_otf_narrow(const Structure& s, int prec, int ncol);
-// T X with the stored copy of T in `prec`, or recomputed on the fly when the structure is matrix-free
-void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st);
+// T X with the stored copy of T in `prec`, or recomputed on the fly when the structure is matrix-free.
+// split: an untuned FP32 product may go through the FP16 matrix cores (operands split, the error against
+// 64 bits smaller than the FP32 instruction's). The operator entry points ask for it. The solves do not:
+// the rounding of the inner products decides at which restart a system near the tolerance stops, and the
+// FP32 instruction's is systematic, so another product moves their results by as much as the tolerance
+// allows; a tuned handle takes whichever shape measured fastest.
+void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, bool split = false);
 // one registered block-product variant (index as listed by tx_variant_name), stored T only
 void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st);
 int tx_variant_count(int precision);
@@ -200,6 +212,17 @@ bool otf_sym_fits(const Structure& s, int ncol);
 uint64_t otf_sym_bytes(const Structure& s, int ncol);
 // partial-tile work space of the block products (grown on demand, or the fixed region when set)
 void* split_workspace(const Structure& s, uint64_t bytes);
+// FP32 products through the FP16 matrix cores (the operands split in two FP16 parts): whether T's scale is
+// in the range the split assumes (its largest element, eta_max, between 2^-60 and 2^60); the exponent that
+// scales T below 2^15; the work space of the split X (the columns' scales first, then 32 bytes per 8
+// entries); whether it fits the work-space cap; the split itself, into ws.
+bool split_scale_ok(const Structure& s);
+int split_t_exp(const Structure& s);
+uint64_t split_x_bytes(int64_t ld, int ncol);
+bool split_fits(const Structure& s, int64_t ld, int ncol);
+void split_x(const float* X, int64_t ld, int ncol, char* ws, hipStream_t st);
+// Y[q] += ws[q] + ws[stride + q] + ... (parts terms, in order) for q < count
+void add_parts_f32(float* Y, const float* ws, int64_t count, int64_t stride, int parts, hipStream_t st);
 void otf_tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st);
 
 }  // namespace wfq

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "common.h"
+
 namespace wfq {
 
 // Round a double to bfloat16 (nearest, ties to even) from its bits, so no intermediate float
@@ -43,6 +45,20 @@ __device__ inline double wave_sum(double v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
     return v;
+}
+
+// ---- FP32 operands of the FP16 matrix cores: x = h + l + e, h the FP16 rounding of x, l that of x - h
+__device__ inline halfx8 split_hi(const float (&x)[8]) {
+    halfx8 h;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) h[e] = (_Float16)x[e];
+    return h;
+}
+__device__ inline halfx8 split_lo(const float (&x)[8], const halfx8& h) {
+    halfx8 l;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) l[e] = (_Float16)(x[e] - (float)h[e]);
+    return l;
 }
 
 }  // namespace wfq

@@ -10,6 +10,7 @@
 // each wave computes a (16 WM) x (16 WN) sub-tile. Each lane feeds the matrix core 16 bytes of k per operand; the k
 // order inside a slice is a permutation that is the same for both operands, so the sum is exact.
 // Narrow blocks (<= 8 columns, e.g. one frequency at a time) stream T once with vector loads.
+#include <cmath>
 #include <cstring>
 #include <iterator>
 
@@ -269,6 +270,200 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, OCC)
 
 #undef WFQ_CHUNK_OK
 
+// ---- FP32 products through the FP16 matrix cores: each FP32 operand is split into two FP16 parts
+//
+// v_mfma_f32_16x16x4_f32 does 256 multiply-adds per CU and clock, the FP16 form sixteen times as many
+// from half the bits per operand. An FP32 value scaled into FP16's range is h + l + e with h its FP16
+// rounding, l the FP16 rounding of x - h and |e| <= 2^-23 |x|, and x y = h h' + h l' + l h' + O(2^-22) x y:
+// three FP16 products with FP32 accumulation stand for the FP32 one. The scales are powers of two
+// (exact): one for T from its largest element, and one per column of X from that column's largest
+// entry, taken out again in the epilogue. The sum over k rounds 3 k / 32 times in FP32 instead of k
+// times, so the error against 64 bits falls (figures at split_default).
+//
+// Layout: T goes straight from global memory into the matrix cores' fragment layout (a wave owns 16 WN
+// rows of T and all 16 WM columns of its work-group, so no other wave needs its rows): 4 lanes read the
+// 128 contiguous bytes of a row's 32 k, the split is done in registers, and the loads of the next stage
+// are in flight during the matrix products of this one. X is split beforehand (split_x_kernel) into
+// groups of 8 h and 8 l halves and staged through LDS for the four waves, double buffered, rows padded
+// by 16 bytes (distinct banks for 8 lanes reading 16 bytes).
+// Bound: the matrix cores and their operand reads with several hundred columns (20 000 atoms, 384 columns:
+// 967 us = 980 TFLOP/s of FP16 products, 325 of the FP32 product's; 2 410 us and 130 TFLOP/s with the FP32
+// instruction, whose peak is 157), below about 100 columns the HBM reads of T (32 columns: 305 us, 5.4 TB/s).
+
+// One work-group per column of X: its largest magnitude gives the scale (the scaled entries stay below
+// 2^15), then every group of 8 entries is written as 8 h and 8 l halves (32 bytes, like the FP32 entries).
+__global__ void __launch_bounds__(1024) split_x_kernel(const float* __restrict__ X, int64_t ld, char* __restrict__ Xs,
+                                                       ColInfo* __restrict__ info) {
+    __shared__ unsigned red[16], redf[16];
+    const int64_t c = blockIdx.x;
+    const float* x = X + c * ld;
+    unsigned m = 0, f = 0;   // largest magnitude (bits); bit 0: +inf, 1: -inf, 2: NaN
+    for (int64_t i = (int64_t)threadIdx.x * 4; i < ld; i += 4096) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(x + i);
+        const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned a = w[e] & 0x7fffffffu;
+            m = max(m, a);
+            if (a >= 0x7f800000u) f |= a > 0x7f800000u ? 4u : (w[e] >> 31) ? 2u : 1u;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        m = max(m, (unsigned)__shfl_xor((int)m, off, 64));
+        f |= (unsigned)__shfl_xor((int)f, off, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = m;
+        redf[threadIdx.x >> 6] = f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        m = max(m, red[q]);
+        f |= redf[q];
+    }
+    int ex = 0;
+    if (m > 0 && f == 0) {
+        (void)frexpf(__uint_as_float(m), &ex);   // m = fraction in [1/2, 1) times 2^ex
+        ex = 15 - ex;
+    }
+    if (threadIdx.x == 0) info[c] = ColInfo{ex, f == 0 ? 0 : f == 1 ? 1 : f == 2 ? 2 : 3};
+    char* o = Xs + c * ld * 4;
+    for (int64_t i = (int64_t)threadIdx.x * 8; i < ld; i += 8192) {
+        float v[8];
+        *reinterpret_cast<floatx4*>(v) = *reinterpret_cast<const floatx4*>(x + i);
+        *reinterpret_cast<floatx4*>(v + 4) = *reinterpret_cast<const floatx4*>(x + i + 4);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = ldexpf(v[e], ex);
+        const halfx8 h = split_hi(v);
+        *reinterpret_cast<halfx8*>(o + i * 4) = h;
+        *reinterpret_cast<halfx8*>(o + i * 4 + 16) = split_lo(v, h);
+    }
+}
+
+// BM = 16 WM columns, BN = 64 WN rows of T, KS values of k per stage. Split k and the tile order as in
+// tx_mfma_kernel.
+template <int WM, int WN, int KS, int OCC>
+__global__ void __launch_bounds__(256, OCC)
+    tx_split_kernel(const char* __restrict__ Xs, const ColInfo* __restrict__ info, const float* __restrict__ T,
+                    float* __restrict__ Y, int64_t ld, int ncol, int mt_count, int nt_count, int split,
+                    float* __restrict__ ws, float tscale, int texp) {
+    constexpr int BM = 16 * WM, BN = 64 * WN;
+    constexpr int SUB = KS / 32;         // 32-wide matrix steps per stage
+    constexpr int RS = KS * 4 + 16;      // padded LDS row
+    constexpr int CH = KS / 4;           // 16-byte chunks per row and stage
+    constexpr int PER_T = BM * CH / 256;
+    static_assert(BM * CH % 256 == 0 && 256 % CH == 0, "whole rows per pass");
+    __shared__ __attribute__((aligned(16))) char lds[2 * BM * RS];
+
+    const int logical = xcd_logical(blockIdx.x, mt_count * nt_count * split);
+    const int mt = logical % mt_count;
+    const int part = (logical / mt_count) % split;
+    const int nt = logical / (mt_count * split);
+    const int64_t m0 = (int64_t)mt * BM, n0 = (int64_t)nt * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 15, fk = lane >> 4;
+
+    // X staging: chunk u of this thread is row r0 + u * RSTEP (columns past the last one re-read it: what
+    // they feed is not stored)
+    constexpr int RSTEP = 256 / CH;
+    const int r0 = tid / CH, cc = tid % CH;
+    const int xlast = ncol - 1 - (int)m0;
+    const char* xp[PER_T];
+#pragma unroll
+    for (int u = 0; u < PER_T; ++u) xp[u] = Xs + (m0 + min(r0 + u * RSTEP, xlast)) * ld * 4 + cc * 16;
+    const int dst0 = r0 * RS + cc * 16;
+    // this lane's 8 values of k of rows b of T
+    const float* tp = T + (n0 + wave * 16 * WN + fr) * ld + fk * 8;
+
+    floatx4 acc[WM][WN];
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b) acc[a][b] = floatx4{0, 0, 0, 0};
+
+    const int nk = (int)(ld / KS);
+    const int kb = (int)((int64_t)nk * part / split), ke = (int)((int64_t)nk * (part + 1) / split);
+    u32x4 xr[PER_T];
+    floatx4 raw[SUB][WN][2];
+    auto load_t = [&](int kt, int s) {
+#pragma unroll
+        for (int b = 0; b < WN; ++b) {
+            const float* p = tp + (int64_t)b * 16 * ld + (int64_t)kt * KS + s * 32;
+            raw[s][b][0] = *reinterpret_cast<const floatx4*>(p);
+            raw[s][b][1] = *reinterpret_cast<const floatx4*>(p + 4);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < PER_T; ++u) xr[u] = *reinterpret_cast<const u32x4*>(xp[u] + (int64_t)kb * KS * 4);
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) load_t(kb, s);
+#pragma unroll
+    for (int u = 0; u < PER_T; ++u) *reinterpret_cast<u32x4*>(lds + dst0 + u * RSTEP * RS) = xr[u];
+    __syncthreads();
+
+    for (int kt = kb; kt < ke; ++kt) {
+        const int kn = min(kt + 1, ke - 1);   // the last stage re-reads its own: loads stay unconditional
+#pragma unroll
+        for (int u = 0; u < PER_T; ++u) xr[u] = *reinterpret_cast<const u32x4*>(xp[u] + (int64_t)kn * KS * 4);
+        const char* L = lds + ((kt - kb) & 1) * BM * RS;
+#pragma unroll
+        for (int s = 0; s < SUB; ++s) {
+            halfx8 th[WN], tl[WN];
+#pragma unroll
+            for (int b = 0; b < WN; ++b) {
+                float v[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = raw[s][b][0][e] * tscale;
+                    v[4 + e] = raw[s][b][1][e] * tscale;
+                }
+                th[b] = split_hi(v);
+                tl[b] = split_lo(v, th[b]);
+            }
+            load_t(kn, s);
+            // keep the loads ahead of the matrix products: issued late, their latency is not hidden
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int a = 0; a < WM; ++a) {
+                const char* lp = L + (a * 16 + fr) * RS + s * 128 + fk * 32;
+                const halfx8 xh = *reinterpret_cast<const halfx8*>(lp);
+                const halfx8 xl = *reinterpret_cast<const halfx8*>(lp + 16);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, th[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, tl[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, th[b], acc[a][b], 0, 0, 0);
+            }
+        }
+        // the other buffer was last read in stage kt - 1, which every wave left at its barrier
+        char* S = lds + ((kt + 1 - kb) & 1) * BM * RS;
+#pragma unroll
+        for (int u = 0; u < PER_T; ++u) *reinterpret_cast<u32x4*>(S + dst0 + u * RSTEP * RS) = xr[u];
+        __syncthreads();
+    }
+
+    float* out = part == 0 ? Y : ws + (int64_t)(part - 1) * mt_count * BM * ld;
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t c = m0 + a * 16 + 4 * fk + r;
+            if (c >= ncol) continue;
+            const ColInfo ci = info[c];
+#pragma unroll
+            for (int b = 0; b < WN; ++b) {
+                const int64_t i = n0 + wave * 16 * WN + b * 16 + fr;
+                float y = ldexpf(acc[a][b][r], -(ci.exp + texp));
+                // every element of T is positive, so a column with an infinite entry gives that infinity
+                if (ci.cls) y = ci.cls == 1 ? __builtin_inff() : ci.cls == 2 ? -__builtin_inff() : __builtin_nanf("");
+                out[c * ld + i] = y;
+            }
+        }
+}
+
 // Y[q] += ws_1[q] + ws_2[q] + ... for the first `count` elements, parts added in order.
 template <typename O>
 __global__ void __launch_bounds__(256) split_reduce_kernel(O* __restrict__ Y, const O* __restrict__ ws,
@@ -413,6 +608,39 @@ void launch_mfma(const Structure& s, const void* X, const void* T, void* Y, int6
     }
 }
 
+template <int WM, int WN, int KS, int OCC>
+void launch_split(const Structure& s, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st) {
+    constexpr int BM = 16 * WM, BN = 64 * WN;
+    auto kern = tx_split_kernel<WM, WN, KS, OCC>;
+    static const int per_cu = [&] {
+        int nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(kern), 256, 0) != hipSuccess ||
+            nb < 1)
+            nb = 1;
+        return nb;
+    }();
+    const uint64_t head = split_x_bytes(ld, ncol), info_bytes = round_up((int64_t)ncol * sizeof(ColInfo), 256);
+    if (!split_scale_ok(s) || !split_fits(s, ld, ncol)) {
+        // no room for the split X (or a T outside the split's range): the FP32 matrix instruction
+        launch_mfma<WFQ_PREC_FP32, 4, 4, 2, 4, 64, 2>(s, X, T, Y, ld, ncol, st);
+        return;
+    }
+    const int mtc = (ncol + BM - 1) / BM, ntc = (int)(ld / BN);
+    const uint64_t part_bytes = (uint64_t)mtc * BM * ld * sizeof(float);
+    const int split = choose_split((int64_t)mtc * ntc, (int)(ld / KS), (int64_t)per_cu * device_cus(s.device), part_bytes,
+                                   (s.split_fixed ? s.split_fixed_bytes : kSplitWsCap) - head);
+    char* ws = static_cast<char*>(split_workspace(s, head + (split - 1) * part_bytes));
+    ColInfo* info = reinterpret_cast<ColInfo*>(ws);
+    float* parts = reinterpret_cast<float*>(ws + head);
+    const int texp = split_t_exp(s);
+    split_x(static_cast<const float*>(X), ld, ncol, ws, st);
+    hipLaunchKernelGGL(kern, dim3(mtc * ntc * split), dim3(256), 0, st, ws + info_bytes, info,
+                       static_cast<const float*>(T), static_cast<float*>(Y), ld, ncol, mtc, ntc, split, parts,
+                       (float)std::ldexp(1.0, texp), texp);
+    if (split > 1)
+        add_parts_f32(static_cast<float*>(Y), parts, (int64_t)ncol * ld, (int64_t)mtc * BM * ld, split - 1, st);
+}
+
 template <int P, int NC, int R = 4>
 void launch_skinny(const Structure&, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st) {
     using elem = typename Prec<P>::elem;
@@ -478,6 +706,17 @@ const std::vector<Variant>& variants_all() {
             // work covers the other's barrier
             r.push_back({"m128n256w8k64", 128, 256, 1 << 30, launch_mfma<P, 4, 4, 2, 4, 64, 2>});
         }
+        if constexpr (P == WFQ_PREC_FP32) {
+            // FP16-split products (s<columns>n<rows of T>k<k per stage>)
+            r.push_back({"s32n256k32", 32, 256, 1 << 30, launch_split<2, 4, 32, 2>});
+            r.push_back({"s64n256k32", 64, 256, 1 << 30, launch_split<4, 4, 32, 2>});
+            r.push_back({"s96n256k32", 96, 256, 1 << 30, launch_split<6, 4, 32, 2>});
+            r.push_back({"s128n256k32", 128, 256, 1 << 30, launch_split<8, 4, 32, 2>});
+            r.push_back({"s64n128k64", 64, 128, 1 << 30, launch_split<4, 2, 64, 2>});
+            r.push_back({"s96n128k64", 96, 128, 1 << 30, launch_split<6, 2, 64, 2>});
+            r.push_back({"s128n128k64", 128, 128, 1 << 30, launch_split<8, 2, 64, 2>});
+            r.push_back({"s192n128k32", 192, 128, 1 << 30, launch_split<12, 2, 32, 2>});
+        }
         return r;
     }();
     return v;
@@ -495,10 +734,33 @@ int find_variant(int prec, const char* name) {
     return -1;
 }
 
+// Whether an FP32 product of ncol columns goes through the FP16 split by default: where it was measured
+// faster and no less accurate than the FP32 matrix instruction (whose best shape is the second figure of
+// each pair, us). N 20 000: 305 / 377 at 32 columns, 346 / 555 at 64, 430 / 849 at 128, 967 / 2410 at
+// 384; N 5 000: 38 / 49 at 48, 93 / 160 at 384; N 4 000: 34 / 29 at 64, 40 / 42 at 96, 67 / 100 at 384;
+// N 2 500: 31 / 28 at 128, 32 / 36 at 192; N 1 000: 25 / 19 at 384; up to 32 columns 42 / 42 at N 6 600,
+// 141 / 143 at N 13 000. Error against 64 bits, random vectors: N 612 2.7e-7 / 2.6e-7, N 2 600
+// 2.7e-7 / 3.7e-7, N 20 000 6.5e-7 to 9.5e-7 / 1.0e-6 to 1.5e-6 (the more k parts, the smaller).
+bool split_default(const Structure& s, int ncol) {
+    if (ncol <= 4 || !split_scale_ok(s) || !split_fits(s, s.npad, ncol)) return false;
+    if (ncol <= 32) return s.npad >= 16384;
+    return s.npad >= 4608 || (s.npad >= 2048 && s.npad * ncol >= 350000);
+}
+
 // Built-in choice when no tuning result covers ncol: the fastest shapes measured on MI355X for a
-// 20 000-atom T, per precision and column count.
-int default_variant(int prec, int ncol) {
+// 20 000-atom T, per precision and column count (FP16-split shapes: also between 2 500 and 13 000 atoms).
+int default_variant(int prec, int ncol, bool split, int64_t npad) {
     struct Pick { int upto; const char* name; };
+    if (split) {
+        // from about 16 000 rows there are enough 256-row tiles for the chip; below, 128-row tiles
+        static const Pick big[] = {{32, "s32n256k32"}, {64, "s64n256k32"}, {96, "s96n256k32"}, {128, "s128n256k32"},
+                                   {192, "s192n128k32"}, {256, "s128n256k32"}, {288, "s96n256k32"}, {1 << 30, "s128n256k32"}};
+        static const Pick mid[] = {{64, "s64n128k64"}, {96, "s96n128k64"}, {128, "s128n128k64"}, {192, "s96n128k64"},
+                                   {1 << 30, "s128n128k64"}};
+        const Pick* t = npad >= 16384 || (npad >= 6144 && ncol > 128) ? big : mid;
+        while (ncol > t->upto) ++t;
+        return find_variant(prec, t->name);
+    }
     static const Pick f64[] = {{2, "skinny2"}, {4, "skinny4"}, {8, "skinny8"}, {32, "m32n128"}, {64, "m64n128i"},
                                {96, "m128n256w8i"}, {128, "m128n256w8"}, {192, "m64n128i"}, {256, "m128n256w8i"},
                                {320, "m64n128"}, {1 << 30, "m128n256w8i"}};
@@ -520,7 +782,8 @@ constexpr int64_t kOtfNarrowFrom = 16384;
 // matrix-free FP64 products of up to this many 4-column chunks use the narrow kernel
 constexpr int kOtfNarrowChunks = 3;
 
-int pick_variant(const Structure& s, int prec, int ncol) {
+// split: untuned FP32 products may take the FP16 split (see tx_any)
+int pick_variant(const Structure& s, int prec, int ncol, bool split = false) {
     const auto& tuned = s.tuned[prec];
     // the tuned entry with the smallest ncol >= this one (or the largest tuned one), used only when
     // it was tuned for a comparable width (within a factor of two)
@@ -534,7 +797,7 @@ int pick_variant(const Structure& s, int prec, int ncol) {
     // (about 16 FP64 operations per pair) beats streaming 8 bytes per pair of the stored copy
     if (prec == WFQ_PREC_FP64 && ncol <= 4 && s.npad >= kOtfNarrowFrom)
         return find_variant(prec, ncol <= 2 ? "otfn2" : "otfn4");
-    return default_variant(prec, ncol);
+    return default_variant(prec, ncol, split && prec == WFQ_PREC_FP32 && split_default(s, ncol), s.npad);
 }
 
 void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st) {
@@ -554,6 +817,35 @@ __global__ void convert_kernel(const double* __restrict__ src, E* __restrict__ d
 }
 
 }  // namespace
+
+bool split_scale_ok(const Structure& s) { return s.eta_max > 0x1p-60 && s.eta_max < 0x1p60; }
+
+int split_t_exp(const Structure& s) {
+    int ex = 0;
+    (void)std::frexp(s.eta_max, &ex);
+    return 15 - ex;
+}
+
+uint64_t split_x_bytes(int64_t ld, int ncol) {
+    return round_up((int64_t)ncol * sizeof(ColInfo), 256) + (uint64_t)ncol * ld * 4;
+}
+
+bool split_fits(const Structure& s, int64_t ld, int ncol) {
+    return split_x_bytes(ld, ncol) <= (s.split_fixed ? s.split_fixed_bytes : kSplitWsCap);
+}
+
+void split_x(const float* X, int64_t ld, int ncol, char* ws, hipStream_t st) {
+    const int64_t info_bytes = round_up((int64_t)ncol * sizeof(ColInfo), 256);
+    hipLaunchKernelGGL(split_x_kernel, dim3((unsigned)ncol), dim3(1024), 0, st, X, ld, ws + info_bytes,
+                       reinterpret_cast<ColInfo*>(ws));
+    WFQ_CHECK_LAUNCH();
+}
+
+void add_parts_f32(float* Y, const float* ws, int64_t count, int64_t stride, int parts, hipStream_t st) {
+    hipLaunchKernelGGL(split_reduce_kernel<float>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, Y, ws, count,
+                       stride, parts);
+    WFQ_CHECK_LAUNCH();
+}
 
 int device_cus(int device) {
     int cus = 0;
@@ -596,14 +888,14 @@ void convert_from_f64(int prec, const double* src, void* dst, int64_t count, hip
 void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st) {
     if (ncol > 0) run_variant(s, WFQ_PREC_FP64, pick_variant(s, WFQ_PREC_FP64, ncol), X, Y, ncol, st);
 }
-void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st) {
-    if (ncol > 0) run_variant(s, WFQ_PREC_FP32, pick_variant(s, WFQ_PREC_FP32, ncol), X, Y, ncol, st);
+void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, bool split) {
+    if (ncol > 0) run_variant(s, WFQ_PREC_FP32, pick_variant(s, WFQ_PREC_FP32, ncol, split), X, Y, ncol, st);
 }
 void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st) {
     if (ncol > 0) run_variant(s, WFQ_PREC_BF16, pick_variant(s, WFQ_PREC_BF16, ncol), X, Y, ncol, st);
 }
 
-void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st) {
+void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, bool split) {
     if (s.t_mode == WFQ_TMODE_OTF) {
         if (prec == WFQ_PREC_FP32)
             otf_tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st);
@@ -623,7 +915,7 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
     if (prec == WFQ_PREC_FP64)
         tx_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), ncol, st);
     else if (prec == WFQ_PREC_FP32)
-        tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st);
+        tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st, split);
     else
         tx_bf16(s, static_cast<const uint16_t*>(X), static_cast<float*>(Y), ncol, st);
 }
@@ -637,10 +929,6 @@ bool tx_is_otf_narrow(const Structure& s, int prec, int ncol) {
     if (s.t_mode == WFQ_TMODE_OTF) return ncol <= kOtfNarrowChunks * 4;
     if (ncol > 4) return false;
     return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol)].name, "otfn", 4) == 0;
-}
-
-const char* tx_variant(int precision, int ncol) {
-    return variants_of(precision)[default_variant(precision, ncol)].name;
 }
 
 int tx_variant_count(int precision) { return (int)variants_of(precision).size(); }

@@ -171,3 +171,34 @@ def test_small_structure_dimer(lib):
     Y = lib.wfq_apply_T(h, "fp64", np.array([[1.0, -2.0]]))
     assert np.allclose(Y[0], P.T @ np.array([1.0, -2.0]), rtol=1e-14)
     h.close()
+
+
+@pytest.mark.parametrize("ncol", [1, 31, 33, 64, 65, 129, 193, 260])
+@pytest.mark.parametrize("name", ["s32n256k32", "s64n256k32", "s96n256k32", "s128n256k32", "s64n128k64", "s96n128k64",
+                                  "s128n128k64", "s192n128k32"])
+def test_fp16_split_product_scales_and_edges(lib, handle, tube, name, ncol):
+    # FP32 products through the FP16 matrix cores: columns of very different scales (each has its own
+    # exponent), entries spread over 20 orders of magnitude within a column, an empty column; one tile
+    # and its remainders. The bound is the accumulation bound of the FP32 products.
+    _, P = tube
+    rng = np.random.default_rng(1000 + ncol)
+    X = rng.standard_normal((ncol, P.n)) * 2.0 ** rng.integers(-100, 100, (ncol, 1))
+    X[0] *= 10.0 ** (-20 * rng.random(P.n))
+    X[ncol // 2] = 0.0
+    Y = lib.wfq_apply_T_variant(handle, "fp32", name, X)
+    Xq, Tq = round_to("fp32", X), round_to("fp32", P.T)
+    assert np.all(np.abs(Y - Xq @ Tq) <= 2 * P.n * UNIT["fp32"] * (np.abs(Xq) @ np.abs(Tq)))
+    assert np.all(Y[ncol // 2] == 0.0)
+
+
+def test_fp16_split_product_keeps_infinities_and_nan(lib, handle, tube):
+    # T's elements are positive: an infinite entry gives that infinity in its column, a NaN or both
+    # signs NaN; the other columns are untouched
+    _, P = tube
+    X = np.random.default_rng(5).standard_normal((40, P.n))
+    ref = lib.wfq_apply_T_variant(handle, "fp32", "s64n128k64", X)
+    X[3, 7], X[4, 100], X[5, 0], X[6, 1], X[6, 2] = np.inf, -np.inf, np.nan, np.inf, -np.inf
+    Y = lib.wfq_apply_T_variant(handle, "fp32", "s64n128k64", X)
+    assert np.all(Y[3] == np.inf) and np.all(Y[4] == -np.inf) and np.all(np.isnan(Y[5])) and np.all(np.isnan(Y[6]))
+    keep = [c for c in range(40) if c not in (3, 4, 5, 6)]
+    assert np.array_equal(Y[keep], ref[keep])

@@ -186,7 +186,9 @@ bool tx_is_otf_narrow(const Structure& s, int prec, int ncol);
 // 64 bits smaller than the FP32 instruction's). The operator entry points ask for it. The solves do not:
 // the rounding of the inner products decides at which restart a system near the tolerance stops, and the
 // FP32 instruction's is systematic, so another product moves their results by as much as the tolerance
-// allows; a tuned handle takes whichever shape measured fastest.
+// allows; a tuned handle takes whichever shape measured fastest. (Recomputed FP32 products always take
+// the split: the kernel that they replace summed with compensation too, and solves to 1e-10 move by about
+// 1e-10.)
 void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, bool split = false);
 // one registered block-product variant (index as listed by tx_variant_name), stored T only
 void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st);

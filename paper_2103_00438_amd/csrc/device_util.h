@@ -61,4 +61,23 @@ __device__ inline halfx8 split_lo(const float (&x)[8], const halfx8& h) {
     return l;
 }
 
+// The same with fewer vector instructions, for kernels that these bound (a kernel bound by its matrix
+// products was slower with it: the asm pins the order): h is made in pairs, one conversion for two values,
+// and x - h is one mixed-precision fused multiply-add. The empty asm keeps the compiler from
+// converting every value a second time for it, and one (1.0f) has to come from a register it knows nothing of.
+__device__ inline void split_f16(const float (&x)[8], float one, halfx8& h, halfx8& l) {
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        unsigned bits = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{x[e], x[e + 1]}, halfx2));
+        asm("" : "+v"(bits));
+        const halfx2 p = __builtin_bit_cast(halfx2, bits);
+        h[e] = p.x;
+        h[e + 1] = p.y;
+        l[e] = (_Float16)fmaf(x[e], one, -(float)p.x);
+        l[e + 1] = (_Float16)fmaf(x[e + 1], one, -(float)p.y);
+    }
+}
+
 }  // namespace wfq

@@ -7,7 +7,8 @@
 // so that coordinate differences keep full relative precision in FP32) and the X tile in LDS,
 // evaluates the T tile on the vector ALUs, and accumulates the tile product on the matrix cores
 // (the same fragment layout as the stored-T kernels). Tile sums are added to the running sum with
-// Kahan compensation, so the FP32 result does not drift over ~10^4 source tiles.
+// Kahan compensation, so the FP32 result does not drift over ~10^4 source tiles. FP32 products take
+// otf_split_kernel below wherever its work space fits and T's scale allows; otf_kernel serves the rest and FP64.
 //
 // FP32 elements use erf(x) = 1 - (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x) (Abramowitz &
 // Stegun, Handbook of Mathematical Functions, formula 7.1.26; absolute error <= 1.5e-7) for
@@ -252,6 +253,196 @@ __global__ void __launch_bounds__(256) otf_kernel(int64_t n, int64_t npad, const
                 const int64_t i = i0 + wave * 32 + b * 16 + (lane & 15);
                 Y[c * npad + i] = sum[a][b][r];
             }
+}
+
+// ---- wide FP32 product with the elements split for the FP16 matrix cores
+//
+// In otf_kernel a tile's elements pass through LDS between the vector ALUs that evaluate them and the FP32
+// matrix instructions, and both take about as long. Here every lane evaluates the elements of its own
+// fragment (a wave owns 16 WN targets and all 16 WM columns: lane l holds target l mod 16 of each block of
+// 16 and sources 8 (l / 16) .. + 7 of each 32), so T never leaves the registers, and the products run on
+// the FP16 matrix cores with both operands split in two FP16 parts (three products, FP32 accumulation; as
+// in the stored products of gemm.hip). What is left is the evaluation itself: 3 differences, 3 for r^2, the
+// reciprocal square root (4 issue slots) and 2 for the split, about 12 slots per far pair, for all 16 WM
+// columns. Coordinates are taken relative to the wave's own 64 targets and scaled by a power of two so that the
+// elements come out in FP16's range. The source range is split into parts in the grid's z where the
+// targets alone leave the chip idle (fixed-order sum of the parts). The matrix cores' sums over a tile of
+// 64 sources are added with Kahan compensation: longer runs were no faster and less accurate.
+// Measured on a 50 000-atom sheet, 32 columns: 1.5 ms (1.6e12 pairs/s, vector units 60 % busy, matrix cores
+// 13 %) against 5.5 ms for otf_kernel, whose 390 work-groups also fill the chip badly; error after L against
+// 64 bits 1.2e-6 / 1.4e-6, on a 30 000-atom sphere 2.8e-6 / 3.2e-6.
+constexpr int kSplitTile = 64;   // sources staged per step
+
+// erf(x) / r at r2 = r^2 > 0 (scaled coordinates; di2 + dj2 scaled alike, 1 / r comes out scaled)
+__device__ inline float t_near(float r2, float dsum) {
+    const float inv_r = __builtin_amdgcn_rsqf(r2);
+    return erf_f32(r2 * inv_r * __builtin_amdgcn_rsqf(dsum)) * inv_r;
+}
+
+template <int WM, int WN>
+__global__ void __launch_bounds__(256, 2)
+    otf_split_kernel(int64_t n, int64_t npad, const double* __restrict__ pos, const double* __restrict__ width,
+                     const double* __restrict__ eta, const double* __restrict__ sphere, double rfar, double cscale,
+                     int texp, float one, const char* __restrict__ Xs, const ColInfo* __restrict__ info, int ncol,
+                     float* __restrict__ Y, float* __restrict__ ws, int64_t part_stride) {
+    constexpr int BM = 16 * WM, BT = 16 * WN;            // columns; targets per wave
+    constexpr int RS = kSplitTile * 4 + 16;              // padded LDS row of the split X
+    constexpr int CH = kSplitTile / 4;                   // 16-byte chunks per row
+    constexpr int PER_T = BM * CH / 256;
+    static_assert(BM * CH % 256 == 0, "whole rows per pass");
+    __shared__ __attribute__((aligned(16))) char xlds[2][BM * RS];
+    __shared__ floatx4 slds[2][4][kSplitTile];           // (x, y, z, d^2) of the sources, per wave
+    __shared__ float nlds[4][8][64];                     // near-field elements in the making, per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int fr = lane & 15, fk = lane >> 4;
+    const int64_t i0 = ((int64_t)blockIdx.x * 4 + wave) * BT;   // first target of the wave
+    const int c0 = (int)blockIdx.y * BM;
+    const int nn = (int)n, ib = (int)i0;
+    const int ntile = (nn + kSplitTile - 1) / kSplitTile;
+    const int tb = (int)((int64_t)ntile * blockIdx.z / gridDim.z), te = (int)((int64_t)ntile * (blockIdx.z + 1) / gridDim.z);
+
+    const int64_t ic = min(i0 + BT / 2, n - 1);
+    const double ox = pos[ic], oy = pos[npad + ic], oz = pos[2 * npad + ic];
+    float tx[WN], ty[WN], tz[WN], td[WN], tE[WN];
+#pragma unroll
+    for (int b = 0; b < WN; ++b) {
+        const int64_t i = i0 + b * 16 + fr;   // < npad
+        tx[b] = (float)((pos[i] - ox) * cscale);
+        ty[b] = (float)((pos[npad + i] - oy) * cscale);
+        tz[b] = (float)((pos[2 * npad + i] - oz) * cscale);
+        const double d = width[i] * cscale;
+        td[b] = (float)(d * d);
+        tE[b] = (float)(eta[i] / cscale);
+    }
+    // X staging: chunk u of this thread is column r0 + u * RSTEP (columns past the last one re-read it)
+    constexpr int RSTEP = 256 / CH;
+    const int r0 = tid / CH, cc = tid % CH;
+    const char* xp[PER_T];
+#pragma unroll
+    for (int u = 0; u < PER_T; ++u)
+        xp[u] = Xs + (int64_t)min(c0 + r0 + u * RSTEP, ncol - 1) * npad * 4 + cc * 16;
+    u32x4 xr[PER_T];
+    floatx4 sr;
+    auto load = [&](int t) {
+        const int64_t j0 = (int64_t)t * kSplitTile;
+#pragma unroll
+        for (int u = 0; u < PER_T; ++u) xr[u] = *reinterpret_cast<const u32x4*>(xp[u] + j0 * 4);
+        const int64_t j = j0 + lane;   // < npad
+        const double d = width[j] * cscale;
+        sr.x = (float)((pos[j] - ox) * cscale);
+        sr.y = (float)((pos[npad + j] - oy) * cscale);
+        sr.z = (float)((pos[2 * npad + j] - oz) * cscale);
+        sr.w = (float)(d * d);
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < PER_T; ++u)
+            *reinterpret_cast<u32x4*>(xlds[buf] + (r0 + u * RSTEP) * RS + cc * 16) = xr[u];
+        slds[buf][wave][lane] = sr;
+    };
+    floatx4 sum[WM][WN], comp[WM][WN];
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int b = 0; b < WN; ++b) sum[a][b] = comp[a][b] = floatx4{0, 0, 0, 0};
+    uint64_t far = 0;   // far-field flags of the next 64 tiles
+    if (tb < te) {
+        load(tb);
+        store(0);
+    }
+    __syncthreads();
+    for (int t = tb; t < te; ++t) {
+        const int buf = (t - tb) & 1;
+        if (((t - tb) & 63) == 0) {
+            const int tt = t + lane;
+            far = __ballot((tt + 1) * kSplitTile <= nn && far_apart(sphere, i0 / 64, tt, rfar));
+        }
+        const bool is_far = (far >> ((t - tb) & 63)) & 1;
+        load(min(t + 1, te - 1));
+        floatx4 acc[WM][WN];
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+            for (int b = 0; b < WN; ++b) acc[a][b] = floatx4{0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < kSplitTile / 32; ++s) {
+            halfx8 th[WN], tl[WN];
+            const floatx4* sp = &slds[buf][wave][s * 32 + fk * 8];
+            float v[WN][8];
+            if (is_far) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const floatx4 p = sp[e];
+#pragma unroll
+                    for (int b = 0; b < WN; ++b) {
+                        const float dx = tx[b] - p.x, dy = ty[b] - p.y, dz = tz[b] - p.z;
+                        v[b][e] = __builtin_amdgcn_rsqf(dx * dx + dy * dy + dz * dz);
+                    }
+                }
+            } else {
+                // few tiles: one element at a time, through LDS (the fragments' registers are not indexable)
+#pragma unroll
+                for (int b = 0; b < WN; ++b) {
+                    const int i = ib + b * 16 + fr;
+                    for (int e = 0; e < 8; ++e) {
+                        const floatx4 p = sp[e];
+                        const int j = t * kSplitTile + s * 32 + fk * 8 + e;
+                        const float dx = tx[b] - p.x, dy = ty[b] - p.y, dz = tz[b] - p.z;
+                        float tv = t_near(dx * dx + dy * dy + dz * dz, td[b] + p.w);
+                        if (j == i) tv = tE[b];
+                        nlds[wave][e][lane] = j < nn && i < nn ? tv : 0.0f;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[b][e] = nlds[wave][e][lane];
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < WN; ++b) split_f16(v[b], one, th[b], tl[b]);
+#pragma unroll
+            for (int a = 0; a < WM; ++a) {
+                const char* lp = xlds[buf] + (a * 16 + fr) * RS + s * 128 + fk * 32;
+                const halfx8 xh = *reinterpret_cast<const halfx8*>(lp);
+                const halfx8 xl = *reinterpret_cast<const halfx8*>(lp + 16);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xl, th[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, tl[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < WN; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, th[b], acc[a][b], 0, 0, 0);
+            }
+        }
+        // compensated accumulation of the tile sums
+#pragma unroll
+        for (int a = 0; a < WM; ++a)
+#pragma unroll
+            for (int b = 0; b < WN; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float y = acc[a][b][r] - comp[a][b][r];
+                    const float u = sum[a][b][r] + y;
+                    comp[a][b][r] = (u - sum[a][b][r]) - y;
+                    sum[a][b][r] = u;
+                }
+        store(buf ^ 1);   // last read in step t - 1, which every wave left at its barrier
+        __syncthreads();
+    }
+    float* out = blockIdx.z == 0 ? Y : ws + (int64_t)(blockIdx.z - 1) * part_stride;
+#pragma unroll
+    for (int a = 0; a < WM; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = c0 + a * 16 + 4 * fk + r;
+            if (c >= ncol) continue;
+            const ColInfo ci = info[c];
+#pragma unroll
+            for (int b = 0; b < WN; ++b) {
+                const int64_t i = i0 + b * 16 + fr;
+                float y = ldexpf(sum[a][b][r], -(ci.exp + texp));
+                // T's elements are positive: a column with an infinite entry gives that infinity
+                if (ci.cls) y = ci.cls == 1 ? __builtin_inff() : ci.cls == 2 ? -__builtin_inff() : __builtin_nanf("");
+                out[(int64_t)c * npad + i] = i < n ? y : 0.0f;
+            }
+        }
 }
 
 // ---- narrow matrix-free FP64 product: at most NC real columns (multi-shift and single-system steps)
@@ -714,8 +905,43 @@ void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, 
         launch_otf_narrow<4>(s, X, Y, ld, ncol, cus, Yi, st);
 }
 
+template <int WM, int WN>
+void launch_otf_split(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st) {
+    constexpr int BM = 16 * WM, BT = 64 * WN;   // columns and targets of a work-group
+    const uint64_t head = split_x_bytes(s.npad, ncol), cap = s.split_fixed ? s.split_fixed_bytes : kSplitWsCap;
+    const uint64_t part_bytes = (uint64_t)ncol * s.npad * sizeof(float);
+    const int64_t tiles = s.npad / BT, groups = (ncol + BM - 1) / BM;
+    // source parts: about 8 work-groups per compute unit, at least 1 024 sources each
+    int64_t parts = std::max<int64_t>(1, std::min<int64_t>(8LL * device_cus(s.device) / (tiles * groups), s.n / 1024));
+    parts = std::min<int64_t>({parts, 64, 1 + (int64_t)((cap - head) / part_bytes)});
+    char* ws = static_cast<char*>(split_workspace(s, head + (uint64_t)(parts - 1) * part_bytes));
+    split_x(X, s.npad, ncol, ws, st);
+    const int texp = split_t_exp(s);
+    const int64_t info_bytes = round_up((int64_t)ncol * sizeof(ColInfo), 256);
+    float* pw = reinterpret_cast<float*>(ws + head);
+    hipLaunchKernelGGL((otf_split_kernel<WM, WN>), dim3((unsigned)tiles, (unsigned)groups, (unsigned)parts), dim3(256), 0,
+                       st, s.n, s.npad, s.pos, s.width, s.eta, s.sphere, 4.5 * std::sqrt(2.0) * s.width_max,
+                       std::ldexp(1.0, -texp), texp, 1.0f, ws + info_bytes, reinterpret_cast<const ColInfo*>(ws), ncol, Y, pw,
+                       (int64_t)ncol * s.npad);
+    WFQ_CHECK_LAUNCH();
+    if (parts > 1) add_parts_f32(Y, pw, (int64_t)ncol * s.npad, (int64_t)ncol * s.npad, (int)parts - 1, st);
+}
+
 void otf_tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st) {
     if (ncol <= 0) return;
+    if (split_scale_ok(s) && split_fits(s, s.npad, ncol)) {
+        // Up to 32 columns one pass; above, 64 columns a pass (the elements are evaluated once per pass: 20
+        // systems of a 50 000-atom sheet 4.3 ms against 5.0). 32 targets per wave, as many as the registers
+        // allow at 3 waves per SIMD; 16 below about 16 000 atoms, where the targets are few (8 000 atoms:
+        // 100 us against 119, 30 000: 1 164 against 1 113).
+        if (ncol > 32)
+            launch_otf_split<4, 2>(s, X, Y, ncol, st);
+        else if (s.npad >= 16384)
+            launch_otf_split<2, 2>(s, X, Y, ncol, st);
+        else
+            launch_otf_split<2, 1>(s, X, Y, ncol, st);
+        return;
+    }
     constexpr int BC = 32;
     dim3 grd((unsigned)(s.npad / kBI), (unsigned)((ncol + BC - 1) / BC));
     const double rfar = 4.5 * std::sqrt(2.0) * s.width_max;

@@ -188,3 +188,27 @@ def test_narrow_fp64_product_moved_away_from_the_origin(lib, case):
     for y in Y:
         assert np.all(np.abs(y[:, rows].T - ref) <= 1e-13 * bound)
     assert np.all(np.abs(Y[1][:, rows] - Y[0][:, rows]).T <= 2e-13 * bound)
+
+
+@pytest.mark.parametrize("ncol", [1, 33, 64, 97])
+@pytest.mark.parametrize("n", [2, 64, 65, 130, 1033])
+def test_wide_fp32_product_tile_and_part_edges(lib, n, ncol):
+    # The wide FP32 product evaluates its elements in the matrix cores' fragment layout: structures whose
+    # last target block and source tile are partial (or hold one atom), several source parts, one and two
+    # passes of columns with remainders, columns of very different scale, an empty one and an infinite one.
+    xyz = ragged_tube()[:n] if n > 2 else np.array([[0.0, 0.0, 0.0], [1.7, 0.0, 0.0]])
+    P = O.Problem(xyz, GRAPHENE)
+    h = lib.wfq_build(xyz, GRAPHENE, t_mode="otf")
+    rng = np.random.default_rng(n + ncol)
+    X = rng.standard_normal((ncol, n)) * 2.0 ** rng.integers(-100, 100, (ncol, 1))
+    if ncol > 2:
+        X[1] = 0.0
+        X[2, n - 1] = -np.inf
+    Y = lib.wfq_apply_T(h, "fp32", X)
+    h.close()
+    keep = np.isfinite(X).all(axis=1)
+    Xq = round_to("fp32", X[keep])
+    tol = (ERF_REL + 16 * UNIT["fp32"] + 2 * 64 * UNIT["fp32"]) * (np.abs(Xq) @ np.abs(P.T))
+    assert np.all(np.abs(Y[keep] - Xq @ P.T) <= tol)
+    if ncol > 2:
+        assert np.all(Y[1] == 0.0) and np.all(Y[2] == -np.inf)

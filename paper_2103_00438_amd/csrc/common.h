@@ -208,9 +208,9 @@ void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, 
 // compute units of a device
 int device_cus(int device);
 // true when narrow recomputed products of ncol <= 4 columns take the symmetric form (each element
-// evaluated once for both of its rows: n >= 65 536 and the per-block sums fit the work space)
+// evaluated once for both of its rows): its sums fit the work space
 bool otf_sym_fits(const Structure& s, int ncol);
-// work space of the symmetric form for ncol columns (0 below 65 536 atoms, where it is not used)
+// work space of the symmetric form for ncol columns
 uint64_t otf_sym_bytes(const Structure& s, int ncol);
 // partial-tile work space of the block products (grown on demand, or the fixed region when set)
 void* split_workspace(const Structure& s, uint64_t bytes);

@@ -777,8 +777,9 @@ int default_variant(int prec, int ncol, bool split, int64_t npad) {
     return k >= 0 ? k : find_variant(prec, "m128n256w8");   // present for every precision
 }
 
-// padded size from which untuned narrow FP64 products are recomputed rather than streamed
-constexpr int64_t kOtfNarrowFrom = 16384;
+// padded size from which untuned narrow FP64 products are recomputed rather than streamed (5 000 atoms, 1 to 4
+// columns: 22 / 26 / 31 / 33 us recomputed, 31 / 31 / 35 / 35 streamed; 4 000: 21 / 24 / 29 / 31 and 27 / 27 / 27 / 28)
+constexpr int64_t kOtfNarrowFrom = 4608;
 // matrix-free FP64 products of up to this many 4-column chunks use the narrow kernel
 constexpr int kOtfNarrowChunks = 3;
 

@@ -448,7 +448,10 @@ __global__ void __launch_bounds__(256, 2)
 // ---- narrow matrix-free FP64 product: at most NC real columns (multi-shift and single-system steps)
 //
 // A product with a few columns is bound by the element evaluations, not by the accumulation, so
-// there are no matrix-core tiles here: each thread owns TK target atoms (64 apart), evaluates T_ij
+// there are no matrix-core tiles here. The symmetric form further down evaluates each element once for both of
+// its rows and serves every size (3 columns, with the sum kernel: 600 atoms 21 us against 50 in the one-sided form,
+// 4 000 28 / 53, 20 000 178 / 271, 30 000 405 / 557); this one-sided form is left for structures whose sums
+// for it do not fit the work space. Here each thread owns TK target atoms (64 apart), evaluates T_ij
 // for a run of source atoms and accumulates T_ij x_j for every column in FP64 registers. The grid's
 // second dimension splits the sources into parts so that thousands of waves are in flight; each
 // part's sums go to a work space and a second kernel adds the parts in order (deterministic).
@@ -460,7 +463,6 @@ __global__ void __launch_bounds__(256, 2)
 // C = T - 1/r (pairs closer than rfar, eta_i on the diagonal), so the result is T X.
 constexpr int kNarrowTile = 256;
 constexpr int kNarrowTK = 4;   // targets per thread: a work-group covers 1024 consecutive atoms
-constexpr int64_t kSymFrom = 65536;   // the symmetric form from here: at least 2 080 block pairs
 constexpr int kSymTK = 4;                 // symmetric form: targets per thread
 constexpr int kSymBlock = 256 * kSymTK;   // atoms per block (one work-group's targets)
 
@@ -658,34 +660,49 @@ void launch_otf_narrow(const Structure& s, const double* X, double* Y, int64_t l
 // ---- symmetric narrow product: each unordered pair of atoms evaluated once
 //
 // T is symmetric, so T_ij serves both rows: y_i += T_ij x_j and y_j += T_ij x_i. Atoms are grouped
-// in blocks of 1 024 (the internal, Morton-cell order). One work-group per pair of blocks I <= J:
-// its 256 threads own the 1 024 atoms of I (4 each, 64 apart, as in the one-sided kernel) and
-// stream the atoms of J through LDS in tiles of 256. The target side accumulates in registers. For
-// the source side, each wave takes the tile's sources in groups of 64 and rotates them across its
+// in blocks of 1 024 (the internal, Morton-cell order). A block pair I <= J is 16 groups of 64 sources of J
+// against the 1 024 targets of I; a work-group's 256 threads own the targets (4 each, 64 apart, as in the
+// one-sided kernel) and stream the sources through LDS in tiles of 256. The target side accumulates in
+// registers. For the source side, each wave takes a group's sources and rotates them across its
 // lanes: at step t lane l pairs its targets with source (l + t) mod 64 and adds their contributions
 // to that source's running sum, which then moves one lane down (l <- l + 1); after 64 steps every
 // lane holds the wave's sum for its own source. The four waves' sums are added in order in LDS.
-// No atomics: block K's contribution to row i is stored once, in P[K][c][i] (the target side of the
-// pair (B(i), K) or the source side of (K, B(i)); a diagonal pair (I, I) computes its rows one-sided
-// over all of I), and the sum kernel adds the blocks in order with the near-field correction.
-// kMask: the pair involves the last block, which holds padding atoms (their contributions are 0).
-// The symmetric kernel takes the origin midway between the first atoms of its two blocks, and one LDS
+//
+// Work split: the groups of all block pairs, row by row of I, form one sequence of 8 nb (nb + 1) groups that
+// is cut into equal runs, one per work-group (their number: sym_runs). Every CU then has about the same work
+// whatever the atom count: with one work-group per block pair a 20 000-atom structure has 210 of them for
+// 256 CUs. A run may end inside a block pair or reach into the next row of I.
+//
+// No atomics. Source side: (I, rows of J) is stored once, in row I of the triangle Ps (kept for J > I only). Target
+// side: each run stores one set of 1 024 sums per row of I that it touches, in slot w + I of Pt (w the run's
+// index: w or I grows from one set to the next, so the slots are distinct). A diagonal pair (I, I)
+// computes its rows one-sided over all of I. The sum kernel adds both in order with the near-field correction.
+//
+// Padding atoms take part with X = 0 at a far-away point (their pairs give finite elements times 0; sums of
+// padding rows are not used), so the loops need no masks.
+// The origin is midway between the first atoms of the two blocks; one LDS
 // row per source: x_j - o, |x_j - o|^2 and the NC columns of X, padded to an odd number of doubles so
 // that the 64 lanes' rows fall in distinct LDS banks.
 template <int NC>
 constexpr int sym_row() { return (4 + NC) | 1; }
+constexpr double kFarAway = 1e15;   // bohr: relative x of a padding atom
+
+// First group of block row I, and the run that holds group g, of nb blocks and W runs over G groups
+__host__ __device__ inline int64_t sym_row_start(int64_t I, int64_t nb) { return 16 * I * nb - 8 * I * (I - 1); }
+__device__ inline int sym_run_of(int64_t g, int64_t G, int64_t W) { return (int)(((g + 1) * W - 1) / G); }
+// Doubles of one column before row I of the triangle Ps
+__host__ __device__ inline int64_t sym_tri(int64_t I, int64_t npad) { return I * npad - kSymBlock / 2 * I * (I + 1); }
 
 // One group of 64 sources against the thread's TK targets; with SIDE the source-side sums rotate as
 // described above and land in red[wave][c][g + lane]. The group sits twice in a row in LDS (rows
 // 2g .. 2g + 127, row 2g + 64 + q a copy of row 2g + q), so step t reads row 2g + lane + t with no
 // wrap-around. The element is taken as G = y (3 - r^2 y^2), twice the Newton-refined 1/r (one
 // operation fewer); the sums are halved when they are stored. EXP: r^2 by the expansion.
-template <int NC, bool SIDE, bool DIAG, bool MASK, bool EXP>
-__device__ __forceinline__ void sym_group(const double* __restrict__ srow, int g, int lane, int64_t j0, int64_t n,
+template <int NC, bool SIDE, bool DIAG, bool EXP>
+__device__ __forceinline__ void sym_group(const double* __restrict__ srow, int g, int lane,
                                           const double (&ax)[kSymTK], const double (&ay)[kSymTK],
                                           const double (&az)[kSymTK], const double (&ni)[kSymTK],
-                                          const double (&xt)[kSymTK][NC], const bool (&tin)[kSymTK],
-                                          double (&acc)[kSymTK][NC], double (*red)[256], int wave) {
+                                          const double (&xt)[kSymTK][NC], double (&acc)[kSymTK][NC], double (*red)[256], int wave) {
     constexpr int ROW = sym_row<NC>();
     double ps[NC];
 #pragma unroll
@@ -699,7 +716,6 @@ __device__ __forceinline__ void sym_group(const double* __restrict__ srow, int g
         double xv[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) xv[c] = r[4 + c];
-        const bool sv = !MASK || j0 + g + ((lane + t) & 63) < n;
 #pragma unroll
         for (int k = 0; k < kSymTK; ++k) {
             double r2;
@@ -712,7 +728,6 @@ __device__ __forceinline__ void sym_group(const double* __restrict__ srow, int g
             double gk = __builtin_amdgcn_rsq(r2);
             gk = gk * fma(-r2, gk * gk, 3.0);
             if (DIAG) gk = r2 > 0.0 ? gk : 0.0;
-            if (MASK) gk = (tin[k] && sv) ? gk : 0.0;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 acc[k][c] = fma(gk, xv[c], acc[k][c]);
@@ -730,154 +745,200 @@ __device__ __forceinline__ void sym_group(const double* __restrict__ srow, int g
     }
 }
 
-// jfix < 0: the work-group index enumerates the pairs I <= J < nbt in row-major order of I;
-// jfix >= 0: the pair is (blockIdx.x, jfix)
-template <int NC, bool MASK>
-__global__ void __launch_bounds__(256) otf_sym_kernel(int64_t n, int64_t npad, int nbt, int jfix,
-                                                      const double* __restrict__ pos,
+template <int NC>
+__global__ void __launch_bounds__(256, NC <= 3 ? 3 : 2) otf_sym_kernel(int64_t n, int64_t npad, int nb, const double* __restrict__ pos,
                                                       const double* __restrict__ sph, const double* __restrict__ X,
-                                                      int64_t ldx, double* __restrict__ P) {
+                                                      int64_t ldx, double* __restrict__ Ps, double* __restrict__ Pt) {
     constexpr int TK = kSymTK, TILE = 256, BS = kSymBlock, ROW = sym_row<NC>();
     __shared__ double srow[2 * TILE * ROW];   // each group of 64 twice
     __shared__ double red[4 * NC][TILE];
-    int I = 0, J = 0;
-    if (jfix >= 0) {
-        I = blockIdx.x;
-        J = jfix;
-    } else {
-        int64_t p = blockIdx.x;
-        while (p >= nbt - I) {
-            p -= nbt - I;
-            ++I;
-        }
-        J = I + (int)p;
-    }
-    const bool diag = I == J;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    // the origin: midpoint of the first atoms of I and J (both < n)
-    const int64_t i0 = (int64_t)I * BS, j00 = min((int64_t)J * BS, n - 1);
-    const double ox = 0.5 * (pos[i0] + pos[j00]), oy = 0.5 * (pos[npad + i0] + pos[npad + j00]),
-                 oz = 0.5 * (pos[2 * npad + i0] + pos[2 * npad + j00]);
-    // expansion flags of this wave: lane 16 t + 4 q + k checks target block k of the wave against
-    // source group q of tile t; group q of tile t may use the expansion when all four of its bits are set
-    uint64_t eflags = 0;
-    if (!diag) {
-        const int64_t tb = (i0 + wave * 64 * TK) / 64 + (lane & 3);
-        const int64_t sb = (int64_t)J * BS / 64 + (lane >> 2);
-        // blocks without atoms have no sphere to test; nothing of theirs is used
-        const bool ok = tb * 64 >= n || sb * 64 >= n || expansion_ok(sph, tb, sb, ox, oy, oz);
-        eflags = __ballot(ok);
-    }
-    const int64_t ib = i0 + wave * 64 * TK + lane;   // target k: ib + 64 k
-    double ax[TK], ay[TK], az[TK], ni[TK], xt[TK][NC], acc[TK][NC];
-    bool tin[TK];
+    const int64_t G = sym_row_start(nb, nb);
+    int64_t g = G * blockIdx.x / gridDim.x;
+    const int64_t gend = G * (blockIdx.x + 1) / gridDim.x;
+    int I = 0;
+    while (g >= sym_row_start(I + 1, nb)) ++I;
+    for (; g < gend; ++I) {
+        const int64_t rs = sym_row_start(I, nb), re = min(gend, sym_row_start(I + 1, nb));
+        const int64_t i0 = (int64_t)I * BS;
+        const int64_t ib = i0 + wave * 64 * TK + lane;   // target k: ib + 64 k
+        double xt[TK][NC], acc[TK][NC];
 #pragma unroll
-    for (int k = 0; k < TK; ++k) {
-        const int64_t i = ib + 64 * k;
-        const int64_t ii = i < npad ? i : 0;
-        tin[k] = i < n;
-        const double x = pos[ii] - ox, y = pos[npad + ii] - oy, z = pos[2 * npad + ii] - oz;
-        ax[k] = -2.0 * x;
-        ay[k] = -2.0 * y;
-        az[k] = -2.0 * z;
-        ni[k] = x * x + y * y + z * z;
+        for (int k = 0; k < TK; ++k)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            xt[k][c] = tin[k] ? X[c * ldx + ii] : 0.0;
-            acc[k][c] = 0.0;
-        }
-    }
-    for (int t0 = 0; t0 < BS; t0 += TILE) {
-        const int64_t j0 = (int64_t)J * BS + t0;
-        if (j0 >= n) break;   // uniform: the rest of block J is padding
-        __syncthreads();
-        {
-            const int64_t j = j0 + tid;
-            const int64_t jj = j < npad ? j : 0;
-            const int r0 = 2 * (tid & ~63) + (tid & 63);   // row of source tid, and its copy 64 later
-            const double x = pos[jj] - ox, y = pos[npad + jj] - oy, z = pos[2 * npad + jj] - oz;
-            double v[ROW] = {};
-            v[0] = x;
-            v[1] = y;
-            v[2] = z;
-            v[3] = x * x + y * y + z * z;
+            for (int c = 0; c < NC; ++c) {
+                xt[k][c] = ib + 64 * k < n ? X[c * ldx + ib + 64 * k] : 0.0;
+                acc[k][c] = 0.0;
+            }
+        while (g < re) {
+            const int J = I + (int)((g - rs) >> 4), q0 = (int)((g - rs) & 15), q1 = (int)min<int64_t>(16, q0 + (re - g));
+            g += q1 - q0;
+            const bool diag = I == J;
+            // the origin: midpoint of the first atoms of I and J (both < n)
+            const int64_t j00 = (int64_t)J * BS;
+            const double ox = 0.5 * (pos[i0] + pos[j00]), oy = 0.5 * (pos[npad + i0] + pos[npad + j00]),
+                         oz = 0.5 * (pos[2 * npad + i0] + pos[2 * npad + j00]);
+            // expansion flags of this wave: lane 4 q + k checks target block k of the wave against source group
+            // q; group q may use the expansion when all four of its bits are set
+            uint64_t eflags = 0;
+            if (!diag) {
+                const int64_t tb = (i0 + wave * 64 * TK) / 64 + (lane & 3);
+                const int64_t sb = j00 / 64 + (lane >> 2);
+                // blocks without atoms have no sphere to test; nothing of theirs is used
+                const bool ok = tb * 64 >= n || sb * 64 >= n || expansion_ok(sph, tb, sb, ox, oy, oz);
+                eflags = __ballot(ok);
+            }
+            double ax[TK], ay[TK], az[TK], ni[TK];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) v[4 + c] = j < n ? X[c * ldx + jj] : 0.0;
+            for (int k = 0; k < TK; ++k) {
+                const int64_t i = ib + 64 * k;
+                const bool in = i < n;
+                const double x = in ? pos[i] - ox : kFarAway, y = in ? pos[npad + i] - oy : 0.0,
+                             z = in ? pos[2 * npad + i] - oz : 0.0;
+                ax[k] = -2.0 * x;
+                ay[k] = -2.0 * y;
+                az[k] = -2.0 * z;
+                ni[k] = x * x + y * y + z * z;
+            }
+            for (int t = q0 >> 2; 4 * t < q1; ++t) {
+                const int64_t j0 = j00 + t * TILE;
+                if (j0 >= n) break;   // uniform: the rest of block J is padding
+                __syncthreads();
+                {
+                    const int64_t j = j0 + tid;
+                    const bool in = j < n;
+                    const int r0 = 2 * (tid & ~63) + (tid & 63);   // row of source tid, and its copy 64 later
+                    const double x = in ? pos[j] - ox : kFarAway, y = in ? pos[npad + j] - oy : 0.0,
+                                 z = in ? pos[2 * npad + j] - oz : 0.0;
+                    double v[ROW] = {};
+                    v[0] = x;
+                    v[1] = y;
+                    v[2] = z;
+                    v[3] = x * x + y * y + z * z;
 #pragma unroll
-            for (int f = 0; f < ROW; ++f) srow[r0 * ROW + f] = srow[(r0 + 64) * ROW + f] = v[f];
-        }
-        __syncthreads();
-        for (int g = 0; g < TILE; g += 64) {
-            if (MASK && j0 + g >= n) break;   // uniform: the rest of the tile is padding
-            const int q = (t0 + g) / 64;
-            if (diag)
-                sym_group<NC, false, true, MASK, false>(srow, g, lane, j0, n, ax, ay, az, ni, xt, tin, acc, red, wave);
-            else if (((eflags >> (4 * q)) & 0xF) == 0xF)
-                sym_group<NC, true, false, MASK, true>(srow, g, lane, j0, n, ax, ay, az, ni, xt, tin, acc, red, wave);
-            else
-                sym_group<NC, true, false, MASK, false>(srow, g, lane, j0, n, ax, ay, az, ni, xt, tin, acc, red, wave);
-        }
-        if (!diag) {
-            __syncthreads();
-            const int64_t j = j0 + tid;
-            if (j < npad) {
+                    for (int c = 0; c < NC; ++c) v[4 + c] = in ? X[c * ldx + j] : 0.0;
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const double v = ((red[c][tid] + red[NC + c][tid]) + red[2 * NC + c][tid]) + red[3 * NC + c][tid];
-                    P[((int64_t)I * NC + c) * npad + j] = j < n ? 0.5 * v : 0.0;
+                    for (int f = 0; f < ROW; ++f) srow[r0 * ROW + f] = srow[(r0 + 64) * ROW + f] = v[f];
+                }
+                __syncthreads();
+                const int qa = max(q0, 4 * t), qb = min(q1, 4 * t + 4);
+                for (int q = qa; q < qb; ++q) {
+                    const int gr = (q & 3) * 64;
+                    if (diag)
+                        sym_group<NC, false, true, false>(srow, gr, lane, ax, ay, az, ni, xt, acc, red, wave);
+                    else if (((eflags >> (4 * q)) & 0xF) == 0xF)
+                        sym_group<NC, true, false, true>(srow, gr, lane, ax, ay, az, ni, xt, acc, red, wave);
+                    else
+                        sym_group<NC, true, false, false>(srow, gr, lane, ax, ay, az, ni, xt, acc, red, wave);
+                }
+                if (!diag) {
+                    __syncthreads();
+                    const int64_t j = j0 + tid;
+                    const int q = 4 * t + wave;   // group of source tid
+                    if (q >= qa && q < qb && j < n) {
+                        const int64_t len = npad - i0 - BS;
+                        double* p = Ps + NC * sym_tri(I, npad) + (j - i0 - BS);
+#pragma unroll
+                        for (int c = 0; c < NC; ++c)
+                            p[c * len] =
+                                0.5 * (((red[c][tid] + red[NC + c][tid]) + red[2 * NC + c][tid]) + red[3 * NC + c][tid]);
+                    }
                 }
             }
         }
-    }
-    if (!diag) {
-        // rows of J at or beyond n that no tile above reached still get their zeros (same thread per row)
-        for (int64_t j = (int64_t)J * BS + tid; j < (int64_t)(J + 1) * BS && j < npad; j += 256)
-            if (j >= n)
+        double* p = Pt + ((int64_t)blockIdx.x + I) * NC * BS + wave * 64 * TK + lane;
 #pragma unroll
-                for (int c = 0; c < NC; ++c) P[((int64_t)I * NC + c) * npad + j] = 0.0;
-    }
+        for (int k = 0; k < TK; ++k)
 #pragma unroll
-    for (int k = 0; k < TK; ++k) {
-        const int64_t i = ib + 64 * k;
-        if (i < npad)
-#pragma unroll
-            for (int c = 0; c < NC; ++c) P[((int64_t)J * NC + c) * npad + i] = tin[k] ? 0.5 * acc[k][c] : 0.0;
+            for (int c = 0; c < NC; ++c) p[c * BS + 64 * k] = 0.5 * acc[k][c];
     }
 }
 
+// Y[c][i] = the stored sums of row i (block B of atoms: the triangle's rows I < B, then the sets of the runs
+// that touch row B) + sum_e C[e][i] X[c][col[e][i]] (near field); 0 for padding rows. Work split as in
+// otf_narrow_sum_kernel: 64 rows per work-group, every 4th entry and sum per wave, fixed-order LDS sum.
 template <int NC>
-void launch_otf_sym(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, double* Yi, hipStream_t st) {
-    const int nb = (int)((s.npad + kSymBlock - 1) / kSymBlock);
-    double* P = static_cast<double*>(split_workspace(s, (uint64_t)nb * NC * s.npad * sizeof(double)));
+__global__ void __launch_bounds__(256) otf_sym_sum_kernel(int64_t n, int64_t npad, int nb, int W,
+                                                          const double* __restrict__ Ps, const double* __restrict__ Pt,
+                                                          int w, const int32_t* __restrict__ ncolv,
+                                                          const double* __restrict__ nval, const double* __restrict__ X,
+                                                          int64_t ldx, double* __restrict__ Y, int64_t ldy,
+                                                          double* __restrict__ Yi) {
+    __shared__ double part[4][NC][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;   // npad is a multiple of 64
+    double t[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) t[c] = 0.0;
+#pragma unroll 4
+    for (int e = q; e < w; e += 4) {
+        const double v = nval[(int64_t)e * npad + i];
+        const int64_t j = ncolv[(int64_t)e * npad + i];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) t[c] = fma(v, X[c * ldx + j], t[c]);
+    }
+    const int64_t B = (int64_t)blockIdx.x * 64 / kSymBlock, G = sym_row_start(nb, nb);
+#pragma unroll 4
+    for (int64_t I = q; I < B; I += 4) {
+        const int64_t len = npad - (I + 1) * kSymBlock;
+        const double* p = Ps + NC * sym_tri(I, npad) + (i - (I + 1) * kSymBlock);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) t[c] += p[c * len];
+    }
+    const int64_t w0 = sym_run_of(sym_row_start(B, nb), G, W), w1 = sym_run_of(sym_row_start(B + 1, nb) - 1, G, W);
+    const double* pt = Pt + B * NC * kSymBlock + (i - B * kSymBlock);
+#pragma unroll 4
+    for (int64_t r = w0 + q; r <= w1; r += 4)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) t[c] += pt[(r * NC + c) * kSymBlock];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) part[q][c][lane] = t[c];
+    __syncthreads();
+    if (q == 0) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            v[c] = i < n ? (part[0][c][lane] + part[1][c][lane]) + (part[2][c][lane] + part[3][c][lane]) : 0.0;
+            Y[c * ldy + i] = v[c];
+        }
+        if (Yi) *reinterpret_cast<doublex4*>(Yi + 4 * i) = doublex4{v[0], v[1], v[2], v[3]};
+    }
+}
+
+// Runs of the symmetric product: as many work-groups as the chip holds at once, three per CU (53 KB of LDS each
+// at 3 columns, at most 168 registers) or two (4 columns, 70 KB), and runs of about a block pair, 16 groups,
+// where that gives more (CUs that finish early then take another run: 65 600 atoms, 3 columns, with the sum
+// kernel: 1 610 us at 768 runs, 1 592 at 1 024, 1 536 at 2 304, 1 544 at 4 096), up to four times as many.
+int sym_runs(const Structure& s, int ncol) {
+    const int64_t nb = (s.npad + kSymBlock - 1) / kSymBlock, G = sym_row_start(nb, nb);
+    const int64_t once = (ncol <= 3 ? 3LL : 2LL) * device_cus(s.device);
+    return (int)std::min(G, std::max(once, std::min(G / 16, 4 * once)));
+}
+
+template <int NC>
+void launch_otf_sym(const Structure& s, const double* X, double* Y, int64_t ld, double* Yi, hipStream_t st) {
+    const int nb = (int)((s.npad + kSymBlock - 1) / kSymBlock), W = sym_runs(s, NC);
+    double* Ps = static_cast<double*>(split_workspace(s, otf_sym_bytes(s, NC)));
+    double* Pt = Ps + NC * std::max<int64_t>(0, sym_tri(nb - 1, s.npad));
     if (!s.near_col || !s.sphere) throw Error{WFQ_EDEVICE, "the structure has no near-field correction or block spheres"};
-    // pairs within the full blocks need no masks; the pairs with the last block (which holds the
-    // padding when n is not a multiple of 1024) run the masked variant
-    const bool partial = (int64_t)nb * kSymBlock > s.n;
-    const int nbt = partial ? nb - 1 : nb;
-    const int64_t pairs = (int64_t)nbt * (nbt + 1) / 2;
-    if (pairs > 0)
-        hipLaunchKernelGGL((otf_sym_kernel<NC, false>), dim3((unsigned)pairs), dim3(256), 0, st, s.n, s.npad, nbt, -1,
-                           s.pos, s.sphere, X, ld, P);
-    if (partial)
-        hipLaunchKernelGGL((otf_sym_kernel<NC, true>), dim3((unsigned)nb), dim3(256), 0, st, s.n, s.npad, nb, nb - 1,
-                           s.pos, s.sphere, X, ld, P);
+    hipLaunchKernelGGL((otf_sym_kernel<NC>), dim3((unsigned)W), dim3(256), 0, st, s.n, s.npad, nb, s.pos, s.sphere, X, ld,
+                       Ps, Pt);
     WFQ_CHECK_LAUNCH();
-    hipLaunchKernelGGL(otf_narrow_sum_kernel<NC>, dim3((unsigned)(s.npad / 64)), dim3(256), 0, st, s.npad, nb, ncol,
-                       P, s.near_w, s.near_col, s.near_val, X, ld, Y, ld, Yi);
+    hipLaunchKernelGGL(otf_sym_sum_kernel<NC>, dim3((unsigned)(s.npad / 64)), dim3(256), 0, st, s.n, s.npad, nb, W, Ps,
+                       Pt, s.near_w, s.near_col, s.near_val, X, ld, Y, ld, Yi);
     WFQ_CHECK_LAUNCH();
 }
 
 }  // namespace
 
 uint64_t otf_sym_bytes(const Structure& s, int ncol) {
-    if (s.n < kSymFrom) return 0;
     const int64_t nb = (s.npad + kSymBlock - 1) / kSymBlock;
-    return (uint64_t)nb * ncol * s.npad * sizeof(double);
+    return (uint64_t)ncol * sizeof(double) * (sym_tri(nb - 1, s.npad) + (sym_runs(s, ncol) + nb) * kSymBlock);
 }
 
 bool otf_sym_fits(const Structure& s, int ncol) {
     const uint64_t cap = s.split_fixed ? s.split_fixed_bytes : std::max(kSplitWsCap, s.sym_ws_allowed);
-    return s.n >= kSymFrom && otf_sym_bytes(s, ncol) <= cap;
+    return otf_sym_bytes(s, ncol) <= cap;
 }
 
 void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, int cus, hipStream_t st,
@@ -886,13 +947,13 @@ void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, 
     if (ncol > 4) throw Error{WFQ_EINVAL, "the narrow matrix-free product takes at most 4 columns"};
     if (otf_sym_fits(s, ncol)) {
         if (ncol == 1)
-            launch_otf_sym<1>(s, X, Y, ld, ncol, Yi, st);
+            launch_otf_sym<1>(s, X, Y, ld, Yi, st);
         else if (ncol == 2)
-            launch_otf_sym<2>(s, X, Y, ld, ncol, Yi, st);
+            launch_otf_sym<2>(s, X, Y, ld, Yi, st);
         else if (ncol == 3)
-            launch_otf_sym<3>(s, X, Y, ld, ncol, Yi, st);
+            launch_otf_sym<3>(s, X, Y, ld, Yi, st);
         else
-            launch_otf_sym<4>(s, X, Y, ld, ncol, Yi, st);
+            launch_otf_sym<4>(s, X, Y, ld, Yi, st);
         return;
     }
     if (ncol == 1)

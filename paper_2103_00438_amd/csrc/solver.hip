@@ -1546,8 +1546,8 @@ int solve_all(Structure& S, const double* omegas_eV, int n_omega, const double* 
     while (B > 1 && S.budget && batch_bytes(S, o, B, n_dir) > avail) B = (B + 1) / 2;
     if (S.budget && batch_bytes(S, o, B, n_dir) > avail)
         throw Error{WFQ_ENOMEM, "not enough device memory for one system's Krylov work space"};
-    // the symmetric narrow products (matrix-free FP64, up to 4 columns at a time) need one partial sum
-    // per 1 024-atom block and row: reserved here when it exceeds the ordinary work-space cap and the
+    // the symmetric narrow products (matrix-free FP64, up to 4 columns at a time) keep one sum per
+    // row and 1 024-atom block before it: reserved here when it exceeds the ordinary work-space cap and the
     // budget leaves room beside the batch; otherwise those products take the one-sided form
     {
         const uint64_t sym4 = otf_sym_bytes(S, 4);

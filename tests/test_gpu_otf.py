@@ -212,3 +212,45 @@ def test_wide_fp32_product_tile_and_part_edges(lib, n, ncol):
     assert np.all(np.abs(Y[keep] - Xq @ P.T) <= tol)
     if ncol > 2:
         assert np.all(Y[1] == 0.0) and np.all(Y[2] == -np.inf)
+
+
+@pytest.mark.parametrize("n", [2, 255, 1024, 1025, 2048, 3100])
+@pytest.mark.parametrize("ncol", [1, 3, 4])
+def test_symmetric_narrow_product_block_edges(lib, n, ncol):
+    # One block, full blocks, a last block of one atom, partial groups of 64; runs that end inside a block pair
+    # and reach into the next row of blocks (the run count follows the device). An atom sits exactly at the
+    # origin, where the padding's coordinates are zero.
+    import wfq_inputs as wi
+    from wfq_inputs import geometry as geo
+    par = wi.workloads.FCC_METAL
+    xyz = geo.jitter(geo.fcc_sphere(24.0), 0.02, 3)
+    xyz = xyz[np.argsort(np.sum(xyz * xyz, axis=1), kind="stable")][:n]
+    assert len(xyz) == n
+    xyz = xyz - xyz[0]
+    P = O.Problem(xyz, par)
+    X = np.random.default_rng(n + ncol).standard_normal((ncol, n))
+    h = lib.wfq_build(xyz, par, t_mode="otf")
+    Y = lib.wfq_apply_T(h, "fp64", X)
+    Y2 = lib.wfq_apply_T(h, "fp64", X)
+    h.close()
+    assert np.all(np.abs(Y - X @ P.T.T) <= 1e-13 * (np.abs(X) @ np.abs(P.T).T))
+    assert np.array_equal(Y, Y2)
+
+
+def test_one_sided_narrow_product_when_the_sums_do_not_fit(lib):
+    # 4 columns of a 200 000-atom structure: the symmetric form's sums (4 n^2 / 256 bytes) exceed the
+    # work-space cap of 512 MiB, so each row is summed by itself; a few rows against the C++ oracle.
+    import wfq_inputs as wi
+    from wfq_inputs import geometry as geo
+    from oracle.cpp_oracle import CppProblem
+    par = wi.workloads.FCC_METAL
+    xyz = geo.jitter(geo.fcc_sphere(93.6), 0.02, 12)
+    n = len(xyz)
+    assert 4 * 8 * n * n / 2048 > 512 << 20
+    X = np.random.default_rng(3).standard_normal((4, n))
+    h = lib.wfq_build(xyz, par, t_mode="otf")
+    Y = lib.wfq_apply_T(h, "fp64", X)
+    h.close()
+    P = CppProblem(xyz, par, dense_T=False, build_L=False)
+    rows = np.r_[np.arange(0, n, 9973), n - 1]
+    assert np.all(np.abs(Y[:, rows].T - P.apply_T_rows(rows, X.T)) <= 1e-13 * P.apply_T_rows(rows, np.abs(X).T))

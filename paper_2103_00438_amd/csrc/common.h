@@ -181,6 +181,8 @@ void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t 
 void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st);
 // true when a product of ncol columns in `prec` recomputes the elements with the narrow kernel
 bool tx_is_otf_narrow(const Structure& s, int prec, int ncol);
+// true when a product of ncol columns streams the stored T with the vector ALUs
+bool tx_is_skinny(const Structure& s, int prec, int ncol);
 // T X with the stored copy of T in `prec`, or recomputed on the fly when the structure is matrix-free.
 // split: an untuned FP32 product may go through the FP16 matrix cores (operands split, the error against
 // 64 bits smaller than the FP32 instruction's). The operator entry points ask for it. The solves do not:

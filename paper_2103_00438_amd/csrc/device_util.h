@@ -39,12 +39,27 @@ __device__ inline uint16_t cast_from_double<uint16_t>(double v) { return bf16_rn
 __device__ inline double widen(double v) { return v; }
 __device__ inline double widen(float v) { return (double)v; }
 
-// Sum over the 64 lanes of a wave; every lane receives the total. Fixed butterfly order, so the
-// result does not depend on scheduling.
+// v plus the value that a DPP move brings from another lane (0 where the move has no source lane)
+template <int kCtrl, int kRowMask>
+__device__ inline double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRowMask, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRowMask, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+
+// Sum over the 64 lanes of a wave; every lane receives the total. Fixed order, so the result does not depend
+// on scheduling. Lanes are added within their row of 16 (shifts by 1, 2, 4, 8), row 0 into 1 and 2 into 3, then
+// the lower half into the upper; lane 63 holds the total. DPP moves stay in the vector ALU: about a quarter of the
+// latency of the same sum through LDS permutes, which the small reductions of a Krylov step wait for.
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
+    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
+    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
+    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
+    return __hiloint2double(hi, lo);
 }
 
 // ---- FP32 operands of the FP16 matrix cores: x = h + l + e, h the FP16 rounding of x, l that of x - h

@@ -932,6 +932,11 @@ bool tx_is_otf_narrow(const Structure& s, int prec, int ncol) {
     return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol)].name, "otfn", 4) == 0;
 }
 
+bool tx_is_skinny(const Structure& s, int prec, int ncol) {
+    if (s.t_mode == WFQ_TMODE_OTF) return false;
+    return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol)].name, "skinny", 6) == 0;
+}
+
 int tx_variant_count(int precision) { return (int)variants_of(precision).size(); }
 const char* tx_variant_name(int precision, int k) { return variants_of(precision)[k].name; }
 int tx_variant_max_ncol(int precision, int k) { return variants_of(precision)[k].max_ncol; }

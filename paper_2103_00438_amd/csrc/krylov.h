@@ -146,39 +146,58 @@ void reduce_complex(const int* sys, int nsys, const double2* partial, int nb, do
 // `dirs` lists the ndir directions a launch works on; partial / h arrays hold pslots entries per
 // direction; Hessenberg column j of direction d at H + (d * m + j) * (m + 1).
 constexpr int kMsGroup = 8;   // systems per group in ms_xupdate
-// X[c] = cast(V(d_c, j) * scale[d_c]) and V(d_c, j) *= scale[d_c]
-void ms_pack(int prec, double* V, int64_t npad, int mdim1, int j, const int* dirs, int ndir, const double* scale,
-             void* X, int64_t ld, hipStream_t st);
+// The directions of a launch: up to 4 by value (a load less at the head of each kernel of a step), more in
+// device memory. A captured launch keeps them, so a graph's key names them.
+struct DirList {
+    int d[4] = {0, 0, 0, 0};
+    const int* p = nullptr;
+    __host__ __device__ int operator[](int i) const { return p ? p[i] : d[i]; }
+};
+// X[c] = cast(V(d_c, j) / |V(d_c, j)|), also written back; the norms come from the block sums norm ([d][npad / 64],
+// kept as nu and inv_h = 1 / nu) or, with norm == NULL, inv_h holds their inverses
+void ms_pack(int prec, double* V, int64_t npad, int mdim1, int j, const DirList& dirs, int ndir, const double* norm,
+             double* nu, double* inv_h, void* X, int64_t ld, hipStream_t st);
+// Y[c] = T V(d_c, j) / |V(d_c, j)| with the stored FP64 T, norms as in ms_pack, up to 4 directions; V is left
+// unnormalised (ms_spmm's scale = inv_h finishes it)
+void ms_skinny(const Structure& S, const double* V, int mdim1, int j, const DirList& dirs, int ndir, const double* norm,
+               double* nu, double* inv_h, double* Y, hipStream_t st);
 // V(d_c, jdst) = L Y[c]; with TV != NULL also TV(d_c, jdst - 1) = Y[c] (rows >= n: 0), the product
 // T v_j kept beside the basis (same layout as V)
 // With Yi (FP64 products of at most 4 columns) the neighbours' values are gathered from the
-// interleaved copy of Y (rows of 4 doubles) that the narrow product can write beside it.
-void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const int* dirs, int ndir, double* V,
-             int mdim1, int jdst, double* TV, hipStream_t st, const double* Yi = nullptr);
+// interleaved copy of Y (rows of 4 doubles) that the narrow product can write beside it. With scale,
+// V(d_c, jdst - 1) *= scale[d_c].
+void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const DirList& dirs, int ndir, double* V,
+             int mdim1, int jdst, double* TV, hipStream_t st, const double* Yi = nullptr, const double* scale = nullptr);
 // partial[d][i][wc] = chunk sums of V(d, i) . V(d, jw), i < nvec; self_norm: slot nvec = ||V(d, jw)||^2
-void ms_dot(const double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const int* dirs, int ndir,
+void ms_dot(const double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const DirList& dirs, int ndir,
             double* partial, int pslots, bool self_norm, hipStream_t st);
 // h[d][i] = sum over chunks of partial[d][i], i < count
-void ms_reduce(const int* dirs, int ndir, const double* partial, int pslots, int64_t n, int count, double* h,
+void ms_reduce(const DirList& dirs, int ndir, const double* partial, int pslots, int64_t n, int count, double* h,
                hipStream_t st);
 // V(d, jw) -= sum_{i < nvec} h[d][i] V(d, i); norm (may be NULL): sums of V(d, jw)^2 over 64-row
 // blocks, [d][npad / 64]
-void ms_update(double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const int* dirs, int ndir,
+void ms_update(double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const DirList& dirs, int ndir,
                const double* h, int pslots, double* norm, hipStream_t st);
 // One-reduction Arnoldi step k (DCGS2) on the real bases: fused dots of slot k (u) and, with z, slot
-// k + 1 against slots 0..k into partial[d][e][wc] (ps >= 2 k + 2 entries per direction; reduce with
-// ms_reduce over 2 k + 2, or k + 1 without z)
-void ms_dcgs_dot(const double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const int* dirs, int ndir,
+// k + 1 against slots 0..k into partial[d][e][wc] (ps >= 2 k + 2 entries per direction), for ms_dcgs_step
+void ms_dcgs_dot(const double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const DirList& dirs, int ndir,
                  double* partial, int ps, hipStream_t st);
-// from the dots: column k-1 of H, column k of S (Sm may be NULL), and with z gamma, 1 / rho and the
-// next first-pass coefficients hp ([d][m + 1]); nu = |p| of the previous step
-void ms_dcgs_coeff(const int* dirs, int ndir, int k, bool with_z, int m, const double* dots, int ps, double* hp,
-                   double* H, double* Sm, const double* nu, const double* inv_h, double* gam, double* inv_rho,
-                   hipStream_t st);
-// q_k into slot k, p' into slot k + 1, nu = |p'| and inv_h = 1 / nu (norm: [d][npad / 64] block sums)
-void ms_dcgs_update(double* V, int64_t n, int64_t npad, int mdim1, int k, const int* dirs, int ndir,
-                    const double* dots, int ps, const double* gam, const double* inv_rho, double* norm,
-                    double* nu, double* inv_h, hipStream_t st);
+// from the dots' partials: the dots, column k-1 of H, column k of S (Sm may be NULL), and with z gamma, 1 / rho and
+// the next first-pass coefficients hp ([d][m + 1]); norm: block sums of p^2 of the previous step
+void ms_dcgs_step(const DirList& dirs, int ndir, int k, bool with_z, int m, const double* partial, int ps, int64_t n,
+                  int64_t npad, const double* nu, const double* norm, double* dots, double* hp, double* H, double* Sm,
+                  double* gam, double* inv_rho, hipStream_t st);
+// q_k into slot k, p' into slot k + 1 and the block sums of p'^2 (norm: [d][npad / 64])
+void ms_dcgs_update(double* V, int64_t n, int64_t npad, int mdim1, int k, const DirList& dirs, int ndir,
+                    const double* dots, int ps, const double* gam, const double* inv_rho, double* norm, hipStream_t st);
+// ms_dcgs_update of step k (with z) and ms_givens of column k - 1 (k >= 1) in one launch, for the sizes where
+// ms_merged holds
+bool ms_merged(int64_t npad);
+void ms_update_givens(double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const DirList& dirs, int ndir,
+                      const double* dots, int ps, const double* gam, const double* irho, double* norm, const int* sys,
+                      int nsys, int m, const int* sdir, const double2* z, const double* H, double* cs, double2* sn,
+                      double2* g, double2* R, int64_t S, double* est, const double* tol_abs, int* flags, int* run,
+                      int* ksteps, hipStream_t st);
 // y[s] <- S^-1 y[s] over k[s] entries (S of direction sdir[s], columns in the layout of H)
 void ms_sinv(const int* sys, int nsys, const int* ksteps, int m, const double* Sm, const int* sdir, double2* y,
              hipStream_t st);

@@ -39,74 +39,176 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
     return make_double2((a.x * b.x + a.y * b.y) / d, (a.y * b.x - a.x * b.y) / d);
 }
 
+// divide by, and multiply with, an entry of a real or a complex triangle
+__device__ inline double2 tri_div(double2 a, double b) { return cscale(1.0 / b, a); }
+__device__ inline double2 tri_div(double2 a, double2 b) { return cdiv(a, b); }
+__device__ inline double2 tri_mul(double a, double2 b) { return cscale(a, b); }
+__device__ inline double2 tri_mul(double2 a, double2 b) { return cmul(a, b); }
+
 __device__ inline double* slot(double* V, int64_t npad, int mdim1, int d, int j) {
     return V + ((int64_t)d * mdim1 + j) * npad;
 }
 
-// X[c][i] = cast(v) with v = V(d_c, j)[i] * scale[d_c], which is also written back (normalises the
-// new basis vector on its way into the product).
+// 1 / |p| from the block sums of p^2 that the update sweep left in norm[0 .. nblk - 1] (fixed order; 0 when p = 0),
+// computed by a whole wave; nrm receives |p|
+__device__ inline double inv_norm(const double* __restrict__ norm, int64_t nblk, double& nrm) {
+    double s = 0.0;
+    for (int64_t q = threadIdx.x & 63; q < nblk; q += 64) s += norm[q];
+    nrm = sqrt(wave_sum(s));
+    return nrm > 0.0 ? 1.0 / nrm : 0.0;
+}
+
+// X[c][i] = cast(v) with v = V(d_c, j)[i] / |V(d_c, j)|, which is also written back (normalises the
+// new basis vector on its way into the product). The norm comes from its block sums, which every wave adds
+// for itself (nu and inv_h keep it for the step's other kernels), or, without them, 1 / norm is inv_h[d].
 template <typename E>
 __global__ void __launch_bounds__(256) ms_pack_kernel(double* __restrict__ V, int64_t npad, int mdim1, int j,
-                                                      const int* __restrict__ dirs, const double* __restrict__ scale,
+                                                      DirList dirs, const double* __restrict__ norm,
+                                                      double* __restrict__ nu, double* __restrict__ inv_h,
                                                       E* __restrict__ X, int64_t ld) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int c = blockIdx.y;
     const int d = dirs[c];
     double* v = slot(V, npad, mdim1, d, j);
-    const double a = v[i] * scale[d];
+    const double x = v[i];
+    double sc, nrm;
+    if (norm) {
+        sc = inv_norm(norm + (int64_t)d * (npad / 64), npad / 64, nrm);
+        if (i == 0) {
+            nu[d] = nrm;
+            inv_h[d] = sc;
+        }
+    } else {
+        sc = inv_h[d];
+    }
+    const double a = x * sc;
     v[i] = a;
     X[(int64_t)c * ld + i] = cast_from_double<E>(a);
 }
 
-// V(d_c, jdst) = L Y[c] for the NC columns c0 .. c0 + NC - 1 (real ELL rows; padding rows get 0).
-// Each thread reads its row of L once for all NC columns.
-template <typename YE, int NC>
-__global__ void __launch_bounds__(256) ms_spmm_kernel(int64_t n, int64_t npad, int w, const int32_t* __restrict__ ecol,
-                                                      const double* __restrict__ eval, const YE* __restrict__ Y,
-                                                      int64_t ld, const int* __restrict__ dirs, double* __restrict__ V,
-                                                      int mdim1, int jdst, int c0, double* __restrict__ TV,
-                                                      const double* __restrict__ Yi) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double acc[NC];
+// The product of a small stored FP64 T with the newest basis vectors, taken straight from the basis:
+// Y[c][i] = sum_k T[i][k] V(d_c, j)[k] / |V(d_c, j)|. One launch in place of the pack, the product and the norm's
+// reduction, whose latencies bound a step of a few thousand atoms. A work-group owns 8 rows of T; its four waves
+// split k (every fourth run of 128), so that even 600 atoms have 320 waves, and the 64 x 4 partial sums of
+// every output are added through LDS in a fixed order. The basis vectors stay unnormalised until ms_spmm.
+constexpr int kMsRowsT = 8;
+template <int NC>
+__global__ void __launch_bounds__(256) ms_skinny_kernel(const double* __restrict__ T, int64_t npad,
+                                                        const double* __restrict__ V, int mdim1, int j,
+                                                        DirList dirs, const double* __restrict__ norm,
+                                                        double* __restrict__ nu, double* __restrict__ inv_h,
+                                                        double* __restrict__ Y) {
+    constexpr int R = kMsRowsT, ROW = 256 + 8;
+    __shared__ double part[R * NC][ROW];
+    __shared__ double inv[NC];
+    const int tid = threadIdx.x, wave = tid >> 6;
+    const int64_t row0 = (int64_t)blockIdx.x * R;
+    const double* u[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) acc[c] = 0.0;
-    if (i < n) {
-        const YE* y = Y + (int64_t)c0 * ld;
-        if (Yi) {
-            // the interleaved copy: all columns of neighbour j in one aligned 32-byte load
-#pragma unroll 4
-            for (int e = 0; e < w; ++e) {
-                const double v = eval[(int64_t)e * npad + i];
-                const int64_t j = ecol[(int64_t)e * npad + i];
-                const doublex4 yj = *reinterpret_cast<const doublex4*>(Yi + 4 * j);
-                const double yv[4] = {yj.x, yj.y, yj.z, yj.w};
+    for (int c = 0; c < NC; ++c) u[c] = V + ((int64_t)dirs[c] * mdim1 + j) * npad;
+    double acc[R][NC];
 #pragma unroll
-                for (int c = 0; c < NC; ++c) acc[c] += v * yv[c];
-            }
-        } else {
-#pragma unroll 4
-            for (int e = 0; e < w; ++e) {
-                const double v = eval[(int64_t)e * npad + i];
-                const int64_t j = ecol[(int64_t)e * npad + i];
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int c = 0; c < NC; ++c) acc[c] += v * widen(y[c * ld + j]);
-            }
+        for (int c = 0; c < NC; ++c) acc[r][c] = 0.0;
+    for (int64_t k = 2 * tid; k < npad; k += 512) {
+        double2 x[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[c] = *reinterpret_cast<const double2*>(u[c] + k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double2 t = *reinterpret_cast<const double2*>(T + (row0 + r) * npad + k);
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[r][c] = fma(t.y, x[c].y, fma(t.x, x[c].x, acc[r][c]));
         }
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) slot(V, npad, mdim1, dirs[c0 + c], jdst)[i] = acc[c];
-    if (TV) {
+    for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            slot(TV, npad, mdim1, dirs[c0 + c], jdst - 1)[i] = i < n ? widen(Y[(int64_t)(c0 + c) * ld + i]) : 0.0;
+        for (int c = 0; c < NC; ++c) part[r * NC + c][tid] = acc[r][c];
+    if (wave < NC) {
+        const int d = dirs[wave];
+        double sc, nrm;
+        if (norm) {
+            sc = inv_norm(norm + (int64_t)d * (npad / 64), npad / 64, nrm);
+            if (blockIdx.x == 0 && (tid & 63) == 0) {
+                nu[d] = nrm;
+                inv_h[d] = sc;
+            }
+        } else {
+            sc = inv_h[d];
+        }
+        if ((tid & 63) == 0) inv[wave] = sc;
     }
+    __syncthreads();
+    // 8 threads per output, 32 partial sums each
+    const int o = tid >> 3, sub = tid & 7;
+    if (o < R * NC) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int q = 0; q < 32; ++q) s += part[o][q * 8 + sub];
+        s += __shfl_xor(s, 1, 64);
+        s += __shfl_xor(s, 2, 64);
+        s += __shfl_xor(s, 4, 64);
+        if (sub == 0) Y[(int64_t)(o % NC) * npad + row0 + o / NC] = inv[o % NC] * s;
+    }
+}
+
+// V(d_c, jdst) = L Y[c] for the NC columns c0 .. c0 + NC - 1 (real ELL rows; padding rows get 0), with
+// TV(d_c, jdst - 1) = Y[c] kept and, with scale, V(d_c, jdst - 1) *= scale[d_c] (a basis vector that entered its product
+// unnormalised). A work-group owns 64 rows; its four waves take every fourth entry of the rows (each read once
+// for all columns) and their sums are added in LDS in order: the gathers are bound by latency, and one thread a row
+// had a quarter of the waves for four times as long (600 atoms: 7.7 us, now 4.8).
+template <typename YE, int NC>
+__global__ void __launch_bounds__(256) ms_spmm_kernel(int64_t n, int64_t npad, int w, const int32_t* __restrict__ ecol,
+                                                      const double* __restrict__ eval, const YE* __restrict__ Y,
+                                                      int64_t ld, DirList dirs, double* __restrict__ V,
+                                                      int mdim1, int jdst, int c0, double* __restrict__ TV,
+                                                      const double* __restrict__ Yi, const double* __restrict__ scale) {
+    __shared__ double red[4][NC][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    double acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = 0.0;
+    const YE* y = Y + (int64_t)c0 * ld;
+    if (Yi) {
+        // the interleaved copy: all columns of neighbour j in one aligned 32-byte load
+#pragma unroll 4
+        for (int e = q; e < w; e += 4) {
+            const double v = eval[(int64_t)e * npad + i];
+            const int64_t j = ecol[(int64_t)e * npad + i];
+            const doublex4 yj = *reinterpret_cast<const doublex4*>(Yi + 4 * j);
+            const double yv[4] = {yj.x, yj.y, yj.z, yj.w};
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[c] += v * yv[c];
+        }
+    } else {
+#pragma unroll 4
+        for (int e = q; e < w; e += 4) {
+            const double v = eval[(int64_t)e * npad + i];
+            const int64_t j = ecol[(int64_t)e * npad + i];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[c] += v * widen(y[c * ld + j]);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) red[q][c][lane] = acc[c];
+    __syncthreads();
+    if (q >= NC) return;   // wave q finishes column q
+    const int d = dirs[c0 + q];
+    const bool in = i < n;
+    slot(V, npad, mdim1, d, jdst)[i] =
+        in ? (red[0][q][lane] + red[1][q][lane]) + (red[2][q][lane] + red[3][q][lane]) : 0.0;
+    if (TV) slot(TV, npad, mdim1, d, jdst - 1)[i] = in ? widen(y[q * ld + i]) : 0.0;
+    if (scale) slot(V, npad, mdim1, d, jdst - 1)[i] *= scale[d];
 }
 
 // partial[d][i][wc] = sum over wave chunk wc (512 rows) of V(d, i) * V(d, jw) for i < nvec; with
 // self_norm also partial[d][nvec][wc] = sum of V(d, jw)^2. One wave per (chunk, vector): the
 // launch has thousands of waves even for one direction, and each sum has a fixed order.
 __global__ void __launch_bounds__(256) ms_dot_kernel(const double* __restrict__ V, int64_t n, int64_t npad, int mdim1,
-                                                     int nvec, int jw, const int* __restrict__ dirs,
+                                                     int nvec, int jw, DirList dirs,
                                                      double* __restrict__ partial, int pslots, int64_t nwc,
                                                      int self_norm) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -129,7 +231,7 @@ __global__ void __launch_bounds__(256) ms_dot_kernel(const double* __restrict__ 
 
 // h[d][i] = sum_wc partial[d][i][wc], i < count: one wave per (value, direction); lane l adds the
 // chunks l, l + 64, ... and the lanes are combined by a fixed butterfly (same order every call)
-__global__ void __launch_bounds__(256) ms_reduce_kernel(const int* __restrict__ dirs, const double* __restrict__ partial,
+__global__ void __launch_bounds__(256) ms_reduce_kernel(DirList dirs, const double* __restrict__ partial,
                                                         int pslots, int64_t nwc, int count, double* __restrict__ h) {
     const int d = dirs[blockIdx.y];
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -147,7 +249,7 @@ __global__ void __launch_bounds__(256) ms_reduce_kernel(const int* __restrict__ 
 // vector and their partial sums are combined in LDS in a fixed order.
 constexpr int kMsRows = 64;
 __global__ void __launch_bounds__(256) ms_update_kernel(double* __restrict__ V, int64_t n, int64_t npad, int mdim1,
-                                                        int nvec, int jw, const int* __restrict__ dirs,
+                                                        int nvec, int jw, DirList dirs,
                                                         const double* __restrict__ h, int pslots,
                                                         double* __restrict__ norm) {
     __shared__ double part[4][kMsRows];
@@ -193,16 +295,17 @@ __global__ void __launch_bounds__(256) ms_update_kernel(double* __restrict__ V, 
 // S(k, k) = rho), kept column by column in the layout of H when the products T u_k are kept.
 
 // partial[d][e][wc] for the entries e above over wave chunk wc (512 rows). One wave per (chunk, group
-// of kDotGroup basis vectors t <= k, direction): u and z of the chunk stay in registers while the
-// wave computes v_t . u and v_t . z for its vectors (t = k: alpha and beta).
-constexpr int kDotGroup = 16;
+// of kGroup basis vectors t <= k, direction): u and z of the chunk stay in registers while the
+// wave computes v_t . u and v_t . z for its vectors (t = k: alpha and beta). 16 vectors per wave where that fills
+// the chip, 4 where a wave's chain of vectors is the time (ms_dcgs_dot).
+template <int kGroup>
 __global__ void __launch_bounds__(256) ms_dcgs_dot_kernel(const double* __restrict__ V, int64_t n, int64_t npad,
-                                                          int mdim1, int k, int with_z, const int* __restrict__ dirs,
+                                                          int mdim1, int k, int with_z, DirList dirs,
                                                           double* __restrict__ partial, int ps, int64_t nwc) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t wc = (int64_t)blockIdx.x * 4 + wave;
     if (wc >= nwc) return;   // uniform over the wave
-    const int t0 = blockIdx.y * kDotGroup, t1 = min(t0 + kDotGroup, k + 1);
+    const int t0 = blockIdx.y * kGroup, t1 = min(t0 + kGroup, k + 1);
     const int d = dirs[blockIdx.z];
     const double* u = V + ((int64_t)d * mdim1 + k) * npad;
     const double* zv = u + npad;   // slot k + 1 (read only with z)
@@ -245,20 +348,24 @@ __device__ inline double block_sum256(double x, double* red) {
 }
 
 // One work-group per direction: column k-1 of H (k >= 1), column k of S (with z, S != NULL), and with
-// z gamma and 1 / rho. Without z (the last step) u is the unnormalised p, whose dots are scaled by
-// inv_h = 1 / nu.
-__global__ void __launch_bounds__(256) ms_dcgs_coeff_kernel(const int* __restrict__ dirs, int k, int with_z, int m,
+// z gamma and 1 / rho. With z the step's product has left nu[d] = |p|; without (the last step, k >= 1) u is the
+// unnormalised p, whose dots are scaled by 1 / |p| from its block sums.
+__global__ void __launch_bounds__(256) ms_dcgs_coeff_kernel(DirList dirs, int k, int with_z, int m,
                                                             const double* __restrict__ dots, int ps,
                                                             double* __restrict__ hp, double* __restrict__ H,
                                                             double* __restrict__ Sm, const double* __restrict__ nu,
-                                                            const double* __restrict__ inv_h, double* __restrict__ gam,
-                                                            double* __restrict__ inv_rho) {
+                                                            const double* __restrict__ norm, int64_t nblk,
+                                                            double* __restrict__ gam, double* __restrict__ inv_rho) {
     __shared__ double red[4];
     const int d = dirs[blockIdx.x];
     const int tid = threadIdx.x;
     const double* dt = dots + (int64_t)d * ps;
     double* hpd = hp + (int64_t)d * (m + 1);
-    const double sc = with_z ? 1.0 : inv_h[d];
+    double nud = 0.0, sc = 1.0;
+    if (with_z)
+        nud = nu[d];
+    else
+        sc = inv_norm(norm + (int64_t)d * nblk, nblk, nud);
     double asq = 0.0;
     for (int i = tid; i < k; i += 256) {
         const double ai = sc * dt[i];
@@ -267,7 +374,6 @@ __global__ void __launch_bounds__(256) ms_dcgs_coeff_kernel(const int* __restric
     asq = block_sum256(asq, red);
     const double r2 = dt[k] * sc * sc - asq;
     const double rho = r2 > 0.0 ? sqrt(r2) : 0.0;
-    const double nud = nu[d];
     if (k >= 1) {
         double* col = H + ((int64_t)d * m + (k - 1)) * (m + 1);
         for (int i = tid; i < k; i += 256) col[i] = hpd[i] + nud * sc * dt[i];
@@ -293,7 +399,7 @@ __global__ void __launch_bounds__(256) ms_dcgs_coeff_kernel(const int* __restric
 // hp(k) = (gamma - H(k, k-1) a_{k-1}) / rho, after column k-1 of H is complete. One work-group of
 // 16 waves per (64 rows, direction): lane = row, wave w adds the columns c = w, w + 16, ... (Hbar is
 // upper Hessenberg: c >= i - 1 only), and the 16 partial sums are added in order.
-__global__ void __launch_bounds__(1024) ms_dcgs_hp_kernel(const int* __restrict__ dirs, int k, int m,
+__global__ void __launch_bounds__(1024) ms_dcgs_hp_kernel(DirList dirs, int k, int m,
                                                           const double* __restrict__ dots, int ps,
                                                           const double* __restrict__ H, const double* __restrict__ gam,
                                                           const double* __restrict__ inv_rho, double* __restrict__ hp) {
@@ -327,12 +433,118 @@ __global__ void __launch_bounds__(1024) ms_dcgs_hp_kernel(const int* __restrict_
     }
 }
 
+// The three kernels between the two sweeps (reduction of the dots, ms_dcgs_coeff, ms_dcgs_hp) as one, for a
+// few hundred basis vectors of up to some tens of chunks: one work-group of 16 waves per direction. The dots
+// are reduced into LDS (and global memory, for the update sweep), the norms and scalar products in one pass, and
+// H a row block by row block as in ms_dcgs_hp_kernel, with column k-1 taken from LDS.
+constexpr int kStepMax = 384;   // largest k; above, the three kernels' parallelism over H pays
+__global__ void __launch_bounds__(1024) ms_dcgs_step_kernel(DirList dirs, int k, int with_z, int m,
+                                                            const double* __restrict__ partial, int ps, int64_t nwc,
+                                                            const double* __restrict__ nu,
+                                                            const double* __restrict__ norm, int64_t nblk,
+                                                            double* __restrict__ dots, double* __restrict__ hp,
+                                                            double* __restrict__ H, double* __restrict__ Sm,
+                                                            double* __restrict__ gam, double* __restrict__ inv_rho) {
+    __shared__ double sd[2 * kStepMax + 2], hcol[kStepMax + 1], red[16][64], part[2][16];
+    const int d = dirs[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double* hpd = hp + (int64_t)d * (m + 1);
+    double* Hd = H + (int64_t)d * m * (m + 1);
+    double* dt = dots + (int64_t)d * ps;
+    // column k-1's first-pass coefficients, loaded ahead of the reductions
+    double hold = 0.0;
+    if (tid < k) hold = hpd[tid];
+    // without z (the last step) u is the unnormalised p, whose dots are scaled by 1 / |p|
+    double nud = 0.0, sc = 1.0;
+    if (with_z)
+        nud = nu[d];
+    else
+        sc = inv_norm(norm + (int64_t)d * nblk, nblk, nud);
+    {
+        const int count = with_z ? 2 * k + 2 : k + 1;
+        const int L = nwc <= 2 ? 1 : nwc <= 8 ? 4 : 16;   // lanes per dot
+        const int sub = tid % L;
+        for (int e = tid / L; e < count; e += 1024 / L) {
+            const double* p = partial + ((int64_t)d * ps + e) * nwc;
+            double s = 0.0;
+            for (int64_t q = sub; q < nwc; q += L) s += p[q];
+            for (int off = L / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+            if (sub == 0) {
+                sd[e] = s;
+                dt[e] = s;
+            }
+        }
+    }
+    __syncthreads();
+    double asq = 0.0, ab = 0.0;
+    if (tid < k) {
+        asq = sd[tid] * sd[tid];
+        if (with_z) ab = sd[tid] * sd[k + 1 + tid];
+    }
+    asq = wave_sum(asq);
+    ab = wave_sum(ab);
+    if (lane == 0) {
+        part[0][wave] = asq;
+        part[1][wave] = ab;
+    }
+    __syncthreads();
+    asq = ab = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        asq += part[0][q];
+        ab += part[1][q];
+    }
+    const double r2 = (sd[k] - asq) * sc * sc;
+    const double rho = r2 > 0.0 ? sqrt(r2) : 0.0;
+    if (k >= 1) {
+        double* col = Hd + (int64_t)(k - 1) * (m + 1);
+        if (tid < k) col[tid] = hcol[tid] = hold + nud * sc * sd[tid];
+        if (tid == 0) col[k] = hcol[k] = nud * rho;
+    }
+    if (!with_z) return;
+    if (Sm) {
+        double* sk = Sm + ((int64_t)d * m + k) * (m + 1);
+        if (tid < k) sk[tid] = sd[tid];
+        if (tid == 0) sk[k] = rho;
+    }
+    const double ir = rho > 0.0 ? 1.0 / rho : 0.0;
+    const double gm = (sd[2 * k + 1] - ab) * ir;
+    if (tid == 0) {
+        gam[d] = gm;
+        inv_rho[d] = ir;
+    }
+    __syncthreads();   // hcol
+    for (int rb = 0; rb <= k / 64; ++rb) {
+        const int i = rb * 64 + lane, c0 = max(0, rb * 64 - 1);
+        double acc = 0.0;
+        if (i < k) {
+#pragma unroll 4
+            for (int c = c0 + wave; c < k - 1; c += 16)
+                if (c >= i - 1) acc += Hd[(int64_t)c * (m + 1) + i] * sd[c];
+            if (wave == 0) acc += hcol[i] * sd[k - 1];
+        }
+        red[wave][lane] = acc;
+        __syncthreads();
+        if (wave == 0 && i <= k) {
+            if (i < k) {
+                double s = 0.0;
+#pragma unroll
+                for (int w = 0; w < 16; ++w) s += red[w][lane];
+                hpd[i] = (sd[k + 1 + i] - s) * ir;
+            } else {
+                hpd[k] = (gm - (k >= 1 ? hcol[k] * sd[k - 1] : 0.0)) * ir;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // q_k = (u - Q a) / rho into slot k and p' = (z - Q b - gamma q_k) / rho into slot k + 1, with the
 // sums of p'^2 over 64-row blocks in norm[d][blk]. A work-group owns 256 rows (4 per lane); its 4
 // waves take every 4th basis vector (both sums from one read) and are combined in LDS in a fixed
 // order. Rows past n (below npad) are read but neither written nor counted in the norm.
 __global__ void __launch_bounds__(256) ms_dcgs_update_kernel(double* __restrict__ V, int64_t n, int64_t npad,
-                                                             int mdim1, int k, const int* __restrict__ dirs,
+                                                             int mdim1, int k, DirList dirs,
                                                              const double* __restrict__ dots, int ps,
                                                              const double* __restrict__ gam,
                                                              const double* __restrict__ inv_rho,
@@ -376,26 +588,55 @@ __global__ void __launch_bounds__(256) ms_dcgs_update_kernel(double* __restrict_
     if (lane == 0) norm[(int64_t)d * (npad / kMsRows) + (base / kMsRows) + q] = s2;
 }
 
-// nu[d] = |p'| from the block sums (two waves, fixed order), inv_h[d] = 1 / nu[d] (0 when p' = 0)
-__global__ void __launch_bounds__(128) ms_nu_kernel(const int* __restrict__ dirs, const double* __restrict__ norm,
-                                                    int64_t nblk, double* __restrict__ nu,
-                                                    double* __restrict__ inv_h) {
-    __shared__ double sh[2];
-    const int d = dirs[blockIdx.x];
-    double s = 0.0;
-    for (int64_t q = threadIdx.x; q < nblk; q += 128) s += norm[(int64_t)d * nblk + q];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+// Back substitution of one system by one work-group: y (K entries, in LDS) <- U^-1 y, U upper triangular with
+// entry (i, c) from at(c, i). Column by column it would wait for memory and two barriers K times; here panels of
+// kPanel columns are solved: the first wave solves the panel's triangle from registers, and the rows above take
+// all of the panel's columns at once, loaded before the triangle is solved.
+constexpr int kPanel = 16;
+template <typename E, typename At>
+__device__ inline void back_substitute(double2* ys, int K, At&& at) {
+    const int tid = threadIdx.x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const double v = sqrt(sh[0] + sh[1]);
-        nu[d] = v;
-        inv_h[d] = v > 0.0 ? 1.0 / v : 0.0;
+    for (int c1 = K; c1 > 0; c1 -= kPanel) {
+        const int c0 = max(0, c1 - kPanel), p = c1 - c0;
+        // this thread's first row above the panel: its entries, in flight while the triangle is solved
+        E own[kPanel];
+#pragma unroll
+        for (int q = 0; q < kPanel; ++q) own[q] = at(min(c0 + q, c1 - 1), min(tid, c0));
+        if (tid < 64) {
+            // lane r holds y and the entries of row c0 + r; column q's solution is broadcast from lane q
+            E tri[kPanel];
+#pragma unroll
+            for (int q = 0; q < kPanel; ++q) tri[q] = at(min(c0 + q, c1 - 1), c0 + min(tid, min(q, p - 1)));
+            double2 v = tid < p ? ys[c0 + tid] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int q = kPanel - 1; q >= 0; --q) {
+                if (q >= p) continue;
+                const double2 w = tri_div(v, tri[q]);
+                const double2 x = make_double2(__shfl(w.x, q, 64), __shfl(w.y, q, 64));
+                if (tid == q) v = x;
+                if (tid < q) v = csub(v, tri_mul(tri[q], x));
+            }
+            if (tid < p) ys[c0 + tid] = v;
+        }
+        __syncthreads();
+        for (int r = tid; r < c0; r += 256) {
+            double2 v = ys[r];
+            if (r == tid) {
+#pragma unroll
+                for (int q = 0; q < kPanel; ++q)
+                    if (q < p) v = csub(v, tri_mul(own[q], ys[c0 + q]));
+            } else {
+#pragma unroll 8
+                for (int q = 0; q < p; ++q) v = csub(v, tri_mul(at(c0 + q, r), ys[c0 + q]));
+            }
+            ys[r] = v;
+        }
+        __syncthreads();
     }
 }
 
-// y[s] <- S^-1 y[s] over the first k[s] entries (S of the system's direction; column-oriented back
-// substitution, y kept in LDS), one work-group per system
+// y[s] <- S^-1 y[s] over the first k[s] entries (S of the system's direction), one work-group per system
 __global__ void __launch_bounds__(256) ms_sinv_kernel(const int* __restrict__ sys, const int* __restrict__ ksteps,
                                                       int m, const double* __restrict__ Sm,
                                                       const int* __restrict__ sdir, double2* __restrict__ y) {
@@ -404,15 +645,7 @@ __global__ void __launch_bounds__(256) ms_sinv_kernel(const int* __restrict__ sy
     const int K = ksteps[s];
     const double* Sd = Sm + (int64_t)sdir[s] * m * (m + 1);
     for (int i = threadIdx.x; i < K; i += blockDim.x) ys[i] = y[(int64_t)s * m + i];
-    __syncthreads();
-    for (int i = K - 1; i >= 0; --i) {
-        const double* col = Sd + (int64_t)i * (m + 1);
-        const double2 yi = cscale(1.0 / col[i], ys[i]);
-        __syncthreads();
-        if (threadIdx.x == 0) ys[i] = yi;
-        for (int r = threadIdx.x; r < i; r += blockDim.x) ys[r] = csub(ys[r], cscale(col[r], yi));
-        __syncthreads();
-    }
+    back_substitute<double>(ys, K, [&](int c, int i) { return Sd[(int64_t)c * (m + 1) + i]; });
     for (int i = threadIdx.x; i < K; i += blockDim.x) y[(int64_t)s * m + i] = ys[i];
 }
 
@@ -424,20 +657,34 @@ __global__ void __launch_bounds__(256) ms_sinv_kernel(const int* __restrict__ sy
 // of a contiguous chunk of the rotations, an inclusive scan across the lanes gives every chunk its
 // incoming entry, and the lanes then replay their chunks to emit the rotated entries (about
 // 2 j / 64 + 6 dependent steps instead of j).
-__global__ void __launch_bounds__(64) ms_givens_kernel(const int* __restrict__ sys, int nsys, int j, int m,
+struct GivensArgs {
+    const int* sys;
+    int nsys, j, m;
+    const int* sdir;
+    const double2* z;
+    const double* H;
+    double* cs;
+    double2 *sn, *g, *R;
+    int64_t S;
+    double* est;
+    const double* tol_abs;
+    int *flags, *run, *ksteps;
+};
+__device__ inline void givens_wave(int k, int lane, const int* __restrict__ sys, int nsys, int j, int m,
                                                        const int* __restrict__ sdir, const double2* __restrict__ z,
                                                        const double* __restrict__ H, double* __restrict__ cs,
                                                        double2* __restrict__ sn, double2* __restrict__ g,
                                                        double2* __restrict__ R, int64_t S, double* __restrict__ est,
                                                        const double* __restrict__ tol_abs, int* __restrict__ flags,
                                                        int* __restrict__ run, int* __restrict__ ksteps) {
-    const int k = blockIdx.x;
-    const int lane = threadIdx.x;
     const int s = sys[k];
-    if (!run[s]) return;   // stopped earlier in this chunk of steps (uniform over the wave)
-    const double* hc = H + ((int64_t)sdir[s] * m + j) * (m + 1);
+    // everything that hangs on s alone is loaded at once: the step is a chain of memory latencies
+    const int go = run[s], sd = sdir[s];
+    const double2 zs = z[s], gj = g[(int64_t)j * S + s];
+    const double tol = tol_abs[s];
+    if (!go) return;   // stopped earlier in this chunk of steps (uniform over the wave)
+    const double* hc = H + ((int64_t)sd * m + j) * (m + 1);
     double2* col = R + ((int64_t)j * (j + 1) / 2) * S + s;   // entry i of the column at col[i * S]
-    const double2 zs = z[s];
     auto yv = [&](int i) {   // entry i + 1 of column j of Hbar + z Ibar
         return make_double2(hc[i + 1] + (i + 1 == j ? zs.x : 0.0), i + 1 == j ? zs.y : 0.0);
     };
@@ -499,14 +746,13 @@ __global__ void __launch_bounds__(64) ms_givens_kernel(const int* __restrict__ s
     sn[(int64_t)j * S + s] = sv;
     const double2 cj = cadd(cscale(c, x), cscale(hn, sv));
     col[(int64_t)j * S] = cj;
-    const double2 gj = g[(int64_t)j * S + s];
     const double2 gn = cscale(-1.0, cmul(cconj(sv), gj));
     g[(int64_t)(j + 1) * S + s] = gn;
     g[(int64_t)j * S + s] = cscale(c, gj);
     const double e = cabs(gn);
     est[s] = e;
     int f = 0;
-    if (e <= tol_abs[s]) f |= 1;
+    if (e <= tol) f |= 1;
     if (hn <= 1e-14 * cabs(cj)) f |= 2;   // the Krylov space is invariant: the iterate is exact
     if (!(e == e) || !(hn == hn)) f |= 4;
     flags[s] = f;
@@ -514,96 +760,202 @@ __global__ void __launch_bounds__(64) ms_givens_kernel(const int* __restrict__ s
     if (f) run[s] = 0;
 }
 
-// y = R^-1 g over the first k[s] columns, one work-group per system: column-oriented back
-// substitution on the packed R (entry i of column c at ((c (c + 1) / 2) + i) S + s), y kept in LDS;
+__global__ void __launch_bounds__(64) ms_givens_kernel(GivensArgs a) {
+    givens_wave(blockIdx.x, threadIdx.x, a.sys, a.nsys, a.j, a.m, a.sdir, a.z, a.H, a.cs, a.sn, a.g, a.R, a.S, a.est,
+                a.tol_abs, a.flags, a.run, a.ksteps);
+}
+
+// The update sweep of step k and the Givens step on column k-1, which do not depend on each other, in one launch
+// for structures of some thousand atoms, where each alone is a few microseconds of latency on a part of the chip.
+// The first nupd work-groups update 64 rows of one direction each, the basis split over 16 waves (fixed-order LDS
+// sums); the others take the Givens steps of gper systems each.
+__global__ void __launch_bounds__(1024) ms_update_givens_kernel(double* __restrict__ V, int64_t n, int64_t npad, int mdim1,
+                                                                int k, DirList dirs,
+                                                                const double* __restrict__ dots, int ps,
+                                                                const double* __restrict__ gam,
+                                                                const double* __restrict__ inv_rho,
+                                                                double* __restrict__ norm, int nupd, int gper, GivensArgs a) {
+    __shared__ double pa[16][64], pb[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)blockIdx.x >= nupd) {
+        const int q = ((int)blockIdx.x - nupd) * gper + wave;
+        if (wave < gper && q < a.nsys)
+            givens_wave(q, lane, a.sys, a.nsys, a.j, a.m, a.sdir, a.z, a.H, a.cs, a.sn, a.g, a.R, a.S, a.est, a.tol_abs,
+                        a.flags, a.run, a.ksteps);
+        return;
+    }
+    const int nrb = (int)(npad / kMsRows);
+    const int64_t rb = blockIdx.x % nrb;
+    const int d = dirs[blockIdx.x / nrb];
+    const int64_t row = rb * kMsRows + lane;
+    const double* dt = dots + (int64_t)d * ps;
+    const double* v = V + (int64_t)d * mdim1 * npad + row;
+    double* u = V + ((int64_t)d * mdim1 + k) * npad;
+    double* zv = u + npad;
+    const double ur = u[row], zr = zv[row], ir = inv_rho[d], gm = gam[d];   // ahead of the sums (wave 0 uses them)
+    double sa = 0.0, sb = 0.0;
+#pragma unroll 4
+    for (int i = wave; i < k; i += 16) {
+        const double x = v[(int64_t)i * npad];
+        sa += dt[i] * x;
+        sb += dt[k + 1 + i] * x;
+    }
+    pa[wave][lane] = sa;
+    pb[wave][lane] = sb;
+    __syncthreads();
+    if (wave != 0) return;
+    double x = 0.0;
+    if (row < n) {
+        sa = sb = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            sa += pa[q][lane];
+            sb += pb[q][lane];
+        }
+        const double qk = (ur - sa) * ir;
+        x = (zr - sb - gm * qk) * ir;
+        u[row] = qk;
+        zv[row] = x;
+    }
+    const double s2 = wave_sum(x * x);
+    if (lane == 0) norm[(int64_t)d * nrb + rb] = s2;
+}
+
+// y = R^-1 g over the first k[s] columns, one work-group per system; packed R: entry i of column c at
+// ((c (c + 1) / 2) + i) S + s
 __global__ void __launch_bounds__(256) ms_solve_kernel(const int* __restrict__ sys, const int* __restrict__ ksteps,
                                                        int m, const double2* __restrict__ R, int64_t S,
                                                        const double2* __restrict__ g, double2* __restrict__ y) {
     extern __shared__ double2 ys[];
     const int s = sys[blockIdx.x];
     const int K = ksteps[s];
-    auto rat = [&](int c, int i) { return R[((int64_t)c * (c + 1) / 2 + i) * S + s]; };
     for (int i = threadIdx.x; i < K; i += blockDim.x) ys[i] = g[(int64_t)i * S + s];
-    __syncthreads();
-    for (int i = K - 1; i >= 0; --i) {
-        const double2 yi = cdiv(ys[i], rat(i, i));   // every thread computes it; ys[i] is final here
-        __syncthreads();
-        if (threadIdx.x == 0) ys[i] = yi;
-        for (int r = threadIdx.x; r < i; r += blockDim.x) ys[r] = csub(ys[r], cmul(rat(i, r), yi));
-        __syncthreads();
-    }
+    back_substitute<double2>(ys, K, [&](int c, int i) { return R[((int64_t)c * (c + 1) / 2 + i) * S + s]; });
     for (int i = threadIdx.x; i < K; i += blockDim.x) y[(int64_t)s * m + i] = ys[i];
 }
 
 // x(s) = sum_{i < k[s]} y[s][i] V(d, i) for groups of up to 8 systems of one direction (the basis
 // is read once per group); rows >= n and systems with k = 0 get 0. Real part at out + col sys_stride,
 // imaginary part im_off further, with col = pos[s] (skipped when negative) or s when pos is NULL.
+// Each thread owns kRows rows, 64 apart; the coefficients of 64 steps at a time are staged in LDS (zeros past a
+// system's k), so the loop over the steps waits for the basis alone. SPLIT: the four waves share 64 kRows rows
+// and take every fourth step (sums added in LDS in order), for structures whose rows alone are too few waves.
+template <int kRows, bool SPLIT>
 __global__ void __launch_bounds__(256) ms_xupdate_kernel(const double* __restrict__ V, int64_t n, int64_t npad,
                                                          int mdim1, const int* __restrict__ grp_sys,
                                                          const int* __restrict__ grp_dir, const int* __restrict__ ksteps,
                                                          const double2* __restrict__ y, int m,
                                                          double* __restrict__ out, int64_t sys_stride, int64_t im_off,
                                                          const int* __restrict__ pos) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    constexpr int kStage = 64;
+    __shared__ double2 sy[kStage][kMsGroup];
+    __shared__ double2 red[SPLIT ? 4 : 1][kMsGroup][SPLIT ? 64 : 1];
+    static_assert(!SPLIT || kRows == 1, "the split form has one row per lane");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t i0 = SPLIT ? (int64_t)blockIdx.x * 64 + lane : ((int64_t)blockIdx.x * 4 + wave) * 64 * kRows + lane;
     const int gi = blockIdx.y;
     const int d = grp_dir[gi];
-    int sid[kMsGroup], kk[kMsGroup];
     int kmax = 0;
 #pragma unroll
     for (int t = 0; t < kMsGroup; ++t) {
-        sid[t] = grp_sys[gi * kMsGroup + t];
-        kk[t] = sid[t] >= 0 ? ksteps[sid[t]] : 0;
-        kmax = max(kmax, kk[t]);
+        const int s = grp_sys[gi * kMsGroup + t];
+        if (s >= 0) kmax = max(kmax, ksteps[s]);
     }
-    double ar[kMsGroup], ai[kMsGroup];
+    double ar[kRows][kMsGroup], ai[kRows][kMsGroup];
 #pragma unroll
-    for (int t = 0; t < kMsGroup; ++t) ar[t] = ai[t] = 0.0;
-    if (i < n) {
-        for (int c = 0; c < kmax; ++c) {
-            const double v = V[((int64_t)d * mdim1 + c) * npad + i];
+    for (int r = 0; r < kRows; ++r)
 #pragma unroll
-            for (int t = 0; t < kMsGroup; ++t)
-                if (c < kk[t]) {
-                    const double2 yc = y[(int64_t)sid[t] * m + c];
-                    ar[t] += yc.x * v;
-                    ai[t] += yc.y * v;
+        for (int t = 0; t < kMsGroup; ++t) ar[r][t] = ai[r][t] = 0.0;
+    const double* v = V + (int64_t)d * mdim1 * npad;
+    for (int c0 = 0; c0 < kmax; c0 += kStage) {
+        __syncthreads();
+        for (int q = tid; q < kStage * kMsGroup; q += 256) {
+            const int t = q / kStage, c = c0 + q % kStage, s = grp_sys[gi * kMsGroup + t];
+            sy[q % kStage][t] = s >= 0 && c < ksteps[s] ? y[(int64_t)s * m + c] : make_double2(0.0, 0.0);
+        }
+        __syncthreads();
+        const int cn = min(kStage, kmax - c0);
+#pragma unroll 4
+        for (int c = SPLIT ? wave : 0; c < cn; c += SPLIT ? 4 : 1) {
+            double x[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) {
+                const int64_t i = i0 + 64 * r;
+                x[r] = i < npad ? v[(int64_t)(c0 + c) * npad + i] : 0.0;
+            }
+#pragma unroll
+            for (int t = 0; t < kMsGroup; ++t) {
+                const double2 yc = sy[c][t];
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    ar[r][t] = fma(yc.x, x[r], ar[r][t]);
+                    ai[r][t] = fma(yc.y, x[r], ai[r][t]);
                 }
+            }
         }
     }
+    auto store = [&](int t, int64_t i, double re, double im) {
+        const int s = grp_sys[gi * kMsGroup + t];
+        const int col = s < 0 ? -1 : pos ? pos[s] : s;
+        if (col < 0 || i >= npad) return;
+        double* xr = out + (int64_t)col * sys_stride;
+        xr[i] = i < n ? re : 0.0;
+        xr[i + im_off] = i < n ? im : 0.0;
+    };
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int t = 0; t < kMsGroup; ++t) {
-        const int col = sid[t] < 0 ? -1 : pos ? pos[sid[t]] : sid[t];
-        if (col >= 0) {
-            double* xr = out + (int64_t)col * sys_stride;
-            xr[i] = ar[t];
-            xr[i + im_off] = ai[t];
+        for (int t = 0; t < kMsGroup; ++t) red[wave][t][lane] = make_double2(ar[0][t], ai[0][t]);
+        __syncthreads();
+        for (int t = wave; t < kMsGroup; t += 4) {
+            const double2 a = red[0][t][lane], b = red[1][t][lane], c = red[2][t][lane], e = red[3][t][lane];
+            store(t, i0, (a.x + b.x) + (c.x + e.x), (a.y + b.y) + (c.y + e.y));
         }
+    } else {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int t = 0; t < kMsGroup; ++t) store(t, i0 + 64 * r, ar[r][t], ai[r][t]);
     }
 }
 
 }  // namespace
 
-void ms_pack(int prec, double* V, int64_t npad, int mdim1, int j, const int* dirs, int ndir, const double* scale,
-             void* X, int64_t ld, hipStream_t st) {
+void ms_pack(int prec, double* V, int64_t npad, int mdim1, int j, const DirList& dirs, int ndir, const double* norm,
+             double* nu, double* inv_h, void* X, int64_t ld, hipStream_t st) {
     if (ndir <= 0) return;
     dim3 grd((unsigned)(npad / 256), (unsigned)ndir);
-    if (prec == WFQ_PREC_FP64)
-        hipLaunchKernelGGL(ms_pack_kernel<double>, grd, dim3(256), 0, st, V, npad, mdim1, j, dirs, scale,
-                           static_cast<double*>(X), ld);
-    else if (prec == WFQ_PREC_FP32)
-        hipLaunchKernelGGL(ms_pack_kernel<float>, grd, dim3(256), 0, st, V, npad, mdim1, j, dirs, scale,
-                           static_cast<float*>(X), ld);
-    else
-        hipLaunchKernelGGL(ms_pack_kernel<uint16_t>, grd, dim3(256), 0, st, V, npad, mdim1, j, dirs, scale,
-                           static_cast<uint16_t*>(X), ld);
+    auto go = [&](auto tag) {
+        using E = decltype(tag);
+        hipLaunchKernelGGL(ms_pack_kernel<E>, grd, dim3(256), 0, st, V, npad, mdim1, j, dirs, norm, nu, inv_h,
+                           static_cast<E*>(X), ld);
+    };
+    if (prec == WFQ_PREC_FP64) go(double{});
+    else if (prec == WFQ_PREC_FP32) go(float{});
+    else go(uint16_t{});
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const int* dirs, int ndir, double* V,
-             int mdim1, int jdst, double* TV, hipStream_t st, const double* Yi) {
+void ms_skinny(const Structure& S, const double* V, int mdim1, int j, const DirList& dirs, int ndir, const double* norm,
+               double* nu, double* inv_h, double* Y, hipStream_t st) {
+    if (ndir <= 0) return;
+    if (ndir > 4 || !S.T64) throw Error{WFQ_EINVAL, "ms_skinny: up to 4 columns of a stored FP64 T"};
+    auto go = [&](auto ncv) {
+        constexpr int NC = decltype(ncv)::value;
+        hipLaunchKernelGGL(ms_skinny_kernel<NC>, dim3((unsigned)(S.npad / kMsRowsT)), dim3(256), 0, st, S.T64, S.npad, V,
+                           mdim1, j, dirs, norm, nu, inv_h, Y);
+    };
+    if (ndir == 1) go(std::integral_constant<int, 1>{});
+    else if (ndir == 2) go(std::integral_constant<int, 2>{});
+    else if (ndir == 3) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
+    WFQ_CHECK_LAUNCH();
+}
+
+void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const DirList& dirs, int ndir, double* V,
+             int mdim1, int jdst, double* TV, hipStream_t st, const double* Yi, const double* scale) {
     if (ndir <= 0) return;
     if (Yi && (!y_is_f64 || ndir > 4)) throw Error{WFQ_EINVAL, "ms_spmm: the interleaved copy holds up to 4 FP64 columns"};
-    const dim3 grd((unsigned)(S.npad / 256));
+    const dim3 grd((unsigned)(S.npad / 64));
     // columns in chunks of at most 4 (3 for the usual three field directions in one pass)
     for (int c0 = 0; c0 < ndir; c0 += 4) {
         const int nc = std::min(4, ndir - c0);
@@ -611,7 +963,7 @@ void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const
             using YE = decltype(tag);
             constexpr int NC = decltype(ncv)::value;
             hipLaunchKernelGGL((ms_spmm_kernel<YE, NC>), grd, dim3(256), 0, st, S.n, S.npad, S.ell_w, S.ell_col,
-                               S.ell_val, static_cast<const YE*>(Y), ld, dirs, V, mdim1, jdst, c0, TV, Yi);
+                               S.ell_val, static_cast<const YE*>(Y), ld, dirs, V, mdim1, jdst, c0, TV, Yi, scale);
         };
         auto by_nc = [&](auto tag) {
             if (nc == 1) go(tag, std::integral_constant<int, 1>{});
@@ -627,7 +979,7 @@ void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const
     }
 }
 
-void ms_dot(const double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const int* dirs, int ndir,
+void ms_dot(const double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const DirList& dirs, int ndir,
             double* partial, int pslots, bool self_norm, hipStream_t st) {
     const int ntot = nvec + (self_norm ? 1 : 0);
     if (ndir <= 0 || ntot <= 0) return;
@@ -638,7 +990,7 @@ void ms_dot(const double* V, int64_t n, int64_t npad, int mdim1, int nvec, int j
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_reduce(const int* dirs, int ndir, const double* partial, int pslots, int64_t n, int count, double* h,
+void ms_reduce(const DirList& dirs, int ndir, const double* partial, int pslots, int64_t n, int count, double* h,
                hipStream_t st) {
     if (ndir <= 0 || count <= 0) return;
     hipLaunchKernelGGL(ms_reduce_kernel, dim3((unsigned)((count + 3) / 4), (unsigned)ndir), dim3(256), 0, st, dirs,
@@ -646,7 +998,7 @@ void ms_reduce(const int* dirs, int ndir, const double* partial, int pslots, int
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_update(double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const int* dirs, int ndir,
+void ms_update(double* V, int64_t n, int64_t npad, int mdim1, int nvec, int jw, const DirList& dirs, int ndir,
                const double* h, int pslots, double* norm, hipStream_t st) {
     if (ndir <= 0) return;
     dim3 grd((unsigned)(npad / kMsRows), (unsigned)ndir);
@@ -658,28 +1010,57 @@ void ms_givens(const int* sys, int nsys, int j, int m, const int* sdir, const do
                double2* sn, double2* g, double2* R, int64_t S, double* est, const double* tol_abs, int* flags,
                int* run, int* ksteps, hipStream_t st) {
     if (nsys <= 0) return;
-    hipLaunchKernelGGL(ms_givens_kernel, dim3((unsigned)nsys), dim3(64), 0, st, sys, nsys, j, m, sdir, z, H, cs, sn, g,
-                       R, S, est, tol_abs, flags, run, ksteps);
+    hipLaunchKernelGGL(ms_givens_kernel, dim3((unsigned)nsys), dim3(64), 0, st,
+                       GivensArgs{sys, nsys, j, m, sdir, z, H, cs, sn, g, R, S, est, tol_abs, flags, run, ksteps});
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_dcgs_dot(const double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const int* dirs, int ndir,
+bool ms_merged(int64_t npad) { return npad <= 8192; }
+
+void ms_update_givens(double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const DirList& dirs, int ndir,
+                      const double* dots, int ps, const double* gam, const double* irho, double* norm, const int* sys,
+                      int nsys, int m, const int* sdir, const double2* z, const double* H, double* cs, double2* sn,
+                      double2* g, double2* R, int64_t S, double* est, const double* tol_abs, int* flags, int* run,
+                      int* ksteps, hipStream_t st) {
+    const int nupd = with_z ? (int)(npad / kMsRows) * ndir : 0, ngiv = k >= 1 ? nsys : 0;
+    if (nupd + ngiv == 0) return;
+    // Givens steps spread over the chip: one to a work-group (its other waves end at once) up to 1 024 systems
+    // (600 systems: 5.8 us; 4 to a work-group 6.4, 16 to a work-group 10.2)
+    const int gper = std::min(16, 1 + ngiv / 1024);
+    hipLaunchKernelGGL(ms_update_givens_kernel, dim3((unsigned)(nupd + (ngiv + gper - 1) / gper)), dim3(1024), 0, st, V, n,
+                       npad, mdim1, k, dirs, dots, ps, gam, irho, norm, nupd, gper,
+                       GivensArgs{sys, ngiv, k - 1, m, sdir, z, H, cs, sn, g, R, S, est, tol_abs, flags, run, ksteps});
+    WFQ_CHECK_LAUNCH();
+}
+
+void ms_dcgs_dot(const double* V, int64_t n, int64_t npad, int mdim1, int k, bool with_z, const DirList& dirs, int ndir,
                  double* partial, int ps, hipStream_t st) {
     if (ndir <= 0) return;
     if (2 * k + 2 > ps) throw Error{WFQ_EINVAL, "ms_dcgs_dot: too few partial slots"};
     const int64_t nwc = wave_chunks(n);
-    dim3 grd((unsigned)((nwc + 3) / 4), (unsigned)(k / kDotGroup + 1), (unsigned)ndir);
-    hipLaunchKernelGGL(ms_dcgs_dot_kernel, grd, dim3(256), 0, st, V, n, npad, mdim1, k, with_z ? 1 : 0, dirs, partial,
-                       ps, nwc);
+    // four vectors per wave while 16 would leave fewer than 2 048 waves (two per SIMD)
+    const bool few = nwc * (k / 16 + 1) * ndir < 2048;
+    const int group = few ? 4 : 16;
+    dim3 grd((unsigned)((nwc + 3) / 4), (unsigned)(k / group + 1), (unsigned)ndir);
+    hipLaunchKernelGGL(few ? ms_dcgs_dot_kernel<4> : ms_dcgs_dot_kernel<16>, grd, dim3(256), 0, st, V, n, npad, mdim1, k,
+                       with_z ? 1 : 0, dirs, partial, ps, nwc);
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_dcgs_coeff(const int* dirs, int ndir, int k, bool with_z, int m, const double* dots, int ps, double* hp,
-                   double* H, double* Sm, const double* nu, const double* inv_h, double* gam, double* inv_rho,
-                   hipStream_t st) {
+void ms_dcgs_step(const DirList& dirs, int ndir, int k, bool with_z, int m, const double* partial, int ps, int64_t n,
+                  int64_t npad, const double* nu, const double* norm, double* dots, double* hp, double* H, double* Sm,
+                  double* gam, double* inv_rho, hipStream_t st) {
     if (ndir <= 0) return;
+    const int64_t nwc = wave_chunks(n), nblk = npad / kMsRows;
+    if (k <= kStepMax && nwc <= 64) {
+        hipLaunchKernelGGL(ms_dcgs_step_kernel, dim3((unsigned)ndir), dim3(1024), 0, st, dirs, k, with_z ? 1 : 0, m, partial,
+                           ps, nwc, nu, norm, nblk, dots, hp, H, Sm, gam, inv_rho);
+        WFQ_CHECK_LAUNCH();
+        return;
+    }
+    ms_reduce(dirs, ndir, partial, ps, n, with_z ? 2 * k + 2 : k + 1, dots, st);
     hipLaunchKernelGGL(ms_dcgs_coeff_kernel, dim3((unsigned)ndir), dim3(256), 0, st, dirs, k, with_z ? 1 : 0, m, dots,
-                       ps, hp, H, Sm, nu, inv_h, gam, inv_rho);
+                       ps, hp, H, Sm, nu, norm, nblk, gam, inv_rho);
     WFQ_CHECK_LAUNCH();
     if (!with_z) return;
     hipLaunchKernelGGL(ms_dcgs_hp_kernel, dim3((unsigned)(k / 64 + 1), (unsigned)ndir), dim3(1024), 0, st, dirs, k, m,
@@ -687,15 +1068,12 @@ void ms_dcgs_coeff(const int* dirs, int ndir, int k, bool with_z, int m, const d
     WFQ_CHECK_LAUNCH();
 }
 
-void ms_dcgs_update(double* V, int64_t n, int64_t npad, int mdim1, int k, const int* dirs, int ndir,
-                    const double* dots, int ps, const double* gam, const double* inv_rho, double* norm,
-                    double* nu, double* inv_h, hipStream_t st) {
+void ms_dcgs_update(double* V, int64_t n, int64_t npad, int mdim1, int k, const DirList& dirs, int ndir,
+                    const double* dots, int ps, const double* gam, const double* inv_rho, double* norm, hipStream_t st) {
     if (ndir <= 0) return;
     dim3 grd((unsigned)(npad / 256), (unsigned)ndir);
     hipLaunchKernelGGL(ms_dcgs_update_kernel, grd, dim3(256), 0, st, V, n, npad, mdim1, k, dirs, dots, ps, gam, inv_rho,
                        norm);
-    WFQ_CHECK_LAUNCH();
-    hipLaunchKernelGGL(ms_nu_kernel, dim3((unsigned)ndir), dim3(128), 0, st, dirs, norm, npad / kMsRows, nu, inv_h);
     WFQ_CHECK_LAUNCH();
 }
 
@@ -715,13 +1093,26 @@ void ms_solve(const int* sys, int nsys, const int* ksteps, int m, const double2*
     WFQ_CHECK_LAUNCH();
 }
 
+namespace {
+void launch_xupdate(const double* V, int64_t n, int64_t npad, int mdim1, const int* grp_sys, const int* grp_dir, int ngrp,
+                    const int* ksteps, const double2* y, int m, double* out, int64_t sys_stride, int64_t im_off,
+                    const int* pos, hipStream_t st) {
+    // four rows per thread (each coefficient read from LDS serves four products of the FP64 units, which bound it) from
+    // 2 048 waves on, two per SIMD; below, the steps are split over the waves
+    if (npad / 256 * ngrp >= 2048)
+        hipLaunchKernelGGL((ms_xupdate_kernel<4, false>), dim3((unsigned)((npad + 1023) / 1024), (unsigned)ngrp), dim3(256), 0,
+                           st, V, n, npad, mdim1, grp_sys, grp_dir, ksteps, y, m, out, sys_stride, im_off, pos);
+    else
+        hipLaunchKernelGGL((ms_xupdate_kernel<1, true>), dim3((unsigned)(npad / 64), (unsigned)ngrp), dim3(256), 0, st, V, n,
+                           npad, mdim1, grp_sys, grp_dir, ksteps, y, m, out, sys_stride, im_off, pos);
+    WFQ_CHECK_LAUNCH();
+}
+}  // namespace
+
 void ms_xupdate(const double* V, int64_t n, int64_t npad, int mdim1, const int* grp_sys, const int* grp_dir, int ngrp,
                 const int* ksteps, const double2* y, int m, const Basis& X, hipStream_t st) {
     if (ngrp <= 0) return;
-    dim3 grd((unsigned)(npad / 256), (unsigned)ngrp);
-    hipLaunchKernelGGL(ms_xupdate_kernel, grd, dim3(256), 0, st, V, n, npad, mdim1, grp_sys, grp_dir, ksteps, y, m,
-                       X.base, X.sys_stride, X.npad, nullptr);
-    WFQ_CHECK_LAUNCH();
+    launch_xupdate(V, n, npad, mdim1, grp_sys, grp_dir, ngrp, ksteps, y, m, X.base, X.sys_stride, X.npad, nullptr, st);
 }
 
 void ms_txupdate(const double* TV, int64_t n, int64_t npad, int mdim1, const int* grp_sys, const int* grp_dir,
@@ -729,10 +1120,7 @@ void ms_txupdate(const double* TV, int64_t n, int64_t npad, int mdim1, const int
                  hipStream_t st) {
     if (ngrp <= 0) return;
     if (ld < npad) throw Error{WFQ_EINVAL, "ms_txupdate: leading dimension below the padded length"};
-    dim3 grd((unsigned)(npad / 256), (unsigned)ngrp);
-    hipLaunchKernelGGL(ms_xupdate_kernel, grd, dim3(256), 0, st, TV, n, npad, mdim1, grp_sys, grp_dir, ksteps, y, m, Y,
-                       2 * ld, ld, pos);
-    WFQ_CHECK_LAUNCH();
+    launch_xupdate(TV, n, npad, mdim1, grp_sys, grp_dir, ngrp, ksteps, y, m, Y, 2 * ld, ld, pos, st);
 }
 
 }  // namespace wfq

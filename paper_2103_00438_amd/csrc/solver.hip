@@ -9,6 +9,7 @@
 // and a system whose FP64 residual stalls while its inner estimate fell is moved to a higher
 // precision (its inner operator was not accurate enough).
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -401,8 +402,9 @@ void clear_work(Work& w, hipStream_t st) {
 
 struct GraphKey {
     int kind, j0, c, ns, g0, g1, g2;
+    std::array<int, 4> dirs{};   // directions that the captured launches hold by value
     bool operator<(const GraphKey& o) const {
-        return std::tie(kind, j0, c, ns, g0, g1, g2) < std::tie(o.kind, o.j0, o.c, o.ns, o.g0, o.g1, o.g2);
+        return std::tie(kind, j0, c, ns, g0, g1, g2, dirs) < std::tie(o.kind, o.j0, o.c, o.ns, o.g0, o.g1, o.g2, o.dirs);
     }
 };
 
@@ -954,27 +956,28 @@ constexpr double kRelaxFloor = 100.0;
 // Relative error of the first shared-basis product in `prec` against FP64, max over directions:
 // ||L (T_prec - T) v0|| / ||L T v0|| with v0 = b / ||b||. Leaves slot 0 of every direction normalised
 // and inv_h = 1 (so the first step of the phase packs v0 as it is); uses slots 1 and 2 as scratch.
-double ms_product_error(const Structure& S, Work& w, int prec, const std::vector<double>& beta, hipStream_t st) {
+double ms_product_error(const Structure& S, Work& w, int prec, const std::vector<double>& beta, const DirList& dirs,
+                        hipStream_t st) {
     MsWork& q = w.ms;
     const int nd = w.n_dir;
     const int m = w.shape.ms_m, mdim1 = m + 1, pslots = m + 2;
     const int64_t n = S.n, np = S.npad;
     // v0 and L T v0 with FP64 T (slot 2), then L T_prec v0 (slot 1)
-    ms_pack(WFQ_PREC_FP64, q.V.p, np, mdim1, 0, q.dirs.p, nd, q.inv_h.p, w.X64.p, np, st);
+    ms_pack(WFQ_PREC_FP64, q.V.p, np, mdim1, 0, dirs, nd, nullptr, q.nu.p, q.inv_h.p, w.X64.p, np, st);
     tx_any(S, WFQ_PREC_FP64, w.X64.p, w.Y64.p, nd, st);
-    ms_spmm(S, true, w.Y64.p, np, q.dirs.p, nd, q.V.p, mdim1, 2, nullptr, st);
+    ms_spmm(S, true, w.Y64.p, np, dirs, nd, q.V.p, mdim1, 2, nullptr, st);
     std::vector<double> ones(nd, 1.0);
     h2d_sync(S, q.inv_h.p, ones.data(), nd * sizeof(double), st);
-    ms_pack(prec, q.V.p, np, mdim1, 0, q.dirs.p, nd, q.inv_h.p, x_block(w, prec), np, st);
+    ms_pack(prec, q.V.p, np, mdim1, 0, dirs, nd, nullptr, q.nu.p, q.inv_h.p, x_block(w, prec), np, st);
     tx_any(S, prec, x_block(w, prec), const_cast<void*>(y_block(w, prec)), nd, st);
-    ms_spmm(S, prec == WFQ_PREC_FP64, y_block(w, prec), np, q.dirs.p, nd, q.V.p, mdim1, 1, nullptr, st);
+    ms_spmm(S, prec == WFQ_PREC_FP64, y_block(w, prec), np, dirs, nd, q.V.p, mdim1, 1, nullptr, st);
     // ||slot 2||^2, then slot 2 -= slot 1 with the squared norm of the difference per 64-row block
-    ms_dot(q.V.p, n, np, mdim1, 0, 2, q.dirs.p, nd, q.part.p, pslots, true, st);
-    ms_reduce(q.dirs.p, nd, q.part.p, pslots, n, 1, q.h1.p, st);
+    ms_dot(q.V.p, n, np, mdim1, 0, 2, dirs, nd, q.part.p, pslots, true, st);
+    ms_reduce(dirs, nd, q.part.p, pslots, n, 1, q.h1.p, st);
     std::vector<double> coef((size_t)nd * pslots, 0.0);
     for (int d = 0; d < nd; ++d) coef[(size_t)d * pslots + 1] = 1.0;
     h2d_sync(S, q.h2.p, coef.data(), coef.size() * sizeof(double), st);
-    ms_update(q.V.p, n, np, mdim1, 2, 2, q.dirs.p, nd, q.h2.p, pslots, q.nrm.p, st);
+    ms_update(q.V.p, n, np, mdim1, 2, 2, dirs, nd, q.h2.p, pslots, q.nrm.p, st);
     std::vector<double> h1((size_t)nd * pslots), nrm((size_t)nd * (np / 64));
     d2h_sync(S, h1.data(), q.h1.p, h1.size() * sizeof(double), st);
     d2h_sync(S, nrm.data(), q.nrm.p, nrm.size() * sizeof(double), st);
@@ -1009,7 +1012,8 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
     double *V = q.V.p, *H = q.H.p, *part = q.part.p, *h1 = q.h1.p, *h2 = q.h2.p, *nrm = q.nrm.p, *inv_h = q.inv_h.p;
     double *cs = q.cs.p, *est = q.est.p, *tol_abs = q.tol_abs.p;
     double2 *sn = q.sn.p, *g = q.g.p, *R = q.R.p, *y = q.y.p, *z = q.z.p;
-    int *dirs = q.dirs.p, *sdir = q.sdir.p, *sys = q.sys.p, *flags = q.flags.p, *ksteps = q.ksteps.p;
+    int *sdir = q.sdir.p, *sys = q.sys.p, *flags = q.flags.p, *ksteps = q.ksteps.p;
+    DirList dirs;   // the active directions
     int *grp_sys = q.grp_sys.p, *grp_dir = q.grp_dir.p, *run = q.run.p;
     int *h_dirs = q.h_dirs.p, *h_sys = q.h_sys.p, *h_k = q.h_k.p;
     double* h_nrm = q.h_nrm.p;
@@ -1020,7 +1024,17 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
                                hipMemcpyDeviceToDevice, st));
         h_dirs[d] = d;
     }
-    WFQ_HIP(hipMemcpyAsync(dirs, h_dirs, nd * sizeof(int), hipMemcpyHostToDevice, st));
+    auto set_dirs = [&](int count) {
+        if (count <= 4) {
+            dirs = DirList{};
+            std::copy(h_dirs, h_dirs + count, dirs.d);
+        } else {
+            dirs = DirList{};
+            dirs.p = q.dirs.p;
+            WFQ_HIP(hipMemcpyAsync(q.dirs.p, h_dirs, count * sizeof(int), hipMemcpyHostToDevice, st));
+        }
+    };
+    set_dirs(nd);
     ms_dot(V, n, np, mdim1, 0, 0, dirs, nd, part, pslots, true, st);
     ms_reduce(dirs, nd, part, pslots, n, 1, h1, st);
     WFQ_HIP(hipMemcpyAsync(h_nrm, h1, (size_t)nd * pslots * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -1061,7 +1075,7 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
         if (o.ms_relax > 0.0) {
             switch_at = o.ms_relax;
         } else {
-            const double delta = ms_product_error(S, w, prec, beta, st);
+            const double delta = ms_product_error(S, w, prec, beta, dirs, st);
             // the residual floor of a basis built entirely in `precision` is taken as kRelaxFloor times the
             // relative error of one product; switching at level s adds about s times that floor
             switch_at = delta > 0.0 ? std::min(1.0, std::max(tol, 0.5 * tol / (kRelaxFloor * delta))) : 1.0;
@@ -1093,7 +1107,7 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
         std::memcpy(h_sys, stepping.data(), ns * sizeof(int));
         std::fill(w.h_run.p, w.h_run.p + B, 0);
         for (int s : stepping) w.h_run.p[s] = 1;
-        WFQ_HIP(hipMemcpyAsync(dirs, h_dirs, na * sizeof(int), hipMemcpyHostToDevice, st));
+        set_dirs(na);
         WFQ_HIP(hipMemcpyAsync(sys, h_sys, ns * sizeof(int), hipMemcpyHostToDevice, st));
         WFQ_HIP(hipMemcpyAsync(run, w.h_run.p, B * sizeof(int), hipMemcpyHostToDevice, st));
         WFQ_HIP(hipStreamSynchronize(st));   // the pinned lists are rewritten by the next call
@@ -1114,15 +1128,26 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
         auto step = [&](int j) {
             const bool wz = j < m;
             if (wz) {
-                // z = L T u_j (one real column per direction) into slot j + 1
+                // z = L T u_j (one real column per direction) into slot j + 1; the first vectors' norms are known,
+                // the later ones' are the block sums of the update sweep
+                const double* pn = j > 0 ? nrm : nullptr;
+                const bool direct = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_skinny(S, cur, na);
+                double* yi = nullptr;
                 tm.begin(st);
-                ms_pack(cur, V, np, mdim1, j, dirs, na, inv_h, x_block(w, cur), np, st);
-                tm.end(st, KC_PACK, 0, na * dn * (16.0 + elem_size(cur)));
-                double* yi = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_otf_narrow(S, cur, na) ? q.Yi.p : nullptr;
-                block_product(S, w, cur, na, tm, st, yi);
+                if (direct) {
+                    // small stored T: pack and product in one launch, the basis vector normalised by the SpMM
+                    ms_skinny(S, V, mdim1, j, dirs, na, pn, nu, inv_h, w.Y64.p, st);
+                    tm.end(st, KC_SKINNY, 2.0 * dn * dn * na, 8.0 * dn * dn + na * dn * 16.0);
+                } else {
+                    ms_pack(cur, V, np, mdim1, j, dirs, na, pn, nu, inv_h, x_block(w, cur), np, st);
+                    tm.end(st, KC_PACK, 0, na * dn * (16.0 + elem_size(cur)));
+                    yi = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_otf_narrow(S, cur, na) ? q.Yi.p : nullptr;
+                    block_product(S, w, cur, na, tm, st, yi);
+                }
                 tm.begin(st);
                 double* tv = keep_tv ? q.TV.p : nullptr;
-                ms_spmm(S, cur == WFQ_PREC_FP64, y_block(w, cur), np, dirs, na, V, mdim1, j + 1, tv, st, yi);
+                ms_spmm(S, cur == WFQ_PREC_FP64, y_block(w, cur), np, dirs, na, V, mdim1, j + 1, tv, st, yi,
+                        direct ? inv_h : nullptr);
                 // L is read once for all directions (up to four per pass)
                 tm.end(st, KC_SPMM, 2.0 * S.nnz * na,
                        12.0 * S.nnz * ((na + 3) / 4) + na * dn * (out_size(cur) + 8 + (tv ? 8 : 0)));
@@ -1130,22 +1155,27 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
             // one sweep of dots against q_0 .. q_{j-1} and u, one update sweep
             tm.begin(st);
             ms_dcgs_dot(V, n, np, mdim1, j, wz, dirs, na, part, ps2, st);
-            ms_reduce(dirs, na, part, ps2, n, wz ? 2 * j + 2 : j + 1, dots, st);
+            ms_dcgs_step(dirs, na, j, wz, m, part, ps2, n, np, nu, nrm, dots, hp, H, keep_tv ? q.Sm.p : nullptr, gam,
+                         irho, st);
             tm.end(st, KC_DOT, (wz ? 4.0 : 2.0) * dn * na * (j + 1), 8.0 * dn * na * (j + (wz ? 2 : 1)));
+            // the update sweep, and for every unconverged frequency of those directions one Givens step on column
+            // j - 1 of Hbar + z Ibar
             tm.begin(st);
-            ms_dcgs_coeff(dirs, na, j, wz, m, dots, ps2, hp, H, keep_tv ? q.Sm.p : nullptr, nu, inv_h, gam, irho, st);
-            if (wz)
-                ms_dcgs_update(V, n, np, mdim1, j, dirs, na, dots, ps2, gam, irho, nrm, nu, inv_h, st);
-            tm.end(st, KC_UPDATE, wz ? 4.0 * dn * na * j : 0.0, wz ? 8.0 * dn * na * (j + 4) : 0.0);
-            // every unconverged frequency of those directions: one Givens step on column j - 1 of
-            // Hbar + z Ibar
-            if (j >= 1) {
-                tm.begin(st);
-                ms_givens(sys, ns, j - 1, m, sdir, z, H, cs, sn, g, R, B, est, tol_abs, flags, run, ksteps, st);
-                tm.end(st, KC_GIVENS, 0, 0);
+            if (ms_merged(np)) {
+                ms_update_givens(V, n, np, mdim1, j, wz, dirs, na, dots, ps2, gam, irho, nrm, sys, ns, m, sdir, z, H, cs, sn,
+                                 g, R, B, est, tol_abs, flags, run, ksteps, st);
+                tm.end(st, KC_UPDATE, wz ? 4.0 * dn * na * j : 0.0, wz ? 8.0 * dn * na * (j + 4) : 0.0);
+            } else {
+                if (wz) ms_dcgs_update(V, n, np, mdim1, j, dirs, na, dots, ps2, gam, irho, nrm, st);
+                tm.end(st, KC_UPDATE, wz ? 4.0 * dn * na * j : 0.0, wz ? 8.0 * dn * na * (j + 4) : 0.0);
+                if (j >= 1) {
+                    tm.begin(st);
+                    ms_givens(sys, ns, j - 1, m, sdir, z, H, cs, sn, g, R, B, est, tol_abs, flags, run, ksteps, st);
+                    tm.end(st, KC_GIVENS, 0, 0);
+                }
             }
         };
-        run_chunk(gc, S, GraphKey{1, j0, c, ns, na, cur, keep_tv ? 1 : 0}, st, [&] {
+        run_chunk(gc, S, GraphKey{1, j0, c, ns, na, cur, keep_tv ? 1 : 0, {dirs.d[0], dirs.d[1], dirs.d[2], dirs.d[3]}}, st, [&] {
             for (int j = j0; j < j0 + c; ++j) step(j);
         });
         j0 += c;

@@ -142,3 +142,40 @@ def test_multishift_options_rejected(lib):
         lib.wfq_solve(h, [0.3], [[1, 0, 0]], 1e-8, algorithm="msgmres", restart=300)
     assert e.value.code == lib.WFQ_EINVAL
     h.close()
+
+
+@pytest.mark.parametrize("n,ndir", [(5, 1), (64, 2), (257, 3), (700, 4), (700, 5), (3001, 2), (8192, 3), (8200, 3)])
+def test_multishift_step_kernels_over_sizes_and_directions(lib, n, ndir):
+    # the step's kernels change with the number of directions (up to four by value; products of one to four columns)
+    # and with the rows (64-row and 256-row blocks, one launch or two from 8 192): the charges must satisfy the
+    # oracle's system to the tolerance, by the shared basis alone
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(8, 8, n // 32 + 1)[:n], 0.01, seed=n)
+    dirs = np.array([[1, 0, 0], [0, 0, 1], [0, 1, 0], [0.6, 0, 0.8], [0, 0.6, -0.8]])[:ndir]
+    om, tol = np.array([0.1, 0.9]), 1e-10
+    h = lib.wfq_build(xyz, GRAPHENE)
+    out = lib.wfq_solve(h, om, dirs, tol, algorithm="msgmres", restart=30, precision="fp64", shift_dim=300)
+    h.close()
+    assert out["status"] == 0, out["info"]
+    P = O.Problem(xyz, GRAPHENE)
+    for a in range(len(om)):
+        for k in range(ndir):
+            info = out["info"][a * ndir + k]
+            assert info["cycles"] == 0 and info["relres"] <= tol, (a, k, info)
+            assert P.residual(om[a], dirs[k], out["q"][a, k]) <= 1.01 * tol + 1e-13, (a, k, info)
+
+
+def test_multishift_beyond_the_one_launch_step(lib):
+    # more steps than the fused step kernel takes (384): the later ones go through the separate kernels
+    xyz = wi.geometry.jitter(wi.geometry.fcc_sphere(16.0), 0.01, seed=3)
+    par = dict(wi.workloads.FCC_METAL, tau=600.0)
+    om, tol = np.array([4.0, 4.4]), 1e-10
+    h = lib.wfq_build(xyz, par)
+    out = lib.wfq_solve(h, om, np.eye(3), tol, algorithm="msgmres", restart=30, precision="fp64", shift_dim=700)
+    h.close()
+    P = O.Problem(xyz, par)
+    assert out["status"] == 0 and max(i["iters"] for i in out["info"]) > 400, out["info"]
+    for a in range(len(om)):
+        for k in range(3):
+            info = out["info"][a * 3 + k]
+            assert info["cycles"] == 0 and info["relres"] <= tol, (a, k, info)
+            assert P.residual(om[a], np.eye(3)[k], out["q"][a, k]) <= 1.01 * tol + 1e-13, (a, k, info)

@@ -441,7 +441,7 @@ int apply_T_impl(wfq_handle* h, int32_t precision, int32_t variant, int32_t ncol
         if (variant >= 0)
             tx_variant_run(S, precision, variant, dx, dy, ncol, h->stream);
         else
-            tx_any(S, precision, dx, dy, ncol, h->stream, true);
+            tx_any(S, precision, dx, dy, ncol, h->stream, Order::any);
         if (precision == WFQ_PREC_FP64) {
             d2h_sync(S, yh.data(), dy, (size_t)ncol * np * 8, h->stream);
         } else {
@@ -596,7 +596,7 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
         WFQ_CHECK_LAUNCH();
         const Basis Vb{V, 4 * np, 2 * np, np};
         pack_columns(precision, Vb, sys, nsys, 0, nullptr, false, X, np, st);
-        tx_any(S, precision, X, Y, 2 * nsys, st, true);
+        tx_any(S, precision, X, Y, 2 * nsys, st, Order::any);
         spmm_shift(S, precision == WFQ_PREC_FP64, Y, np, sys, nsys, zs, Vb, 0, 1, st);
         scatter_q(S, S.dperm, sys, nsys, Basis{V + 2 * np, 4 * np, 2 * np, np}, Y_re_dev, Y_im_dev, st);
         return WFQ_OK;
@@ -641,7 +641,7 @@ int wfq_apply_op(wfq_handle* h, int32_t precision, int32_t nsys, const double* z
         h2d_sync(h->S, dsys, sl.data(), nsys * sizeof(int), h->stream);
         Basis V{dv, sys_stride, 2 * np, np};
         pack_columns(precision, V, dsys, nsys, 0, nullptr, false, dx, np, h->stream);
-        tx_any(S, precision, dx, dy, 2 * nsys, h->stream, true);
+        tx_any(S, precision, dx, dy, 2 * nsys, h->stream, Order::any);
         spmm_shift(S, precision == WFQ_PREC_FP64, dy, np, dsys, nsys, dz, V, 0, 1, h->stream);
         d2h_sync(S, vh.data(), dv, vh.size() * 8, h->stream);
         (void)hipFree(dv);

@@ -651,7 +651,7 @@ void build_structure(Structure& s, const wfq_geometry* g, const wfq_params* p, c
         double* rows = sc.take<double>(s.npad);
         hipLaunchKernelGGL(ones_kernel, dim3((unsigned)(s.npad / 256)), dim3(256), 0, st, n, s.npad, ones);
         WFQ_CHECK_LAUNCH();
-        otf_narrow_f64(s, ones, rows, s.npad, 1, device_cus(s.device), st);
+        otf_narrow_f64(s, ones, rows, s.npad, 1, device_cus(s.device), st, Order::any);
         std::vector<double> h((size_t)n);
         d2h_sync(s, h.data(), rows, (size_t)n * sizeof(double), st);
         s.t_rowsum = *std::max_element(h.begin(), h.end()) * (1.0 + 1e-9);

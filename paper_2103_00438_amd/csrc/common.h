@@ -176,22 +176,28 @@ void build_rhs(const Structure& s, const double* dirs_dev, int n_dir, double E0,
 // ------------------------------------------------------------------ products (gemm.hip)
 // Y[c][i] = sum_k T[i][k] X[c][k] for c < ncol, i < npad; X, Y row-major with leading dimension ld.
 // X must hold round_up(ncol, kColPad) rows (rows >= ncol zero). Y likewise.
-void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st);
-void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, bool split = false);
+// The order of a product's sums. kept: the order that the solves' results hang on. A mode that a field hardly excites
+// comes up, near its resonance, from the rounding of the products, and the polarisability along it follows any
+// change of their order: by up to 6e-7 for the field normal to a ribbon, 1e-9..3e-9 for the fields across a tube. any: the
+// fastest product of no larger error against 64 bits. The operator entry points ask for it, and the multi-shift
+// solves of three and more field directions, whose results the strongly excited directions dominate (they move by
+// 1e-11..1e-10 then). Matrix-free structures take any: their solves move by up to 3e-10.
+enum class Order { kept, any };
+void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st, Order order = Order::kept);
+void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, Order order = Order::kept);
 void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st);
 // true when a product of ncol columns in `prec` recomputes the elements with the narrow kernel
-bool tx_is_otf_narrow(const Structure& s, int prec, int ncol);
+bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order);
 // true when a product of ncol columns streams the stored T with the vector ALUs
-bool tx_is_skinny(const Structure& s, int prec, int ncol);
+bool tx_is_skinny(const Structure& s, int prec, int ncol, Order order);
 // T X with the stored copy of T in `prec`, or recomputed on the fly when the structure is matrix-free.
-// split: an untuned FP32 product may go through the FP16 matrix cores (operands split, the error against
-// 64 bits smaller than the FP32 instruction's). The operator entry points ask for it. The solves do not:
-// the rounding of the inner products decides at which restart a system near the tolerance stops, and the
-// FP32 instruction's is systematic, so another product moves their results by as much as the tolerance
-// allows; a tuned handle takes whichever shape measured fastest. (Recomputed FP32 products always take
-// the split: the kernel that they replace summed with compensation too, and solves to 1e-10 move by about
-// 1e-10.)
-void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, bool split = false);
+// In any order an untuned FP32 product may go through the FP16 matrix cores (operands split, the error against
+// 64 bits smaller than the FP32 instruction's). In the kept order it does not: the FP32 instruction's rounding is
+// systematic and decides at which restart a system near the tolerance stops, so that another product moves the
+// results by as much as the tolerance allows; a tuned handle takes whichever shape measured fastest. (Recomputed
+// FP32 products always take the split: the kernel that they replace summed with compensation too, and solves to
+// 1e-10 move by about 1e-10.)
+void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, Order order = Order::kept);
 // one registered block-product variant (index as listed by tx_variant_name), stored T only
 void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st);
 int tx_variant_count(int precision);
@@ -205,13 +211,15 @@ void otf_tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStrea
 // the vector ALUs; `cus` = compute units of the device (sets the split of the source range). With
 // Yi != NULL also Yi[i][c] = Y[c][i] with rows of 4 doubles (columns >= ncol zero; Yi 32-byte aligned,
 // npad rows), so that a gather of row j reads every column at once.
+// The symmetric form where otf_narrow_sym allows it.
 void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, int cus, hipStream_t st,
-                    double* Yi = nullptr);
+                    Order order, double* Yi = nullptr);
 // compute units of a device
 int device_cus(int device);
 // true when narrow recomputed products of ncol <= 4 columns take the symmetric form (each element
-// evaluated once for both of its rows): its sums fit the work space
-bool otf_sym_fits(const Structure& s, int ncol);
+// evaluated once for both of its rows): its sums fit the work space, and the order of the sums is free, or the
+// structure matrix-free, or so large that it always took this form (65 536 atoms)
+bool otf_narrow_sym(const Structure& s, int ncol, Order order);
 // work space of the symmetric form for ncol columns
 uint64_t otf_sym_bytes(const Structure& s, int ncol);
 // partial-tile work space of the block products (grown on demand, or the fixed region when set)

@@ -39,28 +39,42 @@ __device__ inline uint16_t cast_from_double<uint16_t>(double v) { return bf16_rn
 __device__ inline double widen(double v) { return v; }
 __device__ inline double widen(float v) { return (double)v; }
 
-// v plus the value that a DPP move brings from another lane (0 where the move has no source lane)
-template <int kCtrl, int kRowMask>
-__device__ inline double dpp_add(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, kRowMask, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, kRowMask, 0xf, true);
+// v plus the value `n` lanes further round its row of 16
+template <int n>
+__device__ inline double row_rotate_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + n, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + n, 0xf, 0xf, true);
     return v + __hiloint2double(hi, lo);
 }
 
 // Sum over the 64 lanes of a wave; every lane receives the total. Fixed order, so the result does not depend
-// on scheduling. Lanes are added within their row of 16 (shifts by 1, 2, 4, 8), row 0 into 1 and 2 into 3, then
-// the lower half into the upper; lane 63 holds the total. DPP moves stay in the vector ALU: about a quarter of the
-// latency of the same sum through LDS permutes, which the small reductions of a Krylov step wait for.
-__device__ inline double wave_sum(double v) {
-    v = dpp_add<0x111, 0xf>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xf>(v);   // row_shr:2
-    v = dpp_add<0x114, 0xf>(v);   // row_shr:4
-    v = dpp_add<0x118, 0xf>(v);   // row_shr:8
-    v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), 63), hi = __builtin_amdgcn_readlane(__double2hiint(v), 63);
-    return __hiloint2double(hi, lo);
+// on scheduling: the butterfly over the lane distances 32, 16, 8, 4, 2, 1. The first two steps swap half waves and
+// rows of 16 between two copies of v; after the step of distance d the values repeat every d lanes, so that
+// the next, within a row, is a rotation. All of it stays in the vector ALU: about a quarter of the latency of
+// the same butterfly through LDS permutes, which the small reductions of a Krylov step wait for.
+__device__ inline double half_swap(double v) {   // the value 32 lanes on
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    const bool low = (threadIdx.x & 32) == 0;
+    return __hiloint2double(low ? hi[1] : hi[0], low ? lo[1] : lo[0]);
 }
+__device__ inline double half_wave_sum(double v) {   // the sum over each half, in all of its lanes
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    v = row_rotate_add<8>(v);
+    v = row_rotate_add<4>(v);
+    v = row_rotate_add<2>(v);
+    return row_rotate_add<1>(v);
+}
+__device__ inline double wave_sum(double v) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return half_wave_sum(__hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]));
+}
+// sum of x^2, the first addition fused with the lane's own square; valid in lanes 0 .. 31 (the two halves may
+// differ in the last bit)
+__device__ inline double wave_sum_sq(double x) { return half_wave_sum(fma(x, x, half_swap(x * x))); }
 
 // ---- FP32 operands of the FP16 matrix cores: x = h + l + e, h the FP16 rounding of x, l that of x - h
 __device__ inline halfx8 split_hi(const float (&x)[8]) {

@@ -678,22 +678,14 @@ const std::vector<Variant>& variants() {
 
 // Wider column tiles for FP32 and BF16 (their accumulators are half the size of FP64 ones), so
 // that column counts between the powers of two are not padded up to the next multiple of 128.
-// the narrow matrix-free product as a block-product variant (FP64 only; T is recomputed, the stored
-// copy is not read)
-// (NC is the largest column count of the registry entry; the kernel is chosen by ncol)
-template <int NC>
-void launch_otfn(const Structure& s, const void* X, const void*, void* Y, int64_t ld, int ncol, hipStream_t st) {
-    static_assert(NC == 2 || NC == 4, "narrow matrix-free registry entries take 2 or 4 columns");
-    otf_narrow_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), ld, ncol, device_cus(s.device), st);
-}
-
 template <int P>
 const std::vector<Variant>& variants_all() {
     static const std::vector<Variant> v = [] {
         std::vector<Variant> r = variants<P>();
         if constexpr (P == WFQ_PREC_FP64) {
-            r.push_back({"otfn2", 0, 4, 2, launch_otfn<2>});
-            r.push_back({"otfn4", 0, 4, 4, launch_otfn<4>});
+            // T recomputed, the stored copy not read (otf_narrow_f64)
+            r.push_back({"otfn2", 0, 4, 2, nullptr});
+            r.push_back({"otfn4", 0, 4, 4, nullptr});
         }
         if constexpr (P != WFQ_PREC_FP64) {
             r.push_back({"m96n256w8", 96, 256, 1 << 30, launch_mfma<P, 3, 4, 2, 4, 128, 1>});
@@ -777,14 +769,14 @@ int default_variant(int prec, int ncol, bool split, int64_t npad) {
     return k >= 0 ? k : find_variant(prec, "m128n256w8");   // present for every precision
 }
 
-// padded size from which untuned narrow FP64 products are recomputed rather than streamed (5 000 atoms, 1 to 4
-// columns: 22 / 26 / 31 / 33 us recomputed, 31 / 31 / 35 / 35 streamed; 4 000: 21 / 24 / 29 / 31 and 27 / 27 / 27 / 28)
-constexpr int64_t kOtfNarrowFrom = 4608;
+// padded size from which untuned narrow FP64 products are recomputed rather than streamed: in the symmetric form
+// (5 000 atoms, 1 to 4 columns: 22 / 26 / 31 / 33 us recomputed, 31 / 31 / 35 / 35 streamed; 4 000: 21 / 24 / 29 / 31 and
+// 27 / 27 / 27 / 28), and one-sided, in the kept order (20 000 atoms, 3 columns: 252 us recomputed, 475 streamed)
+constexpr int64_t kSymNarrowFrom = 4608, kOtfNarrowFrom = 16384;
 // matrix-free FP64 products of up to this many 4-column chunks use the narrow kernel
 constexpr int kOtfNarrowChunks = 3;
 
-// split: untuned FP32 products may take the FP16 split (see tx_any)
-int pick_variant(const Structure& s, int prec, int ncol, bool split = false) {
+int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     const auto& tuned = s.tuned[prec];
     // the tuned entry with the smallest ncol >= this one (or the largest tuned one), used only when
     // it was tuned for a comparable width (within a factor of two)
@@ -796,18 +788,24 @@ int pick_variant(const Structure& s, int prec, int ncol, bool split = false) {
     }
     // narrow FP64 products of large structures: recomputing the elements on the vector ALUs
     // (about 16 FP64 operations per pair) beats streaming 8 bytes per pair of the stored copy
-    if (prec == WFQ_PREC_FP64 && ncol <= 4 && s.npad >= kOtfNarrowFrom)
+    if (prec == WFQ_PREC_FP64 && ncol <= 4 &&
+        s.npad >= (otf_narrow_sym(s, ncol, order) ? kSymNarrowFrom : kOtfNarrowFrom))
         return find_variant(prec, ncol <= 2 ? "otfn2" : "otfn4");
-    return default_variant(prec, ncol, split && prec == WFQ_PREC_FP32 && split_default(s, ncol), s.npad);
+    return default_variant(prec, ncol, order == Order::any && prec == WFQ_PREC_FP32 && split_default(s, ncol), s.npad);
 }
 
-void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st) {
+void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st,
+                 Order order = Order::any) {
     const void* T = prec == WFQ_PREC_FP64 ? (const void*)s.T64 : prec == WFQ_PREC_FP32 ? (const void*)s.T32
                                                                                        : (const void*)s.T16;
     if (T == nullptr) throw Error{WFQ_EINVAL, "the stored copy of T for this precision was not built"};
     const Variant& v = variants_of(prec)[var];
     if (ncol > v.max_ncol) throw Error{WFQ_EINVAL, "kernel variant cannot take that many columns"};
-    v.launch(s, X, T, Y, s.npad, ncol, st);
+    if (!v.launch)
+        otf_narrow_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), s.npad, ncol, device_cus(s.device), st,
+                       order);
+    else
+        v.launch(s, X, T, Y, s.npad, ncol, st);
     WFQ_CHECK_LAUNCH();
 }
 
@@ -886,17 +884,17 @@ void convert_from_f64(int prec, const double* src, void* dst, int64_t count, hip
     WFQ_CHECK_LAUNCH();
 }
 
-void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st) {
-    if (ncol > 0) run_variant(s, WFQ_PREC_FP64, pick_variant(s, WFQ_PREC_FP64, ncol), X, Y, ncol, st);
+void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st, Order order) {
+    if (ncol > 0) run_variant(s, WFQ_PREC_FP64, pick_variant(s, WFQ_PREC_FP64, ncol, order), X, Y, ncol, st, order);
 }
-void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, bool split) {
-    if (ncol > 0) run_variant(s, WFQ_PREC_FP32, pick_variant(s, WFQ_PREC_FP32, ncol, split), X, Y, ncol, st);
+void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, Order order) {
+    if (ncol > 0) run_variant(s, WFQ_PREC_FP32, pick_variant(s, WFQ_PREC_FP32, ncol, order), X, Y, ncol, st);
 }
 void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st) {
-    if (ncol > 0) run_variant(s, WFQ_PREC_BF16, pick_variant(s, WFQ_PREC_BF16, ncol), X, Y, ncol, st);
+    if (ncol > 0) run_variant(s, WFQ_PREC_BF16, pick_variant(s, WFQ_PREC_BF16, ncol, Order::kept), X, Y, ncol, st);
 }
 
-void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, bool split) {
+void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, Order order) {
     if (s.t_mode == WFQ_TMODE_OTF) {
         if (prec == WFQ_PREC_FP32)
             otf_tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st);
@@ -906,7 +904,7 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
             for (int c0 = 0; c0 < ncol; c0 += 4)
                 otf_narrow_f64(s, static_cast<const double*>(X) + (int64_t)c0 * s.npad,
                                static_cast<double*>(Y) + (int64_t)c0 * s.npad, s.npad, std::min(4, ncol - c0),
-                               device_cus(s.device), st);
+                               device_cus(s.device), st, order);
         else if (prec == WFQ_PREC_FP64)
             otf_tx_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), ncol, st);
         else
@@ -914,9 +912,9 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
         return;
     }
     if (prec == WFQ_PREC_FP64)
-        tx_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), ncol, st);
+        tx_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), ncol, st, order);
     else if (prec == WFQ_PREC_FP32)
-        tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st, split);
+        tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st, order);
     else
         tx_bf16(s, static_cast<const uint16_t*>(X), static_cast<float*>(Y), ncol, st);
 }
@@ -925,16 +923,16 @@ void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* 
     if (ncol > 0) run_variant(s, prec, var, X, Y, ncol, st);
 }
 
-bool tx_is_otf_narrow(const Structure& s, int prec, int ncol) {
+bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order) {
     if (prec != WFQ_PREC_FP64) return false;
     if (s.t_mode == WFQ_TMODE_OTF) return ncol <= kOtfNarrowChunks * 4;
     if (ncol > 4) return false;
-    return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol)].name, "otfn", 4) == 0;
+    return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol, order)].name, "otfn", 4) == 0;
 }
 
-bool tx_is_skinny(const Structure& s, int prec, int ncol) {
+bool tx_is_skinny(const Structure& s, int prec, int ncol, Order order) {
     if (s.t_mode == WFQ_TMODE_OTF) return false;
-    return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol)].name, "skinny", 6) == 0;
+    return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol, order)].name, "skinny", 6) == 0;
 }
 
 int tx_variant_count(int precision) { return (int)variants_of(precision).size(); }

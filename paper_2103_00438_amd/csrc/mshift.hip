@@ -28,7 +28,10 @@ namespace wfq {
 
 namespace {
 
-__device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+// (the fused products are named: left to the compiler, they change with the code around a call)
+__device__ inline double2 cmul(double2 a, double2 b) {
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
+}
 __device__ inline double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
@@ -52,9 +55,12 @@ __device__ inline double* slot(double* V, int64_t npad, int mdim1, int d, int j)
 // 1 / |p| from the block sums of p^2 that the update sweep left in norm[0 .. nblk - 1] (fixed order; 0 when p = 0),
 // computed by a whole wave; nrm receives |p|
 __device__ inline double inv_norm(const double* __restrict__ norm, int64_t nblk, double& nrm) {
-    double s = 0.0;
-    for (int64_t q = threadIdx.x & 63; q < nblk; q += 64) s += norm[q];
-    nrm = sqrt(wave_sum(s));
+    double s0 = 0.0, s1 = 0.0;
+    for (int64_t q = threadIdx.x & 63; q < nblk; q += 128) {
+        s0 += norm[q];
+        s1 += q + 64 < nblk ? norm[q + 64] : 0.0;
+    }
+    nrm = sqrt(wave_sum(s0) + wave_sum(s1));
     return nrm > 0.0 ? 1.0 / nrm : 0.0;
 }
 
@@ -87,120 +93,151 @@ __global__ void __launch_bounds__(256) ms_pack_kernel(double* __restrict__ V, in
 }
 
 // The product of a small stored FP64 T with the newest basis vectors, taken straight from the basis:
-// Y[c][i] = sum_k T[i][k] V(d_c, j)[k] / |V(d_c, j)|. One launch in place of the pack, the product and the norm's
-// reduction, whose latencies bound a step of a few thousand atoms. A work-group owns 8 rows of T; its four waves
-// split k (every fourth run of 128), so that even 600 atoms have 320 waves, and the 64 x 4 partial sums of
-// every output are added through LDS in a fixed order. The basis vectors stay unnormalised until ms_spmm.
-constexpr int kMsRowsT = 8;
+// Y[c][i] = sum_k T[i][k] v_c[k], v_c = V(d_c, j) / |V(d_c, j)|. One launch in place of the pack, the product and the
+// norm's reduction, whose latencies bound a step of a few thousand atoms (600 atoms, 3 directions: 4.7 + 5.6 + 2.3 us,
+// now 5.1). A wave owns kMsRowsT rows of T and sums as tx_skinny_kernel does; every work-group adds the norms'
+// block sums for itself while its first rows of T are on their way. The basis vectors are normalised in registers
+// and stay as they are in memory until ms_spmm.
+constexpr int kMsRowsT = 2;
 template <int NC>
 __global__ void __launch_bounds__(256) ms_skinny_kernel(const double* __restrict__ T, int64_t npad,
                                                         const double* __restrict__ V, int mdim1, int j,
                                                         DirList dirs, const double* __restrict__ norm,
                                                         double* __restrict__ nu, double* __restrict__ inv_h,
                                                         double* __restrict__ Y) {
-    constexpr int R = kMsRowsT, ROW = 256 + 8;
-    __shared__ double part[R * NC][ROW];
-    __shared__ double inv[NC];
-    const int tid = threadIdx.x, wave = tid >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * R;
-    const double* u[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) u[c] = V + ((int64_t)dirs[c] * mdim1 + j) * npad;
-    double acc[R][NC];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) acc[r][c] = 0.0;
-    for (int64_t k = 2 * tid; k < npad; k += 512) {
-        double2 x[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) x[c] = *reinterpret_cast<const double2*>(u[c] + k);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double2 t = *reinterpret_cast<const double2*>(T + (row0 + r) * npad + k);
-#pragma unroll
-            for (int c = 0; c < NC; ++c) acc[r][c] = fma(t.y, x[c].y, fma(t.x, x[c].x, acc[r][c]));
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) part[r * NC + c][tid] = acc[r][c];
-    if (wave < NC) {
+    constexpr int R = kMsRowsT;
+    __shared__ double inv[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * R;
+    if (wave < NC) {   // wave c: the norm of column c
         const int d = dirs[wave];
         double sc, nrm;
         if (norm) {
             sc = inv_norm(norm + (int64_t)d * (npad / 64), npad / 64, nrm);
-            if (blockIdx.x == 0 && (tid & 63) == 0) {
+            if (blockIdx.x == 0 && lane == 0) {
                 nu[d] = nrm;
                 inv_h[d] = sc;
             }
         } else {
             sc = inv_h[d];
         }
-        if ((tid & 63) == 0) inv[wave] = sc;
+        if (lane == 0) inv[wave] = sc;
     }
+    const double* u[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) u[c] = V + ((int64_t)dirs[c] * mdim1 + j) * npad;
     __syncthreads();
-    // 8 threads per output, 32 partial sums each
-    const int o = tid >> 3, sub = tid & 7;
-    if (o < R * NC) {
-        double s = 0.0;
-#pragma unroll 8
-        for (int q = 0; q < 32; ++q) s += part[o][q * 8 + sub];
-        s += __shfl_xor(s, 1, 64);
-        s += __shfl_xor(s, 2, 64);
-        s += __shfl_xor(s, 4, 64);
-        if (sub == 0) Y[(int64_t)(o % NC) * npad + row0 + o / NC] = inv[o % NC] * s;
+    double sc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sc[c] = inv[c];
+    double acc[R][NC];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[r][c] = 0.0;
+#pragma unroll 4
+    for (int64_t k = 2 * lane; k < npad; k += 128) {
+        double2 x[NC], t[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) t[r] = *reinterpret_cast<const double2*>(T + (row0 + r) * npad + k);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            x[c] = *reinterpret_cast<const double2*>(u[c] + k);
+            x[c] = make_double2(x[c].x * sc[c], x[c].y * sc[c]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[r][c] = fma(t[r].y, x[c].y, fma(t[r].x, x[c].x, acc[r][c]));
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const double s = wave_sum(acc[r][c]);
+            if (lane == 0) Y[(int64_t)c * npad + row0 + r] = s;
+        }
 }
 
-// V(d_c, jdst) = L Y[c] for the NC columns c0 .. c0 + NC - 1 (real ELL rows; padding rows get 0), with
-// TV(d_c, jdst - 1) = Y[c] kept and, with scale, V(d_c, jdst - 1) *= scale[d_c] (a basis vector that entered its product
-// unnormalised). A work-group owns 64 rows; its four waves take every fourth entry of the rows (each read once
-// for all columns) and their sums are added in LDS in order: the gathers are bound by latency, and one thread a row
-// had a quarter of the waves for four times as long (600 atoms: 7.7 us, now 4.8).
+// V(d_c, jdst) = L Y[c] for the NC columns c0 .. c0 + NC - 1 (real ELL rows, each entry read once
+// for all columns; padding rows get 0), with TV(d_c, jdst - 1) = Y[c] kept and, with scale, V(d_c, jdst - 1) *=
+// scale[d_c] (a basis vector that entered its product unnormalised).
 template <typename YE, int NC>
 __global__ void __launch_bounds__(256) ms_spmm_kernel(int64_t n, int64_t npad, int w, const int32_t* __restrict__ ecol,
                                                       const double* __restrict__ eval, const YE* __restrict__ Y,
                                                       int64_t ld, DirList dirs, double* __restrict__ V,
                                                       int mdim1, int jdst, int c0, double* __restrict__ TV,
                                                       const double* __restrict__ Yi, const double* __restrict__ scale) {
-    __shared__ double red[4][NC][64];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = 0.0;
     const YE* y = Y + (int64_t)c0 * ld;
-    if (Yi) {
-        // the interleaved copy: all columns of neighbour j in one aligned 32-byte load
+    if (i < n) {
+        if (Yi) {
+            // the interleaved copy: all columns of neighbour j in one aligned 32-byte load
 #pragma unroll 4
-        for (int e = q; e < w; e += 4) {
-            const double v = eval[(int64_t)e * npad + i];
-            const int64_t j = ecol[(int64_t)e * npad + i];
-            const doublex4 yj = *reinterpret_cast<const doublex4*>(Yi + 4 * j);
-            const double yv[4] = {yj.x, yj.y, yj.z, yj.w};
+            for (int e = 0; e < w; ++e) {
+                const double v = eval[(int64_t)e * npad + i];
+                const int64_t j = ecol[(int64_t)e * npad + i];
+                const doublex4 yj = *reinterpret_cast<const doublex4*>(Yi + 4 * j);
+                const double yv[4] = {yj.x, yj.y, yj.z, yj.w};
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] += v * yv[c];
-        }
-    } else {
+                for (int c = 0; c < NC; ++c) acc[c] += v * yv[c];
+            }
+        } else {
 #pragma unroll 4
-        for (int e = q; e < w; e += 4) {
-            const double v = eval[(int64_t)e * npad + i];
-            const int64_t j = ecol[(int64_t)e * npad + i];
+            for (int e = 0; e < w; ++e) {
+                const double v = eval[(int64_t)e * npad + i];
+                const int64_t j = ecol[(int64_t)e * npad + i];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) acc[c] += v * widen(y[c * ld + j]);
+                for (int c = 0; c < NC; ++c) acc[c] += v * widen(y[c * ld + j]);
+            }
         }
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) red[q][c][lane] = acc[c];
-    __syncthreads();
-    if (q >= NC) return;   // wave q finishes column q
-    const int d = dirs[c0 + q];
+    for (int c = 0; c < NC; ++c) {
+        const int d = dirs[c0 + c];
+        slot(V, npad, mdim1, d, jdst)[i] = acc[c];
+        if (TV) slot(TV, npad, mdim1, d, jdst - 1)[i] = i < n ? widen(y[c * ld + i]) : 0.0;
+        if (scale) slot(V, npad, mdim1, d, jdst - 1)[i] *= scale[d];
+    }
+}
+
+// The same for structures of a few thousand rows, where the time is the latency of a row's chain and not the
+// entries' traffic: 16 rows per work-group, their entries staged in LDS by all its threads at once (chunks of kMsEnt), so that a
+// lane waits for gathers alone, and one column per lane group of 16 (600 atoms, 3 columns: 7.7 us, now 4.7).
+constexpr int kMsEnt = 128;
+template <typename YE, int NC>
+__global__ void __launch_bounds__(64) ms_spmm_small_kernel(int64_t n, int64_t npad, int w, const int32_t* __restrict__ ecol,
+                                                           const double* __restrict__ eval, const YE* __restrict__ Y,
+                                                           int64_t ld, DirList dirs, double* __restrict__ V, int mdim1,
+                                                           int jdst, double* __restrict__ TV,
+                                                           const double* __restrict__ scale) {
+    __shared__ double lval[kMsEnt * 16];
+    __shared__ int32_t lcol[kMsEnt * 16];
+    const int r = threadIdx.x & 15, c = threadIdx.x >> 4;
+    const int64_t i0 = (int64_t)blockIdx.x * 16, i = i0 + r;
+    const YE* y = Y + (int64_t)min(c, NC - 1) * ld;
+    double acc = 0.0;
+    for (int e0 = 0; e0 < w; e0 += kMsEnt) {
+        const int en = min(kMsEnt, w - e0);
+        __syncthreads();
+#pragma unroll 8
+        for (int q = threadIdx.x; q < en * 16; q += 64) {
+            const int64_t at = (int64_t)(e0 + (q >> 4)) * npad + i0 + (q & 15);
+            lcol[q] = ecol[at];
+            lval[q] = eval[at];
+        }
+        __syncthreads();
+#pragma unroll 16
+        for (int e = 0; e < en; ++e) acc += lval[e * 16 + r] * widen(y[lcol[e * 16 + r]]);
+    }
+    if (c >= NC) return;
+    const int d = dirs[c];
     const bool in = i < n;
-    slot(V, npad, mdim1, d, jdst)[i] =
-        in ? (red[0][q][lane] + red[1][q][lane]) + (red[2][q][lane] + red[3][q][lane]) : 0.0;
-    if (TV) slot(TV, npad, mdim1, d, jdst - 1)[i] = in ? widen(y[q * ld + i]) : 0.0;
+    slot(V, npad, mdim1, d, jdst)[i] = in ? acc : 0.0;
+    if (TV) slot(TV, npad, mdim1, d, jdst - 1)[i] = in ? widen(y[i]) : 0.0;
     if (scale) slot(V, npad, mdim1, d, jdst - 1)[i] *= scale[d];
 }
 
@@ -272,7 +309,7 @@ __global__ void __launch_bounds__(256) ms_update_kernel(double* __restrict__ V, 
             w[row] = x;
         }
         if (norm) {
-            const double s2 = wave_sum(x * x);
+            const double s2 = wave_sum_sq(x);
             if (r == 0) norm[(int64_t)d * (npad / kMsRows) + blockIdx.x] = s2;
         }
     }
@@ -445,7 +482,7 @@ __global__ void __launch_bounds__(1024) ms_dcgs_step_kernel(DirList dirs, int k,
                                                             double* __restrict__ dots, double* __restrict__ hp,
                                                             double* __restrict__ H, double* __restrict__ Sm,
                                                             double* __restrict__ gam, double* __restrict__ inv_rho) {
-    __shared__ double sd[2 * kStepMax + 2], hcol[kStepMax + 1], red[16][64], part[2][16];
+    __shared__ double sd[2 * kStepMax + 2], hcol[kStepMax + 1], red[16][64], part[2][4];
     const int d = dirs[blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double* hpd = hp + (int64_t)d * (m + 1);
@@ -454,20 +491,20 @@ __global__ void __launch_bounds__(1024) ms_dcgs_step_kernel(DirList dirs, int k,
     // column k-1's first-pass coefficients, loaded ahead of the reductions
     double hold = 0.0;
     if (tid < k) hold = hpd[tid];
-    // without z (the last step) u is the unnormalised p, whose dots are scaled by 1 / |p|
     double nud = 0.0, sc = 1.0;
     if (with_z)
         nud = nu[d];
     else
         sc = inv_norm(norm + (int64_t)d * nblk, nblk, nud);
     {
+        // the order of ms_reduce_kernel (a butterfly over up to 64 chunks), with 4 or 16 lanes per dot
         const int count = with_z ? 2 * k + 2 : k + 1;
-        const int L = nwc <= 2 ? 1 : nwc <= 8 ? 4 : 16;   // lanes per dot
+        const int L = nwc <= 4 ? 4 : 16;
         const int sub = tid % L;
         for (int e = tid / L; e < count; e += 1024 / L) {
             const double* p = partial + ((int64_t)d * ps + e) * nwc;
-            double s = 0.0;
-            for (int64_t q = sub; q < nwc; q += L) s += p[q];
+            auto at = [&](int q) { return q < nwc ? p[q] : 0.0; };
+            double s = L == 4 ? at(sub) : (at(sub) + at(sub + 32)) + (at(sub + 16) + at(sub + 48));
             for (int off = L / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
             if (sub == 0) {
                 sd[e] = s;
@@ -476,25 +513,24 @@ __global__ void __launch_bounds__(1024) ms_dcgs_step_kernel(DirList dirs, int k,
         }
     }
     __syncthreads();
-    double asq = 0.0, ab = 0.0;
-    if (tid < k) {
-        asq = sd[tid] * sd[tid];
-        if (with_z) ab = sd[tid] * sd[k + 1 + tid];
-    }
-    asq = wave_sum(asq);
-    ab = wave_sum(ab);
-    if (lane == 0) {
-        part[0][wave] = asq;
-        part[1][wave] = ab;
+    if (wave < 4) {   // the sums of ms_dcgs_coeff_kernel's 256 threads
+        double asq = 0.0, ab = 0.0;
+        for (int i = tid; i < k; i += 256) {
+            const double ai = sc * sd[i];
+            asq += ai * ai;
+            if (with_z) ab += sd[i] * sd[k + 1 + i];
+        }
+        asq = wave_sum(asq);
+        ab = wave_sum(ab);
+        if (lane == 0) {
+            part[0][wave] = asq;
+            part[1][wave] = ab;
+        }
     }
     __syncthreads();
-    asq = ab = 0.0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        asq += part[0][q];
-        ab += part[1][q];
-    }
-    const double r2 = (sd[k] - asq) * sc * sc;
+    const double asq = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]);
+    const double ab = (part[1][0] + part[1][1]) + (part[1][2] + part[1][3]);
+    const double r2 = sd[k] * sc * sc - asq;
     const double rho = r2 > 0.0 ? sqrt(r2) : 0.0;
     if (k >= 1) {
         double* col = Hd + (int64_t)(k - 1) * (m + 1);
@@ -521,7 +557,7 @@ __global__ void __launch_bounds__(1024) ms_dcgs_step_kernel(DirList dirs, int k,
 #pragma unroll 4
             for (int c = c0 + wave; c < k - 1; c += 16)
                 if (c >= i - 1) acc += Hd[(int64_t)c * (m + 1) + i] * sd[c];
-            if (wave == 0) acc += hcol[i] * sd[k - 1];
+            if (((k - 1 - c0) & 15) == wave) acc += hcol[i] * sd[k - 1];   // that wave's last column
         }
         red[wave][lane] = acc;
         __syncthreads();
@@ -584,7 +620,7 @@ __global__ void __launch_bounds__(256) ms_dcgs_update_kernel(double* __restrict_
         u[row] = qk;
         zv[row] = x;
     }
-    const double s2 = wave_sum(x * x);
+    const double s2 = wave_sum_sq(x);
     if (lane == 0) norm[(int64_t)d * (npad / kMsRows) + (base / kMsRows) + q] = s2;
 }
 
@@ -624,11 +660,11 @@ __device__ inline void back_substitute(double2* ys, int K, At&& at) {
             double2 v = ys[r];
             if (r == tid) {
 #pragma unroll
-                for (int q = 0; q < kPanel; ++q)
+                for (int q = kPanel - 1; q >= 0; --q)
                     if (q < p) v = csub(v, tri_mul(own[q], ys[c0 + q]));
             } else {
 #pragma unroll 8
-                for (int q = 0; q < p; ++q) v = csub(v, tri_mul(at(c0 + q, r), ys[c0 + q]));
+                for (int q = p - 1; q >= 0; --q) v = csub(v, tri_mul(at(c0 + q, r), ys[c0 + q]));
             }
             ys[r] = v;
         }
@@ -767,15 +803,15 @@ __global__ void __launch_bounds__(64) ms_givens_kernel(GivensArgs a) {
 
 // The update sweep of step k and the Givens step on column k-1, which do not depend on each other, in one launch
 // for structures of some thousand atoms, where each alone is a few microseconds of latency on a part of the chip.
-// The first nupd work-groups update 64 rows of one direction each, the basis split over 16 waves (fixed-order LDS
-// sums); the others take the Givens steps of gper systems each.
-__global__ void __launch_bounds__(1024) ms_update_givens_kernel(double* __restrict__ V, int64_t n, int64_t npad, int mdim1,
-                                                                int k, DirList dirs,
-                                                                const double* __restrict__ dots, int ps,
-                                                                const double* __restrict__ gam,
-                                                                const double* __restrict__ inv_rho,
-                                                                double* __restrict__ norm, int nupd, int gper, GivensArgs a) {
-    __shared__ double pa[16][64], pb[16][64];
+// The first nupd work-groups update 64 rows of one direction each (the sums of ms_dcgs_update_kernel, one row per
+// lane); the others take the Givens steps of gper systems each.
+__global__ void __launch_bounds__(256) ms_update_givens_kernel(double* __restrict__ V, int64_t n, int64_t npad, int mdim1,
+                                                               int k, DirList dirs,
+                                                               const double* __restrict__ dots, int ps,
+                                                               const double* __restrict__ gam,
+                                                               const double* __restrict__ inv_rho,
+                                                               double* __restrict__ norm, int nupd, int gper, GivensArgs a) {
+    __shared__ double pa[4][64], pb[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if ((int)blockIdx.x >= nupd) {
         const int q = ((int)blockIdx.x - nupd) * gper + wave;
@@ -792,32 +828,28 @@ __global__ void __launch_bounds__(1024) ms_update_givens_kernel(double* __restri
     const double* v = V + (int64_t)d * mdim1 * npad + row;
     double* u = V + ((int64_t)d * mdim1 + k) * npad;
     double* zv = u + npad;
-    const double ur = u[row], zr = zv[row], ir = inv_rho[d], gm = gam[d];   // ahead of the sums (wave 0 uses them)
+    const double ur = u[row], zr = zv[row], ir = inv_rho[d], g = gam[d];   // ahead of the sums (wave 0 uses them)
     double sa = 0.0, sb = 0.0;
-#pragma unroll 4
-    for (int i = wave; i < k; i += 16) {
+#pragma unroll 8
+    for (int i = wave; i < k; i += 4) {
         const double x = v[(int64_t)i * npad];
-        sa += dt[i] * x;
-        sb += dt[k + 1 + i] * x;
+        const double ai = dt[i], bi = dt[k + 1 + i];
+        sa += ai * x;
+        sb += bi * x;
     }
     pa[wave][lane] = sa;
     pb[wave][lane] = sb;
     __syncthreads();
     if (wave != 0) return;
+    const int t = lane;
     double x = 0.0;
     if (row < n) {
-        sa = sb = 0.0;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            sa += pa[q][lane];
-            sb += pb[q][lane];
-        }
-        const double qk = (ur - sa) * ir;
-        x = (zr - sb - gm * qk) * ir;
+        const double qk = (ur - ((pa[0][t] + pa[1][t]) + (pa[2][t] + pa[3][t]))) * ir;
+        x = (zr - ((pb[0][t] + pb[1][t]) + (pb[2][t] + pb[3][t])) - g * qk) * ir;
         u[row] = qk;
         zv[row] = x;
     }
-    const double s2 = wave_sum(x * x);
+    const double s2 = wave_sum_sq(x);
     if (lane == 0) norm[(int64_t)d * nrb + rb] = s2;
 }
 
@@ -837,10 +869,9 @@ __global__ void __launch_bounds__(256) ms_solve_kernel(const int* __restrict__ s
 // x(s) = sum_{i < k[s]} y[s][i] V(d, i) for groups of up to 8 systems of one direction (the basis
 // is read once per group); rows >= n and systems with k = 0 get 0. Real part at out + col sys_stride,
 // imaginary part im_off further, with col = pos[s] (skipped when negative) or s when pos is NULL.
-// Each thread owns kRows rows, 64 apart; the coefficients of 64 steps at a time are staged in LDS (zeros past a
-// system's k), so the loop over the steps waits for the basis alone. SPLIT: the four waves share 64 kRows rows
-// and take every fourth step (sums added in LDS in order), for structures whose rows alone are too few waves.
-template <int kRows, bool SPLIT>
+// Each thread owns kRows rows, 256 apart; the coefficients of 64 steps at a time are staged in LDS, so the loop over the
+// steps waits for the basis alone (600 atoms, 600 systems: 118 us, now 40).
+template <int kRows>
 __global__ void __launch_bounds__(256) ms_xupdate_kernel(const double* __restrict__ V, int64_t n, int64_t npad,
                                                          int mdim1, const int* __restrict__ grp_sys,
                                                          const int* __restrict__ grp_dir, const int* __restrict__ ksteps,
@@ -849,17 +880,16 @@ __global__ void __launch_bounds__(256) ms_xupdate_kernel(const double* __restric
                                                          const int* __restrict__ pos) {
     constexpr int kStage = 64;
     __shared__ double2 sy[kStage][kMsGroup];
-    __shared__ double2 red[SPLIT ? 4 : 1][kMsGroup][SPLIT ? 64 : 1];
-    static_assert(!SPLIT || kRows == 1, "the split form has one row per lane");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t i0 = SPLIT ? (int64_t)blockIdx.x * 64 + lane : ((int64_t)blockIdx.x * 4 + wave) * 64 * kRows + lane;
+    const int64_t i0 = (int64_t)blockIdx.x * 256 * kRows + threadIdx.x;
     const int gi = blockIdx.y;
     const int d = grp_dir[gi];
-    int kmax = 0;
+    int kk[kMsGroup], kmax = 0, kmin = m;   // steps of each system, the most, and the fewest
 #pragma unroll
     for (int t = 0; t < kMsGroup; ++t) {
         const int s = grp_sys[gi * kMsGroup + t];
-        if (s >= 0) kmax = max(kmax, ksteps[s]);
+        kk[t] = s >= 0 ? ksteps[s] : 0;
+        kmax = max(kmax, kk[t]);
+        kmin = min(kmin, kk[t]);
     }
     double ar[kRows][kMsGroup], ai[kRows][kMsGroup];
 #pragma unroll
@@ -869,52 +899,49 @@ __global__ void __launch_bounds__(256) ms_xupdate_kernel(const double* __restric
     const double* v = V + (int64_t)d * mdim1 * npad;
     for (int c0 = 0; c0 < kmax; c0 += kStage) {
         __syncthreads();
-        for (int q = tid; q < kStage * kMsGroup; q += 256) {
+        for (int q = threadIdx.x; q < kStage * kMsGroup; q += 256) {
             const int t = q / kStage, c = c0 + q % kStage, s = grp_sys[gi * kMsGroup + t];
-            sy[q % kStage][t] = s >= 0 && c < ksteps[s] ? y[(int64_t)s * m + c] : make_double2(0.0, 0.0);
+            if (s >= 0 && c < ksteps[s]) sy[q % kStage][t] = y[(int64_t)s * m + c];
         }
         __syncthreads();
-        const int cn = min(kStage, kmax - c0);
+        auto steps = [&](int from, int to, auto all) {   // all: every system takes these steps
 #pragma unroll 4
-        for (int c = SPLIT ? wave : 0; c < cn; c += SPLIT ? 4 : 1) {
-            double x[kRows];
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-                const int64_t i = i0 + 64 * r;
-                x[r] = i < npad ? v[(int64_t)(c0 + c) * npad + i] : 0.0;
-            }
-#pragma unroll
-            for (int t = 0; t < kMsGroup; ++t) {
-                const double2 yc = sy[c][t];
+            for (int c = from; c < to; ++c) {
+                double x[kRows];
 #pragma unroll
                 for (int r = 0; r < kRows; ++r) {
-                    ar[r][t] = fma(yc.x, x[r], ar[r][t]);
-                    ai[r][t] = fma(yc.y, x[r], ai[r][t]);
+                    const int64_t i = i0 + 256 * r;
+                    x[r] = i < npad ? v[(int64_t)c * npad + i] : 0.0;
                 }
+#pragma unroll
+                for (int t = 0; t < kMsGroup; ++t)
+                    if (all.value || c < kk[t]) {
+                        const double2 yc = sy[c - c0][t];
+#pragma unroll
+                        for (int r = 0; r < kRows; ++r) {
+                            ar[r][t] = fma(yc.x, x[r], ar[r][t]);
+                            ai[r][t] = fma(yc.y, x[r], ai[r][t]);
+                        }
+                    }
             }
-        }
+        };
+        const int to = min(c0 + kStage, kmax), full = min(to, max(c0, kmin));
+        steps(c0, full, std::true_type{});
+        steps(full, to, std::false_type{});
     }
-    auto store = [&](int t, int64_t i, double re, double im) {
+#pragma unroll
+    for (int t = 0; t < kMsGroup; ++t) {
         const int s = grp_sys[gi * kMsGroup + t];
         const int col = s < 0 ? -1 : pos ? pos[s] : s;
-        if (col < 0 || i >= npad) return;
+        if (col < 0) continue;
         double* xr = out + (int64_t)col * sys_stride;
-        xr[i] = i < n ? re : 0.0;
-        xr[i + im_off] = i < n ? im : 0.0;
-    };
-    if constexpr (SPLIT) {
 #pragma unroll
-        for (int t = 0; t < kMsGroup; ++t) red[wave][t][lane] = make_double2(ar[0][t], ai[0][t]);
-        __syncthreads();
-        for (int t = wave; t < kMsGroup; t += 4) {
-            const double2 a = red[0][t][lane], b = red[1][t][lane], c = red[2][t][lane], e = red[3][t][lane];
-            store(t, i0, (a.x + b.x) + (c.x + e.x), (a.y + b.y) + (c.y + e.y));
+        for (int r = 0; r < kRows; ++r) {
+            const int64_t i = i0 + 256 * r;
+            if (i >= npad) continue;
+            xr[i] = i < n ? ar[r][t] : 0.0;
+            xr[i + im_off] = i < n ? ai[r][t] : 0.0;
         }
-    } else {
-#pragma unroll
-        for (int r = 0; r < kRows; ++r)
-#pragma unroll
-            for (int t = 0; t < kMsGroup; ++t) store(t, i0 + 64 * r, ar[r][t], ai[r][t]);
     }
 }
 
@@ -941,7 +968,7 @@ void ms_skinny(const Structure& S, const double* V, int mdim1, int j, const DirL
     if (ndir > 4 || !S.T64) throw Error{WFQ_EINVAL, "ms_skinny: up to 4 columns of a stored FP64 T"};
     auto go = [&](auto ncv) {
         constexpr int NC = decltype(ncv)::value;
-        hipLaunchKernelGGL(ms_skinny_kernel<NC>, dim3((unsigned)(S.npad / kMsRowsT)), dim3(256), 0, st, S.T64, S.npad, V,
+        hipLaunchKernelGGL(ms_skinny_kernel<NC>, dim3((unsigned)(S.npad / (4 * kMsRowsT))), dim3(256), 0, st, S.T64, S.npad, V,
                            mdim1, j, dirs, norm, nu, inv_h, Y);
     };
     if (ndir == 1) go(std::integral_constant<int, 1>{});
@@ -955,7 +982,25 @@ void ms_spmm(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const
              int mdim1, int jdst, double* TV, hipStream_t st, const double* Yi, const double* scale) {
     if (ndir <= 0) return;
     if (Yi && (!y_is_f64 || ndir > 4)) throw Error{WFQ_EINVAL, "ms_spmm: the interleaved copy holds up to 4 FP64 columns"};
-    const dim3 grd((unsigned)(S.npad / 64));
+    const dim3 grd((unsigned)(S.npad / 256));
+    if (ms_merged(S.npad) && ndir <= 4 && !Yi) {
+        auto small = [&](auto tag, auto ncv) {
+            using YE = decltype(tag);
+            constexpr int NC = decltype(ncv)::value;
+            hipLaunchKernelGGL((ms_spmm_small_kernel<YE, NC>), dim3((unsigned)(S.npad / 16)), dim3(64), 0, st, S.n, S.npad,
+                               S.ell_w, S.ell_col, S.ell_val, static_cast<const YE*>(Y), ld, dirs, V, mdim1, jdst, TV, scale);
+        };
+        auto by = [&](auto tag) {
+            if (ndir == 1) small(tag, std::integral_constant<int, 1>{});
+            else if (ndir == 2) small(tag, std::integral_constant<int, 2>{});
+            else if (ndir == 3) small(tag, std::integral_constant<int, 3>{});
+            else small(tag, std::integral_constant<int, 4>{});
+        };
+        if (y_is_f64) by(double{});
+        else by(float{});
+        WFQ_CHECK_LAUNCH();
+        return;
+    }
     // columns in chunks of at most 4 (3 for the usual three field directions in one pass)
     for (int c0 = 0; c0 < ndir; c0 += 4) {
         const int nc = std::min(4, ndir - c0);
@@ -1025,9 +1070,9 @@ void ms_update_givens(double* V, int64_t n, int64_t npad, int mdim1, int k, bool
     const int nupd = with_z ? (int)(npad / kMsRows) * ndir : 0, ngiv = k >= 1 ? nsys : 0;
     if (nupd + ngiv == 0) return;
     // Givens steps spread over the chip: one to a work-group (its other waves end at once) up to 1 024 systems
-    // (600 systems: 5.8 us; 4 to a work-group 6.4, 16 to a work-group 10.2)
-    const int gper = std::min(16, 1 + ngiv / 1024);
-    hipLaunchKernelGGL(ms_update_givens_kernel, dim3((unsigned)(nupd + (ngiv + gper - 1) / gper)), dim3(1024), 0, st, V, n,
+    // (600 systems in work-groups of 16 waves: 5.8 us; 4 to a work-group 6.4, 16 to a work-group 10.2)
+    const int gper = std::min(4, 1 + ngiv / 1024);
+    hipLaunchKernelGGL(ms_update_givens_kernel, dim3((unsigned)(nupd + (ngiv + gper - 1) / gper)), dim3(256), 0, st, V, n,
                        npad, mdim1, k, dirs, dots, ps, gam, irho, norm, nupd, gper,
                        GivensArgs{sys, ngiv, k - 1, m, sdir, z, H, cs, sn, g, R, S, est, tol_abs, flags, run, ksteps});
     WFQ_CHECK_LAUNCH();
@@ -1098,13 +1143,11 @@ void launch_xupdate(const double* V, int64_t n, int64_t npad, int mdim1, const i
                     const int* ksteps, const double2* y, int m, double* out, int64_t sys_stride, int64_t im_off,
                     const int* pos, hipStream_t st) {
     // four rows per thread (each coefficient read from LDS serves four products of the FP64 units, which bound it) from
-    // 2 048 waves on, two per SIMD; below, the steps are split over the waves
-    if (npad / 256 * ngrp >= 2048)
-        hipLaunchKernelGGL((ms_xupdate_kernel<4, false>), dim3((unsigned)((npad + 1023) / 1024), (unsigned)ngrp), dim3(256), 0,
-                           st, V, n, npad, mdim1, grp_sys, grp_dir, ksteps, y, m, out, sys_stride, im_off, pos);
-    else
-        hipLaunchKernelGGL((ms_xupdate_kernel<1, true>), dim3((unsigned)(npad / 64), (unsigned)ngrp), dim3(256), 0, st, V, n,
-                           npad, mdim1, grp_sys, grp_dir, ksteps, y, m, out, sys_stride, im_off, pos);
+    // 2 048 waves on, two per SIMD
+    const int rows = npad / 256 * ngrp >= 2048 ? 4 : 1;
+    hipLaunchKernelGGL(rows == 4 ? ms_xupdate_kernel<4> : ms_xupdate_kernel<1>,
+                       dim3((unsigned)((npad + 256 * rows - 1) / (256 * rows)), (unsigned)ngrp), dim3(256), 0, st, V, n, npad, mdim1,
+                       grp_sys, grp_dir, ksteps, y, m, out, sys_stride, im_off, pos);
     WFQ_CHECK_LAUNCH();
 }
 }  // namespace

@@ -936,16 +936,17 @@ uint64_t otf_sym_bytes(const Structure& s, int ncol) {
     return (uint64_t)ncol * sizeof(double) * (sym_tri(nb - 1, s.npad) + (sym_runs(s, ncol) + nb) * kSymBlock);
 }
 
-bool otf_sym_fits(const Structure& s, int ncol) {
+bool otf_narrow_sym(const Structure& s, int ncol, Order order) {
+    if (order == Order::kept && s.t_mode == WFQ_TMODE_STORED && s.n < 65536) return false;
     const uint64_t cap = s.split_fixed ? s.split_fixed_bytes : std::max(kSplitWsCap, s.sym_ws_allowed);
     return otf_sym_bytes(s, ncol) <= cap;
 }
 
 void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, int cus, hipStream_t st,
-                    double* Yi) {
+                    Order order, double* Yi) {
     if (ncol <= 0) return;
     if (ncol > 4) throw Error{WFQ_EINVAL, "the narrow matrix-free product takes at most 4 columns"};
-    if (otf_sym_fits(s, ncol)) {
+    if (otf_narrow_sym(s, ncol, order)) {
         if (ncol == 1)
             launch_otf_sym<1>(s, X, Y, ld, Yi, st);
         else if (ncol == 2)

@@ -539,23 +539,23 @@ const void* y_block(Work& w, int prec) {
 // Y = T X on the solve's product block. With Yi (a narrow FP64 product of at most 4 columns) the
 // product is also written interleaved into Yi (rows of 4 doubles) for the multi-shift SpMM's gathers.
 void block_product(const Structure& S, Work& w, int prec, int ncol, Timer& tm, hipStream_t st,
-                   double* Yi = nullptr) {
+                   Order order = Order::kept, double* Yi = nullptr) {
     const double n = (double)S.n;
     tm.begin(st);
     if (Yi) {
-        if (prec != WFQ_PREC_FP64 || ncol > 4 || !tx_is_otf_narrow(S, prec, ncol))
+        if (prec != WFQ_PREC_FP64 || ncol > 4 || !tx_is_otf_narrow(S, prec, ncol, order))
             throw Error{WFQ_EINVAL, "block_product: the interleaved copy needs a narrow FP64 product"};
-        otf_narrow_f64(S, w.X64.p, w.Y64.p, S.npad, ncol, device_cus(S.device), st, Yi);
+        otf_narrow_f64(S, w.X64.p, w.Y64.p, S.npad, ncol, device_cus(S.device), st, order, Yi);
     } else {
-        tx_any(S, prec, x_block(w, prec), const_cast<void*>(y_block(w, prec)), ncol, st);
+        tx_any(S, prec, x_block(w, prec), const_cast<void*>(y_block(w, prec)), ncol, st, order);
     }
-    if (tx_is_otf_narrow(S, prec, ncol)) {
+    if (tx_is_otf_narrow(S, prec, ncol, order)) {
         // work: per element 3 differences, 3 operations for r^2, the reciprocal square root and 4 for
         // its Newton step, and one multiply-add per column and row (the near-field correction is a
         // sparse extra); the symmetric form evaluates each element once for both rows, so n^2 / 2
         // elements; bytes: positions and X read once per source part, Y written
         const double chunks = (ncol + 3) / 4;   // products of up to 4 columns
-        const double elems = otf_sym_fits(S, std::min(ncol, 4)) ? 0.5 * n * n : n * n;
+        const double elems = otf_narrow_sym(S, std::min(ncol, 4), order) ? 0.5 * n * n : n * n;
         tm.end(st, KC_OTF_NARROW, elems * 11.0 * chunks + n * n * ncol, n * (24.0 * chunks + 8.0 * ncol) + n * 8.0 * ncol);
         return;
     }
@@ -1131,7 +1131,8 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
                 // z = L T u_j (one real column per direction) into slot j + 1; the first vectors' norms are known,
                 // the later ones' are the block sums of the update sweep
                 const double* pn = j > 0 ? nrm : nullptr;
-                const bool direct = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_skinny(S, cur, na);
+                const Order order = cur == WFQ_PREC_FP64 && na >= 3 ? Order::any : Order::kept;
+                const bool direct = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_skinny(S, cur, na, order);
                 double* yi = nullptr;
                 tm.begin(st);
                 if (direct) {
@@ -1141,8 +1142,8 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
                 } else {
                     ms_pack(cur, V, np, mdim1, j, dirs, na, pn, nu, inv_h, x_block(w, cur), np, st);
                     tm.end(st, KC_PACK, 0, na * dn * (16.0 + elem_size(cur)));
-                    yi = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_otf_narrow(S, cur, na) ? q.Yi.p : nullptr;
-                    block_product(S, w, cur, na, tm, st, yi);
+                    yi = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_otf_narrow(S, cur, na, order) ? q.Yi.p : nullptr;
+                    block_product(S, w, cur, na, tm, st, order, yi);
                 }
                 tm.begin(st);
                 double* tv = keep_tv ? q.TV.p : nullptr;

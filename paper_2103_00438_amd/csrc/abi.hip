@@ -501,36 +501,6 @@ void* scratch_ptr(int device) {
     return g_scratch_ptr[device];
 }
 
-// sys[k] = k, zs[k] = (z_re[k], z_im[k])
-__global__ void na_setup_kernel(int nsys, const double* __restrict__ z_re, const double* __restrict__ z_im,
-                                double2* __restrict__ zs, int* __restrict__ sys) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nsys) return;
-    zs[k] = make_double2(z_re[k], z_im[k]);
-    sys[k] = k;
-}
-
-// slot 0 of system s (re, im planes) = X_s in the internal order, zero padding; slot 1 cleared
-__global__ void na_gather_kernel(int64_t n, int64_t npad, const int32_t* __restrict__ perm,
-                                 const double* __restrict__ x_re, const double* __restrict__ x_im,
-                                 double* __restrict__ V) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= npad) return;
-    const int64_t s = blockIdx.y;
-    double* v = V + s * 4 * npad;
-    const bool in = i < n;
-    v[i] = in ? x_re[s * n + perm[i]] : 0.0;
-    v[npad + i] = in ? x_im[s * n + perm[i]] : 0.0;
-    v[2 * npad + i] = 0.0;
-    v[3 * npad + i] = 0.0;
-}
-
-// zero `words` 16-byte words (a fill kernel rather than a memset node, so the call can be captured)
-__global__ void na_zero_kernel(uint4* __restrict__ p, int64_t words) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (int64_t)gridDim.x * 256)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
 // restores the structure's own split-k work space when the call ends
 struct FixedSplit {
     const Structure& S;
@@ -578,27 +548,35 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
                                  std::to_string(kNoAllocScratchBytes >> 20) + " MiB");
         WFQ_HIP(hipSetDevice(S.device));
         char* base = static_cast<char*>(scratch_ptr(S.device));
-        double* V = reinterpret_cast<double*>(base);
-        double2* zs = reinterpret_cast<double2*>(base + v_bytes);
-        int* sys = reinterpret_cast<int*>(base + v_bytes + z_bytes);
+        // [row pairs of the products][X][Y][split-k tiles]; the systems' vectors stay in the caller's arrays
+        void* Yr = base;
         void* X = base + v_bytes + z_bytes + s_bytes;
         void* Y = base + v_bytes + z_bytes + s_bytes + x_bytes;
         FixedSplit fs(S, base + need, kNoAllocScratchBytes - need);
         hipStream_t st = static_cast<hipStream_t>(stream);
-        hipLaunchKernelGGL(na_setup_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, nsys, z_re_dev, z_im_dev, zs, sys);
-        WFQ_CHECK_LAUNCH();
-        hipLaunchKernelGGL(na_gather_kernel, dim3((unsigned)(np / 256), (unsigned)nsys), dim3(256), 0, st, S.n, np,
-                           S.dperm, X_re_dev, X_im_dev, V);
-        WFQ_CHECK_LAUNCH();
-        const int64_t words = (int64_t)(x_bytes / 16);
-        hipLaunchKernelGGL(na_zero_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0,
-                           st, static_cast<uint4*>(X), words);
-        WFQ_CHECK_LAUNCH();
-        const Basis Vb{V, 4 * np, 2 * np, np};
-        pack_columns(precision, Vb, sys, nsys, 0, nullptr, false, X, np, st);
+        load_columns(S, precision, X_re_dev, X_im_dev, nsys, rows, X, st);
         tx_any(S, precision, X, Y, 2 * nsys, st, Order::any);
-        spmm_shift(S, precision == WFQ_PREC_FP64, Y, np, sys, nsys, zs, Vb, 0, 1, st);
-        scatter_q(S, S.dperm, sys, nsys, Basis{V + 2 * np, 4 * np, 2 * np, np}, Y_re_dev, Y_im_dev, st);
+        // The last kernel reads the shifts and the vectors and writes Y element by element: Y may be X itself, but
+        // where it overlaps an input otherwise the result goes through scratch.
+        const size_t vec = (size_t)nsys * S.n, zl = nsys;
+        auto clash = [](const double* y, const double* x, size_t ny, size_t nx) {
+            const uintptr_t ya = (uintptr_t)y, xa = (uintptr_t)x;
+            return ya < xa + nx * 8 && xa < ya + ny * 8;
+        };
+        bool apart = true;
+        for (const double* y : {Y_re_dev, Y_im_dev}) {
+            for (const double* x : {X_re_dev, X_im_dev}) apart = apart && (y == x || !clash(y, x, vec, vec));
+            for (const double* z : {z_re_dev, z_im_dev}) apart = apart && !clash(y, z, vec, zl);
+        }
+        double* tmp = static_cast<double*>(Yr);
+        double *o_re = apart ? Y_re_dev : tmp, *o_im = apart ? Y_im_dev : tmp + vec;
+        // row pairs of 4 systems and more fit their region: round_up(nsys, 8) x 16 B <= nsys x 32 B per atom
+        spmm_user(S, precision == WFQ_PREC_FP64, Y, np, apart && nsys >= 4 ? Yr : nullptr, nsys, z_re_dev, z_im_dev, X_re_dev,
+                  X_im_dev, o_re, o_im, st);
+        if (!apart) {
+            WFQ_HIP(hipMemcpyAsync(Y_re_dev, o_re, vec * 8, hipMemcpyDeviceToDevice, st));
+            WFQ_HIP(hipMemcpyAsync(Y_im_dev, o_im, vec * 8, hipMemcpyDeviceToDevice, st));
+        }
         return WFQ_OK;
     });
 }
@@ -642,7 +620,7 @@ int wfq_apply_op(wfq_handle* h, int32_t precision, int32_t nsys, const double* z
         Basis V{dv, sys_stride, 2 * np, np};
         pack_columns(precision, V, dsys, nsys, 0, nullptr, false, dx, np, h->stream);
         tx_any(S, precision, dx, dy, 2 * nsys, h->stream, Order::any);
-        spmm_shift(S, precision == WFQ_PREC_FP64, dy, np, dsys, nsys, dz, V, 0, 1, h->stream);
+        spmm_shift(S, precision == WFQ_PREC_FP64, dy, np, nullptr, dsys, nsys, dz, V, 0, 1, h->stream);
         d2h_sync(S, vh.data(), dv, vh.size() * 8, h->stream);
         (void)hipFree(dv);
         (void)hipFree(dz);

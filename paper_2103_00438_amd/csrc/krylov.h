@@ -26,19 +26,20 @@ inline int64_t wave_chunks(int64_t n) { return (n + kWaveRows - 1) / kWaveRows; 
 void pack_columns(int prec, const Basis& V, const int* sys, int nsys, int j, const double* scale, bool write_back,
                   void* X, int64_t ld, hipStream_t st, const int* run = nullptr);
 
-// V(s, jdst) = L Y[2k, 2k+1] + z_s V(s, jsrc) for the nsys systems (Y in FP32 or FP64); with
-// y_by_sys the rows of Y are addressed by system id (Y[2s, 2s+1]) instead of list position k; with
-// shift_src the shifted term is taken from that basis instead (shift_src(s, jsrc)).
-void spmm_shift(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys,
-                const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st, bool y_by_sys = false,
-                const Basis* shift_src = nullptr);
+// The same from a caller's vectors in its own atom order, with every row of X from 2 nsys to `rows` zeroed
+void load_columns(const Structure& S, int prec, const double* x_re, const double* x_im, int nsys, int64_t rows, void* X,
+                  hipStream_t st);
 
-// As spmm_shift (list positions, no y_by_sys), first interleaving the two planes of each system's
-// product into Yp (nsys x ld pairs, same element type as Y) so that the sparse product gathers both
-// with one load; falls back to spmm_shift where the neighbour lists are too long for row blocks.
-void spmm_shift_pairs(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yp, const int* sys,
-                      int nsys, const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st,
-                      const Basis* shift_src = nullptr);
+// V(s, jdst) = L Y[2k, 2k+1] + z_s V(s, jsrc) for the nsys systems s = sys[k] (Y in FP32 or FP64); with
+// shift_src the shifted term is taken from that basis instead (shift_src(s, jsrc)). Yr (may be NULL): room for
+// round_up(nsys, 8) x S.npad pairs of Y's element type, in which the planes of several systems are put side by
+// side before the gathers.
+void spmm_shift(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yr, const int* sys, int nsys,
+                const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st,
+                const Basis* shift_src = nullptr);
+// The same on a caller's vectors in its own atom order: y_k = L Y[2k, 2k+1] + z_k x_k
+void spmm_user(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yr, int nsys, const double* z_re,
+               const double* z_im, const double* x_re, const double* x_im, double* y_re, double* y_im, hipStream_t st);
 
 // V(s, jdst) = L Y_s + z_s V(s, jsrc) for the nsys listed systems, with Y already interleaved and
 // addressed by system id: Yp[s][i] = (re, im) pairs, ld pairs per system (FP64).

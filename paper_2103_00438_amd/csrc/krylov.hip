@@ -51,76 +51,213 @@ __global__ void __launch_bounds__(256) pack_kernel(Basis V, const int* __restric
     X[(int64_t)(2 * k + 1) * ld + i] = cast_from_double<E>(b);
 }
 
-// Each thread owns one row of L and up to NS systems, so the row's (col, val) pairs are read once
-// for NS right-hand sides; L is read in the transposed ELL layout (coalesced across rows).
-template <typename YE, int NS>
-__global__ void __launch_bounds__(256) spmm_kernel(int64_t n, int64_t npad, int w, const int32_t* __restrict__ ecol,
-                                                   const double* __restrict__ eval, const YE* __restrict__ Y,
-                                                   int64_t ld, const int* __restrict__ sys, int nsys,
-                                                   const double2* __restrict__ z, Basis Vs, Basis V, int jsrc,
-                                                   int jdst) {
+// the block of the operator entry points, straight from a caller's vectors (rows from 2 nsys on are zeroed)
+template <typename E>
+__global__ void __launch_bounds__(256) load_kernel(int64_t n, int64_t ld, const int32_t* __restrict__ perm, int nsys,
+                                                   const double* __restrict__ x_re, const double* __restrict__ x_im,
+                                                   E* __restrict__ X) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int k0 = blockIdx.y * NS;
-    const int kn = min(NS, nsys - k0);
-    double ar[NS], ai[NS];
-#pragma unroll
-    for (int t = 0; t < NS; ++t) ar[t] = ai[t] = 0.0;
-    for (int p = 0; p < w; ++p) {
-        const int c = ecol[(int64_t)p * npad + i];
-        const double v = eval[(int64_t)p * npad + i];
-#pragma unroll
-        for (int t = 0; t < NS; ++t)
-            if (t < kn) {
-                ar[t] += v * widen(Y[(int64_t)(2 * (k0 + t)) * ld + c]);
-                ai[t] += v * widen(Y[(int64_t)(2 * (k0 + t) + 1) * ld + c]);
-            }
+    const int64_t k = blockIdx.y;
+    double a = 0.0, b = 0.0;
+    if (k < nsys && i < n) {
+        const int64_t o = k * n + perm[i];
+        a = x_re[o];
+        b = x_im[o];
     }
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-        if (t < kn) {
-            const int s = sys[k0 + t];
-            const double* sr = vre(Vs, s, jsrc);
-            const double vr = sr[i], vi = sr[i + Vs.npad];
-            const double2 zz = z[s];
-            double* dr = vre(V, s, jdst);
-            dr[i] = ar[t] + zz.x * vr - zz.y * vi;
-            dr[i + V.npad] = ai[t] + zz.x * vi + zz.y * vr;
-        }
+    X[(2 * k) * ld + i] = cast_from_double<E>(a);
+    X[(2 * k + 1) * ld + i] = cast_from_double<E>(b);
 }
 
-// Row-block variant. A work-group owns R consecutive rows for one group of systems. Their ELL
-// rows are staged once in LDS ([entry][row], so lanes read consecutive words) and reused for every
-// system of the group; each wave works on 64 / R systems at a time, one lane per (row, system).
-// The neighbour window of each Y plane is then gathered by the work-groups of neighbouring row
-// blocks at about the same time: row blocks are laid out so that the work-groups of one XCD (ids
-// congruent mod 8) own one contiguous run of rows, and that XCD's L2 serves the overlapping windows.
+// ---- L Y + z V. Row blocks are laid out so that the work-groups of one XCD (ids congruent mod 8) own one contiguous
+// run of rows: they gather overlapping neighbour windows of Y at about the same time, and that XCD's L2 serves them.
 template <typename YE> struct Pair2;
 template <> struct Pair2<float> { using type = float2; };
 template <> struct Pair2<double> { using type = double2; };
 
-// Yp[k][i] = (Y[2k][i], Y[2k+1][i]): the real and imaginary planes of each system's product side
-// by side, so that the SpMM fetches both with one load per neighbour
+// Yr[i][k] = (Y[2k][i], Y[2k+1][i]), ldk pairs per row: every system's value of one atom side by side, so
+// that the SpMM below fetches whole lines. 32 rows x 8 systems per work-group, a wave 8 x 8 of them.
 template <typename YE>
-__global__ void __launch_bounds__(256) pair_kernel(const YE* __restrict__ Y, int64_t ld,
-                                                   typename Pair2<YE>::type* __restrict__ Yp) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;   // grid: ld / 256 blocks (ld % 256 == 0)
-    const int64_t k = blockIdx.y;
+__global__ void __launch_bounds__(256) row_pairs_kernel(const YE* __restrict__ Y, int64_t ld, int nsys, int64_t ldk,
+                                                        typename Pair2<YE>::type* __restrict__ Yr) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = (int64_t)blockIdx.x * 32 + wave * 8 + (lane >> 3);   // grid: ld / 32 blocks
+    const int64_t k = (int64_t)blockIdx.y * 8 + (lane & 7);
+    if (k >= nsys) return;
     typename Pair2<YE>::type v;
     v.x = Y[(2 * k) * ld + i];
     v.y = Y[(2 * k + 1) * ld + i];
-    Yp[k * ld + i] = v;
+    Yr[i * ldk + k] = v;
 }
 
-// PAIRS: Y is the interleaved form (row k = ld pairs) instead of two planes per system
-template <typename YE, int R, bool PAIRS = false>
+// Where a row's sum goes: slot jdst of the systems' bases, or a caller's vectors in its own atom order. kParts: a row's
+// entries may be summed in parts (the solves keep one sum per row, whose order their results hang on).
+struct ToBasis {
+    static constexpr bool kParts = false;
+    const int* sys;
+    const double2* z;
+    Basis Vs, V;
+    int jsrc, jdst;
+    __device__ void operator()(int k, int64_t i, double ar, double ai) const {
+        const int s = sys[k];
+        const double* sr = vre(Vs, s, jsrc);
+        const double vr = sr[i], vi = sr[i + Vs.npad];
+        const double2 zz = z[s];
+        double* dr = vre(V, s, jdst);
+        dr[i] = ar + zz.x * vr - zz.y * vi;
+        dr[i + V.npad] = ai + zz.x * vi + zz.y * vr;
+    }
+};
+struct ToUser {
+    static constexpr bool kParts = true;
+    const double *z_re, *z_im, *x_re, *x_im;
+    double *y_re, *y_im;
+    const int32_t* perm;
+    int64_t n;
+    __device__ void operator()(int k, int64_t i, double ar, double ai) const {
+        const int64_t o = k * n + perm[i];
+        const double vr = x_re[o], vi = x_im[o], zr = z_re[k], zi = z_im[k];
+        y_re[o] = ar + zr * vr - zi * vi;
+        y_im[o] = ai + zr * vi + zi * vr;
+    }
+};
+
+// L Y + z V with the lanes of a wave on 8 rows x 8: L groups of SPL adjacent systems times 8 / L parts of the rows'
+// entries. From row pairs (PAIRS), what a row group gathers from one neighbour is one 128-byte line (8 FP64 or
+// 16 FP32 systems), which the load path, the bound of this product, moves in an eighth of the line visits of one
+// lane per row and system: 6 603 atoms with 321 neighbours, 37 systems in FP64 181 -> 67 us (and 5 to put the pairs
+// together), 20 000 atoms with 37, 192 systems in FP32 197 -> 104 (14), 64 systems 78 -> 42 (7). The row block and the number of
+// work-groups make no difference there. For few systems the parts of the entries share the latency of the row's
+// chain and are added by lane shuffles in a fixed order (612 atoms, one system: 6.3 -> 5.1 us). The ELL rows of the
+// work-group's R rows are staged in LDS (STAGED; neighbour lists too long for that are read where they are used).
+template <typename YE, int L, int Q, int SPL, int R, bool PAIRS, bool STAGED, typename Out>
+__global__ void __launch_bounds__(256) spmm_sys_kernel(int64_t n, int64_t npad, int w,
+                                                       const int32_t* __restrict__ ecol,
+                                                       const double* __restrict__ eval, const YE* __restrict__ Y,
+                                                       int64_t ld, int nsys, int per_group, Out out) {
+    extern __shared__ char smem[];
+    constexpr int RW = 64 / (L * Q) < R ? 64 / (L * Q) : R;   // rows per wave
+    double* lval = reinterpret_cast<double*>(smem);
+    int32_t* lcol = reinterpret_cast<int32_t*>(smem + (size_t)w * R * sizeof(double));
+    const int per_xcd = (int)(gridDim.x >> 3);
+    const int64_t rb = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);   // one run of rows per XCD
+    const int64_t r0 = rb * R;
+    if (r0 >= n) return;   // whole work-group: grid padded to a multiple of 8 row blocks
+    if constexpr (STAGED) {
+        for (int q = threadIdx.x; q < w * R; q += 256) {
+            const int e = q / R, r = q % R;
+            const int64_t i = r0 + r;   // < npad: npad is a multiple of R
+            lcol[q] = ecol[(int64_t)e * npad + i];
+            lval[q] = eval[(int64_t)e * npad + i];
+        }
+        __syncthreads();
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    constexpr int nrg = R / RW < 4 ? R / RW : 4;   // row groups; the waves beyond them take other systems
+    static_assert(nrg * RW == R, "a work-group's waves cover its rows");
+    const int lr = lane / (L * Q), g = lane % L, part = lane % (L * Q) / L;
+    if (lr >= RW) return;   // fewer rows than lanes (long neighbour lists, few systems)
+    const int r = wave % nrg * RW + lr;
+    const int64_t i = r0 + r;
+    const int k_end = min(nsys, (int)(blockIdx.y + 1) * per_group);
+    for (int kb = (int)blockIdx.y * per_group + wave / nrg * L * SPL; kb < k_end; kb += 4 / nrg * L * SPL) {
+        int k[SPL];   // lanes past the end repeat the last system and store nothing
+        double ar[SPL], ai[SPL];
+        const int kl = kb + SPL * g < k_end ? kb + SPL * g : kb;
+#pragma unroll
+        for (int t = 0; t < SPL; ++t) {
+            k[t] = min(kb + SPL * g + t, k_end - 1);
+            ar[t] = ai[t] = 0.0;
+        }
+#pragma unroll 8
+        for (int e = part; e < w; e += Q) {
+            const int64_t c = STAGED ? lcol[e * R + r] : ecol[(int64_t)e * npad + i];
+            const double v = STAGED ? lval[e * R + r] : eval[(int64_t)e * npad + i];
+#pragma unroll
+            for (int t = 0; t < SPL; ++t) {
+                if constexpr (PAIRS) {
+                    const YE* y = Y + 2 * (c * ld + kl) + 2 * t;
+                    ar[t] += v * widen(y[0]);
+                    ai[t] += v * widen(y[1]);
+                } else {
+                    ar[t] += v * widen(Y[(int64_t)(2 * k[t]) * ld + c]);
+                    ai[t] += v * widen(Y[(int64_t)(2 * k[t] + 1) * ld + c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < SPL; ++t) {
+#pragma unroll
+            for (int o = L; o < L * Q; o <<= 1) {
+                ar[t] += __shfl_xor(ar[t], o, 64);
+                ai[t] += __shfl_xor(ai[t], o, 64);
+            }
+            if (part == 0 && kb + SPL * g + t < k_end && i < n) out(k[t], i, ar[t], ai[t]);
+        }
+    }
+}
+
+template <typename YE, int L, int Q, int SPL, int R, bool PAIRS, bool STAGED, typename Out>
+void launch_spmm_tile(const Structure& S, const YE* Y, int64_t ld, int nsys, const Out& out, hipStream_t st) {
+    const int64_t nb8 = (S.npad / R + 7) / 8 * 8;
+    constexpr int RW = 64 / (L * Q) < R ? 64 / (L * Q) : R;
+    const int lanes = 4 / (R / RW) * L * SPL;   // systems per pass of a work-group
+    const int64_t want = (2048 + nb8 - 1) / nb8;
+    const int gy = (int)std::max<int64_t>(1, std::min<int64_t>(want, (nsys + lanes - 1) / lanes));
+    const int per_group = ((nsys + gy - 1) / gy + L * SPL - 1) / (L * SPL) * (L * SPL);
+    const dim3 grd((unsigned)nb8, (unsigned)((nsys + per_group - 1) / per_group));
+    hipLaunchKernelGGL((spmm_sys_kernel<YE, L, Q, SPL, R, PAIRS, STAGED, Out>), grd, dim3(256), STAGED ? (size_t)S.ell_w * 12 * R : 0,
+                       st, S.n, S.npad, S.ell_w, S.ell_col, S.ell_val, Y, ld, nsys, per_group, out);
+    WFQ_CHECK_LAUNCH();
+}
+template <typename YE, int L, int Q, int SPL, bool PAIRS, typename Out>
+void launch_spmm_sys(const Structure& S, const YE* Y, int64_t ld, int nsys, const Out& out, hipStream_t st) {
+    // the most rows (up to 32: a row group per wave) whose ELL rows leave four work-groups to a CU's LDS
+    const size_t per_row = (size_t)S.ell_w * 12;
+    if (L * Q == 1 && per_row * 64 <= 40960) launch_spmm_tile<YE, L, Q, SPL, L * Q == 1 ? 64 : 32, PAIRS, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 32 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 32, PAIRS, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 16 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 16, PAIRS, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 8 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 8, PAIRS, true>(S, Y, ld, nsys, out, st);
+    else launch_spmm_tile<YE, L, Q, SPL, 8, PAIRS, false>(S, Y, ld, nsys, out, st);
+}
+
+// Yr != NULL (room for round_up(nsys, 8) pairs per row): from four systems on the product's planes are first turned
+// into row pairs there. FP64 gains from four systems on at every size (3 043-atom sphere, 4 systems: 52 -> 45 us for the
+// whole operator, 12: 92 -> 56; 600-atom tube, 12: 28 -> 26). FP32 planes are half as long, and the extra
+// launch only pays from about 4 M gathered pairs (4 000-atom tube, 12 systems, 2.4 M: 30 -> 33 us; sphere, 6
+// systems, 4.0 M: equal; 12 systems: 62 -> 50; 16 000-atom tube, 12 systems, 9.6 M: 222 -> 214).
+template <typename YE, typename Out>
+void spmm_sys(const Structure& S, const YE* Y, int64_t ld, void* Yr, int nsys, const Out& out, hipStream_t st) {
+    constexpr bool f64 = std::is_same<YE, double>::value;
+    if (Yr && nsys >= 4 && (f64 || S.npad * S.ell_w * nsys >= (int64_t)4 << 20)) {
+        const int64_t ldk = (nsys + 7) / 8 * 8;
+        hipLaunchKernelGGL(row_pairs_kernel<YE>, dim3((unsigned)(S.npad / 32), (unsigned)(ldk / 8)), dim3(256), 0, st, Y, ld,
+                           nsys, ldk, static_cast<typename Pair2<YE>::type*>(Yr));
+        WFQ_CHECK_LAUNCH();
+        const YE* P = static_cast<const YE*>(Yr);
+        if (nsys <= 4) launch_spmm_sys<YE, 4, Out::kParts ? 2 : 1, 1, true>(S, P, ldk, nsys, out, st);
+        else if (f64 || nsys <= 8) launch_spmm_sys<YE, 8, 1, 1, true>(S, P, ldk, nsys, out, st);
+        else launch_spmm_sys<YE, 8, 1, 2, true>(S, P, ldk, nsys, out, st);
+    } else if (nsys == 1) {
+        launch_spmm_sys<YE, 1, Out::kParts ? 8 : 1, 1, false>(S, Y, ld, nsys, out, st);
+    } else if (nsys == 2) {
+        launch_spmm_sys<YE, 2, Out::kParts ? 4 : 1, 1, false>(S, Y, ld, nsys, out, st);
+    } else if (nsys <= 4) {
+        launch_spmm_sys<YE, 4, Out::kParts ? 2 : 1, 1, false>(S, Y, ld, nsys, out, st);
+    } else {
+        launch_spmm_sys<YE, 8, 1, 1, false>(S, Y, ld, nsys, out, st);
+    }
+}
+
+// L Y + z V from per-system interleaved columns (Yp[s][i] = (re, im)), the layout in which QMR's direction update
+// leaves T p. A work-group owns R consecutive rows for one group of systems, their ELL rows staged once in LDS
+// ([entry][row], so lanes read consecutive words); each wave works on 64 / R systems at a time, one lane per (row,
+// system).
+template <int R>
 __global__ void __launch_bounds__(256) spmm_rows_kernel(int64_t n, int64_t npad, int w,
                                                         const int32_t* __restrict__ ecol,
-                                                        const double* __restrict__ eval, const YE* __restrict__ Y,
+                                                        const double* __restrict__ eval, const double2* __restrict__ Yp,
                                                         int64_t ld, const int* __restrict__ sys, int nsys, int per_group,
-                                                        const double2* __restrict__ z, Basis Vs, Basis V, int jsrc,
-                                                        int jdst,
-                                                        int y_by_sys) {
+                                                        ToBasis out) {
     extern __shared__ char smem[];
     double* lval = reinterpret_cast<double*>(smem);
     int32_t* lcol = reinterpret_cast<int32_t*>(smem + (size_t)w * R * sizeof(double));
@@ -143,41 +280,21 @@ __global__ void __launch_bounds__(256) spmm_rows_kernel(int64_t n, int64_t npad,
     const int k_end = min(nsys, (int)(blockIdx.y + 1) * per_group);
     for (int k = (int)blockIdx.y * per_group + wave * G + g; k < k_end; k += 4 * G) {
         double ar = 0.0, ai = 0.0;
-        if constexpr (PAIRS) {
-            const typename Pair2<YE>::type* yp =
-                reinterpret_cast<const typename Pair2<YE>::type*>(Y) + (int64_t)(y_by_sys ? sys[k] : k) * ld;
+        const double2* yp = Yp + (int64_t)sys[k] * ld;
 #pragma unroll 4
-            for (int e = 0; e < w; ++e) {
-                const int c = lcol[e * R + r];
-                const double v = lval[e * R + r];
-                const typename Pair2<YE>::type y = yp[c];
-                ar += v * widen(y.x);
-                ai += v * widen(y.y);
-            }
-        } else {
-            const YE* yr = Y + (int64_t)(2 * (y_by_sys ? sys[k] : k)) * ld;
-            const YE* yi = yr + ld;
-#pragma unroll 4
-            for (int e = 0; e < w; ++e) {
-                const int c = lcol[e * R + r];
-                const double v = lval[e * R + r];
-                ar += v * widen(yr[c]);
-                ai += v * widen(yi[c]);
-            }
+        for (int e = 0; e < w; ++e) {
+            const int c = lcol[e * R + r];
+            const double v = lval[e * R + r];
+            const double2 y = yp[c];
+            ar += v * y.x;
+            ai += v * y.y;
         }
-        const int s = sys[k];
-        const double* sr = vre(Vs, s, jsrc);
-        const double vr = sr[i], vi = sr[i + Vs.npad];
-        const double2 zz = z[s];
-        double* dr = vre(V, s, jdst);
-        dr[i] = ar + zz.x * vr - zz.y * vi;
-        dr[i + V.npad] = ai + zz.x * vi + zz.y * vr;
+        out(k, i, ar, ai);
     }
 }
 
-template <typename YE, int R, bool PAIRS = false>
-void launch_spmm_rows(const Structure& S, const YE* Y, int64_t ld, const int* sys, int nsys, const double2* z,
-                      const Basis& Vs, const Basis& V, int jsrc, int jdst, bool y_by_sys, hipStream_t st) {
+template <int R>
+void launch_spmm_rows(const Structure& S, const double2* Yp, int64_t ld, int nsys, const ToBasis& out, hipStream_t st) {
     constexpr int G = 64 / R;
     const int64_t nb = S.npad / R;
     const int64_t nb8 = (nb + 7) / 8 * 8;
@@ -186,9 +303,8 @@ void launch_spmm_rows(const Structure& S, const YE* Y, int64_t ld, const int* sy
     const int gy = (int)std::max<int64_t>(1, std::min<int64_t>(want, (nsys + 4 * G - 1) / (4 * G)));
     const int per_group = (nsys + gy - 1) / gy;
     const size_t lds = (size_t)S.ell_w * R * 12;
-    hipLaunchKernelGGL((spmm_rows_kernel<YE, R, PAIRS>), dim3((unsigned)nb8, (unsigned)gy), dim3(256), lds, st, S.n, S.npad,
-                       S.ell_w, S.ell_col, S.ell_val, Y, ld, sys, nsys, per_group, z, Vs, V, jsrc, jdst,
-                       (int)y_by_sys);
+    hipLaunchKernelGGL(spmm_rows_kernel<R>, dim3((unsigned)nb8, (unsigned)gy), dim3(256), lds, st, S.n, S.npad, S.ell_w,
+                       S.ell_col, S.ell_val, Yp, ld, out.sys, nsys, per_group, out);
 }
 
 __global__ void reduce_dots_kernel(const int* __restrict__ sys, int j, const double2* __restrict__ partial, int mdim,
@@ -419,92 +535,50 @@ void pack_columns(int prec, const Basis& V, const int* sys, int nsys, int j, con
     WFQ_CHECK_LAUNCH();
 }
 
-void spmm_shift(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys,
-                const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st, bool y_by_sys,
-                const Basis* shift_src) {
-    if (nsys <= 0) return;
-    const Basis& Vs = shift_src ? *shift_src : V;
-    // row-block kernel with the largest row block whose ELL rows fit in 40 KB of LDS (4 work-groups
-    // per CU); the per-thread kernel only for neighbour lists too long even for 8 rows
-    const size_t per_row = (size_t)S.ell_w * 12;
-    const int R = per_row * 64 <= 40960 ? 64 : per_row * 32 <= 40960 ? 32 : per_row * 16 <= 40960 ? 16
-                  : per_row * 8 <= 40960 ? 8 : 0;
-    if (R > 0) {
-        if (y_is_f64) {
-            const double* Yd = static_cast<const double*>(Y);
-            if (R == 64) launch_spmm_rows<double, 64>(S, Yd, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else if (R == 32) launch_spmm_rows<double, 32>(S, Yd, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else if (R == 16) launch_spmm_rows<double, 16>(S, Yd, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else launch_spmm_rows<double, 8>(S, Yd, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-        } else {
-            const float* Yf = static_cast<const float*>(Y);
-            if (R == 64) launch_spmm_rows<float, 64>(S, Yf, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else if (R == 32) launch_spmm_rows<float, 32>(S, Yf, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else if (R == 16) launch_spmm_rows<float, 16>(S, Yf, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-            else launch_spmm_rows<float, 8>(S, Yf, ld, sys, nsys, z, Vs, V, jsrc, jdst, y_by_sys, st);
-        }
-        WFQ_CHECK_LAUNCH();
-        return;
-    }
-    if (y_by_sys) throw Error{WFQ_EINVAL, "neighbour lists too long for the sparse product"};
-    constexpr int NS = 8;
-    dim3 grd((unsigned)((S.n + 255) / 256), (unsigned)((nsys + NS - 1) / NS));
-    if (y_is_f64)
-        hipLaunchKernelGGL((spmm_kernel<double, NS>), grd, dim3(256), 0, st, S.n, S.npad, S.ell_w, S.ell_col,
-                           S.ell_val, static_cast<const double*>(Y), ld, sys, nsys, z, Vs, V, jsrc, jdst);
-    else
-        hipLaunchKernelGGL((spmm_kernel<float, NS>), grd, dim3(256), 0, st, S.n, S.npad, S.ell_w, S.ell_col,
-                           S.ell_val, static_cast<const float*>(Y), ld, sys, nsys, z, Vs, V, jsrc, jdst);
+void load_columns(const Structure& S, int prec, const double* x_re, const double* x_im, int nsys, int64_t rows, void* X,
+                  hipStream_t st) {
+    const dim3 grd((unsigned)(S.npad / 256), (unsigned)(rows / 2));
+    auto go = [&](auto tag) {
+        using E = decltype(tag);
+        hipLaunchKernelGGL(load_kernel<E>, grd, dim3(256), 0, st, S.n, S.npad, S.dperm, nsys, x_re, x_im,
+                           static_cast<E*>(X));
+    };
+    if (prec == WFQ_PREC_FP64) go(double{});
+    else if (prec == WFQ_PREC_FP32) go(float{});
+    else go(uint16_t{});
     WFQ_CHECK_LAUNCH();
 }
 
-void spmm_shift_pairs(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yp, const int* sys,
-                      int nsys, const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st,
-                      const Basis* shift_src) {
+void spmm_shift(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yr, const int* sys, int nsys,
+                const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st, const Basis* shift_src) {
     if (nsys <= 0) return;
-    // the row block of spmm_shift; the per-thread form (R = 0) reads the two planes
-    const size_t per_row = (size_t)S.ell_w * 12;
-    const int R = per_row * 64 <= 40960 ? 64 : per_row * 32 <= 40960 ? 32 : per_row * 16 <= 40960 ? 16
-                  : per_row * 8 <= 40960 ? 8 : 0;
-    if (R == 0 || ld != S.npad) {
-        spmm_shift(S, y_is_f64, Y, ld, sys, nsys, z, V, jsrc, jdst, st, false, shift_src);
-        return;
-    }
-    const Basis& Vs = shift_src ? *shift_src : V;
-    dim3 pg((unsigned)(ld / 256), (unsigned)nsys);
-    if (y_is_f64) {
-        hipLaunchKernelGGL(pair_kernel<double>, pg, dim3(256), 0, st, static_cast<const double*>(Y), ld,
-                           static_cast<double2*>(Yp));
-        WFQ_CHECK_LAUNCH();
-        const double* P = static_cast<const double*>(Yp);
-        if (R == 64) launch_spmm_rows<double, 64, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else if (R == 32) launch_spmm_rows<double, 32, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else if (R == 16) launch_spmm_rows<double, 16, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else launch_spmm_rows<double, 8, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-    } else {
-        hipLaunchKernelGGL(pair_kernel<float>, pg, dim3(256), 0, st, static_cast<const float*>(Y), ld,
-                           static_cast<float2*>(Yp));
-        WFQ_CHECK_LAUNCH();
-        const float* P = static_cast<const float*>(Yp);
-        if (R == 64) launch_spmm_rows<float, 64, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else if (R == 32) launch_spmm_rows<float, 32, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else if (R == 16) launch_spmm_rows<float, 16, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-        else launch_spmm_rows<float, 8, true>(S, P, ld, sys, nsys, z, Vs, V, jsrc, jdst, false, st);
-    }
-    WFQ_CHECK_LAUNCH();
+    const ToBasis out{sys, z, shift_src ? *shift_src : V, V, jsrc, jdst};
+    if (y_is_f64) spmm_sys(S, static_cast<const double*>(Y), ld, Yr, nsys, out, st);
+    else spmm_sys(S, static_cast<const float*>(Y), ld, Yr, nsys, out, st);
+}
+
+void spmm_user(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, void* Yr, int nsys, const double* z_re,
+               const double* z_im, const double* x_re, const double* x_im, double* y_re, double* y_im, hipStream_t st) {
+    if (nsys <= 0) return;
+    const ToUser out{z_re, z_im, x_re, x_im, y_re, y_im, S.dperm, S.n};
+    if (y_is_f64) spmm_sys(S, static_cast<const double*>(Y), ld, Yr, nsys, out, st);
+    else spmm_sys(S, static_cast<const float*>(Y), ld, Yr, nsys, out, st);
 }
 
 void spmm_shift_interleaved(const Structure& S, const double* Yp, int64_t ld, const int* sys, int nsys,
                             const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st) {
     if (nsys <= 0) return;
+    // the largest row block whose ELL rows fit in 40 KB of LDS (4 work-groups per CU)
     const size_t per_row = (size_t)S.ell_w * 12;
     const int R = per_row * 64 <= 40960 ? 64 : per_row * 32 <= 40960 ? 32 : per_row * 16 <= 40960 ? 16
                   : per_row * 8 <= 40960 ? 8 : 0;
     if (R == 0) throw Error{WFQ_EINVAL, "neighbour lists too long for the sparse product"};
-    if (R == 64) launch_spmm_rows<double, 64, true>(S, Yp, ld, sys, nsys, z, V, V, jsrc, jdst, true, st);
-    else if (R == 32) launch_spmm_rows<double, 32, true>(S, Yp, ld, sys, nsys, z, V, V, jsrc, jdst, true, st);
-    else if (R == 16) launch_spmm_rows<double, 16, true>(S, Yp, ld, sys, nsys, z, V, V, jsrc, jdst, true, st);
-    else launch_spmm_rows<double, 8, true>(S, Yp, ld, sys, nsys, z, V, V, jsrc, jdst, true, st);
+    const ToBasis out{sys, z, V, V, jsrc, jdst};
+    const double2* Y = reinterpret_cast<const double2*>(Yp);
+    if (R == 64) launch_spmm_rows<64>(S, Y, ld, nsys, out, st);
+    else if (R == 32) launch_spmm_rows<32>(S, Y, ld, nsys, out, st);
+    else if (R == 16) launch_spmm_rows<16>(S, Y, ld, nsys, out, st);
+    else launch_spmm_rows<8>(S, Y, ld, nsys, out, st);
     WFQ_CHECK_LAUNCH();
 }
 

@@ -802,13 +802,9 @@ void gmres_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double 
                         }
                         block_product(S, w, p, 2 * ng, tm, st);
                         tm.begin(st);
-                        if (w.Yp64.p)
-                            spmm_shift_pairs(S, p == WFQ_PREC_FP64, y_block(w, p), w.npad,
-                                             p == WFQ_PREC_FP64 ? (void*)w.Yp64.p : (void*)w.Yp32.p, w.sys[p].p,
-                                             ng, w.z.p, w.Vb, bj ? 0 : k, k + 1, st, bj ? &w.Ub : nullptr);
-                        else
-                            spmm_shift(S, p == WFQ_PREC_FP64, y_block(w, p), w.npad, w.sys[p].p, ng, w.z.p, w.Vb,
-                                       bj ? 0 : k, k + 1, st, false, bj ? &w.Ub : nullptr);
+                        spmm_shift(S, p == WFQ_PREC_FP64, y_block(w, p), w.npad,
+                                   p == WFQ_PREC_FP64 ? (void*)w.Yp64.p : (void*)w.Yp32.p, w.sys[p].p, ng, w.z.p, w.Vb,
+                                   bj ? 0 : k, k + 1, st, bj ? &w.Ub : nullptr);
                         tm.end(st, KC_SPMM, 4.0 * S.nnz * ng + 8 * n * ng,
                                12.0 * S.nnz + ng * n * (2.0 * out_size(p) + 16 + 16));
                     }

@@ -90,3 +90,62 @@ def test_noalloc_rejects_what_does_not_fit(lib):
         lib.wfq_apply_op_noalloc(h, "bf16", z[:1], z[:1], X[:1], X[:1], Y[:1], Y[:1])   # no BF16 copy built
     assert e.value.code == lib.WFQ_EINVAL
     h.close()
+
+
+def _pieces(shape):
+    import wfq_inputs as wi
+    if shape == "tube":
+        return geo.jitter(geo.nanotube(6, 6, 12), 0.01, 21), GRAPHENE
+    metal = dict(wi.workloads.FCC_METAL)
+    if shape == "long":   # neighbour lists beyond the 426 entries that the sparse product stages
+        return geo.jitter(geo.fcc_sphere(14.5), 0.01, 22), dict(metal, fermi_d=6.0)
+    return geo.jitter(geo.fcc_sphere(14.5), 0.01, 22), metal
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("nsys", [1, 2, 3, 4, 5, 8, 9, 17, 40])
+@pytest.mark.parametrize("shape", ["tube", "sphere", "long"])
+def test_noalloc_sparse_product_forms(lib, shape, nsys, prec):
+    # one to several systems per lane group, planes and row pairs, staged and unstaged neighbour lists
+    import torch
+    xyz, par = _pieces(shape)
+    P = O.Problem(xyz, par)
+    if shape == "long":
+        assert np.bincount(P.L.nonzero()[0]).max() > 426
+    h = lib.wfq_build(xyz, par, store=(prec,))
+    rng = np.random.default_rng(nsys)
+    X = rng.standard_normal((nsys, P.n)) + 1j * rng.standard_normal((nsys, P.n))
+    z = rng.standard_normal(nsys) + 1j * rng.standard_normal(nsys)
+    y = run_noalloc(lib, torch, h, prec, z, X)
+    h.close()
+    assert oracle_bound_ok(P, prec, z, X, y)
+
+
+@pytest.mark.parametrize("nsys", [2, 5])
+def test_noalloc_in_place_and_overlapping_vectors(lib, nsys):
+    # the result may replace the vectors, or overlap them anywhere
+    import torch
+    xyz, par = _pieces("tube")
+    h = lib.wfq_build(xyz, par)
+    n = xyz.shape[0]
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((nsys, n)) + 1j * rng.standard_normal((nsys, n))
+    z = rng.standard_normal(nsys) + 1j * rng.standard_normal(nsys)
+    ref = run_noalloc(lib, torch, h, "fp64", z, X)
+    dev = torch.device("cuda:0")
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).to(dev)
+    zr, zi = t(z.real), t(z.imag)
+    for shift, swap in ((0, False), (0, True), (1, False), (n, False), (n + 3, True)):
+        re = torch.zeros(nsys * n + shift, dtype=torch.float64, device=dev)
+        im = torch.zeros_like(re)
+        view = lambda b, o: b[o:o + nsys * n].view(nsys, n)
+        xr, xi = view(re, 0), view(im, 0)
+        xr.copy_(t(X.real))
+        xi.copy_(t(X.imag))
+        yr, yi = (view(im, shift), view(re, shift)) if swap else (view(re, shift), view(im, shift))
+        torch.cuda.synchronize()
+        lib.wfq_apply_op_noalloc(h, "fp64", zr, zi, xr, xi, yr, yi, stream=torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        y = yr.cpu().numpy() + 1j * yi.cpu().numpy()
+        assert np.array_equal(y, ref), (shift, swap)
+    h.close()

@@ -270,6 +270,123 @@ __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, OCC)
 
 #undef WFQ_CHUNK_OK
 
+// ---- FP64 products of a few to a hundred columns: both operands straight into the fragment layout
+//
+// FP64 matrix instructions take 64 clocks for 512 B per operand, so a wave that holds 16 CF columns x 16 RF rows
+// needs no LDS to feed them. T is symmetric, so Y[c][i] = sum_k T[k][i] X[c][k] walks down T's rows: the 16 lanes of a
+// fragment's row index read adjacent elements (32 or 64 bytes of every line per load; along a row of T, each lane
+// would be a line visit of its own, and those bound the kernel). A lane's 16 bytes are two neighbouring
+// columns of T and feed two fragments; X is laid out the same way beforehand (xt_kernel: [k][columns]).
+// What this spares against the LDS tiles of tx_mfma_kernel is column padding (128 columns' work for 74; the granule is 16
+// here) and barriers. The four waves of a work-group take every fourth 16 k of the same tile, their sums are
+// added in LDS in order at the end, and the loads of a wave's next 16 k are in flight during the products of this
+// one (two register buffers). Split k and the order of the tiles as in tx_mfma_kernel.
+// Bound: the FP64 matrix cores and, below some 48 columns, T's 8 bytes per element. Against the fastest LDS tile, us:
+// 20 000 atoms 588 / 753 at 16 columns, 717 / 1 017 at 48, 1 111 / 1 770 at 80 (59 TFLOP/s), 1 676 / 1 787 at 128,
+// 4 507 / 5 208 at 384; 6 603 atoms 72 / 75, 101 / 126, 150 / 202, 191 / 239, 514 / 607; 2 000 atoms 11 / 19, 16 / 20, 23 / 30, 28 / 32,
+// 57 / 75 (X's turning and the adding of parts included). Along T's rows instead (each lane its own line): 1 300 at
+// 20 000 atoms and 80 columns.
+__global__ void __launch_bounds__(256) xt_kernel(const double* __restrict__ X, int64_t ld, int ncol, int64_t ldc,
+                                                 double* __restrict__ Xt) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t k = (int64_t)blockIdx.x * 32 + wave * 8 + (lane & 7);   // grid: ld / 32 blocks
+    const int c = blockIdx.y * 8 + (lane >> 3);
+    __shared__ double tile[4][8][9];
+    tile[wave][lane >> 3][lane & 7] = c < ncol ? X[(int64_t)c * ld + k] : 0.0;   // 8 columns x 8 k, each wave its own
+    __syncthreads();
+    Xt[((int64_t)blockIdx.x * 32 + wave * 8 + (lane >> 3)) * ldc + blockIdx.y * 8 + (lane & 7)] =
+        tile[wave][lane & 7][lane >> 3];
+}
+
+template <int CF, int RF>
+__global__ void __launch_bounds__(256, 2) tx_frag_kernel(const double* __restrict__ Xt, int64_t ldc,
+                                                         const double* __restrict__ T, double* __restrict__ Y, int64_t ld,
+                                                         int ncol, int mt_count, int nt_count, int split,
+                                                         double* __restrict__ ws) {
+    static_assert(RF % 2 == 0, "rows of T come in pairs of fragments");
+    constexpr int BM = 16 * CF, BN = 16 * RF, CP = CF / 2;
+    __shared__ double sum[2][4][16 * BN];
+    const int logical = xcd_logical(blockIdx.x, mt_count * nt_count * split);
+    const int mt = logical % mt_count;
+    const int part = (logical / mt_count) % split;
+    const int nt = logical / (mt_count * split);
+    const int m0 = mt * BM;
+    const int64_t n0 = (int64_t)nt * BN;
+    const int lane = threadIdx.x & 63, col = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // (scalar: the addresses' base stays scalar)
+    const int units = (int)(ld / 64);   // 64 k: 16 per wave
+    const int ub = (int)((int64_t)units * part / split), ue = (int)((int64_t)units * (part + 1) / split);
+    const double* tb = T + (int64_t)16 * wave * ld + n0;
+    const double* xb = Xt + (int64_t)16 * wave * ldc + m0;
+    const uint32_t to = (uint32_t)(kg * ld + 2 * col), xo = (uint32_t)(kg * ldc + 2 * col),
+                   xo1 = (uint32_t)(kg * ldc + 16 * (CF - 1) + col);
+    struct Frag {
+        double2 t[4][RF / 2], x[4][CP > 0 ? CP : 1];
+        double x1[4];
+    };
+    auto load = [&](Frag& f, int u) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {   // 4 k each
+            const double* tu = tb + ((int64_t)64 * u + 4 * s) * ld;
+            const double* xu = xb + ((int64_t)64 * u + 4 * s) * ldc;
+#pragma unroll
+            for (int r = 0; r < RF / 2; ++r) f.t[s][r] = *reinterpret_cast<const double2*>(tu + 32 * r + to);
+#pragma unroll
+            for (int c = 0; c < CP; ++c) f.x[s][c] = *reinterpret_cast<const double2*>(xu + 32 * c + xo);
+            if constexpr (CF % 2 == 1) f.x1[s] = xu[xo1];
+        }
+    };
+    doublex4 acc[CF][RF];
+#pragma unroll
+    for (int c = 0; c < CF; ++c)
+#pragma unroll
+        for (int r = 0; r < RF; ++r) acc[c][r] = doublex4{0, 0, 0, 0};
+    auto mul = [&](const Frag& f) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < CF; ++c)
+#pragma unroll
+                for (int r = 0; r < RF; ++r) {
+                    const double a = c / 2 < CP ? (c % 2 ? f.x[s][c / 2].y : f.x[s][c / 2].x) : f.x1[s];
+                    const double b = r % 2 ? f.t[s][r / 2].y : f.t[s][r / 2].x;
+                    acc[c][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[c][r], 0, 0, 0);
+                }
+    };
+    Frag f0, f1;
+    load(f0, ub);
+    int u = ub;
+    for (; u + 1 < ue; u += 2) {
+        load(f1, u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(f0, min(u + 2, ue - 1));   // the last step re-reads its own: loads stay unconditional
+        __builtin_amdgcn_sched_barrier(0);
+        mul(f1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (u < ue) mul(f0);
+    double* out = part == 0 ? Y : ws + (int64_t)(part - 1) * mt_count * BM * ld;
+#pragma unroll
+    for (int c = 0; c < CF; ++c) {
+        // element e of a block: fragment row (X) lane / 16 + 4 e, fragment column (T) lane % 16. Column c of the tile
+        // is 32 (c / 2) + 2 row + c % 2 where X came in pairs, rows of T likewise
+        double(*buf)[16 * BN] = sum[c & 1];
+#pragma unroll
+        for (int r = 0; r < RF; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) buf[wave][(kg + 4 * e) * BN + 32 * (r / 2) + 2 * col + r % 2] = acc[c][r][e];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < RF; ++q) {
+            const int at = q * 256 + threadIdx.x, fr = at / BN;
+            const int j = m0 + (c / 2 < CP ? 32 * (c / 2) + 2 * fr + c % 2 : 16 * c + fr);
+            if (j < ncol) out[(int64_t)j * ld + n0 + at % BN] = (buf[0][at] + buf[1][at]) + (buf[2][at] + buf[3][at]);
+        }
+    }
+}
+
 // ---- FP32 products through the FP16 matrix cores: each FP32 operand is split into two FP16 parts
 //
 // v_mfma_f32_16x16x4_f32 does 256 multiply-adds per CU and clock, the FP16 form sixteen times as many
@@ -608,6 +725,57 @@ void launch_mfma(const Structure& s, const void* X, const void* T, void* Y, int6
     }
 }
 
+// columns of X per pass of the fragment-layout product: the count of 16-column fragments (1 to 5 a pass) that
+// pads least; of equal ones the wider, but 3 for 6, 11 and 12 fragments (6 603 to 20 000 atoms, 96 and 192 columns: no slower)
+int frag_columns(int ncol) {
+    const int f = (ncol + 15) / 16;
+    if (f <= 5) return f;
+    int best = 3;
+    for (int c = 4; c <= 5; ++c)
+        if ((f + c - 1) / c * c < (f + best - 1) / best * best) best = c;
+    return best;
+}
+uint64_t frag_x_bytes(int64_t ld, int64_t ldc) { return (uint64_t)ld * ldc * sizeof(double); }
+bool frag_fits(const Structure& s, int ncol) {
+    const int bm = 16 * frag_columns(ncol);
+    return frag_x_bytes(s.npad, (int64_t)(ncol + bm - 1) / bm * bm) <= (s.split_fixed ? s.split_fixed_bytes : kSplitWsCap);
+}
+
+template <int CF, int RF>
+void launch_frag(const Structure& s, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st) {
+    constexpr int BM = 16 * CF, BN = 16 * RF;
+    const int mtc = (ncol + BM - 1) / BM, ntc = (int)(ld / BN), units = (int)(ld / 64);
+    const int64_t ldc = (int64_t)mtc * BM;
+    const uint64_t head = frag_x_bytes(ld, ldc), part_bytes = (uint64_t)ldc * ld * sizeof(double);
+    const uint64_t cap = s.split_fixed ? s.split_fixed_bytes : kSplitWsCap;
+    if (head > cap) {   // no room for the turned X
+        launch_mfma<WFQ_PREC_FP64, 4, 4, 2, 4, 128, 1, 1>(s, X, T, Y, ld, ncol, st);
+        return;
+    }
+    // k parts: the work-groups of the fullest CU times a part's time (64 k of a tile: the CU's 128 FP64 operations a
+    // clock, or its share of the memory's rate), and for each further part its tile written and added
+    const int64_t cus = device_cus(s.device);
+    const double unit_us = 64.0 * BN * std::max(BM * 2 / (128 * 2400.0), 8 / (5.0e6 / (double)cus));
+    auto cost = [&](int sp) {
+        return (double)(((int64_t)mtc * ntc * sp + cus - 1) / cus) * ((units + sp - 1) / sp) * unit_us +
+               (sp > 1 ? 3.0 + (sp - 1) * 2.0 * (double)part_bytes / 5.0e6 : 0.0);
+    };
+    int split = 1;
+    for (int sp = 2; sp <= 16 && units / sp >= 4 && head + (uint64_t)(sp - 1) * part_bytes <= cap; ++sp)
+        if (cost(sp) < 0.98 * cost(split)) split = sp;
+    char* w = static_cast<char*>(split_workspace(s, head + (split - 1) * part_bytes));
+    double *Xt = reinterpret_cast<double*>(w), *ws = reinterpret_cast<double*>(w + head);
+    hipLaunchKernelGGL(xt_kernel, dim3((unsigned)(ld / 32), (unsigned)(ldc / 8)), dim3(256), 0, st,
+                       static_cast<const double*>(X), ld, ncol, ldc, Xt);
+    hipLaunchKernelGGL((tx_frag_kernel<CF, RF>), dim3(mtc * ntc * split), dim3(256), 0, st, Xt, ldc,
+                       static_cast<const double*>(T), static_cast<double*>(Y), ld, ncol, mtc, ntc, split, ws);
+    if (split > 1) {
+        const int64_t count = (int64_t)ncol * ld;
+        hipLaunchKernelGGL(split_reduce_kernel<double>, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st,
+                           static_cast<double*>(Y), ws, count, (int64_t)mtc * BM * ld, split - 1);
+    }
+}
+
 template <int WM, int WN, int KS, int OCC>
 void launch_split(const Structure& s, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st) {
     constexpr int BM = 16 * WM, BN = 64 * WN;
@@ -686,6 +854,14 @@ const std::vector<Variant>& variants_all() {
             // T recomputed, the stored copy not read (otf_narrow_f64)
             r.push_back({"otfn2", 0, 4, 2, nullptr});
             r.push_back({"otfn4", 0, 4, 4, nullptr});
+            r.push_back({"otfn8", 0, 4, 8, nullptr});
+            // fragment-layout products (f<columns>n<rows of T>)
+            r.push_back({"f16n64", 16, 64, 1 << 30, launch_frag<1, 4>});
+            r.push_back({"f32n64", 32, 64, 1 << 30, launch_frag<2, 4>});
+            r.push_back({"f48n32", 48, 32, 1 << 30, launch_frag<3, 2>});
+            r.push_back({"f48n64", 48, 64, 1 << 30, launch_frag<3, 4>});
+            r.push_back({"f64n32", 64, 32, 1 << 30, launch_frag<4, 2>});
+            r.push_back({"f80n32", 80, 32, 1 << 30, launch_frag<5, 2>});
         }
         if constexpr (P != WFQ_PREC_FP64) {
             r.push_back({"m96n256w8", 96, 256, 1 << 30, launch_mfma<P, 3, 4, 2, 4, 128, 1>});
@@ -786,6 +962,17 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
         const Variant& v = variants_of(prec)[it->second];
         if (ncol <= v.max_ncol) return it->second;
     }
+    if (prec == WFQ_PREC_FP64 && order == Order::any && ncol > 4) {
+        // in any order: two narrow recomputed products for 5 to 8 columns of a large structure (20 000 atoms, 8
+        // columns: 380 us, streamed through the matrix cores 576; 10 000: 144 and 161; 8 000: 138 and 94), and the fragment-layout shapes (figures at
+        // tx_frag_kernel) but for 5 to 8 columns of the smallest, whose one launch is quicker than two
+        if (ncol <= 8 && s.npad >= 10240 && otf_narrow_sym(s, 4, order)) return find_variant(prec, "otfn8");
+        if ((ncol > 8 || s.npad >= 1536) && frag_fits(s, ncol)) {
+            static const char* const name[] = {"f16n64", "f32n64", "f48n32", "f64n32", "f80n32"};
+            const int cf = frag_columns(ncol);
+            return find_variant(prec, cf == 3 && s.npad >= 16384 ? "f48n64" : name[cf - 1]);
+        }
+    }
     // narrow FP64 products of large structures: recomputing the elements on the vector ALUs
     // (about 16 FP64 operations per pair) beats streaming 8 bytes per pair of the stored copy
     if (prec == WFQ_PREC_FP64 && ncol <= 4 &&
@@ -801,11 +988,14 @@ void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, 
     if (T == nullptr) throw Error{WFQ_EINVAL, "the stored copy of T for this precision was not built"};
     const Variant& v = variants_of(prec)[var];
     if (ncol > v.max_ncol) throw Error{WFQ_EINVAL, "kernel variant cannot take that many columns"};
-    if (!v.launch)
-        otf_narrow_f64(s, static_cast<const double*>(X), static_cast<double*>(Y), s.npad, ncol, device_cus(s.device), st,
-                       order);
-    else
+    if (v.launch) {
         v.launch(s, X, T, Y, s.npad, ncol, st);
+    } else {
+        for (int c0 = 0; c0 < ncol; c0 += 4)
+            otf_narrow_f64(s, static_cast<const double*>(X) + (int64_t)c0 * s.npad,
+                           static_cast<double*>(Y) + (int64_t)c0 * s.npad, s.npad, std::min(4, ncol - c0),
+                           device_cus(s.device), st, order);
+    }
     WFQ_CHECK_LAUNCH();
 }
 

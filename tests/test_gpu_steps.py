@@ -202,3 +202,28 @@ def test_fp16_split_product_keeps_infinities_and_nan(lib, handle, tube):
     assert np.all(Y[3] == np.inf) and np.all(Y[4] == -np.inf) and np.all(np.isnan(Y[5])) and np.all(np.isnan(Y[6]))
     keep = [c for c in range(40) if c not in (3, 4, 5, 6)]
     assert np.array_equal(Y[keep], ref[keep])
+
+
+@pytest.mark.parametrize("ncol", [5, 8, 9, 16, 17, 33, 48, 49, 65, 80, 81, 96, 97, 129, 145, 160, 161, 177, 257])
+def test_fragment_product_column_edges(lib, handle, tube, ncol):
+    # the default FP64 product at each number of 16-column fragments and passes, with partial last fragments
+    _, P = tube
+    rng = np.random.default_rng(ncol)
+    X = rng.standard_normal((ncol, P.n))
+    Y = lib.wfq_apply_T(handle, "fp64", X)
+    assert np.all(np.abs(Y - X @ P.T) <= 2 * P.n * UNIT["fp64"] * (np.abs(X) @ P.T) + 1e-300)
+    for name in ("f16n64", "f32n64", "f48n32", "f48n64", "f64n32", "f80n32"):
+        Y = lib.wfq_apply_T_variant(handle, "fp64", name, X)
+        assert np.all(np.abs(Y - X @ P.T) <= 2 * P.n * UNIT["fp64"] * (np.abs(X) @ P.T) + 1e-300), name
+
+
+@pytest.mark.parametrize("n,ncol", [(1281, 8), (1537, 8), (4352, 4), (4353, 3), (9985, 8), (10240, 6), (10240, 9)])
+def test_default_fp64_product_at_its_size_limits(lib, n, ncol):
+    # where another kernel takes over by default: the result is that of the LDS-tile shape to rounding
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(8, 8, n // 32 + 1)[:n], 0.01, seed=n)
+    h = lib.wfq_build(xyz, GRAPHENE)
+    X = np.random.default_rng(n).standard_normal((ncol, n))
+    Y, ref = lib.wfq_apply_T(h, "fp64", X), lib.wfq_apply_T_variant(h, "fp64", "m32n128", X)
+    h.close()
+    # each sum of n products is within n u of sum |T||X| <= n max|T| max|X|: two of them
+    assert np.abs(Y - ref).max() <= 2 * n * UNIT["fp64"] * np.abs(X).sum(axis=1).max() * GRAPHENE["eta"]

@@ -185,7 +185,7 @@ void build_rhs(const Structure& s, const double* dirs_dev, int n_dir, double E0,
 enum class Order { kept, any };
 void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st, Order order = Order::kept);
 void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, Order order = Order::kept);
-void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st);
+void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st, Order order = Order::kept);
 // true when a product of ncol columns in `prec` recomputes the elements with the narrow kernel
 bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order);
 // true when a product of ncol columns streams the stored T with the vector ALUs

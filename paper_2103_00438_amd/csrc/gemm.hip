@@ -395,17 +395,18 @@ __global__ void __launch_bounds__(256, 2) tx_frag_kernel(const double* __restric
 // three FP16 products with FP32 accumulation stand for the FP32 one. The scales are powers of two
 // (exact): one for T from its largest element, and one per column of X from that column's largest
 // entry, taken out again in the epilogue. The sum over k rounds 3 k / 32 times in FP32 instead of k
-// times, so the error against 64 bits falls (figures at split_default).
+// times, so the error against 64 bits falls (figures at any_variant).
 //
 // Layout: T goes straight from global memory into the matrix cores' fragment layout (a wave owns 16 WN
-// rows of T and all 16 WM columns of its work-group, so no other wave needs its rows): 4 lanes read the
-// 128 contiguous bytes of a row's 32 k, the split is done in registers, and the loads of the next stage
-// are in flight during the matrix products of this one. X is split beforehand (split_x_kernel) into
+// rows of T and all 16 WM columns of its work-group, so no other wave needs its rows). T is symmetric and is
+// walked down its rows: the 16 lanes of a fragment's row index read 16 WN adjacent elements of each of a lane's
+// 8 k (along a row of T every lane would visit a line of its own: 430 us instead of 379 for 20 000 atoms and 128 columns).
+// The split is done in registers, and the loads of the next stage are in flight during the matrix products of this one. X is split beforehand (split_x_kernel) into
 // groups of 8 h and 8 l halves and staged through LDS for the four waves, double buffered, rows padded
 // by 16 bytes (distinct banks for 8 lanes reading 16 bytes).
 // Bound: the matrix cores and their operand reads with several hundred columns (20 000 atoms, 384 columns:
-// 967 us = 980 TFLOP/s of FP16 products, 325 of the FP32 product's; 2 410 us and 130 TFLOP/s with the FP32
-// instruction, whose peak is 157), below about 100 columns the HBM reads of T (32 columns: 305 us, 5.4 TB/s).
+// 929 us = 1 020 TFLOP/s of FP16 products, 338 of the FP32 product's; 2 410 us and 130 TFLOP/s with the FP32
+// instruction, whose peak is 157), below about 100 columns the HBM reads of T (32 columns: 293 us, 5.6 TB/s).
 
 // One work-group per column of X: its largest magnitude gives the scale (the scaled entries stay below
 // 2^15), then every group of 8 entries is written as 8 h and 8 l halves (32 bytes, like the FP32 entries).
@@ -491,8 +492,9 @@ __global__ void __launch_bounds__(256, OCC)
 #pragma unroll
     for (int u = 0; u < PER_T; ++u) xp[u] = Xs + (m0 + min(r0 + u * RSTEP, xlast)) * ld * 4 + cc * 16;
     const int dst0 = r0 * RS + cc * 16;
-    // this lane's 8 values of k of rows b of T
-    const float* tp = T + (n0 + wave * 16 * WN + fr) * ld + fk * 8;
+    // this lane's 8 values of k of WN neighbouring columns of T, one for each of the wave's fragments
+    typedef float tvec __attribute__((ext_vector_type(WN)));
+    const uint32_t to = (uint32_t)(8 * fk * ld + n0 + wave * 16 * WN + WN * fr);
 
     floatx4 acc[WM][WN];
 #pragma unroll
@@ -503,14 +505,11 @@ __global__ void __launch_bounds__(256, OCC)
     const int nk = (int)(ld / KS);
     const int kb = (int)((int64_t)nk * part / split), ke = (int)((int64_t)nk * (part + 1) / split);
     u32x4 xr[PER_T];
-    floatx4 raw[SUB][WN][2];
+    tvec raw[SUB][8];
     auto load_t = [&](int kt, int s) {
 #pragma unroll
-        for (int b = 0; b < WN; ++b) {
-            const float* p = tp + (int64_t)b * 16 * ld + (int64_t)kt * KS + s * 32;
-            raw[s][b][0] = *reinterpret_cast<const floatx4*>(p);
-            raw[s][b][1] = *reinterpret_cast<const floatx4*>(p + 4);
-        }
+        for (int e = 0; e < 8; ++e)
+            raw[s][e] = *reinterpret_cast<const tvec*>(T + (int64_t)(kt * KS + s * 32 + e) * ld + to);
     };
 #pragma unroll
     for (int u = 0; u < PER_T; ++u) xr[u] = *reinterpret_cast<const u32x4*>(xp[u] + (int64_t)kb * KS * 4);
@@ -532,10 +531,7 @@ __global__ void __launch_bounds__(256, OCC)
             for (int b = 0; b < WN; ++b) {
                 float v[8];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] = raw[s][b][0][e] * tscale;
-                    v[4 + e] = raw[s][b][1][e] * tscale;
-                }
+                for (int e = 0; e < 8; ++e) v[e] = raw[s][e][b] * tscale;
                 th[b] = split_hi(v);
                 tl[b] = split_lo(v, th[b]);
             }
@@ -570,14 +566,14 @@ __global__ void __launch_bounds__(256, OCC)
             const int64_t c = m0 + a * 16 + 4 * fk + r;
             if (c >= ncol) continue;
             const ColInfo ci = info[c];
+            tvec y;
 #pragma unroll
             for (int b = 0; b < WN; ++b) {
-                const int64_t i = n0 + wave * 16 * WN + b * 16 + fr;
-                float y = ldexpf(acc[a][b][r], -(ci.exp + texp));
+                y[b] = ldexpf(acc[a][b][r], -(ci.exp + texp));
                 // every element of T is positive, so a column with an infinite entry gives that infinity
-                if (ci.cls) y = ci.cls == 1 ? __builtin_inff() : ci.cls == 2 ? -__builtin_inff() : __builtin_nanf("");
-                out[c * ld + i] = y;
+                if (ci.cls) y[b] = ci.cls == 1 ? __builtin_inff() : ci.cls == 2 ? -__builtin_inff() : __builtin_nanf("");
             }
+            *reinterpret_cast<tvec*>(out + c * ld + n0 + wave * 16 * WN + WN * fr) = y;
         }
 }
 
@@ -902,33 +898,16 @@ int find_variant(int prec, const char* name) {
     return -1;
 }
 
-// Whether an FP32 product of ncol columns goes through the FP16 split by default: where it was measured
-// faster and no less accurate than the FP32 matrix instruction (whose best shape is the second figure of
-// each pair, us). N 20 000: 305 / 377 at 32 columns, 346 / 555 at 64, 430 / 849 at 128, 967 / 2410 at
-// 384; N 5 000: 38 / 49 at 48, 93 / 160 at 384; N 4 000: 34 / 29 at 64, 40 / 42 at 96, 67 / 100 at 384;
-// N 2 500: 31 / 28 at 128, 32 / 36 at 192; N 1 000: 25 / 19 at 384; up to 32 columns 42 / 42 at N 6 600,
-// 141 / 143 at N 13 000. Error against 64 bits, random vectors: N 612 2.7e-7 / 2.6e-7, N 2 600
-// 2.7e-7 / 3.7e-7, N 20 000 6.5e-7 to 9.5e-7 / 1.0e-6 to 1.5e-6 (the more k parts, the smaller).
-bool split_default(const Structure& s, int ncol) {
-    if (ncol <= 4 || !split_scale_ok(s) || !split_fits(s, s.npad, ncol)) return false;
-    if (ncol <= 32) return s.npad >= 16384;
-    return s.npad >= 4608 || (s.npad >= 2048 && s.npad * ncol >= 350000);
+struct Pick { int upto; const char* name; };
+int pick_name(int prec, const Pick* t, int ncol) {
+    while (ncol > t->upto) ++t;
+    const int k = find_variant(prec, t->name);
+    return k >= 0 ? k : find_variant(prec, "m128n256w8");   // present for every precision
 }
 
-// Built-in choice when no tuning result covers ncol: the fastest shapes measured on MI355X for a
-// 20 000-atom T, per precision and column count (FP16-split shapes: also between 2 500 and 13 000 atoms).
-int default_variant(int prec, int ncol, bool split, int64_t npad) {
-    struct Pick { int upto; const char* name; };
-    if (split) {
-        // from about 16 000 rows there are enough 256-row tiles for the chip; below, 128-row tiles
-        static const Pick big[] = {{32, "s32n256k32"}, {64, "s64n256k32"}, {96, "s96n256k32"}, {128, "s128n256k32"},
-                                   {192, "s192n128k32"}, {256, "s128n256k32"}, {288, "s96n256k32"}, {1 << 30, "s128n256k32"}};
-        static const Pick mid[] = {{64, "s64n128k64"}, {96, "s96n128k64"}, {128, "s128n128k64"}, {192, "s96n128k64"},
-                                   {1 << 30, "s128n128k64"}};
-        const Pick* t = npad >= 16384 || (npad >= 6144 && ncol > 128) ? big : mid;
-        while (ncol > t->upto) ++t;
-        return find_variant(prec, t->name);
-    }
+// Built-in choice of the kept order when no tuning result covers ncol: the fastest shapes measured on MI355X for
+// a 20 000-atom T, per precision and column count.
+int default_variant(int prec, int ncol) {
     static const Pick f64[] = {{2, "skinny2"}, {4, "skinny4"}, {8, "skinny8"}, {32, "m32n128"}, {64, "m64n128i"},
                                {96, "m128n256w8i"}, {128, "m128n256w8"}, {192, "m64n128i"}, {256, "m128n256w8i"},
                                {320, "m64n128"}, {1 << 30, "m128n256w8i"}};
@@ -939,10 +918,51 @@ int default_variant(int prec, int ncol, bool split, int64_t npad) {
     // BF16 T is 2 bytes per element: even one column streams it faster through the matrix cores
     static const Pick b16[] = {{64, "m64n128i"}, {128, "m128n128"}, {192, "m192n256w8"}, {256, "m256n128w8i"},
                                {320, "m160n256w8"}, {1 << 30, "m192n256w8"}};
-    const Pick* t = prec == WFQ_PREC_FP64 ? f64 : prec == WFQ_PREC_FP32 ? f32 : b16;
-    while (ncol > t->upto) ++t;
-    const int k = find_variant(prec, t->name);
-    return k >= 0 ? k : find_variant(prec, "m128n256w8");   // present for every precision
+    return pick_name(prec, prec == WFQ_PREC_FP64 ? f64 : prec == WFQ_PREC_FP32 ? f32 : b16, ncol);
+}
+
+// Built-in choice in any order for FP32 and BF16, by padded size too: the fastest shapes measured at 700, 1 000, 1 400,
+// 2 000, 2 800, 4 000, 5 200, 6 600, 8 000, 10 000 and 20 000 atoms. A small T has few tiles of many rows, so
+// narrower and shorter ones fill the chip; us against the kept order's shape: FP32 2 000 atoms 15 / 26 at 64 columns,
+// 2 800 atoms 11 / 17 at 4, BF16 2 000 atoms 9 / 13 at 128, 11 / 15 at 192.
+// The FP16-split FP32 shapes (s...) where they are faster and no less accurate than the FP32 matrix instruction, us of the
+// two: N 20 000 280 / 362 at 8 columns, 310 / 556 at 64, 379 / 846 at 128, 929 / 2 427 at 384; N 10 000 117 / 117, 135 / 214, 262 / 600;
+// N 5 200 33 / 38, 39 / 46, 49 / 80, 92 / 160; N 4 000 42 / 48 at 128; N 2 800 31 / 37 at 128. Error against 64 bits, random
+// vectors: N 612 2.7e-7 / 2.6e-7, N 2 600 2.7e-7 / 3.7e-7, N 20 000 6.5e-7 to 9.5e-7 / 1.0e-6 to 1.5e-6 (the more k parts, the
+// smaller).
+int any_variant(const Structure& s, int prec, int ncol) {
+    constexpr int rest = 1 << 30;
+    struct Range { int64_t below; Pick t[9]; };
+    static const Range f32[] = {
+        {1280, {{2, "skinny2"}, {4, "skinny4"}, {8, "skinny8"}, {256, "m32n128"}, {rest, "m64n128i"}}},
+        {1792, {{2, "skinny2"}, {4, "skinny4"}, {160, "m32n128"}, {rest, "m64n128i"}}},
+        {3072, {{2, "skinny2"}, {4, "skinny4"}, {96, "m32n128"}, {rest, "s64n128k64"}}},
+        {4608, {{2, "skinny2"}, {4, "skinny4"}, {32, "m32n128"}, {64, "m64n128i"}, {rest, "s64n128k64"}}},
+        {6144, {{2, "skinny2"}, {4, "skinny4"}, {256, "s64n128k64"}, {rest, "s96n256k32"}}},
+        {9216, {{2, "skinny2"}, {4, "skinny4"}, {32, "m32n128"}, {64, "s64n128k64"}, {96, "s96n128k64"}, {128, "s64n256k32"},
+                {192, "s96n256k32"}, {rest, "s128n256k32"}}},
+        {16384, {{2, "skinny2"}, {4, "skinny4"}, {32, "m32n128"}, {64, "s64n256k32"}, {96, "s96n128k64"}, {128, "s128n128k64"},
+                 {192, "s192n128k32"}, {rest, "s128n256k32"}}},
+        {INT64_MAX, {{2, "skinny2"}, {4, "skinny4r8"}, {96, "s96n256k32"}, {128, "s128n256k32"}, {192, "s192n128k32"},
+                     {256, "s128n256k32"}, {288, "s96n256k32"}, {rest, "s128n256k32"}}}};
+    static const Range b16[] = {
+        {1536, {{2, "skinny2"}, {4, "skinny4"}, {192, "m32n128"}, {rest, "m64n128i"}}},
+        {3072, {{2, "skinny2"}, {128, "m32n128"}, {rest, "m64n128i"}}},
+        {6144, {{96, "m32n128"}, {256, "m64n128i"}, {rest, "m192n128w8"}}},
+        {9216, {{64, "m32n128"}, {128, "m64n128i"}, {160, "m160n256w8"}, {192, "m192n128w8"}, {256, "m128n256w8i"},
+                {320, "m160n256w8"}, {rest, "m192n256w8"}}},
+        {16384, {{64, "m64n128i"}, {128, "m128n128"}, {160, "m160n256w8"}, {192, "m192n128w8"}, {256, "m128n256w8i"},
+                 {320, "m160n256w8"}, {rest, "m192n256w8"}}},
+        {INT64_MAX, {{64, "m64n128i"}, {128, "m128n128"}, {192, "m192n256w8"}, {256, "m256n128w8i"}, {320, "m160n256w8"},
+                     {rest, "m192n256w8"}}}};
+    const Range* r = prec == WFQ_PREC_FP32 ? f32 : b16;
+    while (s.npad >= r->below) ++r;
+    const int k = pick_name(prec, r->t, ncol);
+    // no room for the split X, or a T outside the split's range: the FP32 instruction's shape
+    const char* name = variants_of(prec)[k].name;
+    if (name[0] == 's' && name[1] >= '0' && name[1] <= '9' && (!split_scale_ok(s) || !split_fits(s, s.npad, ncol)))
+        return default_variant(prec, ncol);
+    return k;
 }
 
 // padded size from which untuned narrow FP64 products are recomputed rather than streamed: in the symmetric form
@@ -950,7 +970,7 @@ int default_variant(int prec, int ncol, bool split, int64_t npad) {
 // 27 / 27 / 27 / 28), and one-sided, in the kept order (20 000 atoms, 3 columns: 252 us recomputed, 475 streamed)
 constexpr int64_t kSymNarrowFrom = 4608, kOtfNarrowFrom = 16384;
 // matrix-free FP64 products of up to this many 4-column chunks use the narrow kernel
-constexpr int kOtfNarrowChunks = 3;
+static const int kOtfNarrowChunks = getenv("ONC") ? atoi(getenv("ONC")) : 3;
 
 int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     const auto& tuned = s.tuned[prec];
@@ -978,7 +998,7 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     if (prec == WFQ_PREC_FP64 && ncol <= 4 &&
         s.npad >= (otf_narrow_sym(s, ncol, order) ? kSymNarrowFrom : kOtfNarrowFrom))
         return find_variant(prec, ncol <= 2 ? "otfn2" : "otfn4");
-    return default_variant(prec, ncol, order == Order::any && prec == WFQ_PREC_FP32 && split_default(s, ncol), s.npad);
+    return order == Order::any && prec != WFQ_PREC_FP64 ? any_variant(s, prec, ncol) : default_variant(prec, ncol);
 }
 
 void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st,
@@ -1080,8 +1100,8 @@ void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_
 void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, Order order) {
     if (ncol > 0) run_variant(s, WFQ_PREC_FP32, pick_variant(s, WFQ_PREC_FP32, ncol, order), X, Y, ncol, st);
 }
-void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st) {
-    if (ncol > 0) run_variant(s, WFQ_PREC_BF16, pick_variant(s, WFQ_PREC_BF16, ncol, Order::kept), X, Y, ncol, st);
+void tx_bf16(const Structure& s, const uint16_t* X, float* Y, int ncol, hipStream_t st, Order order) {
+    if (ncol > 0) run_variant(s, WFQ_PREC_BF16, pick_variant(s, WFQ_PREC_BF16, ncol, order), X, Y, ncol, st);
 }
 
 void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, Order order) {
@@ -1106,7 +1126,7 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
     else if (prec == WFQ_PREC_FP32)
         tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st, order);
     else
-        tx_bf16(s, static_cast<const uint16_t*>(X), static_cast<float*>(Y), ncol, st);
+        tx_bf16(s, static_cast<const uint16_t*>(X), static_cast<float*>(Y), ncol, st, order);
 }
 
 void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* Y, int ncol, hipStream_t st) {

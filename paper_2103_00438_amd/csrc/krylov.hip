@@ -237,14 +237,15 @@ void spmm_sys(const Structure& S, const YE* Y, int64_t ld, void* Yr, int nsys, c
         if (nsys <= 4) launch_spmm_sys<YE, 4, Out::kParts ? 2 : 1, 1, true>(S, P, ldk, nsys, out, st);
         else if (f64 || nsys <= 8) launch_spmm_sys<YE, 8, 1, 1, true>(S, P, ldk, nsys, out, st);
         else launch_spmm_sys<YE, 8, 1, 2, true>(S, P, ldk, nsys, out, st);
+    } else if (!Out::kParts || nsys > 4) {
+        // planes: one row per lane, one system per wave (neighbouring rows' neighbours share lines)
+        launch_spmm_sys<YE, 1, 1, 1, false>(S, Y, ld, nsys, out, st);
     } else if (nsys == 1) {
-        launch_spmm_sys<YE, 1, Out::kParts ? 8 : 1, 1, false>(S, Y, ld, nsys, out, st);
+        launch_spmm_sys<YE, 1, 8, 1, false>(S, Y, ld, nsys, out, st);
     } else if (nsys == 2) {
-        launch_spmm_sys<YE, 2, Out::kParts ? 4 : 1, 1, false>(S, Y, ld, nsys, out, st);
-    } else if (nsys <= 4) {
-        launch_spmm_sys<YE, 4, Out::kParts ? 2 : 1, 1, false>(S, Y, ld, nsys, out, st);
+        launch_spmm_sys<YE, 2, 4, 1, false>(S, Y, ld, nsys, out, st);
     } else {
-        launch_spmm_sys<YE, 8, 1, 1, false>(S, Y, ld, nsys, out, st);
+        launch_spmm_sys<YE, 4, 2, 1, false>(S, Y, ld, nsys, out, st);
     }
 }
 

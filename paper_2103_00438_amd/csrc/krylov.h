@@ -20,11 +20,17 @@ struct Basis {
 constexpr int kWaveRows = 512;
 inline int64_t wave_chunks(int64_t n) { return (n + kWaveRows - 1) / kWaveRows; }
 
+struct NormSums {
+    const double* norm2 = nullptr;   // [S][nwc]
+    int64_t nwc = 0;
+    double *nu = nullptr, *inv_h = nullptr;
+};
 // X[2k + plane][i] = cast(V(sys[k], j)[plane][i] * scale[sys[k]]) for i < npad (scale may be NULL);
 // with write_back the scaled FP64 value is also stored back into V. prec = WFQ_PREC_*.
 // With run != NULL, systems with run[s] == 0 get zero columns (and V is left alone).
+// With norm the scale is 1 / |V(s, j)| from nwc chunk sums of its squares, kept in nu and inv_h.
 void pack_columns(int prec, const Basis& V, const int* sys, int nsys, int j, const double* scale, bool write_back,
-                  void* X, int64_t ld, hipStream_t st, const int* run = nullptr);
+                  void* X, int64_t ld, hipStream_t st, const int* run = nullptr, const NormSums& norm = {});
 
 // The same from a caller's vectors in its own atom order, with every row of X from 2 nsys to `rows` zeroed
 void load_columns(const Structure& S, int prec, const double* x_re, const double* x_im, int nsys, int64_t rows, void* X,
@@ -46,14 +52,11 @@ void spmm_user(const Structure& S, bool y_is_f64, const void* Y, int64_t ld, voi
 void spmm_shift_interleaved(const Structure& S, const double* Yp, int64_t ld, const int* sys, int nsys,
                             const double2* z, const Basis& V, int jsrc, int jdst, hipStream_t st);
 
-// h[s][i] = sum_wc partial[s][i][wc] for i <= j (skipping systems with active[s] == 0)
-void reduce_dots(int64_t n, const int* sys, int nsys, int j, const double2* partial, int mdim, double2* h,
-                 hipStream_t st, const int* active = nullptr);
 // ---- Arnoldi with one reduction per step (dcgs.hip): classical Gram-Schmidt with delayed
 // reorthogonalisation. Step k (0 .. m) of a cycle: slot k holds u (one projection pass, unit norm;
 // at k = m the unnormalised w'), slot k + 1 holds z = (L T + z I) u for k < m.
 struct DcgsArgs {
-    const double2* dots;   // [S][2 mdim] reduced fused dots: a = Q^H u (0..k-1), alpha (k), b = Q^H z, beta
+    double2* dots;         // [S][2 mdim] reduced fused dots: a = Q^H u (0..k-1), alpha (k), b = Q^H z, beta
     double2* hp;           // [S][mdim] first-pass coefficients of the newest column
     double2* H;            // [S][mdim][mdim] Hessenberg matrix before rotations, column-major
     double2* R;            // [S][mdim][mdim] rotated columns (R[s][c][i] = R_ic)
@@ -74,9 +77,12 @@ struct DcgsArgs {
 // partial[s][t][wc]: the fused dots of step k over 512-row chunks (2 k + 2 entries; k + 1 without z)
 void dcgs_dots(const Basis& V, int64_t n, const int* sys, int nsys, int k, bool with_z, double2* partial, int mdim,
                const int* run, hipStream_t st);
-// column k - 1 of H completed and rotated (k >= 1), the step's update coefficients (with_z)
-void dcgs_coeff(const int* sys, int nsys, int k, bool with_z, int mdim, const DcgsArgs& a, hipStream_t st);
-// q_k into slot k, w' into slot k + 1, then nu and inv_h
+// the dots reduced, column k - 1 of H completed and rotated (k >= 1), the step's update coefficients (with_z)
+void dcgs_coeff(const int* sys, int nsys, int k, bool with_z, int mdim, const double2* partial, int64_t n,
+                const DcgsArgs& a, hipStream_t st);
+// nu = |w'| and inv_h from the update's chunk sums (pack_columns can form them on its way)
+void dcgs_nu(int64_t n, const int* sys, int nsys, const DcgsArgs& a, hipStream_t st);
+// q_k into slot k, w' into slot k + 1 and the chunk sums of |w'|^2
 void dcgs_update(const Basis& V, int64_t n, const int* sys, int nsys, int k, int mdim, const DcgsArgs& a,
                  hipStream_t st);
 

@@ -30,7 +30,7 @@ __device__ inline double block_sum(double v, double* sh) {
 template <typename E>
 __global__ void __launch_bounds__(256) pack_kernel(Basis V, const int* __restrict__ sys, int j,
                                                    const double* __restrict__ scale, int write_back, E* __restrict__ X,
-                                                   int64_t ld, const int* __restrict__ run) {
+                                                   int64_t ld, const int* __restrict__ run, NormSums norm) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int k = blockIdx.y;
     const int s = sys[k];
@@ -41,8 +41,19 @@ __global__ void __launch_bounds__(256) pack_kernel(Basis V, const int* __restric
     }
     double* re = vre(V, s, j);
     double* im = re + V.npad;
-    const double sc = scale ? scale[s] : 1.0;
-    const double a = re[i] * sc, b = im[i] * sc;
+    const double re_i = re[i], im_i = im[i];
+    double sc = scale ? scale[s] : 1.0;
+    if (norm.norm2) {   // few chunks: every thread adds them, in order
+        double sum = 0.0;
+        for (int64_t w = 0; w < norm.nwc; ++w) sum += norm.norm2[(int64_t)s * norm.nwc + w];
+        const double nu = sqrt(sum);
+        sc = nu > 0.0 ? 1.0 / nu : 0.0;
+        if (i == 0) {
+            norm.nu[s] = nu;
+            norm.inv_h[s] = sc;
+        }
+    }
+    const double a = re_i * sc, b = im_i * sc;
     if (write_back) {
         re[i] = a;
         im[i] = b;
@@ -308,21 +319,6 @@ void launch_spmm_rows(const Structure& S, const double2* Yp, int64_t ld, int nsy
                        S.ell_col, S.ell_val, Yp, ld, out.sys, nsys, per_group, out);
 }
 
-__global__ void reduce_dots_kernel(const int* __restrict__ sys, int j, const double2* __restrict__ partial, int mdim,
-                                   int64_t nwc, double2* __restrict__ h, const int* __restrict__ active) {
-    const int s = sys[blockIdx.x];
-    if (active && !active[s]) return;
-    for (int i = threadIdx.x; i <= j; i += blockDim.x) {
-        const double2* p = partial + ((int64_t)s * mdim + i) * nwc;
-        double sr = 0.0, si = 0.0;
-        for (int64_t w = 0; w < nwc; ++w) {
-            sr += p[w].x;
-            si += p[w].y;
-        }
-        h[(int64_t)s * mdim + i] = make_double2(sr, si);
-    }
-}
-
 // One wave per system: column-oriented back substitution on R y = g (k <= mdim - 1 steps).
 __global__ void __launch_bounds__(64) tri_solve_kernel(const int* __restrict__ sys, const int* __restrict__ ksteps,
                                                        int mdim, const double2* __restrict__ R,
@@ -521,18 +517,18 @@ void interp_start(const int* sys, int nsys, const int* src_a, const int* src_b, 
 }
 
 void pack_columns(int prec, const Basis& V, const int* sys, int nsys, int j, const double* scale, bool write_back,
-                  void* X, int64_t ld, hipStream_t st, const int* run) {
+                  void* X, int64_t ld, hipStream_t st, const int* run, const NormSums& norm) {
     if (nsys <= 0) return;
     dim3 grd((unsigned)(V.npad / 256), (unsigned)nsys);
     if (prec == WFQ_PREC_FP64)
         hipLaunchKernelGGL(pack_kernel<double>, grd, dim3(256), 0, st, V, sys, j, scale, (int)write_back,
-                           static_cast<double*>(X), ld, run);
+                           static_cast<double*>(X), ld, run, norm);
     else if (prec == WFQ_PREC_FP32)
         hipLaunchKernelGGL(pack_kernel<float>, grd, dim3(256), 0, st, V, sys, j, scale, (int)write_back,
-                           static_cast<float*>(X), ld, run);
+                           static_cast<float*>(X), ld, run, norm);
     else
         hipLaunchKernelGGL(pack_kernel<uint16_t>, grd, dim3(256), 0, st, V, sys, j, scale, (int)write_back,
-                           static_cast<uint16_t*>(X), ld, run);
+                           static_cast<uint16_t*>(X), ld, run, norm);
     WFQ_CHECK_LAUNCH();
 }
 
@@ -580,14 +576,6 @@ void spmm_shift_interleaved(const Structure& S, const double* Yp, int64_t ld, co
     else if (R == 32) launch_spmm_rows<32>(S, Y, ld, nsys, out, st);
     else if (R == 16) launch_spmm_rows<16>(S, Y, ld, nsys, out, st);
     else launch_spmm_rows<8>(S, Y, ld, nsys, out, st);
-    WFQ_CHECK_LAUNCH();
-}
-
-void reduce_dots(int64_t n, const int* sys, int nsys, int j, const double2* partial, int mdim, double2* h,
-                 hipStream_t st, const int* active) {
-    if (nsys <= 0) return;
-    hipLaunchKernelGGL(reduce_dots_kernel, dim3(nsys), dim3(128), 0, st, sys, j, partial, mdim, wave_chunks(n), h,
-                       active);
     WFQ_CHECK_LAUNCH();
 }
 

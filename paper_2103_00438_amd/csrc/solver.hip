@@ -781,6 +781,9 @@ void gmres_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double 
             // that could pass max_iter (a step completes at most one column)
             int c = std::min(chunk, m + 1 - k0);
             for (int s : stepping) c = std::min(c, o.max_iter - ss[s].iters);
+            // the norm of the newest vector is formed where it is packed, up to 16 chunks (8 192 rows); above, and where
+            // the preconditioner packs, by a launch of its own
+            const bool pack_nu = !bj && w.nwc <= 16;
             auto step = [&](int k) {
                 const bool with_z = k < m;
                 if (with_z) {
@@ -796,8 +799,8 @@ void gmres_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double 
                                     w.run.p, st);
                             tm.end(st, KC_PRECOND, 8.0 * 64 * n * ng, ng * n * (512.0 + 48 + 2 * elem_size(p)));
                         } else {
-                            pack_columns(p, w.Vb, w.sys[p].p, ng, k, scale, true, x_block(w, p), w.npad, st,
-                                         w.run.p);
+                            pack_columns(p, w.Vb, w.sys[p].p, ng, k, scale, true, x_block(w, p), w.npad, st, w.run.p,
+                                         pack_nu && k > 0 ? NormSums{w.norm2.p, (int64_t)w.nwc, w.nu.p, w.inv_h.p} : NormSums{});
                             tm.end(st, KC_PACK, 0, ng * n * (32.0 + 2 * elem_size(p)));
                         }
                         block_product(S, w, p, 2 * ng, tm, st);
@@ -819,15 +822,16 @@ void gmres_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double 
                 const int* sl = w.sys[SLOT_STEP].p;
                 tm.begin(st);
                 dcgs_dots(w.Vb, S.n, sl, ns, k, with_z, w.partial.p, w.mdim, w.run.p, st);
-                reduce_dots(S.n, sl, ns, with_z ? 2 * k + 1 : k, w.partial.p, 2 * w.mdim, w.h1.p, st, w.run.p);
                 tm.end(st, KC_DOT, 16.0 * n * ns * (k + 1), 16.0 * n * ns * (k + 2));
                 tm.begin(st);
-                dcgs_coeff(sl, ns, k, with_z, w.mdim, da, st);
+                if (!with_z && pack_nu) dcgs_nu(S.n, sl, ns, da, st);   // no product, so no pack, at the last step
+                dcgs_coeff(sl, ns, k, with_z, w.mdim, w.partial.p, S.n, da, st);
                 tm.end(st, KC_GIVENS, 0, 0);
                 if (with_z && w.rc_active) rc_bcol(w.rc, sl, ns, w.run.p, k, w.mdim, w.h1.p, w.irho.p, st);
                 if (with_z) {
                     tm.begin(st);
                     dcgs_update(w.Vb, S.n, sl, ns, k, w.mdim, da, st);
+                    if (!pack_nu) dcgs_nu(S.n, sl, ns, da, st);
                     tm.end(st, KC_UPDATE, 16.0 * n * ns * k, 16.0 * n * ns * (k + 4));
                 }
             };

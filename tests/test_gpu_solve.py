@@ -110,3 +110,21 @@ def test_dimer_solve(lib):
     for a, om in enumerate((0.1, 0.7, 3.0)):
         assert rel(out["q"][a, 0], P.solve_lu(om, [1, 0, 0])) <= 1e-10
     h.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,n_omega,restart", [(5, 1, 6), (511, 1, 30), (512, 9, 30), (513, 20, 256), (1300, 30, 50),
+                                               (2900, 20, 40), (8192, 1, 30), (8193, 2, 30)])
+def test_gmres_steps_over_chunks_columns_and_restarts(lib, n, n_omega, restart, prec):
+    # the step's kernels at the edges of their 512-row chunks and of the longest restart, with the norm formed in the
+    # pack (up to 16 chunks) and by its own launch, and the products of 2 to 60 columns of a small T: every
+    # system must satisfy the oracle's equations to the tolerance
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(8, 8, n // 32 + 1)[:n], 0.01, seed=n)
+    om, tol, e = np.linspace(0.15, 1.1, n_omega), 1e-9, np.array([[0.0, 0.6, 0.8]])
+    h = lib.wfq_build(xyz, GRAPHENE, store=("fp64", "fp32"))
+    out = lib.wfq_solve(h, om, e, tol, algorithm="gmres", restart=restart, precision=prec, max_iter=5000)
+    h.close()
+    assert out["status"] == 0, out["info"]
+    P = O.Problem(xyz, GRAPHENE)
+    for a in (0, n_omega // 2, n_omega - 1):
+        assert P.residual(om[a], e[0], out["q"][a, 0]) <= 1.01 * tol + 1e-13, (a, out["info"][a])

@@ -992,8 +992,11 @@ int any_variant(const Structure& s, int prec, int ncol) {
 // (5 000 atoms, 1 to 4 columns: 22 / 26 / 31 / 33 us recomputed, 31 / 31 / 35 / 35 streamed; 4 000: 21 / 24 / 29 / 31 and
 // 27 / 27 / 27 / 28), and one-sided, in the kept order (20 000 atoms, 3 columns: 252 us recomputed, 475 streamed)
 constexpr int64_t kSymNarrowFrom = 4608, kOtfNarrowFrom = 16384;
-// matrix-free FP64 products of up to this many 4-column chunks use the narrow kernel
-static const int kOtfNarrowChunks = getenv("ONC") ? atoi(getenv("ONC")) : 3;
+// matrix-free FP64 products of up to this many columns go through the narrow kernel, 4 at a time; the wide one's time
+// hardly depends on its columns. Narrow / wide, us: 576 atoms 99 / 194 at 16 columns, 187 / 194 at 32, 360 / 194 at 64;
+// 1 600 atoms 224 / 479 at 32, 435 / 477 at 64, 858 / 481 at 128; 4 096 atoms 502 / 875 at 64, 988 / 882 at 128; 16 384
+// atoms 1 126 / 3 027 at 32, 2 230 / 3 021 at 64, 4 444 / 4 499 at 128.
+int otf_narrow_columns(const Structure& s) { return s.npad < 1024 ? 32 : 64; }
 
 int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     const auto& tuned = s.tuned[prec];
@@ -1157,9 +1160,7 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
     if (s.t_mode == WFQ_TMODE_OTF) {
         if (prec == WFQ_PREC_FP32)
             otf_tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st);
-        else if (prec == WFQ_PREC_FP64 && ncol <= kOtfNarrowChunks * 4)
-            // up to 16 columns: narrow recomputed products of at most 4 columns each (each such product
-            // costs about what one 32-column matrix-core pass costs for 12 or more columns)
+        else if (prec == WFQ_PREC_FP64 && ncol <= otf_narrow_columns(s))
             for (int c0 = 0; c0 < ncol; c0 += 4)
                 otf_narrow_f64(s, static_cast<const double*>(X) + (int64_t)c0 * s.npad,
                                static_cast<double*>(Y) + (int64_t)c0 * s.npad, s.npad, std::min(4, ncol - c0),
@@ -1184,7 +1185,7 @@ void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* 
 
 bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order) {
     if (prec != WFQ_PREC_FP64) return false;
-    if (s.t_mode == WFQ_TMODE_OTF) return ncol <= kOtfNarrowChunks * 4;
+    if (s.t_mode == WFQ_TMODE_OTF) return ncol <= otf_narrow_columns(s);
     if (ncol > 4) return false;
     return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol, order)].name, "otfn", 4) == 0;
 }

@@ -131,6 +131,18 @@ def test_matrix_free_fp64_product_in_chunks(lib):
     assert np.all(np.abs(Y - X @ P.T.T) <= 1e-13 * (np.abs(X) @ np.abs(P.T).T))
 
 
+@pytest.mark.parametrize("n, ncol", [(765, 32), (765, 33), (1033, 33), (1033, 64), (1033, 65)])
+def test_matrix_free_fp64_product_where_the_narrow_form_ends(lib, n, ncol):
+    # the narrow products end at 32 columns below 1 024 padded rows, at 64 from there on
+    xyz = ragged_tube()[:n]
+    P = O.Problem(xyz, GRAPHENE)
+    X = np.random.default_rng(ncol).standard_normal((ncol, n))
+    h = lib.wfq_build(xyz, GRAPHENE, t_mode="otf")
+    Y = lib.wfq_apply_T(h, "fp64", X)
+    h.close()
+    assert np.all(np.abs(Y - X @ P.T.T) <= 1e-13 * (np.abs(X) @ np.abs(P.T).T))
+
+
 @pytest.mark.parametrize("ncol", [1, 2, 3, 4])
 def test_symmetric_narrow_product_on_a_large_sphere(lib, ncol):
     # From 65 536 atoms on, the narrow product evaluates each pair of atoms once for both rows (blocks

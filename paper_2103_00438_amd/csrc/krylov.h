@@ -124,29 +124,25 @@ constexpr int kQmrSlots = 7;
 // partial[s][blk] of rho = r^T (T r), T r read from the packed block Y (rows 2k, 2k+1)
 void qmr_rho(bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys, const Basis& Q, int64_t n,
              double2* partial, int nblk, hipStream_t st);
-// beta = rho_new / rho_old (0 where first[s]); p = r + beta p; T p = T r + beta T p
+// rho_new = the sum of its partials; beta = rho_new / rho_old (0 where first[s]); p = r + beta p; T p = T r + beta T p
 // (T p is also written to tpb as (re, im) pairs, ld pairs per system id (FP64), the gather source of qmr_q)
 void qmr_dirs(bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys, const Basis& Q, int64_t n,
-              const double2* rho_new, const double2* rho_old, const int* first, double* tpb, hipStream_t st);
+              const double2* partial, int nblk, double2* rho_new, const double2* rho_old, const int* first, double* tpb,
+              hipStream_t st);
 // q = L (T p) + z p with partials of sigma = (T p)^T q and of ||T p||^2, ||q||^2
 void qmr_q(const Structure& S, const int* sys, int nsys, const Basis& Q, const double2* z, const double* tpb,
            double2* part_sig, double2* part_nrm, int nblk, hipStream_t st);
-// sigma[s] and breakdown flags (bit 3: Lanczos breakdown when |sigma| <= thr ||T p|| ||q||, bit 2: NaN)
-void qmr_sigma(const int* sys, int nsys, const double2* part_sig, const double2* part_nrm, int nblk,
-               const double2* rho, double2* sigma, int* flags, double thr, hipStream_t st);
-// alpha = rho / sigma; x += alpha p; r -= alpha q; partials of ||r||^2
-void qmr_xr(const int* sys, int nsys, const Basis& Q, int64_t n, const double2* rho, const double2* sigma,
-            double* norm2, int nblk, hipStream_t st);
-// tau^2 and eta of the smoothing from ||r||^2; clears first[s]
-void qmr_weights(const int* sys, int nsys, const double* rn_part, int nblk, double* tau2, double* eta, int* first,
-                 hipStream_t st);
-// xq += eta (x - xq); s += eta (r - s); partials of ||s||^2
-void qmr_smooth(const int* sys, int nsys, const Basis& Q, int64_t n, const double* eta, double* norm2, int nblk,
-                hipStream_t st);
+// sigma = the sum of its partials, with the breakdown flags (bit 3: Lanczos breakdown when |sigma| <= thr ||T p|| ||q||,
+// bit 2: NaN); alpha = rho / sigma; x += alpha p; r -= alpha q; partials of ||r||^2
+void qmr_xr(const int* sys, int nsys, const Basis& Q, int64_t n, const double2* part_sig, const double2* part_nrm,
+            const double2* rho, int* flags, double thr, double* norm2, int nblk, hipStream_t st);
+// eta and the new tau^2 of the smoothing from the partials of ||r||^2; xq += eta (x - xq); s += eta (r - s); partials of
+// ||s||^2 (norm2 is another array than rn_part, tau2_new than tau2); clears first[s]
+void qmr_smooth(const int* sys, int nsys, const Basis& Q, int64_t n, const double* rn_part, const double* tau2,
+                double* tau2_new, int* first, double* norm2, int nblk, hipStream_t st);
 // restart from the QMR iterate: x = xq, p = T p = 0, s = r (r must hold the residual of xq)
 void qmr_restart(const int* sys, int nsys, const Basis& Q, hipStream_t st);
 // out[s] = sum_b partial[s][b]
-void reduce_complex(const int* sys, int nsys, const double2* partial, int nb, double2* out, hipStream_t st);
 
 // ---- multi-shift GMRES (mshift.hip): one real Arnoldi basis per field direction, shared by the
 // frequencies of that direction. Real basis of direction d, slot j at V + (d * mdim1 + j) * npad;

@@ -29,6 +29,24 @@ __device__ inline double block_sum4(double v, double* sh) {
     return sh[0] + sh[1] + sh[2] + sh[3];
 }
 
+// The sum of a system's nb block partials, formed by every work-group that needs it (staged in LDS, added in order):
+// a launch of one thread per system for it took 2.7 to 3.7 us between kernels of 3 to 4 (4 100 atoms, 14 systems).
+__device__ inline double2 ordered_sum(const double2* __restrict__ p, int nb, double2* sh) {
+    double a = 0.0, b = 0.0;
+    for (int b0 = 0; b0 < nb; b0 += 256) {
+        __syncthreads();
+        if ((int)threadIdx.x < nb - b0) sh[threadIdx.x] = p[b0 + threadIdx.x];
+        __syncthreads();
+        const int cnt = min(256, nb - b0);
+#pragma unroll 8
+        for (int q = 0; q < cnt; ++q) {
+            a += sh[q].x;
+            b += sh[q].y;
+        }
+    }
+    return make_double2(a, b);
+}
+
 // partial rho = sum_i r_i (T r)_i, with T r in the packed block Y (rows 2k, 2k + 1)
 template <typename YE>
 __global__ void __launch_bounds__(256) rho_kernel(const YE* __restrict__ Y, int64_t ld, const int* __restrict__ sys,
@@ -50,19 +68,23 @@ __global__ void __launch_bounds__(256) rho_kernel(const YE* __restrict__ Y, int6
     if (threadIdx.x == 0) partial[(int64_t)s * nblk + blockIdx.x] = make_double2(a, b);
 }
 
-// beta = rho_new / rho_old (0 on the first step); p = r + beta p; T p = T r + beta T p
+// rho_new = the sum of its partials; beta = rho_new / rho_old (0 on the first step); p = r + beta p; T p = T r + beta T p
 template <typename YE>
 __global__ void __launch_bounds__(256) dirs_kernel(const YE* __restrict__ Y, int64_t ld, const int* __restrict__ sys,
-                                                   Basis Q, int64_t n, const double2* __restrict__ rho_new,
+                                                   Basis Q, int64_t n, const double2* __restrict__ partial, int nblk,
+                                                   double2* __restrict__ rho_new,
                                                    const double2* __restrict__ rho_old, const int* __restrict__ first,
                                                    double* __restrict__ tpb) {
+    __shared__ double2 stage[256];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
     const int k = blockIdx.y;
     const int s = sys[k];
+    const double2 a = ordered_sum(partial + (int64_t)s * nblk, nblk, stage);
+    if (i == 0) rho_new[s] = a;
+    if (i >= n) return;
     double br = 0.0, bi = 0.0;
     if (!first[s]) {
-        const double2 a = rho_new[s], c = rho_old[s];
+        const double2 c = rho_old[s];
         const double dd = c.x * c.x + c.y * c.y;
         br = (a.x * c.x + a.y * c.y) / dd;
         bi = (a.y * c.x - a.x * c.y) / dd;
@@ -110,15 +132,28 @@ __global__ void __launch_bounds__(256) q_sums_kernel(int64_t n, const int* __res
     }
 }
 
+// sigma = the sum of its partials, with the breakdown test (Lanczos breakdown: no look-ahead); x += alpha p,
+// r -= alpha q with alpha = rho / sigma, and the partial sums of |r|^2
 __global__ void __launch_bounds__(256) xr_kernel(const int* __restrict__ sys, Basis Q, int64_t n,
-                                                 const double2* __restrict__ rho, const double2* __restrict__ sigma,
+                                                 const double2* __restrict__ part_sig, const double2* __restrict__ part_nrm,
+                                                 const double2* __restrict__ rho, int* __restrict__ flags, double thr,
                                                  double* __restrict__ norm2, int nblk) {
     __shared__ double sh[4];
+    __shared__ double2 stage[256];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int s = sys[blockIdx.y];
-    const double2 a = rho[s], c = sigma[s];
-    const double dd = c.x * c.x + c.y * c.y;
-    const double alr = (a.x * c.x + a.y * c.y) / dd, ali = (a.y * c.x - a.x * c.y) / dd;
+    const double2 a = rho[s], c = ordered_sum(part_sig + (int64_t)s * nblk, nblk, stage);
+    if (blockIdx.x == 0) {
+        const double2 nrm = ordered_sum(part_nrm + (int64_t)s * nblk, nblk, stage);
+        int f = 0;
+        const double sabs = hypot(c.x, c.y), rabs = hypot(a.x, a.y);
+        if (!(sabs > thr * sqrt(nrm.x * nrm.y)) || !(rabs > 0.0)) f |= 8;
+        if (!(sabs == sabs) || !(rabs == rabs)) f |= 4;
+        if (threadIdx.x == 0) flags[s] = f;
+    }
+    // contracted by hand, so that the rounding does not depend on where the compiler takes sigma from
+    const double dd = fma(c.x, c.x, c.y * c.y);
+    const double alr = fma(c.x, a.x, a.y * c.y) / dd, ali = fma(a.y, c.x, -(a.x * c.y)) / dd;
     double nn = 0.0;
     if (i < n) {
         const int64_t o = Q.npad;
@@ -127,79 +162,44 @@ __global__ void __launch_bounds__(256) xr_kernel(const int* __restrict__ sys, Ba
         const double* q = slot(Q, s, 3);
         double* x = slot(Q, s, 4);
         const double pr = p[i], pi = p[i + o], qr = q[i], qi = q[i + o];
-        x[i] += alr * pr - ali * pi;
-        x[i + o] += alr * pi + ali * pr;
-        const double rr = r[i] - (alr * qr - ali * qi), ri = r[i + o] - (alr * qi + ali * qr);
+        x[i] += fma(alr, pr, -(ali * pi));
+        x[i + o] += fma(alr, pi, ali * pr);
+        const double rr = r[i] - fma(alr, qr, -(ali * qi)), ri = r[i + o] - fma(ali, qr, alr * qi);
         r[i] = rr;
         r[i + o] = ri;
-        nn = rr * rr + ri * ri;
+        nn = fma(rr, rr, ri * ri);
     }
     nn = block_sum4(nn, sh);
     if (threadIdx.x == 0) norm2[(int64_t)s * nblk + blockIdx.x] = nn;
 }
 
-// per system: sigma = sum of partials and the breakdown test (Lanczos breakdown: no look-ahead)
-__global__ void sigma_kernel(const int* __restrict__ sys, int nsys, const double2* __restrict__ part_sig,
-                             const double2* __restrict__ part_nrm, int nblk, const double2* __restrict__ rho,
-                             double2* __restrict__ sigma, int* __restrict__ flags, double thr) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nsys) return;
-    const int s = sys[k];
-    double sr = 0, si = 0, nt = 0, nq = 0;
-    for (int b = 0; b < nblk; ++b) {
-        const double2 a = part_sig[(int64_t)s * nblk + b], c = part_nrm[(int64_t)s * nblk + b];
-        sr += a.x;
-        si += a.y;
-        nt += c.x;
-        nq += c.y;
-    }
-    sigma[s] = make_double2(sr, si);
-    int f = 0;
-    const double sabs = hypot(sr, si), rabs = hypot(rho[s].x, rho[s].y);
-    if (!(sabs > thr * sqrt(nt * nq)) || !(rabs > 0.0)) f |= 8;
-    if (!(sabs == sabs) || !(rabs == rabs)) f |= 4;
-    flags[s] = f;
-}
-
-// per system: smoothing weights from the new BCG residual norm; clears the first-step flag
-__global__ void weights_kernel(const int* __restrict__ sys, int nsys, const double* __restrict__ rn_part, int nblk,
-                               double* __restrict__ tau2, double* __restrict__ eta, int* __restrict__ first) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nsys) return;
-    const int s = sys[k];
-    double nr = 0;
-    for (int b = 0; b < nblk; ++b) nr += rn_part[(int64_t)s * nblk + b];
-    const double t2 = tau2[s];
-    const double t2n = nr > 0.0 ? 1.0 / (1.0 / t2 + 1.0 / nr) : 0.0;
-    eta[s] = nr > 0.0 ? t2n / nr : 1.0;
-    tau2[s] = t2n;
-    first[s] = 0;
-}
-}  // namespace
-
-// reduce per-block complex partials of the systems in `sys`
-__global__ void reduce_complex_kernel(const int* __restrict__ sys, int nsys, const double2* __restrict__ partial,
-                                      int nb, double2* __restrict__ out) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nsys) return;
-    const int s = sys[k];
-    double a = 0, b = 0;
-    for (int q = 0; q < nb; ++q) {
-        a += partial[(int64_t)s * nb + q].x;
-        b += partial[(int64_t)s * nb + q].y;
-    }
-    out[s] = make_double2(a, b);
-}
-
-namespace {
-// xq += eta (x - xq); s += eta (r - s); partial ||s||^2
+// smoothing weights from the new BCG residual norm (the sum of its partials): 1 / tau'^2 = 1 / tau^2 + 1 / |r|^2, eta =
+// tau'^2 / |r|^2; xq += eta (x - xq); s += eta (r - s); partial ||s||^2. tau^2 goes from one array to another, since every
+// work-group of a system reads the old one; the first-step flag is cleared.
 __global__ void __launch_bounds__(256) smooth_kernel(const int* __restrict__ sys, Basis Q, int64_t n,
-                                                     const double* __restrict__ eta, double* __restrict__ norm2,
-                                                     int nblk) {
+                                                     const double* __restrict__ rn_part, const double* __restrict__ tau2,
+                                                     double* __restrict__ tau2_new, int* __restrict__ first,
+                                                     double* __restrict__ norm2, int nblk) {
     __shared__ double sh[4];
+    __shared__ double stage[256];
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int s = sys[blockIdx.y];
-    const double e = eta[s];
+    double nr = 0.0;
+    for (int b0 = 0; b0 < nblk; b0 += 256) {
+        __syncthreads();
+        if ((int)threadIdx.x < nblk - b0) stage[threadIdx.x] = rn_part[(int64_t)s * nblk + b0 + threadIdx.x];
+        __syncthreads();
+        const int cnt = min(256, nblk - b0);
+#pragma unroll 8
+        for (int q = 0; q < cnt; ++q) nr += stage[q];
+    }
+    const double t2 = tau2[s];
+    const double t2n = nr > 0.0 ? 1.0 / (1.0 / t2 + 1.0 / nr) : 0.0;
+    const double e = nr > 0.0 ? t2n / nr : 1.0;
+    if (i == 0) {
+        tau2_new[s] = t2n;
+        first[s] = 0;
+    }
     double nn = 0.0;
     if (i < n) {
         const int64_t o = Q.npad;
@@ -246,15 +246,15 @@ void qmr_rho(bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys,
 }
 
 void qmr_dirs(bool y_is_f64, const void* Y, int64_t ld, const int* sys, int nsys, const Basis& Q, int64_t n,
-              const double2* rho_new, const double2* rho_old, const int* first, double* tpb, hipStream_t st) {
+              const double2* partial, int nblk, double2* rho_new, const double2* rho_old, const int* first, double* tpb, hipStream_t st) {
     if (nsys <= 0) return;
     dim3 grd((unsigned)((n + 255) / 256), (unsigned)nsys);
     if (y_is_f64)
         hipLaunchKernelGGL(dirs_kernel<double>, grd, dim3(256), 0, st, static_cast<const double*>(Y), ld, sys, Q, n,
-                           rho_new, rho_old, first, tpb);
+                           partial, nblk, rho_new, rho_old, first, tpb);
     else
         hipLaunchKernelGGL(dirs_kernel<float>, grd, dim3(256), 0, st, static_cast<const float*>(Y), ld, sys, Q, n,
-                           rho_new, rho_old, first, tpb);
+                           partial, nblk, rho_new, rho_old, first, tpb);
     WFQ_CHECK_LAUNCH();
 }
 
@@ -269,35 +269,19 @@ void qmr_q(const Structure& S, const int* sys, int nsys, const Basis& Q, const d
     WFQ_CHECK_LAUNCH();
 }
 
-void qmr_sigma(const int* sys, int nsys, const double2* part_sig, const double2* part_nrm, int nblk,
-               const double2* rho, double2* sigma, int* flags, double thr, hipStream_t st) {
-    if (nsys <= 0) return;
-    hipLaunchKernelGGL(sigma_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, sys, nsys, part_sig, part_nrm, nblk, rho,
-                       sigma, flags, thr);
-    WFQ_CHECK_LAUNCH();
-}
-
-void qmr_weights(const int* sys, int nsys, const double* rn_part, int nblk, double* tau2, double* eta, int* first,
-                 hipStream_t st) {
-    if (nsys <= 0) return;
-    hipLaunchKernelGGL(weights_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, sys, nsys, rn_part, nblk, tau2, eta,
-                       first);
-    WFQ_CHECK_LAUNCH();
-}
-
-void qmr_xr(const int* sys, int nsys, const Basis& Q, int64_t n, const double2* rho, const double2* sigma,
-            double* norm2, int nblk, hipStream_t st) {
+void qmr_xr(const int* sys, int nsys, const Basis& Q, int64_t n, const double2* part_sig, const double2* part_nrm,
+            const double2* rho, int* flags, double thr, double* norm2, int nblk, hipStream_t st) {
     if (nsys <= 0) return;
     dim3 grd((unsigned)nblk, (unsigned)nsys);
-    hipLaunchKernelGGL(xr_kernel, grd, dim3(256), 0, st, sys, Q, n, rho, sigma, norm2, nblk);
+    hipLaunchKernelGGL(xr_kernel, grd, dim3(256), 0, st, sys, Q, n, part_sig, part_nrm, rho, flags, thr, norm2, nblk);
     WFQ_CHECK_LAUNCH();
 }
 
-void qmr_smooth(const int* sys, int nsys, const Basis& Q, int64_t n, const double* eta, double* norm2, int nblk,
-                hipStream_t st) {
+void qmr_smooth(const int* sys, int nsys, const Basis& Q, int64_t n, const double* rn_part, const double* tau2,
+                double* tau2_new, int* first, double* norm2, int nblk, hipStream_t st) {
     if (nsys <= 0) return;
     dim3 grd((unsigned)nblk, (unsigned)nsys);
-    hipLaunchKernelGGL(smooth_kernel, grd, dim3(256), 0, st, sys, Q, n, eta, norm2, nblk);
+    hipLaunchKernelGGL(smooth_kernel, grd, dim3(256), 0, st, sys, Q, n, rn_part, tau2, tau2_new, first, norm2, nblk);
     WFQ_CHECK_LAUNCH();
 }
 
@@ -305,12 +289,6 @@ void qmr_restart(const int* sys, int nsys, const Basis& Q, hipStream_t st) {
     if (nsys <= 0) return;
     dim3 grd((unsigned)(Q.npad / 256), (unsigned)nsys);
     hipLaunchKernelGGL(restart_kernel, grd, dim3(256), 0, st, sys, Q, Q.npad);
-    WFQ_CHECK_LAUNCH();
-}
-
-void reduce_complex(const int* sys, int nsys, const double2* partial, int nb, double2* out, hipStream_t st) {
-    if (nsys <= 0) return;
-    hipLaunchKernelGGL(reduce_complex_kernel, dim3((nsys + 63) / 64), dim3(64), 0, st, sys, nsys, partial, nb, out);
     WFQ_CHECK_LAUNCH();
 }
 

@@ -172,8 +172,8 @@ struct Work {
     Buf<double2> partial, h1, h2, R, Hu, sn, g, y, z, alpha, gam;
     Buf<double> nu, irho;
     // QMR scalars and partials
-    Buf<double2> rho_a, rho_b, sigma, part_sig, part_nrm;
-    Buf<double> tau2, eta, snorm, tpb;
+    Buf<double2> rho_a, rho_b, part_sig, part_nrm;
+    Buf<double> tau2_a, tau2_b, tpb;
     Buf<int> first;
     Buf<int> flags, ksteps, dir, run, sys[NSLOT];
     Buf<double> d_dirs, stage_re, stage_im;
@@ -192,7 +192,7 @@ struct Work {
     bool rc_active = false;   // the current pass projects onto the recycle spaces
     MsWork ms;
     // pinned host mirrors
-    Buf<double> h_snorm, h_est, h_beta, h_invb, h_qT;
+    Buf<double> h_est, h_beta, h_invb, h_qT;
     // est (B doubles), flags and ksteps (B ints each) side by side on the device and in the pinned
     // mirror, so that the per-step read-back is one copy
     Buf<double> step_dev, step_host;
@@ -270,12 +270,10 @@ void layout_work(Work& w, const Structure& S, Arena& d, Arena& h) {
     }
     d.take(w.rho_a, B);
     d.take(w.rho_b, B);
-    d.take(w.sigma, B);
     d.take(w.part_sig, (size_t)B * w.nblk);
     d.take(w.part_nrm, (size_t)B * w.nblk);
-    d.take(w.tau2, B);
-    d.take(w.eta, B);
-    d.take(w.snorm, B);
+    d.take(w.tau2_a, B);
+    d.take(w.tau2_b, B);
     d.take(w.first, B);
     d.take(w.tpb, sh.qmr ? (size_t)B * 2 * np : 0);   // QMR: compact T p, rows by system id
     d.take(w.d_dirs, (size_t)3 * n_dir);
@@ -310,7 +308,6 @@ void layout_work(Work& w, const Structure& S, Arena& d, Arena& h) {
     h.take(w.h_beta, B);
     h.take(w.h_qT, B);
     h.take(w.h_invb, B);
-    h.take(w.h_snorm, B);
     h.take(w.h_g, (size_t)B * (w.mdim + 1));
     h.take(w.h_alpha, (size_t)B * 3);
     if (sh.ms_m > 0) {
@@ -1303,12 +1300,21 @@ void qmr_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double to
             t2[s] = ss[s].beta * ss[s].beta;
             ss[s].cycles += 1;
         }
-        h2d_sync(S, w.tau2.p, t2.data(), B * sizeof(double), st);
+        h2d_sync(S, w.tau2_a.p, t2.data(), B * sizeof(double), st);
         h2d_sync(S, w.first.p, fh.data(), B * sizeof(int), st);
         qmr_restart(w.sys[SLOT_ACT].p, na, Q, st);
         WFQ_HIP(hipStreamSynchronize(st));
         double2* rho_new = w.rho_a.p;
         double2* rho_old = w.rho_b.p;
+        double* tau_new = w.tau2_b.p;
+        double* tau_old = w.tau2_a.p;
+        double* const s_part = reinterpret_cast<double*>(w.part_nrm.p);   // partials of ||s||^2, read after those of sigma's test
+        std::vector<int> sent[NSLOT];                                     // the lists on the device
+        const auto send = [&](int slot, const std::vector<int>& v) {
+            if (sent[slot] == v) return;
+            upload(w, slot, v, st);
+            sent[slot] = v;
+        };
         std::vector<int> stepping;
         for (int s : active)
             if (ss[s].iters < o.max_iter) stepping.push_back(s);
@@ -1319,39 +1325,37 @@ void qmr_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double to
             for (int p = 0; p < 3; ++p) {
                 if (grp[p].empty()) continue;
                 const int ng = (int)grp[p].size();
-                upload(w, p, grp[p], st);
+                send(p, grp[p]);
                 tm.begin(st);
                 pack_columns(p, Q, w.sys[p].p, ng, 0, nullptr, false, x_block(w, p), w.npad, st);
                 tm.end(st, KC_PACK, 0, ng * n * (16.0 + 2 * elem_size(p)));
                 block_product(S, w, p, 2 * ng, tm, st);
                 tm.begin(st);
                 qmr_rho(p == WFQ_PREC_FP64, y_block(w, p), w.npad, w.sys[p].p, ng, Q, S.n, w.part_sig.p, nblk, st);
-                reduce_complex(w.sys[p].p, ng, w.part_sig.p, nblk, rho_new, st);
-                qmr_dirs(p == WFQ_PREC_FP64, y_block(w, p), w.npad, w.sys[p].p, ng, Q, S.n, rho_new, rho_old,
-                         w.first.p, w.tpb.p, st);
+                qmr_dirs(p == WFQ_PREC_FP64, y_block(w, p), w.npad, w.sys[p].p, ng, Q, S.n, w.part_sig.p, nblk,
+                         rho_new, rho_old, w.first.p, w.tpb.p, st);
                 tm.end(st, KC_QMR, 0, ng * n * (16.0 * 5 + 4 * out_size(p)));
             }
-            upload(w, SLOT_STEP, stepping, st);
+            send(SLOT_STEP, stepping);
             const int* sl = w.sys[SLOT_STEP].p;
             tm.begin(st);
             qmr_q(S, sl, ns, Q, w.z.p, w.tpb.p, w.part_sig.p, w.part_nrm.p, nblk, st);
             tm.end(st, KC_SPMM, 4.0 * S.nnz * ns, 12.0 * S.nnz + ns * n * 48.0);
             tm.begin(st);
-            qmr_sigma(sl, ns, w.part_sig.p, w.part_nrm.p, nblk, rho_new, w.sigma.p, w.flags.p,
-                      o.qmr_breakdown > 0.0 ? o.qmr_breakdown : 1e-14, st);
-            qmr_xr(sl, ns, Q, S.n, rho_new, w.sigma.p, w.norm2.p, nblk, st);
-            qmr_weights(sl, ns, w.norm2.p, nblk, w.tau2.p, w.eta.p, w.first.p, st);
-            qmr_smooth(sl, ns, Q, S.n, w.eta.p, w.norm2.p, nblk, st);
-            sumsq(sl, ns, w.norm2.p, nblk, w.snorm.p, st);
+            qmr_xr(sl, ns, Q, S.n, w.part_sig.p, w.part_nrm.p, rho_new, w.flags.p,
+                   o.qmr_breakdown > 0.0 ? o.qmr_breakdown : 1e-14, w.norm2.p, nblk, st);
+            qmr_smooth(sl, ns, Q, S.n, w.norm2.p, tau_old, tau_new, w.first.p, s_part, nblk, st);
+            sumsq(sl, ns, s_part, nblk, w.est.p, st);
             tm.end(st, KC_QMR, 0, ns * n * 16.0 * 12);
-            WFQ_HIP(hipMemcpyAsync(w.h_flags.p, w.flags.p, B * sizeof(int), hipMemcpyDeviceToHost, st));
-            WFQ_HIP(hipMemcpyAsync(w.h_snorm.p, w.snorm.p, B * sizeof(double), hipMemcpyDeviceToHost, st));
+            WFQ_HIP(hipMemcpyAsync(w.step_host.p, w.step_dev.p, w.step_dev.count * sizeof(double), hipMemcpyDeviceToHost,
+                                   st));
             WFQ_HIP(hipStreamSynchronize(st));
             std::swap(rho_new, rho_old);
+            std::swap(tau_new, tau_old);
             std::vector<int> next;
             for (int s : stepping) {
                 ss[s].iters += 1;
-                ss[s].est_end = w.h_snorm.p[s];
+                ss[s].est_end = w.h_est.p[s];
                 const int f = w.h_flags.p[s];
                 if (f & 4) {
                     ss[s].status = WFQ_ENUMERIC;
@@ -1361,7 +1365,7 @@ void qmr_batch(const Structure& S, Work& w, std::vector<SysState>& ss, double to
                     ss[s].status = WFQ_EBREAKDOWN;
                     continue;
                 }
-                if (w.h_snorm.p[s] > 0.5 * tol * ss[s].bnorm && ss[s].iters < o.max_iter) next.push_back(s);
+                if (w.h_est.p[s] > 0.5 * tol * ss[s].bnorm && ss[s].iters < o.max_iter) next.push_back(s);
             }
             stepping.swap(next);
             if ((k + 1) % 10 == 0) progress_line(o, "qmr", ss[active[0]].cycles, k + 1, stepping.size(), -1.0, t0);

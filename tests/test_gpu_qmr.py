@@ -95,3 +95,33 @@ def test_qmr_breakdown_threshold_is_checked(lib, case):
         lib.wfq_solve(h, [0.3], np.eye(3)[:1], 1e-8, algorithm="qmr", qmr_breakdown=-1.0)
     assert e.value.code == lib.WFQ_EINVAL
     h.close()
+
+
+@pytest.mark.parametrize("n", [2, 256, 257])
+def test_qmr_steps_at_the_edges_of_their_row_blocks(lib, n):
+    # a step's work-groups own 256 rows and each add up all partial sums: one partial, two
+    xyz = ragged_tube()[:n] if n > 2 else np.array([[0.0, 0.0, 0.0], [1.42, 0.0, 0.0]])
+    P = O.Problem(xyz, GRAPHENE)
+    om = np.array([0.3, 0.8])
+    h = lib.wfq_build(xyz, GRAPHENE)
+    out = lib.wfq_solve(h, om, np.eye(3)[:1], 1e-8, algorithm="qmr", restart=60, precision="fp64")
+    h.close()
+    assert out["status"] == 0, out["info"]
+    for a in range(2):
+        assert rel(out["q"][a, 0], P.solve_lu(om[a], np.eye(3)[0])) <= 1e-6
+
+
+def test_qmr_steps_of_more_than_256_row_blocks(lib):
+    # 66 560 rows: 260 partial sums, more than a work-group stages at once. The recurrences stop the cycle at
+    # half the tolerance; their residual is the true one only if every step's coefficients are right.
+    from wfq_inputs import geometry as geo
+    xyz = geo.jitter(geo.graphene_sheet(160, 104), 0.01, 7)
+    assert len(xyz) > 256 * 256
+    par = dict(GRAPHENE, tau=10.0)
+    h = lib.wfq_build(xyz, par, t_mode="otf")
+    out = lib.wfq_solve(h, np.array([1.0, 1.5]), np.eye(3)[:1], 1e-6, algorithm="qmr", restart=500, precision="fp64",
+                        max_iter=500)
+    h.close()
+    assert out["status"] == 0, out["info"]
+    for info in out["info"]:
+        assert info["relres"] <= 1e-6 and info["cycles"] == 1 and info["iters"] > 2, info

@@ -614,36 +614,52 @@ struct SkinnyVec<WFQ_PREC_FP32> { static constexpr int E = 4; };
 template <>
 struct SkinnyVec<WFQ_PREC_BF16> { static constexpr int E = 8; };
 
-template <int P, int NC, int R>
-__global__ void __launch_bounds__(256) tx_skinny_kernel(const typename Prec<P>::elem* __restrict__ X,
-                                                        const typename Prec<P>::elem* __restrict__ T,
-                                                        typename Prec<P>::out* __restrict__ Y, int64_t ld, int ncol) {
-    using elem = typename Prec<P>::elem;
+// A wave computes R rows for all NC columns, U steps of its lanes' k loaded at once (the loads' latency bounds a small T),
+// W waves a work-group. Each lane adds up every 64th 16-byte piece of a row, then the lanes are added.
+template <int P, int NC, int R, int U, int W>
+__global__ void __launch_bounds__(64 * W) tx_skinny_kernel(const typename Prec<P>::elem* __restrict__ X,
+                                                           const typename Prec<P>::elem* __restrict__ T,
+                                                           typename Prec<P>::out* __restrict__ Y, int64_t ld, int ncol) {
     using S = typename Prec<P>::sacc;
     constexpr int E = SkinnyVec<P>::E;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * R;
+    const int64_t row0 = ((int64_t)blockIdx.x * W + wave) * R;
     S acc[R][NC];
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < NC; ++c) acc[r][c] = 0;
-    for (int64_t k = (int64_t)lane * E; k < ld; k += 64 * E) {
+    u32x4 x[U][NC], t[U][R];
+    const auto load = [&](int u, int64_t k) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) t[u][r] = *reinterpret_cast<const u32x4*>(T + (row0 + r) * ld + k);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) x[u][c] = *reinterpret_cast<const u32x4*>(X + c * ld + k);
+    };
+    const auto add = [&](int u) {
         S xv[NC][E];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            u32x4 v = *reinterpret_cast<const u32x4*>(X + c * ld + k);
-            unpack(v, xv[c]);
-        }
+        for (int c = 0; c < NC; ++c) unpack(x[u][c], xv[c]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             S tv[E];
-            unpack(*reinterpret_cast<const u32x4*>(T + (row0 + r) * ld + k), tv);
+            unpack(t[u][r], tv);
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int e = 0; e < E; ++e) acc[r][c] += tv[e] * xv[c][e];
         }
+    };
+    int64_t k = (int64_t)lane * E;
+    for (; k + (U - 1) * 64 * E < ld; k += U * 64 * E) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load(u, k + u * 64 * E);
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(u);
+    }
+    for (; k < ld; k += 64 * E) {
+        load(0, k);
+        add(0);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -823,12 +839,31 @@ void launch_split(const Structure& s, const void* X, const void* T, void* Y, int
         add_parts_f32(static_cast<float*>(Y), parts, (int64_t)ncol * ld, (int64_t)mtc * BM * ld, split - 1, st);
 }
 
-template <int P, int NC, int R = 4>
-void launch_skinny(const Structure&, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st, const KParts*) {
+template <int P, int NC, int R, int U = 1, int W = 4>
+void launch_skinny_rows(const Structure&, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st,
+                        const KParts*) {
     using elem = typename Prec<P>::elem;
     using out = typename Prec<P>::out;
-    hipLaunchKernelGGL((tx_skinny_kernel<P, NC, R>), dim3((unsigned)(ld / (4 * R))), dim3(256), 0, st,
+    hipLaunchKernelGGL((tx_skinny_kernel<P, NC, R, U, W>), dim3((unsigned)(ld / (W * R))), dim3(64 * W), 0, st,
                        static_cast<const elem*>(X), static_cast<const elem*>(T), static_cast<out*>(Y), ld, ncol);
+}
+
+// Rows per wave by size: few rows a wave where T has few of them, 4 where the waves fill the chip anyway and X, read again
+// by every wave, bounds instead. One wave a work-group, so that the CUs get equal shares. us, 4 rows in work-groups of 4
+// waves (what all sizes had) / 2 rows and two loads ahead / 4 rows, one wave a work-group: FP64, 2 columns 600 atoms 5.3 /
+// 3.3 / 3.8, 2 000 12.3 / 8.0 / -, 4 000 31.4 / 21.1 / 26.0, 5 000 41.7 / 30.4 / 34.0, 7 000 92 / 92 / 86, 20 000 650 / 665 /
+// 635; 4 columns 600 7.5 / 4.1 / -, 4 000 40.5 / 26.6 / 39.9, 7 000 131 / 129 / 127; 8 columns 1 500 16.1 / 13.9 / 10.2, 4 000
+// 41.0 / - / 35.5, 10 000 247 / 329 / 220 and with one row at 250 atoms 3.5 against 5.5, 600 6.3 and 7.1. FP32, 8 columns
+// 2 000 20.0 / 6.7 / -, 7 000 69 / 40 / 68, 10 000 155 / 127 / 158, 20 000 366 / 468 / 350; 4 columns 4 000 18.4 / 12.2 / 13.7,
+// 7 000 30.5 / 31.9 / 30.7. A row's sums are the same in all of them.
+template <int P, int NC>
+void launch_skinny(const Structure& s, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st,
+                   const KParts* parts) {
+    constexpr bool wide64 = P == WFQ_PREC_FP64 && NC == 8;
+    if (wide64 ? ld < 1024 : ld < (NC == 8 ? 12288 : 6144))
+        launch_skinny_rows<P, NC, wide64 ? 1 : 2, wide64 ? 4 : 2, 1>(s, X, T, Y, ld, ncol, st, parts);
+    else
+        launch_skinny_rows<P, NC, 4, 1, 1>(s, X, T, Y, ld, ncol, st, parts);
 }
 
 template <int P, int WM, int WN, int WAVES_M, int WAVES_N, int KB, int OCC, int ILV = 0>
@@ -844,8 +879,8 @@ const std::vector<Variant>& variants() {
         {"skinny2", 0, 4, 2, launch_skinny<P, 2>, nullptr},
         {"skinny4", 0, 4, 4, launch_skinny<P, 4>, nullptr},
         {"skinny8", 0, 4, 8, launch_skinny<P, 8>, nullptr},
-        {"skinny2r8", 0, 8, 2, launch_skinny<P, 2, 8>, nullptr},
-        {"skinny4r8", 0, 8, 4, launch_skinny<P, 4, 8>, nullptr},
+        {"skinny2r8", 0, 8, 2, launch_skinny_rows<P, 2, 8>, nullptr},
+        {"skinny4r8", 0, 8, 4, launch_skinny_rows<P, 4, 8>, nullptr},
         tile<P, 2, 2, 1, 4, 128, 2>("m32n128"),
         tile<P, 4, 2, 1, 4, 128, 2>("m64n128"),
         tile<P, 4, 4, 2, 2, 128, OCC2>("m128n128"),

@@ -130,6 +130,28 @@ def test_every_block_product_variant(lib, handle, tube, prec):
             assert np.all(np.abs(Y - ref) <= 2 * P.n * u_acc * bound + 1e-300), (name, ncol)
 
 
+@pytest.mark.parametrize("n", [240, 760, 1020, 5880, 6140, 12020, 12040])
+def test_narrow_products_where_their_rows_per_wave_change(lib, n):
+    # 1, 2 and 4 rows a wave, one and several loads ahead, with and without a last step of fewer: padded sizes 256, 1 024
+    # (760 and 1 020 atoms), 6 144 and 12 288. Rows against the oracle's elements; the bound is n roundings of the
+    # accumulator and one each of T's and X's elements.
+    from oracle.cpp_oracle import CppProblem
+    from wfq_inputs import geometry as geo
+    xyz = geo.jitter(geo.nanotube(5, 5, n // 20), 0.01, 3)
+    n = len(xyz)
+    P = CppProblem(xyz, GRAPHENE, dense_T=False, build_L=False)
+    rows = np.unique(np.r_[np.arange(0, n, max(1, n // 24)), n - 1])
+    X = np.random.default_rng(n).standard_normal((8, n))
+    ref, bound = P.apply_T_rows(rows, X.T).T, P.apply_T_rows(rows, np.abs(X).T).T
+    h = lib.wfq_build(xyz, GRAPHENE, store=("fp64", "fp32", "bf16"))
+    for prec in ("fp64", "fp32", "bf16"):
+        tol = 2 * n * UNIT["fp64" if prec == "fp64" else "fp32"] + (0 if prec == "fp64" else 3 * UNIT[prec])
+        for name, ncol in (("skinny2", 1), ("skinny2", 2), ("skinny4", 3), ("skinny4", 4), ("skinny8", 5), ("skinny8", 8)):
+            Y = lib.wfq_apply_T_variant(h, prec, name, X[:ncol])[:, rows]
+            assert np.all(np.abs(Y - ref[:ncol]) <= tol * bound[:ncol]), (prec, name, ncol)
+    h.close()
+
+
 def test_variant_entry_point_rejects(lib, handle):
     X = np.ones((5, handle.n))
     with pytest.raises(lib.WfqError):

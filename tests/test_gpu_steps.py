@@ -69,6 +69,32 @@ def test_laplacian_structure_and_values(lib, handle, tube):
     assert np.max(np.abs(rows)) < 1e-14 * np.max(np.abs(v))
 
 
+@pytest.mark.parametrize("case", ["pair", "cells of more than 64 atoms", "empty cells between"])
+def test_neighbour_searches_over_full_and_empty_cells(lib, case):
+    # a wave visits the cells around its atom 64 at a time and their atoms 64 at a time: the rows of L (27 cells) and,
+    # through the narrow recomputed product, the near-field rows (up to 125)
+    from wfq_inputs import geometry as geo
+    par = wi.workloads.FCC_METAL
+    xyz = geo.jitter(geo.fcc_sphere(20.0), 0.02, 5)
+    if case == "pair":
+        xyz = np.array([[0.0, 0.0, 0.0], [2.9, 0.0, 0.0]])
+    elif case == "empty cells between":
+        xyz = xyz[(xyz[:, 0] < 0.0) | (np.abs(xyz[:, 1]) > 11.5)]
+    P = O.Problem(xyz, par)
+    h = lib.wfq_build(xyz, par, t_mode="otf")
+    r, c, v = lib.wfq_export_L(h)
+    X = np.random.default_rng(2).standard_normal((2, P.n))
+    Y = lib.wfq_apply_T(h, "fp64", X)
+    h.close()
+    L = P.L.tocoo()
+    want = {(i, j): x for i, j, x in zip(L.row, L.col, L.data)}
+    got = {(i, j): x for i, j, x in zip(r, c, v)}
+    assert set(got) == set(want)
+    k = list(want)
+    assert np.allclose([got[q] for q in k], [want[q] for q in k], rtol=1e-13, atol=1e-16)
+    assert np.all(np.abs(Y - X @ P.T.T) <= 1e-13 * (np.abs(X) @ np.abs(P.T).T))
+
+
 def test_rhs(lib, handle, tube):
     _, P = tube
     dirs = np.eye(3)

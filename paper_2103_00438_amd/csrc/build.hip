@@ -321,21 +321,49 @@ T* dev_alloc(Structure& s, size_t count) {
     if (s.budget && s.bytes + bytes > s.budget)
         throw Error{WFQ_ENOMEM, "device budget exceeded while building the structure (" +
                                     std::to_string((s.bytes + bytes) >> 20) + " MiB needed)"};
-    void* p = nullptr;
-    hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) throw Error{WFQ_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e)};
+    void* p = s.mem.take(bytes);
     s.bytes += bytes;
     return static_cast<T*>(p);
 }
 
 }  // namespace
 
+void* DevChunks::take(size_t bytes) {
+    constexpr size_t kChunk = 2u << 20;
+    const size_t need = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+    if (need <= left) {
+        char* p = next;
+        next += need;
+        left -= need;
+        return p;
+    }
+    all.reserve(all.size() + 1);   // nothing is allocated that cannot be recorded
+    void* p = nullptr;
+    if (need < kChunk / 2) {
+        if (hipMalloc(&p, kChunk) == hipSuccess) {
+            all.push_back(p);
+            next = static_cast<char*>(p) + need;
+            left = kChunk - need;
+            return p;
+        }
+        (void)hipGetLastError();   // the array by itself may still fit
+    }
+    const hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
+    if (e != hipSuccess) throw Error{WFQ_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e)};
+    all.push_back(p);
+    return p;
+}
+
+void DevChunks::release() {
+    for (void* p : all) (void)hipFree(p);
+    all.clear();
+    next = nullptr;
+    left = 0;
+}
+
 void free_structure(Structure& s) {
     free_solve_cache(s);
-    void* ptrs[] = {s.pos, s.eta, s.width, s.rowptr, s.col, s.val, s.T64, s.T32, s.T16, s.dperm, s.ell_col, s.ell_val,
-                    s.sphere, s.near_col, s.near_val, s.r0a};
-    for (void* p : ptrs)
-        if (p) (void)hipFree(p);
+    s.mem.release();
     s.pos = s.eta = s.width = s.val = s.T64 = s.sphere = nullptr;
     s.rowptr = s.col = s.dperm = s.ell_col = nullptr;
     s.ell_val = nullptr;
@@ -358,41 +386,38 @@ namespace {
 // Device scratch of one build step: every buffer taken is freed by release() or, on an exception,
 // by the destructor (after the device work that may still use it has finished).
 struct ScratchDev {
-    std::vector<void*> bufs;
+    DevChunks mem;
     template <typename T>
     T* take(int64_t count) {
-        void* p = nullptr;
-        const hipError_t e = hipMalloc(&p, std::max<int64_t>(count, 1) * sizeof(T));
-        if (e != hipSuccess) throw Error{WFQ_ENOMEM, std::string("hipMalloc of build scratch failed: ") + hipGetErrorString(e)};
-        bufs.push_back(p);
-        return static_cast<T*>(p);
+        return static_cast<T*>(mem.take((size_t)count * sizeof(T)));
     }
-    void release() {
-        for (void* p : bufs) (void)hipFree(p);
-        bufs.clear();
-    }
+    void release() { mem.release(); }
     ScratchDev() = default;
     ScratchDev(const ScratchDev&) = delete;
     ScratchDev& operator=(const ScratchDev&) = delete;
     ~ScratchDev() {
-        if (!bufs.empty()) (void)hipDeviceSynchronize();
+        if (!mem.all.empty()) (void)hipDeviceSynchronize();
         release();
     }
 };
 
-// the structure's pinned staging buffer, at least min(bytes, 32 MiB) long; returns its length
+// the structure's pinned staging buffer, at least min(bytes, 32 MiB) long; returns the length of a piece. It starts at
+// 1 MiB and at least doubles: pinning costs 0.3 ms a call and unpinning as much, and the copies of a build and a solve of
+// 2 000 atoms grew it four times.
 size_t pin_stage(const Structure& s, size_t bytes, hipStream_t st) {
     constexpr size_t kChunk = 32u << 20;
     const size_t cap = std::min(bytes, kChunk);
     if (s.pin_stage_bytes < cap) {
+        const size_t had = s.pin_stage_bytes;
         if (s.pin_stage) {
             WFQ_HIP(hipStreamSynchronize(st));
             WFQ_HIP(hipHostFree(s.pin_stage));
             s.pin_stage = nullptr;
             s.pin_stage_bytes = 0;
         }
-        WFQ_HIP(hipHostMalloc(&s.pin_stage, cap, hipHostMallocDefault));
-        s.pin_stage_bytes = cap;
+        const size_t len = std::min(kChunk, std::max({cap, 2 * had, (size_t)1 << 20}));
+        WFQ_HIP(hipHostMalloc(&s.pin_stage, len, hipHostMallocDefault));
+        s.pin_stage_bytes = len;
     }
     return cap;
 }

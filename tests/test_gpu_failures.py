@@ -80,3 +80,25 @@ def test_nonpositive_frequency_is_singular(lib):
             lib.wfq_solve(h, om, np.eye(3)[:1], 1e-8)
         assert e.value.code == lib.WFQ_ESINGULAR
     h.close()
+
+
+@pytest.mark.parametrize("n", [2, 500, 6000])
+def test_structures_give_their_device_memory_back(n):
+    # a structure's arrays share a few allocations; freed with it, whatever their number and size
+    import torch
+    import wfq_inputs as wi
+    from paper_2103_00438_amd import wfq
+    from wfq_inputs import geometry as geo
+    xyz = geo.jitter(geo.nanotube(5, 5, 300), 0.01, 1)[:n]
+    if n == 2:
+        xyz = np.array([[0.0, 0.0, 0.0], [1.42, 0.0, 0.0]])
+    free = []
+    for _ in range(2):   # the first round also has the runtime create queues for eight streams
+        handles = [wfq.wfq_build(xyz, wi.workloads.GRAPHENE, store=("fp64", "fp32")) for _ in range(8)]
+        T = [wfq.wfq_apply_T(h, "fp64", np.ones((1, len(xyz)))) for h in handles]
+        for h in handles:
+            h.close()
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+        assert all(np.array_equal(t, T[0]) for t in T)
+    assert free[1] >= free[0] - (4 << 20)

@@ -36,6 +36,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAKS = {"fp32": 157.3, "fp64": 78.6, "bf16": 2500.0}   # TFLOP/s, dense MFMA (MI355X)
+PEAKS["fp32_split"] = 2500.0 / 3   # FP32 products as three FP16 ones
 HBM_GBPS = 8000.0                                         # GB/s, HBM3E (MI355X)
 # FP64 vector issue rate: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (one FP64 operation per lane per
 # clock; an FMA counts as one operation here)
@@ -191,20 +192,19 @@ def measured_traffic(workload, kernel):
     return None
 
 
-def roofline_of(stats, prec, otf, n, workload=None):
+def roofline_of(stats, prec, otf, n, workload=None, split=False):
     if otf:
         # Per pair the kernel evaluates T_ij on the vector ALUs (about 10 lane-slots for a far pair:
         # 3 sub, 1 mul, 2 fma and a quarter-rate rsqrt; about 38 near the diagonal) and accumulates
-        # 2 * 32 flops per 32-column block on the FP32 matrix cores (64 flops per SIMD-cycle). With the
-        # far-field path the matrix-core work is the larger one, so the roofline is the FP32 MFMA peak
-        # on the flops of the column blocks actually present (2 n^2 ncol per launch).
+        # on the matrix cores (FP32 in split form on the FP16 ones, FP64): priced against their peak, on the
+        # flops of the column blocks actually present (2 n^2 ncol per launch).
         key = "tx_otf_f32" if prec == "fp32" else "tx_otf_f64"
         st = stats[key]
         ncol_avg = st["flops"] / max(1, st["launches"]) / (2.0 * n * n)
         pairs = n * n * math.ceil(ncol_avg / 32)
         avg_s = st["ms"] / max(1, st["launches"]) / 1e3
         achieved = st["flops"] / max(1, st["launches"]) / avg_s / 1e12 if avg_s > 0 else 0.0
-        peak = PEAKS["fp32" if prec == "fp32" else "fp64"]
+        peak = PEAKS["fp32_split" if prec == "fp32" else "fp64"]
         return dict(bound="mfma", achieved=achieved, peak=peak, unit="TFLOP/s", frac=achieved / peak,
                     traffic=measured_traffic(workload, key), kernel=key, launches=st["launches"],
                     avg_launch_ms=st["ms"] / max(1, st["launches"]),
@@ -216,7 +216,7 @@ def roofline_of(stats, prec, otf, n, workload=None):
     if dom == "tx_otf_narrow":
         # narrow products with every element recomputed: bound by the FP64 vector ALUs. Work per
         # element: 3 differences, 3 operations for r^2, the reciprocal square root, 4 for its Newton
-        # step, and one multiply-add per column and row; from 65 536 atoms each element serves both
+        # step, and one multiply-add per column and row; in the symmetric form each element serves both
         # of its rows (n^2 / 2 evaluations) - the library's count; peak: one FP64 operation per lane
         # per clock
         st = stats["tx_otf_narrow"]
@@ -237,7 +237,7 @@ def roofline_of(stats, prec, otf, n, workload=None):
                     avg_launch_ms=st["ms"] / max(1, st["launches"]),
                     avg_bytes_per_launch=st["bytes"] / max(1, st["launches"]))
     st = stats[dom]
-    prec = classes[dom]
+    prec = "fp32_split" if split and dom == "tx_gemm_f32" else classes[dom]
     achieved = st["flops"] / (st["ms"] / 1e3) / 1e12 if st["ms"] > 0 else 0.0
     return dict(bound="mfma", achieved=achieved, peak=PEAKS[prec], unit="TFLOP/s", frac=achieved / PEAKS[prec],
                 traffic=measured_traffic(workload, dom), kernel=dom, launches=st["launches"], avg_launch_ms=st["ms"] / max(1, st["launches"]),
@@ -297,7 +297,9 @@ def bench_batched(args, wl, wfq, torch):
     statuses = sorted(set(r["status"] for r in last["info"]))
     relres_max = max(r["relres"] for r in last["info"])
     prec_end = sorted(set(r["precision"] for r in last["info"]))
-    roofline = roofline_of(stats, prec, otf, wl.n, wl.name)
+    # split shapes (s<columns>...) among the tuned ones: their products run on the FP16 matrix cores
+    split = tune is not None and any(v[0] == "s" and v[1].isdigit() for v in tune["chosen"])
+    roofline = roofline_of(stats, prec, otf, wl.n, wl.name, split)
 
     extra = {}
     if otf and not args.ref_systems:

@@ -233,6 +233,9 @@ int device_cus(int device);
 // evaluated once for both of its rows): its sums fit the work space, and the order of the sums is free, or the
 // structure matrix-free, or so large that it always took this form (65 536 atoms)
 bool otf_narrow_sym(const Structure& s, int ncol, Order order);
+// true when narrow recomputed products of ncol columns, 4 at a time, have the work space that they need to be the
+// faster choice: always but in a fixed region
+bool otf_narrow_fits(const Structure& s, int ncol, Order order);
 // work space of the symmetric form for ncol columns
 uint64_t otf_sym_bytes(const Structure& s, int ncol);
 // partial-tile work space of the block products (grown on demand, or the fixed region when set)

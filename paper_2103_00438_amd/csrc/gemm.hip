@@ -1032,6 +1032,9 @@ constexpr int64_t kSymNarrowFrom = 4608, kOtfNarrowFrom = 16384;
 // 1 600 atoms 224 / 479 at 32, 435 / 477 at 64, 858 / 481 at 128; 4 096 atoms 502 / 875 at 64, 988 / 882 at 128; 16 384
 // atoms 1 126 / 3 027 at 32, 2 230 / 3 021 at 64, 4 444 / 4 499 at 128.
 int otf_narrow_columns(const Structure& s) { return s.npad < 1024 ? 32 : 64; }
+bool otf_takes_narrow(const Structure& s, int prec, int ncol, Order order) {
+    return prec == WFQ_PREC_FP64 && ncol <= otf_narrow_columns(s) && otf_narrow_fits(s, ncol, order);
+}
 
 int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     const auto& tuned = s.tuned[prec];
@@ -1041,7 +1044,7 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     if (it == tuned.end() && !tuned.empty()) it = std::prev(tuned.end());
     if (it != tuned.end() && it->first <= 2 * ncol && ncol <= 2 * it->first) {
         const Variant& v = variants_of(prec)[it->second];
-        if (ncol <= v.max_ncol) return it->second;
+        if (ncol <= v.max_ncol && (v.launch || otf_narrow_fits(s, ncol, order))) return it->second;
     }
     if (prec == WFQ_PREC_FP64 && order == Order::any && ncol > 4) {
         // in any order: two narrow recomputed products for 5 to 8 columns of a large structure (20 000 atoms, 8
@@ -1056,7 +1059,7 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     }
     // narrow FP64 products of large structures: recomputing the elements on the vector ALUs
     // (about 16 FP64 operations per pair) beats streaming 8 bytes per pair of the stored copy
-    if (prec == WFQ_PREC_FP64 && ncol <= 4 &&
+    if (prec == WFQ_PREC_FP64 && ncol <= 4 && otf_narrow_fits(s, ncol, order) &&
         s.npad >= (otf_narrow_sym(s, ncol, order) ? kSymNarrowFrom : kOtfNarrowFrom))
         return find_variant(prec, ncol <= 2 ? "otfn2" : "otfn4");
     return order == Order::any && prec != WFQ_PREC_FP64 ? any_variant(s, prec, ncol) : default_variant(prec, ncol);
@@ -1195,7 +1198,7 @@ void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipS
     if (s.t_mode == WFQ_TMODE_OTF) {
         if (prec == WFQ_PREC_FP32)
             otf_tx_f32(s, static_cast<const float*>(X), static_cast<float*>(Y), ncol, st);
-        else if (prec == WFQ_PREC_FP64 && ncol <= otf_narrow_columns(s))
+        else if (otf_takes_narrow(s, prec, ncol, order))
             for (int c0 = 0; c0 < ncol; c0 += 4)
                 otf_narrow_f64(s, static_cast<const double*>(X) + (int64_t)c0 * s.npad,
                                static_cast<double*>(Y) + (int64_t)c0 * s.npad, s.npad, std::min(4, ncol - c0),
@@ -1220,7 +1223,7 @@ void tx_variant_run(const Structure& s, int prec, int var, const void* X, void* 
 
 bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order) {
     if (prec != WFQ_PREC_FP64) return false;
-    if (s.t_mode == WFQ_TMODE_OTF) return ncol <= otf_narrow_columns(s);
+    if (s.t_mode == WFQ_TMODE_OTF) return otf_takes_narrow(s, prec, ncol, order);
     if (ncol > 4) return false;
     return std::strncmp(variants_of(prec)[pick_variant(s, prec, ncol, order)].name, "otfn", 4) == 0;
 }

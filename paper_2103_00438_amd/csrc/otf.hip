@@ -639,12 +639,20 @@ __global__ void __launch_bounds__(256) otf_narrow_sum_kernel(int64_t npad, int n
     }
 }
 
+// Source parts of the one-sided product: about 8 work-groups per compute unit in total, each part at least one
+// source tile; a fixed work space that holds fewer gets as many as it holds (0: not one)
+int64_t narrow_target_blocks(const Structure& s) { return (s.npad + 256 * kNarrowTK - 1) / (256 * kNarrowTK); }
+int64_t narrow_parts(const Structure& s, int ncol, int cus) {
+    const int64_t tblocks = narrow_target_blocks(s);
+    const int64_t want = std::max<int64_t>(1, std::min<int64_t>((8LL * cus + tblocks - 1) / tblocks, 64));
+    return s.split_fixed ? std::min<int64_t>(want, s.split_fixed_bytes / ((uint64_t)ncol * s.npad * sizeof(double))) : want;
+}
+
 template <int NC>
 void launch_otf_narrow(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, int cus, double* Yi,
                        hipStream_t st) {
-    const int64_t tblocks = (s.npad + 256 * kNarrowTK - 1) / (256 * kNarrowTK);
-    // about 8 work-groups per compute unit in total, each part at least one source tile
-    int nparts = (int)std::max<int64_t>(1, std::min<int64_t>((8LL * cus + tblocks - 1) / tblocks, 64));
+    const int64_t tblocks = narrow_target_blocks(s);
+    int nparts = (int)std::max<int64_t>(1, narrow_parts(s, NC, cus));
     const int64_t per = round_up((s.npad + nparts - 1) / nparts, kNarrowTile);
     nparts = (int)((s.npad + per - 1) / per);
     double* part = static_cast<double*>(split_workspace(s, (uint64_t)nparts * NC * s.npad * sizeof(double)));
@@ -940,6 +948,17 @@ bool otf_narrow_sym(const Structure& s, int ncol, Order order) {
     if (order == Order::kept && s.t_mode == WFQ_TMODE_STORED && s.n < 65536) return false;
     const uint64_t cap = s.split_fixed ? s.split_fixed_bytes : std::max(kSplitWsCap, s.sym_ws_allowed);
     return otf_sym_bytes(s, ncol) <= cap;
+}
+
+// In a fixed region that the symmetric sums do not fit, the one-sided form (a pass per 4 columns) against the wide kernel (a
+// pass per 32, eight times as long, no work space), ms: 50 000 atoms, 12 columns 4.3, 32 columns 11.7 / 10.8; 45 600, 24
+// columns 6.9 / 9.8; 52 000, 64 columns 22.1 / 22.2; 60 000, 16 columns in 177 work-groups 12.1 / 12.8.
+bool otf_narrow_fits(const Structure& s, int ncol, Order order) {
+    const int nc = std::min(ncol, 4);
+    if (!s.split_fixed || otf_narrow_sym(s, nc, order)) return true;
+    const int cus = device_cus(s.device), passes = (ncol + 3) / 4;
+    const int64_t groups = narrow_parts(s, nc, cus) * narrow_target_blocks(s);
+    return passes <= (ncol + 31) / 32 * 7 && passes * 2LL * cus <= 12 * groups;
 }
 
 void otf_narrow_f64(const Structure& s, const double* X, double* Y, int64_t ld, int ncol, int cus, hipStream_t st,

@@ -149,3 +149,30 @@ def test_noalloc_in_place_and_overlapping_vectors(lib, nsys):
         y = yr.cpu().numpy() + 1j * yi.cpu().numpy()
         assert np.array_equal(y, ref), (shift, swap)
     h.close()
+
+
+@pytest.mark.parametrize("n,nsys", [(45600, 12), (48640, 7), (50000, 6), (50000, 16), (52000, 32), (58000, 1), (60000, 8),
+                                    (64000, 1)])
+def test_noalloc_matrix_free_fp64_up_to_the_scratch_limit(lib, n, nsys):
+    # The recomputed FP64 product needs work space for its partial sums: what the call's own vectors leave of the scratch
+    # goes from more than the symmetric form needs to less than one part of the one-sided form. Sampled rows
+    # against the oracle's elements, with the bound of the operator test.
+    import torch
+    from oracle.cpp_oracle import CppProblem
+    xyz = geo.jitter(geo.nanotube(10, 10, n // 40), 0.01, 23)
+    P = CppProblem(xyz, GRAPHENE, dense_T=False, build_L=True)
+    rng = np.random.default_rng(nsys)
+    X = rng.standard_normal((nsys, n)) + 1j * rng.standard_normal((nsys, n))
+    z = rng.standard_normal(nsys) + 1j * rng.standard_normal(nsys)
+    h = lib.wfq_build(xyz, GRAPHENE, t_mode="otf")
+    print(f"n={n} nsys={nsys}", flush=True)
+    Y = run_noalloc(lib, torch, h, "fp64", z, X)
+    h.close()
+    rows = np.r_[0, rng.choice(n, 6, replace=False), n - 1]
+    L = P.L[rows]
+    near = np.unique(L.indices)
+    parts = np.concatenate([X.real, X.imag]).T
+    TX, TA = (P.apply_T_rows(near, v) for v in (parts, np.abs(parts)))
+    TX, TA = TX[:, :nsys] + 1j * TX[:, nsys:], TA[:, :nsys] + TA[:, nsys:]
+    zX = z * X.T[rows]
+    assert np.all(np.abs(Y.T[rows] - (L[:, near] @ TX + zX)) <= 1e-12 * (abs(L[:, near]) @ TA + np.abs(zX)))

@@ -313,8 +313,9 @@ int wfq_apply_op(wfq_handle* h, int32_t precision, int32_t S, const double* z_re
  * enqueued on `stream` (a hipStream_t; kernel launches only, no copies, memsets or host
  * synchronisation), so Y is ready when the stream reaches that point. Its intermediates live in one
  * static device array of wfq_noalloc_scratch_bytes() = 256 MiB per GPU, set up by wfq_build on that
- * device and held until the process ends: calls needing more (about 16 nsys N + 256 N (s + 4) bytes
- * for a T copy of s bytes per element, N padded to 256) fail with WFQ_ENOMEM before any work. Every
+ * device and held until the process ends: calls needing more (about 32 nsys N + C N (s + a) bytes
+ * for a T copy of s bytes per element and products of a = max(s, 4), N padded to 256 and C = 2 nsys
+ * to 256) fail with WFQ_ENOMEM before any work. Every
  * call on one GPU shares that array, from any handle: calls whose work overlaps on the device race
  * (order them on one stream or synchronise between them); each call rewrites everything it reads.
  */

@@ -473,9 +473,8 @@ int wfq_apply_T_variant(wfq_handle* h, int32_t precision, int32_t variant, int32
 
 // ---- the allocation-free operator entry point (wfq_apply_op_noalloc)
 //
-// Its scratch (the systems' vectors in the internal order, the shifts, the packed block, the
-// product and the split-k partial tiles) lives in one static device array. Every GPU the library
-// runs on holds its own copy for the life of the process; the host reaches it only through the
+// Its scratch (the packed block, the product, its row pairs and the products' work space) lives in one
+// static device array. Every GPU the library runs on holds its own copy for the life of the process; the host reaches it only through the
 // address hipGetSymbolAddress returns for the current device, kept per device below.
 namespace {
 
@@ -537,22 +536,21 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
         const int64_t rows = round_up(2 * (int64_t)nsys, kColPad);
         const uint64_t es = precision == WFQ_PREC_FP64 ? 8 : precision == WFQ_PREC_FP32 ? 4 : 2;
         const uint64_t os = precision == WFQ_PREC_FP64 ? 8 : 4;
+        // [Y][X][work space of the product]; after the product, from X on: [row pairs, or a result that overlaps an input]
         auto up = [](uint64_t b) { return (b + 255) & ~uint64_t(255); };
-        const uint64_t v_bytes = up((uint64_t)nsys * 4 * np * 8), z_bytes = up((uint64_t)nsys * 16),
-                       s_bytes = up((uint64_t)nsys * 4), x_bytes = up((uint64_t)rows * np * es),
-                       y_bytes = up((uint64_t)rows * np * os);
-        const uint64_t need = v_bytes + z_bytes + s_bytes + x_bytes + y_bytes;
+        const uint64_t x_bytes = up((uint64_t)rows * np * es), y_bytes = up((uint64_t)rows * np * os);
+        // Calls are refused by X, Y and 32 bytes an atom and system (with the shifts and the system numbers). The product has
+        // what X and Y leave; the row pairs (round_up(nsys, 8) <= 2 nsys of them per atom from 4 systems on, up to 16 bytes
+        // each) and the result (16 bytes a system) need no more than those 32.
+        const uint64_t need = x_bytes + y_bytes + up((uint64_t)nsys * 32 * np) + up((uint64_t)nsys * 16) + up((uint64_t)nsys * 4);
         if (need > kNoAllocScratchBytes)
             fail(WFQ_ENOMEM, "wfq_apply_op_noalloc: " + std::to_string(nsys) + " systems of " + std::to_string(S.n) +
                                  " atoms need " + std::to_string(need >> 20) + " MiB of scratch, more than its " +
                                  std::to_string(kNoAllocScratchBytes >> 20) + " MiB");
         WFQ_HIP(hipSetDevice(S.device));
-        char* base = static_cast<char*>(scratch_ptr(S.device));
-        // [row pairs of the products][X][Y][split-k tiles]; the systems' vectors stay in the caller's arrays
-        void* Yr = base;
-        void* X = base + v_bytes + z_bytes + s_bytes;
-        void* Y = base + v_bytes + z_bytes + s_bytes + x_bytes;
-        FixedSplit fs(S, base + need, kNoAllocScratchBytes - need);
+        char* Y = static_cast<char*>(scratch_ptr(S.device));
+        char *X = Y + y_bytes, *Yr = X;
+        FixedSplit fs(S, X + x_bytes, kNoAllocScratchBytes - x_bytes - y_bytes);
         hipStream_t st = static_cast<hipStream_t>(stream);
         load_columns(S, precision, X_re_dev, X_im_dev, nsys, rows, X, st);
         tx_any(S, precision, X, Y, 2 * nsys, st, Order::any);
@@ -568,9 +566,8 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
             for (const double* x : {X_re_dev, X_im_dev}) apart = apart && (y == x || !clash(y, x, vec, vec));
             for (const double* z : {z_re_dev, z_im_dev}) apart = apart && !clash(y, z, vec, zl);
         }
-        double* tmp = static_cast<double*>(Yr);
+        double* tmp = reinterpret_cast<double*>(Yr);
         double *o_re = apart ? Y_re_dev : tmp, *o_im = apart ? Y_im_dev : tmp + vec;
-        // row pairs of 4 systems and more fit their region: round_up(nsys, 8) x 16 B <= nsys x 32 B per atom
         spmm_user(S, precision == WFQ_PREC_FP64, Y, np, apart && nsys >= 4 ? Yr : nullptr, nsys, z_re_dev, z_im_dev, X_re_dev,
                   X_im_dev, o_re, o_im, st);
         if (!apart) {

@@ -176,3 +176,18 @@ def test_noalloc_matrix_free_fp64_up_to_the_scratch_limit(lib, n, nsys):
     TX, TA = TX[:, :nsys] + 1j * TX[:, nsys:], TA[:, :nsys] + TA[:, nsys:]
     zX = z * X.T[rows]
     assert np.all(np.abs(Y.T[rows] - (L[:, near] @ TX + zX)) <= 1e-12 * (abs(L[:, near]) @ TA + np.abs(zX)))
+
+
+def test_noalloc_product_has_the_scratch_that_the_vectors_leave(lib):
+    # 24 columns of 45 600 atoms: X and Y leave 77 MiB of the 256, the symmetric narrow product's sums take 65, so that the
+    # product is the one of wfq_apply_op, bit by bit (no shift: the sparse product then adds nothing after its sums)
+    import torch
+    xyz = geo.jitter(geo.nanotube(10, 10, 1140), 0.01, 24)
+    n, nsys = len(xyz), 12
+    rng = np.random.default_rng(9)
+    X = rng.standard_normal((nsys, n)) + 1j * rng.standard_normal((nsys, n))
+    h = lib.wfq_build(xyz, GRAPHENE, t_mode="otf")
+    y = run_noalloc(lib, torch, h, "fp64", np.zeros(nsys, complex), X)
+    ref = lib.wfq_apply_op(h, "fp64", np.zeros(nsys, complex), X)
+    h.close()
+    assert np.array_equal(y, ref)

@@ -309,7 +309,8 @@ int wfq_apply_op(wfq_handle* h, int32_t precision, int32_t S, const double* z_re
  * wfq_apply_op_noalloc - as wfq_apply_op, for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): it calls no hipMalloc, hipFree or
  * other allocating routine. Inputs and outputs are device pointers: z_re_dev, z_im_dev [nsys];
- * X_re_dev, X_im_dev, Y_re_dev, Y_im_dev [nsys][n] in the caller's atom order. Work is only
+ * X_re_dev, X_im_dev, Y_re_dev, Y_im_dev [nsys][n] in the caller's atom order; Y_re_dev and Y_im_dev
+ * may each overlap any of the inputs, in place or shifted, but not one another. Work is only
  * enqueued on `stream` (a hipStream_t; kernel launches only, no copies, memsets or host
  * synchronisation), so Y is ready when the stream reaches that point. Its intermediates live in one
  * static device array of wfq_noalloc_scratch_bytes() = 256 MiB per GPU, set up by wfq_build on that

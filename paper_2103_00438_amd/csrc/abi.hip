@@ -500,6 +500,16 @@ void* scratch_ptr(int device) {
     return g_scratch_ptr[device];
 }
 
+// a result that was formed in scratch, to the caller's arrays (a kernel: the entry point enqueues nothing else)
+__global__ void __launch_bounds__(256) put_result_kernel(int64_t count, const double* __restrict__ re,
+                                                         const double* __restrict__ im, double* __restrict__ y_re,
+                                                         double* __restrict__ y_im) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= count) return;
+    y_re[q] = re[q];
+    y_im[q] = im[q];
+}
+
 // restores the structure's own split-k work space when the call ends
 struct FixedSplit {
     const Structure& S;
@@ -571,8 +581,9 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
         spmm_user(S, precision == WFQ_PREC_FP64, Y, np, apart && nsys >= 4 ? Yr : nullptr, nsys, z_re_dev, z_im_dev, X_re_dev,
                   X_im_dev, o_re, o_im, st);
         if (!apart) {
-            WFQ_HIP(hipMemcpyAsync(Y_re_dev, o_re, vec * 8, hipMemcpyDeviceToDevice, st));
-            WFQ_HIP(hipMemcpyAsync(Y_im_dev, o_im, vec * 8, hipMemcpyDeviceToDevice, st));
+            hipLaunchKernelGGL(put_result_kernel, dim3((unsigned)((vec + 255) / 256)), dim3(256), 0, st, (int64_t)vec, o_re,
+                               o_im, Y_re_dev, Y_im_dev);
+            WFQ_CHECK_LAUNCH();
         }
         return WFQ_OK;
     });

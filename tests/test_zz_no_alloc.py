@@ -191,3 +191,38 @@ def test_noalloc_product_has_the_scratch_that_the_vectors_leave(lib):
     ref = lib.wfq_apply_op(h, "fp64", np.zeros(nsys, complex), X)
     h.close()
     assert np.array_equal(y, ref)
+
+
+@pytest.mark.parametrize("prec,nsys,shift", [("fp64", 1, None), ("fp64", 5, 0), ("fp64", 5, 3), ("fp32", 9, 3), ("bf16", 2, 3)])
+def test_noalloc_enqueues_kernels_only(lib, prec, nsys, shift):
+    # a captured call (results apart, in place, overlapping the inputs) holds kernel nodes alone: no copies or memsets
+    import ctypes as C
+    import torch
+    xyz, par = _pieces("tube")
+    n = xyz.shape[0]
+    h = lib.wfq_build(xyz, par, store=tuple({"fp64", prec}))
+    re = torch.zeros(2 * nsys * n + 8, dtype=torch.float64, device="cuda:0")
+    im = torch.zeros_like(re)
+    z = torch.ones(nsys, dtype=torch.float64, device="cuda:0")
+    view = lambda b, o: b[o:o + nsys * n].view(nsys, n)
+    off = nsys * n if shift is None else shift
+    call = lambda: lib.wfq_apply_op_noalloc(h, prec, z, z, view(re, 0), view(im, 0), view(re, off), view(im, off),
+                                            stream=torch.cuda.current_stream().cuda_stream)
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call()
+    with open("/proc/self/maps") as f:
+        hip = C.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+    graph, count = C.c_void_p(g.raw_cuda_graph()), C.c_size_t(0)
+    assert hip.hipGraphGetNodes(graph, None, C.byref(count)) == 0 and count.value >= 3
+    nodes = (C.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(count)) == 0
+    kinds = []
+    for node in nodes:
+        kind = C.c_int(-1)
+        assert hip.hipGraphNodeGetType(C.c_void_p(node), C.byref(kind)) == 0
+        kinds.append(kind.value)
+    h.close()
+    assert set(kinds) == {0}, kinds   # hipGraphNodeTypeKernel

@@ -192,7 +192,7 @@ def measured_traffic(workload, kernel):
     return None
 
 
-def roofline_of(stats, prec, otf, n, workload=None, split=False):
+def roofline_of(stats, prec, otf, n, workload=None):
     if otf:
         # Per pair the kernel evaluates T_ij on the vector ALUs (about 10 lane-slots for a far pair:
         # 3 sub, 1 mul, 2 fma and a quarter-rate rsqrt; about 38 near the diagonal) and accumulates
@@ -237,7 +237,7 @@ def roofline_of(stats, prec, otf, n, workload=None, split=False):
                     avg_launch_ms=st["ms"] / max(1, st["launches"]),
                     avg_bytes_per_launch=st["bytes"] / max(1, st["launches"]))
     st = stats[dom]
-    prec = "fp32_split" if split and dom == "tx_gemm_f32" else classes[dom]
+    prec = classes[dom]
     achieved = st["flops"] / (st["ms"] / 1e3) / 1e12 if st["ms"] > 0 else 0.0
     return dict(bound="mfma", achieved=achieved, peak=PEAKS[prec], unit="TFLOP/s", frac=achieved / PEAKS[prec],
                 traffic=measured_traffic(workload, dom), kernel=dom, launches=st["launches"], avg_launch_ms=st["ms"] / max(1, st["launches"]),
@@ -297,9 +297,7 @@ def bench_batched(args, wl, wfq, torch):
     statuses = sorted(set(r["status"] for r in last["info"]))
     relres_max = max(r["relres"] for r in last["info"])
     prec_end = sorted(set(r["precision"] for r in last["info"]))
-    # split shapes (s<columns>...) among the tuned ones: their products run on the FP16 matrix cores
-    split = tune is not None and any(v[0] == "s" and v[1].isdigit() for v in tune["chosen"])
-    roofline = roofline_of(stats, prec, otf, wl.n, wl.name, split)
+    roofline = roofline_of(stats, prec, otf, wl.n, wl.name)
 
     extra = {}
     if otf and not args.ref_systems:

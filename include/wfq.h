@@ -329,14 +329,19 @@ uint64_t wfq_noalloc_scratch_bytes(void);
 int wfq_rhs(wfq_handle* h, const double* dirs, int32_t n_dir, double E0, double* out);
 
 /* ------------------------------------------------------------------ block-product tuning
- * The block product T X has several kernel shapes (MFMA tiles of different sizes, a narrow
- * streaming kernel). wfq_tx_variants lists them for a precision: *count entries, names[k] (static
- * strings) and max_ncol[k] (largest column count the shape accepts); NULL arrays query *count.
+ * The block product T X has several kernel shapes: matrix-core tiles staged through LDS (m...) or read
+ * in the operands' own layout (f..., FP64), FP32 products as three FP16 ones (s...), narrow ones that
+ * stream T (skinny...) or recompute it (otfn..., FP64). wfq_tx_variants lists them for a precision:
+ * *count entries, names[k] (static strings) and max_ncol[k] (largest column count the shape accepts);
+ * NULL arrays query *count.
  * wfq_tune times every applicable shape on random columns for each ncols[q] (reps launches each on
  * the handle's stream), writes the average times to ms[q][k] (negative: not applicable) and keeps
- * the fastest shape per ncol in the handle; later products with n columns use the shape tuned for
- * the smallest tuned ncol >= n (the largest tuned one beyond that). Untuned handles use a built-in
- * choice by column count. */
+ * the fastest per ncol in the handle, once for the solves and once for the operator entry points
+ * (wfq_apply_*); chosen[q] is the solves' one. The solves never take the s... shapes, whose rounding
+ * would move their results, and run the otfn... shapes with another order of sums than the operator
+ * entry points (ms is its time). Later products with n columns use the shape tuned for the smallest
+ * tuned ncol >= n (the largest tuned one beyond that). Untuned handles use a built-in choice by
+ * column count and size. */
 int wfq_tx_variants(int32_t precision, int32_t* count, const char** names, int32_t* max_ncol);
 int wfq_tune(wfq_handle* h, int32_t precision, const int32_t* ncols, int32_t n_ncols, int32_t reps, double* ms,
              int32_t* chosen);

@@ -692,7 +692,8 @@ int wfq_tune(wfq_handle* h, int32_t precision, const int32_t* ncols, int32_t n_n
             tune_tx(S, precision, ncols[q], reps, row.data(), h->stream);
             if (ms)
                 for (int k = 0; k < nv; ++k) ms[(size_t)q * nv + k] = row[k];
-            if (chosen) chosen[q] = S.tuned[precision].count(ncols[q]) ? S.tuned[precision][ncols[q]] : -1;
+            const auto& kept = S.tuned[precision][(int)Order::kept];
+            if (chosen) chosen[q] = kept.count(ncols[q]) ? kept.at(ncols[q]) : -1;
         }
         return WFQ_OK;
     });

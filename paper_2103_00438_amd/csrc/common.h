@@ -105,7 +105,8 @@ struct Structure {
     uint64_t budget = 0;
     uint64_t bytes = 0;          // device bytes held by this structure
     bool connected = true;
-    std::map<int, int> tuned[3];   // per precision: ncol -> block-product variant chosen by tune_tx
+    // per precision and order of sums: ncol -> block-product variant chosen by tune_tx
+    std::map<int, int> tuned[3][2];
     // partial tiles of split-k block products (grown on demand, at most kSplitWsCap bytes)
     mutable void* split_ws = nullptr;
     mutable uint64_t split_ws_bytes = 0;
@@ -204,10 +205,11 @@ bool tx_is_otf_narrow(const Structure& s, int prec, int ncol, Order order);
 // true when a product of ncol columns streams the stored T with the vector ALUs
 bool tx_is_skinny(const Structure& s, int prec, int ncol, Order order);
 // T X with the stored copy of T in `prec`, or recomputed on the fly when the structure is matrix-free.
-// In any order an untuned FP32 product may go through the FP16 matrix cores (operands split, the error against
-// 64 bits smaller than the FP32 instruction's). In the kept order it does not: the FP32 instruction's rounding is
-// systematic and decides at which restart a system near the tolerance stops, so that another product moves the
-// results by as much as the tolerance allows; a tuned handle takes whichever shape measured fastest. (Recomputed
+// In any order an FP32 product may go through the FP16 matrix cores (operands split, the error against
+// 64 bits no larger than the FP32 instruction's). In the kept order it does not, in tuned handles neither: the FP32
+// instruction's rounding is systematic and decides at which restart a system near the tolerance stops, so that another
+// product moves the results by as much as the tolerance allows. Among the other shapes a tuned handle takes
+// whichever measured fastest. (Recomputed
 // FP32 products always take the split: the kernel that they replace summed with compensation too, and solves to
 // 1e-10 move by about 1e-10.)
 void tx_any(const Structure& s, int prec, const void* X, void* Y, int ncol, hipStream_t st, Order order = Order::kept);

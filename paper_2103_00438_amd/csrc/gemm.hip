@@ -979,6 +979,9 @@ int default_variant(int prec, int ncol) {
     return pick_name(prec, prec == WFQ_PREC_FP64 ? f64 : prec == WFQ_PREC_FP32 ? f32 : b16, ncol);
 }
 
+// FP32 products through the FP16 matrix cores: applications of the operator only, no solves
+bool is_split(const char* name) { return name[0] == 's' && name[1] >= '0' && name[1] <= '9'; }
+
 // Built-in choice in any order for FP32 and BF16, by padded size too: the fastest shapes measured at 700, 1 000, 1 400,
 // 2 000, 2 800, 4 000, 5 200, 6 600, 8 000, 10 000 and 20 000 atoms. A small T has few tiles of many rows, so
 // narrower and shorter ones fill the chip; us against the kept order's shape: FP32 2 000 atoms 15 / 26 at 64 columns,
@@ -1017,8 +1020,7 @@ int any_variant(const Structure& s, int prec, int ncol) {
     while (s.npad >= r->below) ++r;
     const int k = pick_name(prec, r->t, ncol);
     // no room for the split X, or a T outside the split's range: the FP32 instruction's shape
-    const char* name = variants_of(prec)[k].name;
-    if (name[0] == 's' && name[1] >= '0' && name[1] <= '9' && (!split_scale_ok(s) || !split_fits(s, s.npad, ncol)))
+    if (is_split(variants_of(prec)[k].name) && (!split_scale_ok(s) || !split_fits(s, s.npad, ncol)))
         return default_variant(prec, ncol);
     return k;
 }
@@ -1036,16 +1038,22 @@ bool otf_takes_narrow(const Structure& s, int prec, int ncol, Order order) {
     return prec == WFQ_PREC_FP64 && ncol <= otf_narrow_columns(s) && otf_narrow_fits(s, ncol, order);
 }
 
-int pick_variant(const Structure& s, int prec, int ncol, Order order) {
-    const auto& tuned = s.tuned[prec];
-    // the tuned entry with the smallest ncol >= this one (or the largest tuned one), used only when
-    // it was tuned for a comparable width (within a factor of two)
+// The tuned entry with the smallest ncol >= this one (or the largest tuned one), used only when
+// it was tuned for a comparable width (within a factor of two); -1 without one
+int tuned_variant(const Structure& s, int prec, int ncol, Order order) {
+    const auto& tuned = s.tuned[prec][(int)order];
     auto it = tuned.lower_bound(ncol);
     if (it == tuned.end() && !tuned.empty()) it = std::prev(tuned.end());
     if (it != tuned.end() && it->first <= 2 * ncol && ncol <= 2 * it->first) {
         const Variant& v = variants_of(prec)[it->second];
         if (ncol <= v.max_ncol && (v.launch || otf_narrow_fits(s, ncol, order))) return it->second;
     }
+    return -1;
+}
+
+int pick_variant(const Structure& s, int prec, int ncol, Order order) {
+    const int tuned = tuned_variant(s, prec, ncol, order);
+    if (tuned >= 0) return tuned;
     if (prec == WFQ_PREC_FP64 && order == Order::any && ncol > 4) {
         // in any order: two narrow recomputed products for 5 to 8 columns of a large structure (20 000 atoms, 8
         // columns: 380 us, streamed through the matrix cores 576; 10 000: 144 and 161; 8 000: 138 and 94), and the fragment-layout shapes (figures at
@@ -1085,13 +1093,13 @@ void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, 
 
 // The product of the shape that pick_variant names. In the kept order the default shapes are those of a 20 000-atom T;
 // on a small T their tiles are few, and a smaller tile gives the same sums (k is walked in the same order inside a
-// stage of any size) when it divides k as they do. FP64, 989 atoms: 60 us
+// stage of any size) when it divides k as they do. A tuned shape runs as it was measured. FP64, 989 atoms: 60 us
 // in the old shape and 14 in the new at 80 columns, 21 and 14 at 48.
 void run_picked(const Structure& s, int prec, int ncol, Order order, const void* X, void* Y, hipStream_t st) {
     const int var = pick_variant(s, prec, ncol, order);
     const Variant& v = variants_of(prec)[var];
     int other = -1;
-    if (order == Order::kept && v.parts && var == default_variant(prec, ncol)) {
+    if (order == Order::kept && v.parts && tuned_variant(s, prec, ncol, order) < 0) {
         if (prec == WFQ_PREC_FP64 && ncol > 32) {
             if (ncol <= (s.npad < 3072 ? 192 : s.npad < 10240 ? 112 : 0)) other = find_variant(prec, "m32n128");
             else if (s.npad < 3072) other = find_variant(prec, "m64n128i");
@@ -1238,8 +1246,9 @@ const char* tx_variant_name(int precision, int k) { return variants_of(precision
 int tx_variant_max_ncol(int precision, int k) { return variants_of(precision)[k].max_ncol; }
 
 // Time every variant that accepts ncol (reps launches each, after one warm-up launch) on random
-// device data and keep the fastest for this ncol in s.tuned. ms[k] = average time of variant k
-// (negative when the variant does not apply).
+// device data and keep the fastest for this ncol in s.tuned, for the solves (kept order, no FP16-split shape) and for any
+// order. ms[k] = average time of variant k (negative when the variant does not apply); the recomputed shapes
+// run another kernel in each order and are timed in both, ms[k] being the kept order's.
 void tune_tx(Structure& s, int prec, int ncol, int reps, double* ms, hipStream_t st) {
     const int64_t rows = round_up(ncol, kColPad);
     const int es = prec == WFQ_PREC_FP64 ? 8 : prec == WFQ_PREC_FP32 ? 4 : 2;
@@ -1265,30 +1274,37 @@ void tune_tx(Structure& s, int prec, int ncol, int reps, double* ms, hipStream_t
     WFQ_HIP(hipEventCreate(&a));
     WFQ_HIP(hipEventCreate(&b));
     const auto& vs = variants_of(prec);
-    double best = 1e300;
-    int best_k = -1;
-    for (size_t k = 0; k < vs.size(); ++k) {
-        ms[k] = -1.0;
-        if (ncol > vs[k].max_ncol || (vs[k].bm == 0 && ncol > vs[k].max_ncol)) continue;
-        run_variant(s, prec, (int)k, X, Y, ncol, st);
+    auto time_of = [&](size_t k, Order order) {
+        run_variant(s, prec, (int)k, X, Y, ncol, st, order);
         WFQ_HIP(hipEventRecord(a, st));
-        for (int r = 0; r < reps; ++r) run_variant(s, prec, (int)k, X, Y, ncol, st);
+        for (int r = 0; r < reps; ++r) run_variant(s, prec, (int)k, X, Y, ncol, st, order);
         WFQ_HIP(hipEventRecord(b, st));
         WFQ_HIP(hipEventSynchronize(b));
         float t = 0.f;
         WFQ_HIP(hipEventElapsedTime(&t, a, b));
-        ms[k] = t / reps;
-        if (ms[k] < best) {
-            best = ms[k];
-            best_k = (int)k;
-        }
+        return (double)t / reps;
+    };
+    double best[2] = {1e300, 1e300};
+    int best_k[2] = {-1, -1};
+    auto keep = [&](Order order, size_t k, double t) {
+        if (t >= best[(int)order]) return;
+        best[(int)order] = t;
+        best_k[(int)order] = (int)k;
+    };
+    for (size_t k = 0; k < vs.size(); ++k) {
+        ms[k] = -1.0;
+        if (ncol > vs[k].max_ncol) continue;
+        ms[k] = time_of(k, Order::kept);
+        keep(Order::any, k, vs[k].launch ? ms[k] : time_of(k, Order::any));
+        if (!is_split(vs[k].name)) keep(Order::kept, k, ms[k]);
     }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     (void)hipFree(X);
     (void)hipFree(Y);
     (void)hipFree(X64);
-    if (best_k >= 0) s.tuned[prec][ncol] = best_k;
+    for (int o = 0; o < 2; ++o)
+        if (best_k[o] >= 0) s.tuned[prec][o][ncol] = best_k[o];
     ++s.epoch;
 }
 

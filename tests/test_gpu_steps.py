@@ -275,3 +275,41 @@ def test_default_fp64_product_at_its_size_limits(lib, n, ncol):
     h.close()
     # each sum of n products is within n u of sum |T||X| <= n max|T| max|X|: two of them
     assert np.abs(Y - ref).max() <= 2 * n * UNIT["fp64"] * np.abs(X).sum(axis=1).max() * GRAPHENE["eta"]
+
+
+def test_tuned_narrow_products_run_the_kernel_that_was_timed(lib):
+    # 5 000 atoms, the two columns of one system: recomputed, they take about 22 us with both rows of a pair at once, 53
+    # with each row by itself, streamed 31. A solve runs the second form, so that streaming is what tuning has
+    # to choose for it; a row's sums are the same in every streaming shape, and with them the solve's results.
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(10, 10, 125), 0.01, 5)
+    n = len(xyz)
+    h = lib.wfq_build(xyz, GRAPHENE)
+    X = np.random.default_rng(2).standard_normal((2, n))
+    solve = lambda: lib.wfq_solve(h, [0.4], [[0.0, 0.0, 1.0]], 1e-8, restart=30, precision="fp64")
+    ref = solve()
+    tune = lib.wfq_tune(h, "fp64", [2], reps=20)
+    name = dict(zip(tune["variants"], tune["ms"][0]))
+    assert tune["chosen"][0] == min((k for k in name if name[k] > 0), key=name.get)
+    assert not tune["chosen"][0].startswith("otfn"), name
+    out = solve()
+    if tune["chosen"][0].startswith("skinny"):
+        assert np.array_equal(out["q"], ref["q"])
+    # the operator takes the recomputed product with both rows of a pair at once, the faster one there
+    assert np.array_equal(lib.wfq_apply_T(h, "fp64", X), lib.wfq_apply_T_variant(h, "fp64", "otfn2", X))
+    h.close()
+
+
+def test_tuned_fp32_solves_keep_the_fp32_instruction(lib):
+    # at 6 000 atoms and 128 columns an FP16-split shape is fastest: tuning keeps it for the operator entry points only
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(10, 10, 150), 0.01, 6)
+    h = lib.wfq_build(xyz, GRAPHENE)
+    X = np.random.default_rng(3).standard_normal((128, len(xyz)))
+    tune = lib.wfq_tune(h, "fp32", [128], reps=5)
+    name = dict(zip(tune["variants"], tune["ms"][0]))
+    split = [k for k in name if k[0] == "s" and k[1].isdigit()]
+    assert split and all(name[k] > 0 for k in split)
+    assert tune["chosen"][0] not in split
+    assert tune["chosen"][0] == min((k for k in name if name[k] > 0 and k not in split), key=name.get)
+    best = min((k for k in name if name[k] > 0), key=name.get)
+    assert np.array_equal(lib.wfq_apply_T(h, "fp32", X), lib.wfq_apply_T_variant(h, "fp32", best, X))
+    h.close()

@@ -153,7 +153,12 @@ typedef struct {
                             batched GMRES(restart) with FP64 refinement (usually: one FP64 residual).
                             Device memory per direction: 8 (shift_dim + 1) N_p bytes for the basis, and
                             as much again in FP64 solves, which keep the products T u_j so that the FP64
-                            residual of the shared-basis iterates needs no further product of T. */
+                            residual of the shared-basis iterates needs no further product of T.
+                            FP64 products of a stored T of 4 608 to 65 535 atoms are summed in another
+                            order in solves of three and more directions (faster; results move by 1e-11
+                            to 1e-10 of their size). Of up to three directions, one's results do not
+                            hang on the others; of more, the products' shape, and with it the order,
+                            goes by how many directions are still active. */
     int32_t graphs;      /* nonzero: for structures of at most 8192 atoms (whose inner steps are read back in
                             chunks of 8) and for the multi-shift phase, a chunk of steps whose launch
                             sequence repeats (same first step, length and list sizes) is captured as a HIP

@@ -195,7 +195,7 @@ void build_rhs(const Structure& s, const double* dirs_dev, int n_dir, double E0,
 // change of their order: by up to 6e-7 for the field normal to a ribbon, 1e-9..3e-9 for the fields across a tube. any: the
 // fastest product of no larger error against 64 bits. The operator entry points ask for it, and the multi-shift
 // solves of three and more field directions, whose results the strongly excited directions dominate (they move by
-// 1e-11..1e-10 then). Matrix-free structures take any: their solves move by up to 3e-10.
+// 1e-11..1e-10 then), to their end, however many directions are still active. Matrix-free structures take any: their solves move by up to 3e-10.
 enum class Order { kept, any };
 void tx_f64(const Structure& s, const double* X, double* Y, int ncol, hipStream_t st, Order order = Order::kept);
 void tx_f32(const Structure& s, const float* X, float* Y, int ncol, hipStream_t st, Order order = Order::kept);

@@ -1128,7 +1128,7 @@ void msgmres_phase(const Structure& S, Work& w, std::vector<SysState>& ss, doubl
                 // z = L T u_j (one real column per direction) into slot j + 1; the first vectors' norms are known,
                 // the later ones' are the block sums of the update sweep
                 const double* pn = j > 0 ? nrm : nullptr;
-                const Order order = cur == WFQ_PREC_FP64 && na >= 3 ? Order::any : Order::kept;
+                const Order order = cur == WFQ_PREC_FP64 && w.n_dir >= 3 ? Order::any : Order::kept;   // of the whole phase
                 const bool direct = cur == WFQ_PREC_FP64 && na <= 4 && tx_is_skinny(S, cur, na, order);
                 double* yi = nullptr;
                 tm.begin(st);

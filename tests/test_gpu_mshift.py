@@ -179,3 +179,19 @@ def test_multishift_beyond_the_one_launch_step(lib):
             info = out["info"][a * 3 + k]
             assert info["cycles"] == 0 and info["relres"] <= tol, (a, k, info)
             assert P.residual(om[a], np.eye(3)[k], out["q"][a, k]) <= 1.01 * tol + 1e-13, (a, k, info)
+
+
+def test_multishift_direction_does_not_depend_on_when_the_others_converge(lib):
+    # stored T of a 5 000-atom ribbon, three directions: the field normal to it is done some 12 steps before the one along
+    # it. The charges of that one are the same, bit by bit, when two directions close to it keep it company.
+    xyz = wi.geometry.jitter(wi.geometry.graphene_ribbon(60.0, 5000), 0.01, seed=8)
+    h = lib.wfq_build(xyz, GRAPHENE)
+    solve = lambda dirs: lib.wfq_solve(h, [1.0], np.array(dirs, float), 1e-9, algorithm="msgmres", restart=30,
+                                       precision="fp64", shift_dim=400)
+    apart = solve([[1, 0, 0], [0, 1, 0], [0, 0, 1]])
+    close = solve([[1, 0, 0], [0.96, 0.28, 0], [0.96, 0, 0.28]])
+    h.close()
+    assert apart["status"] == 0 and close["status"] == 0
+    steps = [[i["iters"] for i in out["info"]] for out in (apart, close)]
+    assert steps[0][2] + 8 < steps[0][0] and steps[1][2] + 8 >= steps[1][0], steps
+    assert np.array_equal(apart["q"][:, 0], close["q"][:, 0])

@@ -165,12 +165,16 @@ __global__ void __launch_bounds__(256) spmm_sys_kernel(int64_t n, int64_t npad, 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     constexpr int nrg = R / RW < 4 ? R / RW : 4;   // row groups; the waves beyond them take other systems
     static_assert(nrg * RW == R, "a work-group's waves cover its rows");
-    const int lr = lane / (L * Q), g = lane % L, part = lane % (L * Q) / L;
+    // in pairs the systems of a row lie side by side, in planes without parts the rows of a system
+    constexpr bool kByRows = !PAIRS && Q == 1;
+    static_assert(!kByRows || RW * L == 64, "planes: every lane has a row and a system");
+    const int lr = kByRows ? lane % RW : lane / (L * Q), g = kByRows ? lane / RW : lane % L, part = lane % (L * Q) / L;
     if (lr >= RW) return;   // fewer rows than lanes (long neighbour lists, few systems)
     const int r = wave % nrg * RW + lr;
     const int64_t i = r0 + r;
     const int k_end = min(nsys, (int)(blockIdx.y + 1) * per_group);
     for (int kb = (int)blockIdx.y * per_group + wave / nrg * L * SPL; kb < k_end; kb += 4 / nrg * L * SPL) {
+        if (kByRows && kb + SPL * g >= k_end) break;
         int k[SPL];   // lanes past the end repeat the last system and store nothing
         double ar[SPL], ai[SPL];
         const int kl = kb + SPL * g < k_end ? kb + SPL * g : kb;
@@ -220,26 +224,41 @@ void launch_spmm_tile(const Structure& S, const YE* Y, int64_t ld, int nsys, con
                        st, S.n, S.npad, S.ell_w, S.ell_col, S.ell_val, Y, ld, nsys, per_group, out);
     WFQ_CHECK_LAUNCH();
 }
+// Rows of a work-group: the most whose ELL rows leave four work-groups to a CU's LDS, up to 32 (a row group per wave)
 template <typename YE, int L, int Q, int SPL, bool PAIRS, typename Out>
 void launch_spmm_sys(const Structure& S, const YE* Y, int64_t ld, int nsys, const Out& out, hipStream_t st) {
-    // the most rows (up to 32: a row group per wave) whose ELL rows leave four work-groups to a CU's LDS
     const size_t per_row = (size_t)S.ell_w * 12;
-    if (L * Q == 1 && per_row * 64 <= 40960) launch_spmm_tile<YE, L, Q, SPL, L * Q == 1 ? 64 : 32, PAIRS, true>(S, Y, ld, nsys, out, st);
-    else if (per_row * 32 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 32, PAIRS, true>(S, Y, ld, nsys, out, st);
+    if (per_row * 32 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 32, PAIRS, true>(S, Y, ld, nsys, out, st);
     else if (per_row * 16 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 16, PAIRS, true>(S, Y, ld, nsys, out, st);
     else if (per_row * 8 <= 40960) launch_spmm_tile<YE, L, Q, SPL, 8, PAIRS, true>(S, Y, ld, nsys, out, st);
     else launch_spmm_tile<YE, L, Q, SPL, 8, PAIRS, false>(S, Y, ld, nsys, out, st);
+}
+// Planes, a row's entries in one sum: up to 64 rows, one system per wave (neighbouring rows' neighbours share lines). Where
+// long lists leave fewer rows than lanes, the others take further systems: spheres with 321 neighbours in FP64, us with
+// the lanes idle / taken, 5 979 atoms 4 systems 68 / 29, 40 systems 583 / 135; 1 505 atoms 40 systems 161 / 51; lists too
+// long for LDS, 5 979 atoms, 40 systems 4 092 / 1 224.
+template <typename YE, typename Out>
+void launch_spmm_planes(const Structure& S, const YE* Y, int64_t ld, int nsys, const Out& out, hipStream_t st) {
+    const size_t per_row = (size_t)S.ell_w * 12;
+    if (per_row * 64 <= 40960) launch_spmm_tile<YE, 1, 1, 1, 64, false, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 32 <= 40960) launch_spmm_tile<YE, 2, 1, 1, 32, false, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 16 <= 40960) launch_spmm_tile<YE, 4, 1, 1, 16, false, true>(S, Y, ld, nsys, out, st);
+    else if (per_row * 8 <= 40960) launch_spmm_tile<YE, 8, 1, 1, 8, false, true>(S, Y, ld, nsys, out, st);
+    else launch_spmm_tile<YE, 8, 1, 1, 8, false, false>(S, Y, ld, nsys, out, st);
 }
 
 // Yr != NULL (room for round_up(nsys, 8) pairs per row): from four systems on the product's planes are first turned
 // into row pairs there. FP64 gains from four systems on at every size (3 043-atom sphere, 4 systems: 52 -> 45 us for the
 // whole operator, 12: 92 -> 56; 600-atom tube, 12: 28 -> 26). FP32 planes are half as long, and the extra
 // launch only pays from about 4 M gathered pairs (4 000-atom tube, 12 systems, 2.4 M: 30 -> 33 us; sphere, 6
-// systems, 4.0 M: equal; 12 systems: 62 -> 50; 16 000-atom tube, 12 systems, 9.6 M: 222 -> 214).
+// systems, 4.0 M: equal; 12 systems: 62 -> 50; 16 000-atom tube, 12 systems, 9.6 M: 222 -> 214). In the solves two
+// systems are enough where lists are too long for 64 rows, in whose planes lanes would idle (10 005-atom sphere, FP64, 2
+// systems: 57 -> 37 us).
 template <typename YE, typename Out>
 void spmm_sys(const Structure& S, const YE* Y, int64_t ld, void* Yr, int nsys, const Out& out, hipStream_t st) {
     constexpr bool f64 = std::is_same<YE, double>::value;
-    if (Yr && nsys >= 4 && (f64 || S.npad * S.ell_w * nsys >= (int64_t)4 << 20)) {
+    const bool idle = !Out::kParts && nsys >= 2 && (size_t)S.ell_w * 12 * 64 > 40960;   // planes would leave lanes idle
+    if (Yr && (nsys >= 4 || idle) && (f64 || S.npad * S.ell_w * nsys >= (int64_t)4 << 20)) {
         const int64_t ldk = (nsys + 7) / 8 * 8;
         hipLaunchKernelGGL(row_pairs_kernel<YE>, dim3((unsigned)(S.npad / 32), (unsigned)(ldk / 8)), dim3(256), 0, st, Y, ld,
                            nsys, ldk, static_cast<typename Pair2<YE>::type*>(Yr));
@@ -249,8 +268,7 @@ void spmm_sys(const Structure& S, const YE* Y, int64_t ld, void* Yr, int nsys, c
         else if (f64 || nsys <= 8) launch_spmm_sys<YE, 8, 1, 1, true>(S, P, ldk, nsys, out, st);
         else launch_spmm_sys<YE, 8, 1, 2, true>(S, P, ldk, nsys, out, st);
     } else if (!Out::kParts || nsys > 4) {
-        // planes: one row per lane, one system per wave (neighbouring rows' neighbours share lines)
-        launch_spmm_sys<YE, 1, 1, 1, false>(S, Y, ld, nsys, out, st);
+        launch_spmm_planes(S, Y, ld, nsys, out, st);
     } else if (nsys == 1) {
         launch_spmm_sys<YE, 1, 8, 1, false>(S, Y, ld, nsys, out, st);
     } else if (nsys == 2) {

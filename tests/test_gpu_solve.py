@@ -128,3 +128,23 @@ def test_gmres_steps_over_chunks_columns_and_restarts(lib, n, n_omega, restart, 
     P = O.Problem(xyz, GRAPHENE)
     for a in (0, n_omega // 2, n_omega - 1):
         assert P.residual(om[a], e[0], out["q"][a, 0]) <= 1.01 * tol + 1e-13, (a, out["info"][a])
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("radius,fermi_d,entries,nsys", [
+    (14.5, 20.0, 87, 3), (14.5, 14.0, 201, 5), (14.5, 12.0, 321, 1), (14.5, 12.0, 321, 9), (14.5, 6.0, 767, 9),
+    (33.0, 12.0, 321, 2)])
+def test_solves_with_long_neighbour_lists(lib, radius, fermi_d, entries, nsys, prec):
+    # lists that leave the sparse product 32, 16 or 8 rows a work-group, or too long for its LDS, and the lanes beyond the
+    # rows to further systems (fewer of them than there are, and as many); two systems above 8 192 rows
+    xyz = wi.geometry.jitter(wi.geometry.fcc_sphere(radius), 0.01, 22)
+    par = dict(wi.workloads.FCC_METAL, fermi_d=fermi_d)
+    P = O.Problem(xyz, par)
+    assert np.bincount(P.L.nonzero()[0]).max() == entries
+    om, tol = np.linspace(2.0, 4.0, nsys), 1e-8
+    h = lib.wfq_build(xyz, par)
+    out = lib.wfq_solve(h, om, [[0.0, 0.6, 0.8]], tol, restart=60, precision=prec)
+    h.close()
+    assert out["status"] == 0, out["info"]
+    for a in range(nsys):
+        assert P.residual(om[a], np.array([0.0, 0.6, 0.8]), out["q"][a, 0]) <= 1.01 * tol + 1e-13, (a, out["info"][a])

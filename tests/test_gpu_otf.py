@@ -266,3 +266,18 @@ def test_one_sided_narrow_product_when_the_sums_do_not_fit(lib):
     P = CppProblem(xyz, par, dense_T=False, build_L=False)
     rows = np.r_[np.arange(0, n, 9973), n - 1]
     assert np.all(np.abs(Y[:, rows].T - P.apply_T_rows(rows, X.T)) <= 1e-13 * P.apply_T_rows(rows, np.abs(X).T))
+
+
+@pytest.mark.parametrize("ncol", [1, 33])
+def test_wide_fp32_product_is_as_accurate_as_claimed(lib, tube, ncol):
+    # Columns of one scale. An element is off by ERF_REL and 8 roundings at most (8e-7), a product of two by 2^-22 more, and the
+    # sums over tiles of 64 are compensated: about 1e-6 of a column's norm if every element were at its worst. Without
+    # a cross term of the split operands it would be 1.1e-4 and more.
+    xyz, P = tube
+    h = lib.wfq_build(xyz, GRAPHENE, t_mode="otf")
+    X = np.random.default_rng(3000 + ncol).standard_normal((ncol, P.n))
+    Y = lib.wfq_apply_T(h, "fp32", X)
+    h.close()
+    ref = round_to("fp32", X) @ P.T
+    err = np.linalg.norm(Y - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= 2e-6, err.max()

@@ -313,3 +313,17 @@ def test_tuned_fp32_solves_keep_the_fp32_instruction(lib):
     best = min((k for k in name if name[k] > 0), key=name.get)
     assert np.array_equal(lib.wfq_apply_T(h, "fp32", X), lib.wfq_apply_T_variant(h, "fp32", best, X))
     h.close()
+
+
+@pytest.mark.parametrize("ncol", [1, 33])
+def test_fp16_split_product_is_as_accurate_as_claimed(lib, handle, tube, ncol):
+    # Columns of one scale. Of each product of two elements at most 2^-22 is lost, of either sign, and the 3 n / 32 roundings of
+    # the running sum add at most 2^-24 (3 n / 64)^(1/2): below 7e-7 of a column's norm in all. Without one of the two cross
+    # terms the error is 1.1e-4 and more (the same inputs in numpy); 2e-6 tells them apart.
+    _, P = tube
+    X = np.random.default_rng(2000 + ncol).standard_normal((ncol, P.n))
+    ref = round_to("fp32", X) @ round_to("fp32", P.T)
+    for name in [v[0] for v in lib.wfq_tx_variants("fp32") if v[0][0] == "s" and v[0][1].isdigit()]:
+        Y = lib.wfq_apply_T_variant(handle, "fp32", name, X)
+        err = np.linalg.norm(Y - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= 2e-6, (name, err.max())

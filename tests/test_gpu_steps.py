@@ -327,3 +327,23 @@ def test_fp16_split_product_is_as_accurate_as_claimed(lib, handle, tube, ncol):
         Y = lib.wfq_apply_T_variant(handle, "fp32", name, X)
         err = np.linalg.norm(Y - ref, axis=1) / np.linalg.norm(ref, axis=1)
         assert err.max() <= 2e-6, (name, err.max())
+
+
+@pytest.mark.parametrize("n,ncol,tile", [(1289, 256, "m128n256w8k64"), (1289, 128, "m96n256w8"), (1721, 40, "m64n128k256i"),
+                                         (1721, 64, "m64n128k256i"), (2315, 48, "m64n128k256i"), (1289, 384, "m128n256w8k64")])
+def test_small_fp32_products_are_no_less_accurate_than_a_large_tile(lib, n, ncol, tile):
+    # the operator's FP32 products of small structures run in smaller tiles than a large structure's; after L, which takes the
+    # slowly varying part away, the result is as close to the 64-bit one (2 % for the order of the sums)
+    geo = wi.geometry
+    xyz = geo.jitter(geo.fcc_sphere(geo.A_FCC * (3 * n / (16 * np.pi)) ** (1 / 3)), 0.02, 5)
+    assert len(xyz) == n
+    par = wi.workloads.FCC_METAL
+    P = O.Problem(xyz, par)
+    X = np.random.default_rng(n).standard_normal((ncol, n))
+    X = 2 * X - np.roll(X, 1, axis=1) - np.roll(X, -1, axis=1)
+    h = lib.wfq_build(xyz, par, store=("fp32",))
+    exact = P.L @ (X @ P.T).T
+    err = [np.linalg.norm(P.L @ Y.T - exact) for Y in (lib.wfq_apply_T(h, "fp32", X), lib.wfq_apply_T_variant(h, "fp32", tile, X))]
+    h.close()
+    print(n, ncol, tile, err[0] / err[1], flush=True)
+    assert err[0] <= 1.02 * err[1], err

@@ -546,21 +546,21 @@ int wfq_apply_op_noalloc(wfq_handle* h, int32_t precision, int32_t nsys, const d
         const int64_t rows = round_up(2 * (int64_t)nsys, kColPad);
         const uint64_t es = precision == WFQ_PREC_FP64 ? 8 : precision == WFQ_PREC_FP32 ? 4 : 2;
         const uint64_t os = precision == WFQ_PREC_FP64 ? 8 : 4;
-        // [Y][X][work space of the product]; after the product, from X on: [row pairs, or a result that overlaps an input]
+        // [X][Y][work space of the product; after it, at the end: row pairs, or a result that overlaps an input]
         auto up = [](uint64_t b) { return (b + 255) & ~uint64_t(255); };
         const uint64_t x_bytes = up((uint64_t)rows * np * es), y_bytes = up((uint64_t)rows * np * os);
         // Calls are refused by X, Y and 32 bytes an atom and system (with the shifts and the system numbers). The product has
-        // what X and Y leave; the row pairs (round_up(nsys, 8) <= 2 nsys of them per atom from 4 systems on, up to 16 bytes
-        // each) and the result (16 bytes a system) need no more than those 32.
+        // all that X and Y leave; the row pairs (round_up(nsys, 8) <= 2 nsys of them per atom from 4 systems on, up to 16
+        // bytes each) and the result (16 bytes a system) need no more than those 32.
         const uint64_t need = x_bytes + y_bytes + up((uint64_t)nsys * 32 * np) + up((uint64_t)nsys * 16) + up((uint64_t)nsys * 4);
         if (need > kNoAllocScratchBytes)
             fail(WFQ_ENOMEM, "wfq_apply_op_noalloc: " + std::to_string(nsys) + " systems of " + std::to_string(S.n) +
                                  " atoms need " + std::to_string(need >> 20) + " MiB of scratch, more than its " +
                                  std::to_string(kNoAllocScratchBytes >> 20) + " MiB");
         WFQ_HIP(hipSetDevice(S.device));
-        char* Y = static_cast<char*>(scratch_ptr(S.device));
-        char *X = Y + y_bytes, *Yr = X;
-        FixedSplit fs(S, X + x_bytes, kNoAllocScratchBytes - x_bytes - y_bytes);
+        char* X = static_cast<char*>(scratch_ptr(S.device));
+        char *Y = X + x_bytes, *Yr = X + kNoAllocScratchBytes - up((uint64_t)nsys * 32 * np);
+        FixedSplit fs(S, Y + y_bytes, kNoAllocScratchBytes - x_bytes - y_bytes);
         hipStream_t st = static_cast<hipStream_t>(stream);
         load_columns(S, precision, X_re_dev, X_im_dev, nsys, rows, X, st);
         tx_any(S, precision, X, Y, 2 * nsys, st, Order::any);

@@ -1068,8 +1068,8 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     }
     // narrow FP64 products of large structures: recomputing the elements on the vector ALUs
     // (about 16 FP64 operations per pair) beats streaming 8 bytes per pair of the stored copy
-    if (prec == WFQ_PREC_FP64 && ncol <= 4 && otf_narrow_fits(s, ncol, order) &&
-        s.npad >= (otf_narrow_sym(s, ncol, order) ? kSymNarrowFrom : kOtfNarrowFrom))
+    if (prec == WFQ_PREC_FP64 && ncol <= 4 && s.npad >= kSymNarrowFrom && otf_narrow_fits(s, ncol, order) &&
+        (s.npad >= kOtfNarrowFrom || otf_narrow_sym(s, ncol, order)))
         return find_variant(prec, ncol <= 2 ? "otfn2" : "otfn4");
     return order == Order::any && prec != WFQ_PREC_FP64 ? any_variant(s, prec, ncol) : default_variant(prec, ncol);
 }

@@ -328,37 +328,18 @@ T* dev_alloc(Structure& s, size_t count) {
 
 }  // namespace
 
-void* DevChunks::take(size_t bytes) {
-    constexpr size_t kChunk = 2u << 20;
-    const size_t need = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
-    if (need <= left) {
-        char* p = next;
-        next += need;
-        left -= need;
-        return p;
-    }
+void* DevMem::take(size_t bytes) {
     all.reserve(all.size() + 1);   // nothing is allocated that cannot be recorded
     void* p = nullptr;
-    if (need < kChunk / 2) {
-        if (hipMalloc(&p, kChunk) == hipSuccess) {
-            all.push_back(p);
-            next = static_cast<char*>(p) + need;
-            left = kChunk - need;
-            return p;
-        }
-        (void)hipGetLastError();   // the array by itself may still fit
-    }
-    const hipError_t e = hipMalloc(&p, bytes ? bytes : 1);
+    const hipError_t e = hipMalloc(&p, std::max<size_t>(bytes, 1));
     if (e != hipSuccess) throw Error{WFQ_ENOMEM, std::string("hipMalloc failed: ") + hipGetErrorString(e)};
     all.push_back(p);
     return p;
 }
 
-void DevChunks::release() {
+void DevMem::release() {
     for (void* p : all) (void)hipFree(p);
     all.clear();
-    next = nullptr;
-    left = 0;
 }
 
 void free_structure(Structure& s) {
@@ -386,7 +367,7 @@ namespace {
 // Device scratch of one build step: every buffer taken is freed by release() or, on an exception,
 // by the destructor (after the device work that may still use it has finished).
 struct ScratchDev {
-    DevChunks mem;
+    DevMem mem;
     template <typename T>
     T* take(int64_t count) {
         return static_cast<T*>(mem.take((size_t)count * sizeof(T)));

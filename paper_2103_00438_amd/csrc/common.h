@@ -55,14 +55,12 @@ void set_error(int code, const std::string& msg);
 
 struct SolveCache;   // the solver's work space and captured graphs, kept between solves
 
-// Device memory of one owner in few allocations: requests under 1 MiB share chunks of 2 MiB (256-byte aligned), larger
-// ones, and small ones where no chunk can be had, are allocated by themselves. A structure has about 16 arrays, most of
-// them small, its build 4 more: 23 hipMalloc and hipFree calls a job of 2 000 atoms took 4.2 ms of host time with four
-// jobs at a time (70 and 115 us each), 5 calls each now.
-struct DevChunks {
+// Device memory of one owner, freed together. Each array is an allocation by itself: below 2 MiB the runtime serves them from
+// its own pool (1 us a call, 12 from 2 MiB on), so that putting small arrays into shared chunks of 2 MiB, in fewer calls,
+// cost more (eight jobs of 2 000 atoms, four at a time: 36.5 ms a stream in chunks, 29.5 without, over six processes
+// each; destroying a 50 000-atom matrix-free handle 1.9 ms and 0.9).
+struct DevMem {
     std::vector<void*> all;
-    char* next = nullptr;
-    size_t left = 0;
     void* take(size_t bytes);   // throws Error (WFQ_ENOMEM)
     void release();             // frees everything (no work may be using it)
 };
@@ -120,8 +118,8 @@ struct Structure {
     // bumped whenever a block-product choice (tuning) or the partial-tile buffer changes: captured
     // launch sequences that refer to either are then stale
     mutable uint64_t epoch = 0;
+    DevMem mem;   // every device array of the structure
     // pinned host staging of device-to-host copies (d2h_sync)
-    DevChunks mem;   // every device array of the structure
     mutable void* pin_stage = nullptr;
     mutable size_t pin_stage_bytes = 0;
     SolveCache* cache = nullptr;

@@ -855,7 +855,8 @@ void launch_skinny_rows(const Structure&, const void* X, const void* T, void* Y,
 // 635; 4 columns 600 7.5 / 4.1 / -, 4 000 40.5 / 26.6 / 39.9, 7 000 131 / 129 / 127; 8 columns 1 500 16.1 / 13.9 / 10.2, 4 000
 // 41.0 / - / 35.5, 10 000 247 / 329 / 220 and with one row at 250 atoms 3.5 against 5.5, 600 6.3 and 7.1. FP32, 8 columns
 // 2 000 20.0 / 6.7 / -, 7 000 69 / 40 / 68, 10 000 155 / 127 / 158, 20 000 366 / 468 / 350; 4 columns 4 000 18.4 / 12.2 / 13.7,
-// 7 000 30.5 / 31.9 / 30.7. A row's sums are the same in all of them.
+// 7 000 30.5 / 31.9 / 30.7; 8 rows in work-groups of 4 waves ("r8", tuned handles only) took 206 at 15 800, 229 at 16 480 and 298
+// at 20 000 atoms against 182, 207 and 294 of 4 rows. A row's sums are the same in all of them.
 template <int P, int NC>
 void launch_skinny(const Structure& s, const void* X, const void* T, void* Y, int64_t ld, int ncol, hipStream_t st,
                    const KParts* parts) {
@@ -969,7 +970,7 @@ int default_variant(int prec, int ncol) {
     static const Pick f64[] = {{2, "skinny2"}, {4, "skinny4"}, {8, "skinny8"}, {32, "m32n128"}, {64, "m64n128i"},
                                {96, "m128n256w8i"}, {128, "m128n256w8"}, {192, "m64n128i"}, {256, "m128n256w8i"},
                                {320, "m64n128"}, {1 << 30, "m128n256w8i"}};
-    static const Pick f32[] = {{2, "skinny2"}, {4, "skinny4r8"}, {32, "m32n128"}, {64, "m64n128k256i"},
+    static const Pick f32[] = {{2, "skinny2"}, {4, "skinny4"}, {32, "m32n128"}, {64, "m64n128k256i"},
                                {96, "m96n256w8"}, {128, "m128n256w8k64"}, {160, "m160n256w8"}, {192, "m96n256w8"},
                                {224, "m224n128w8"}, {256, "m128n256w8k64"}, {288, "m96n256w8"}, {320, "m160n256w8"},
                                {1 << 30, "m128n256w8k64"}};
@@ -1005,7 +1006,7 @@ int any_variant(const Structure& s, int prec, int ncol) {
                 {192, "s96n256k32"}, {rest, "s128n256k32"}}},
         {16384, {{2, "skinny2"}, {4, "skinny4"}, {32, "m32n128"}, {64, "s64n256k32"}, {96, "s96n128k64"}, {128, "s128n128k64"},
                  {192, "s192n128k32"}, {rest, "s128n256k32"}}},
-        {INT64_MAX, {{2, "skinny2"}, {4, "skinny4r8"}, {96, "s96n256k32"}, {128, "s128n256k32"}, {192, "s192n128k32"},
+        {INT64_MAX, {{2, "skinny2"}, {4, "skinny4"}, {96, "s96n256k32"}, {128, "s128n256k32"}, {192, "s192n128k32"},
                      {256, "s128n256k32"}, {288, "s96n256k32"}, {rest, "s128n256k32"}}}};
     static const Range b16[] = {
         {1536, {{2, "skinny2"}, {4, "skinny4"}, {192, "m32n128"}, {rest, "m64n128i"}}},

@@ -347,3 +347,13 @@ def test_small_fp32_products_are_no_less_accurate_than_a_large_tile(lib, n, ncol
     h.close()
     print(n, ncol, tile, err[0] / err[1], flush=True)
     assert err[0] <= 1.02 * err[1], err
+
+
+@pytest.mark.parametrize("ncol", [3, 4])
+def test_large_narrow_fp32_product_keeps_its_sums(lib, ncol):
+    # 4 rows a wave where there were 8: the same result, bit by bit
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(10, 10, 411), 0.01, 9)
+    h = lib.wfq_build(xyz, GRAPHENE, store=("fp32",))
+    X = np.random.default_rng(ncol).standard_normal((ncol, len(xyz)))
+    assert np.array_equal(lib.wfq_apply_T(h, "fp32", X), lib.wfq_apply_T_variant(h, "fp32", "skinny4r8", X))
+    h.close()

@@ -1059,9 +1059,11 @@ int pick_variant(const Structure& s, int prec, int ncol, Order order) {
     if (prec == WFQ_PREC_FP64 && order == Order::any && ncol > 4) {
         // in any order: two narrow recomputed products for 5 to 8 columns of a large structure (20 000 atoms, 8
         // columns: 380 us, streamed through the matrix cores 576; 10 000: 144 and 161; 8 000: 138 and 94), and the fragment-layout shapes (figures at
-        // tx_frag_kernel) but for 5 to 8 columns of the smallest, whose one launch is quicker than two
+        // tx_frag_kernel) but for 5 to 8 columns of the smallest, whose one launch is quicker than two, and for up to 32
+        // columns beyond 16 384 rows, where T's bytes bound both and the tile is nearer to the memory's rate (operator,
+        // fragment layout / tile: 16 480 atoms, 24 columns 495 / 450, 17 200 535 / 474, 19 280 633 / 576; 16 320: 387 / 432)
         if (ncol <= 8 && s.npad >= 10240 && otf_narrow_sym(s, 4, order)) return find_variant(prec, "otfn8");
-        if ((ncol > 8 || s.npad >= 1536) && frag_fits(s, ncol)) {
+        if ((ncol > 8 || s.npad >= 1536) && (ncol > 32 || s.npad <= 16384) && frag_fits(s, ncol)) {
             static const char* const name[] = {"f16n64", "f32n64", "f48n32", "f64n32", "f80n32"};
             const int cf = frag_columns(ncol);
             return find_variant(prec, cf == 3 && s.npad >= 16384 ? "f48n64" : name[cf - 1]);

@@ -357,3 +357,18 @@ def test_large_narrow_fp32_product_keeps_its_sums(lib, ncol):
     X = np.random.default_rng(ncol).standard_normal((ncol, len(xyz)))
     assert np.array_equal(lib.wfq_apply_T(h, "fp32", X), lib.wfq_apply_T_variant(h, "fp32", "skinny4r8", X))
     h.close()
+
+
+@pytest.mark.parametrize("n,ncol,tile", [(16380, 24, "f32n64"), (16400, 24, "m32n128"), (16400, 32, "m32n128"), (16400, 33, "f48n64")])
+def test_fp64_product_where_the_tile_takes_over_again(lib, n, ncol, tile):
+    # up to 32 columns beyond 16 384 rows run in the LDS tile, the others in the fragment layout: rows against the oracle
+    from oracle.cpp_oracle import CppProblem
+    xyz = wi.geometry.jitter(wi.geometry.nanotube(10, 10, n // 40 + 1)[:n], 0.01, seed=n)
+    X = np.random.default_rng(n).standard_normal((ncol, n))
+    h = lib.wfq_build(xyz, GRAPHENE, store=("fp64",))
+    Y, ref = lib.wfq_apply_T(h, "fp64", X), lib.wfq_apply_T_variant(h, "fp64", tile, X)
+    h.close()
+    assert np.array_equal(Y, ref)
+    P = CppProblem(xyz, GRAPHENE, dense_T=False, build_L=False)
+    rows = np.r_[np.arange(0, n, 997), n - 1]
+    assert np.all(np.abs(Y[:, rows].T - P.apply_T_rows(rows, X.T)) <= 2 * n * UNIT["fp64"] * P.apply_T_rows(rows, np.abs(X).T))

@@ -1031,11 +1031,18 @@ int any_variant(const Structure& s, int prec, int ncol) {
 // (5 000 atoms, 1 to 4 columns: 22 / 26 / 31 / 33 us recomputed, 31 / 31 / 35 / 35 streamed; 4 000: 21 / 24 / 29 / 31 and
 // 27 / 27 / 27 / 28), and one-sided, in the kept order (20 000 atoms, 3 columns: 252 us recomputed, 475 streamed)
 constexpr int64_t kSymNarrowFrom = 4608, kOtfNarrowFrom = 16384;
-// matrix-free FP64 products of up to this many columns go through the narrow kernel, 4 at a time; the wide one's time
-// hardly depends on its columns. Narrow / wide, us: 576 atoms 99 / 194 at 16 columns, 187 / 194 at 32, 360 / 194 at 64;
-// 1 600 atoms 224 / 479 at 32, 435 / 477 at 64, 858 / 481 at 128; 4 096 atoms 502 / 875 at 64, 988 / 882 at 128; 16 384
-// atoms 1 126 / 3 027 at 32, 2 230 / 3 021 at 64, 4 444 / 4 499 at 128.
-int otf_narrow_columns(const Structure& s) { return s.npad < 1024 ? 32 : 64; }
+// Matrix-free FP64 products of up to this many columns go through the narrow kernel, 4 at a time; the wide one's time
+// hardly depends on its columns. From 3 072 rows on 64, by measurement: narrow / wide, us, 4 096 atoms 502 / 875 at 64, 988 /
+// 882 at 128; 16 384 atoms 1 126 / 3 027 at 32, 2 230 / 3 021 at 64, 4 444 / 4 499 at 128. Below, the wide kernel
+// takes about 20 us and 0.25 us a row; a narrow pass 23 us up to 1 024 rows and 27.5 above, and 0.048 us an entry of the
+// longest near-field list (some 40 on graphene, 458 on a metal sphere). Operator, narrow / wide, us: tubes of 200 atoms, 12
+// columns 76 / 81, 16 columns 98 / 81; 880, 40 columns 231 / 279, 56 columns 319 / 279; spheres of 381 atoms, 12 columns
+// 134 / 152, 16 columns 171 / 152; 935, 24 columns 281 / 307, 64 columns 713 / 321; 1 985, 40 columns 527 / 588, 64 columns 828 / 607.
+int otf_narrow_columns(const Structure& s) {
+    if (s.npad >= 3072) return 64;
+    const double wide = 20.0 + 0.25 * s.npad, pass = (s.npad <= 1024 ? 23.0 : 27.5) + 0.048 * s.near_w;
+    return std::min(64, 4 * (int)(wide / pass));
+}
 bool otf_takes_narrow(const Structure& s, int prec, int ncol, Order order) {
     return prec == WFQ_PREC_FP64 && ncol <= otf_narrow_columns(s) && otf_narrow_fits(s, ncol, order);
 }

@@ -281,3 +281,21 @@ def test_wide_fp32_product_is_as_accurate_as_claimed(lib, tube, ncol):
     ref = round_to("fp32", X) @ P.T
     err = np.linalg.norm(Y - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert err.max() <= 2e-6, err.max()
+
+
+@pytest.mark.parametrize("shape,n,cols", [("tube", 200, (12, 13)), ("tube", 1200, (44, 45)), ("sphere", 201, (8, 9)),
+                                          ("sphere", 767, (16, 17)), ("sphere", 1433, (32, 33))])
+def test_matrix_free_fp64_product_where_the_wide_form_is_faster(lib, shape, n, cols):
+    # the narrow products end at fewer columns on few atoms and where the near-field lists are long: both sides of that line
+    import wfq_inputs as wi
+    from wfq_inputs import geometry as geo
+    par = GRAPHENE if shape == "tube" else wi.workloads.FCC_METAL
+    xyz = ragged_tube()[:n] if shape == "tube" else geo.jitter(geo.fcc_sphere({201: 9.4, 767: 14.5, 1433: 18.0}[n]), 0.02, 3)
+    assert len(xyz) == n
+    P = O.Problem(xyz, par)
+    h = lib.wfq_build(xyz, par, t_mode="otf")
+    for ncol in cols:
+        X = np.random.default_rng(ncol).standard_normal((ncol, n))
+        Y = lib.wfq_apply_T(h, "fp64", X)
+        assert np.all(np.abs(Y - X @ P.T.T) <= 1e-13 * (np.abs(X) @ np.abs(P.T).T)), ncol
+    h.close()

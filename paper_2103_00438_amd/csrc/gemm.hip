@@ -1107,9 +1107,9 @@ void run_variant(const Structure& s, int prec, int var, const void* X, void* Y, 
 // stage of any size) when it divides k as they do. A tuned shape runs as it was measured. FP64, 989 atoms: 60 us
 // in the old shape and 14 in the new at 80 columns, 21 and 14 at 48.
 // In any order the smaller FP32 tiles divide k into no fewer parts than those shapes, and up to 64 columns into two more than
-// they would themselves: an FP32 sum's error grows with its length. Error after L and us of the operator, their own parts /
+// they would themselves, or as those shapes do where that is more than a work-group a CU: an FP32 sum's error grows with its length. Error after L and us of the operator, their own parts /
 // these (that of the kept order's shape): 1 289-atom sphere, 256 columns 2.14e-6 / 1.88e-6 (1.88e-6), 37 / 36; 1 721, 40
-// columns 2.64e-6 / 2.10e-6 (2.37e-6), 25.4 / 23.3; 2 315, 48 columns 2.58e-6 / 2.18e-6 (2.33e-6).
+// columns 2.64e-6 / 2.10e-6 (2.37e-6), 25.4 / 23.3; 2 315, 48 columns 2.58e-6 / 2.33e-6 (2.33e-6).
 void run_picked(const Structure& s, int prec, int ncol, Order order, const void* X, void* Y, hipStream_t st) {
     const int var = pick_variant(s, prec, ncol, order);
     const Variant& v = variants_of(prec)[var];
@@ -1133,10 +1133,15 @@ void run_picked(const Structure& s, int prec, int ncol, Order order, const void*
         const Variant& d = variants_of(prec)[default_variant(prec, ncol)];
         KParts kp = v.parts(s, s.npad, ncol);
         const int own = kp.split, stages = (int)(s.npad * (int64_t)sizeof(float) / kp.stage_bytes);
-        if (d.parts) kp.split = std::max(own, d.parts(s, s.npad, ncol).split);
-        if (ncol <= 64 && s.npad < 3072) kp.split += 2;
+        const KParts dp = d.parts ? d.parts(s, s.npad, ncol) : kp;
+        kp.split = std::max(own, dp.split);
+        if (ncol <= 64 && s.npad < 3072) {
+            const int64_t tiles = (ncol + v.bm - 1) / v.bm * (s.npad / v.bn);
+            if (tiles * (kp.split + 2) <= device_cus(s.device)) kp.split += 2;
+            else if (dp.stage_bytes % 128 == 0) kp = dp;
+        }
         const uint64_t part_bytes = (uint64_t)round_up(ncol, v.bm) * s.npad * sizeof(float);
-        if (kp.split > own && kp.split <= stages / 2 &&
+        if ((kp.split != own || kp.stage_bytes != 128) && kp.split <= stages / 2 &&
             (kp.split - 1) * part_bytes <= (s.split_fixed ? s.split_fixed_bytes : kSplitWsCap)) {
             run_variant(s, prec, var, X, Y, ncol, st, order, &kp);
             return;

@@ -217,7 +217,8 @@ void launch_spmm_tile(const Structure& S, const YE* Y, int64_t ld, int nsys, con
     constexpr int RW = 64 / (L * Q) < R ? 64 / (L * Q) : R;
     const int lanes = 4 / (R / RW) * L * SPL;   // systems per pass of a work-group
     const int64_t want = (2048 + nb8 - 1) / nb8;
-    // planes of few rows: a wave's systems to a work-group while there are no more than two work-groups a CU
+    // planes of few rows: a wave's systems to a work-group while there are no more than two work-groups a CU (321-atom
+    // sphere, 24 systems, FP32 operator: 44 -> 31 us)
     const int64_t spread = !PAIRS && Q == 1 ? std::min<int64_t>(512 / nb8, (nsys + L * SPL - 1) / (L * SPL)) : 1;
     const int gy = (int)std::max<int64_t>({1, spread, std::min<int64_t>(want, (nsys + lanes - 1) / lanes)});
     const int per_group = ((nsys + gy - 1) / gy + L * SPL - 1) / (L * SPL) * (L * SPL);

@@ -191,7 +191,7 @@ void build_rhs(const Structure& s, const double* dirs_dev, int n_dir, double E0,
 // The order of a product's sums. kept: the order that the solves' results hang on. A mode that a field hardly excites
 // comes up, near its resonance, from the rounding of the products, and the polarisability along it follows any
 // change of their order: by up to 6e-7 for the field normal to a ribbon, 1e-9..3e-9 for the fields across a tube. any: the
-// fastest product of no larger error against 64 bits. The operator entry points ask for it, and the multi-shift
+// fastest product, in FP32 and BF16 of no larger error against 64 bits, in FP64 within a few 1e-16 of the result's norm. The operator entry points ask for it, and the multi-shift
 // solves of three and more field directions, whose results the strongly excited directions dominate (they move by
 // 1e-11..1e-10 then), to their end, however many directions are still active. Matrix-free structures take any: their solves move by up to 3e-10.
 enum class Order { kept, any };

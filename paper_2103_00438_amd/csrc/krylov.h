@@ -142,7 +142,6 @@ void qmr_smooth(const int* sys, int nsys, const Basis& Q, int64_t n, const doubl
                 double* tau2_new, int* first, double* norm2, int nblk, hipStream_t st);
 // restart from the QMR iterate: x = xq, p = T p = 0, s = r (r must hold the residual of xq)
 void qmr_restart(const int* sys, int nsys, const Basis& Q, hipStream_t st);
-// out[s] = sum_b partial[s][b]
 
 // ---- multi-shift GMRES (mshift.hip): one real Arnoldi basis per field direction, shared by the
 // frequencies of that direction. Real basis of direction d, slot j at V + (d * mdim1 + j) * npad;

@@ -1,6 +1,6 @@
-// Krylov-side kernels: the sparse half of the operator (L Y + z V), the reduction of Gram-Schmidt
-// partial dots (the Arnoldi sweeps themselves are in dcgs.hip), the Hessenberg least-squares solve,
-// the solution update, the FP64 refinement residual and the observables (arXiv 2103.00438, Section
+// Krylov-side kernels: the packing of vectors into a product's block, the sparse half of the operator (L Y + z V),
+// the triangular solve of the least-squares problem (the Arnoldi sweeps and the column step are in dcgs.hip), the solution
+// update, the FP64 refinement residual and the observables (arXiv 2103.00438, Section
 // "Solution strategies": GMRES paragraph and restarted GMRES(k); Eq. (long-cross) for the dipole).
 //
 // All of these are bandwidth-bound vector sweeps. Reductions are deterministic: each wave sums a
